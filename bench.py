@@ -42,7 +42,7 @@ def algorithmic_bytes(cfg, act_bytes: int = 4, xc_bytes: int | None = None) -> d
     bw = {0: 4, 1: 2, 2: 1, 3: 0.5}[cfg.w_dtype]
     a = act_bytes
     if xc_bytes is None:
-        xc_bytes = 1 if (cfg.act_bits == 8 and k % 4 == 0) else 4
+        xc_bytes = 1 if cfg.act_bits == 8 else 4
     return {
         "haar_fwd": a * B * Ci * N + 4 * B * N,                    # read x, write norms
         "norm_select": 4 * B * N + 4 * B * k,                      # read norms, write I
@@ -197,7 +197,7 @@ def block_algorithmic_bytes(cfg, act_bytes: int, chained: bool) -> dict:
     alg["depthwise"] = 0 if cfg.W % 4 == 0 else 8 * cfg.B * cfg.C_mid * cfg.N
     if chained:
         l1 = cfg.layer(1)
-        xcb = 1 if (cfg.act_bits == 8 and cfg.k % 4 == 0) else 4
+        xcb = 1 if cfg.act_bits == 8 else 4
         src = 4 * cfg.B * cfg.C_mid * cfg.k + 4 * cfg.B * cfg.N       # Y_wt of the expand layer + its rank map
         alg["l0_scatter_ihaar"] = 0
         alg["l1_haar_fwd"] = src + 4 * cfg.B * cfg.N
@@ -590,7 +590,7 @@ def main() -> int:
     act_bytes = 2 if args.act == "bf16" else 4
     # kept coefficients travel as 8-bit codes whenever the clipping parameter is known before the
     # second transform pass: from the caller, or from the selection (not with a fixed list)
-    codes = cfg.act_bits == 8 and cfg.k % 4 == 0 and (args.alpha == "static" or args.index_list == "select")
+    codes = cfg.act_bits == 8 and (args.alpha == "static" or args.index_list == "select")
     alg = algorithmic_bytes(cfg, act_bytes, 1 if codes else 4)
     if args.index_list == "prefix":  # no norm pass, no selection: only the rank map is written
         alg["haar_fwd"], alg["norm_select"] = 0, 4 * cfg.B * cfg.N

@@ -104,9 +104,12 @@ wcc_status need_ws(const wcc_ctx *ctx, const WsLayout &L) {
 // get slower again: measured at 256 and 480 workgroups)
 constexpr size_t kSelectMinBlocks = 512;
 
-WsLayout ws_layout(const wcc_desc &d, int front) {
+WsLayout ws_layout(const wcc_desc &d, int front, bool pad) {
   WsLayout L{};
   const size_t N = (size_t)d.H * d.W, B = d.B, k = (size_t)k_of(d);
+  // Rows of the compressed signals are whole words of four positions, so that the contraction can
+  // load and store them whatever k is (the padding holds anything: it is never scattered).
+  L.ks = pad ? ((int64_t)k + 3) & ~(int64_t)3 : (int64_t)k;
   L.G = forward_groups(d, front);
   // select workgroups take 1024, 2048 or 4096 keys: the most that still leaves kSelectMinBlocks
   // of them (fewer, fatter workgroups merge fewer histograms and read the previous pass's
@@ -129,10 +132,15 @@ WsLayout ws_layout(const wcc_desc &d, int front) {
   L.alpha = take(256);
   L.block_top = take(d.act_quant_bits == 8 ? B * (size_t)L.nblk * 4 : 0);
   L.scratch = take(kInvScratchBytes);
-  L.xc32 = take(B * (size_t)d.C_in * k * 4);
-  L.yc = take(B * (size_t)d.C_out * k * 4);
+  L.xc32 = take(B * (size_t)d.C_in * L.ks * 4);
+  L.yc = take(B * (size_t)d.C_out * L.ks * 4);
   L.w8 = take(d.w_dtype == WCC_I4 ? (size_t)d.C_out * d.C_in : 0);
   L.total = off;
+  // (a layer that fits the static scratch array only without the padding goes without it)
+  if (pad && L.total > (size_t)WCC_STATIC_SCRATCH_BYTES) {
+    const WsLayout bare = ws_layout(d, front, false);
+    if (bare.total <= (size_t)WCC_STATIC_SCRATCH_BYTES) return bare;
+  }
   return L;
 }
 
@@ -169,6 +177,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
                       const int32_t *idx_given = nullptr, const ChainSrc *src = nullptr,
                       bool stop_before_inverse = false) {
   const int64_t k = k_of(d);
+  const int64_t ks = L.ks;  // row stride of the compressed signals in the workspace
   const bool quant = d.act_quant_bits == 8;
 
   float *part = reinterpret_cast<float *>(ws + L.norm_part);
@@ -191,8 +200,8 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   //                    selection's last kernel reduces it over the positions each of its
   //                    workgroups keeps (block_top), so alpha is known before the second pass,
   //                    which again decides the codes itself;
-  //   fixed list (no first pass), k % 4 != 0 (the contraction reads four codes a word), or more
-  //   workgroup maxima than a consumer should have to combine:
+  //   fixed list (no first pass), rows that are not whole words (ks % 4 != 0: the contraction
+  //   reads four codes a word), or more workgroup maxima than a consumer should have to combine:
   //                    the second pass writes fp32 and raises the slots, the contraction's
   //                    loader quantises.
   const bool given = quant && alpha_in > 0.f;
@@ -203,8 +212,8 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   // 851 us at keep 1/4)
   const bool small_layer = (int64_t)d.H * d.W <= kEarlyAlphaMinPositions &&
                            (int64_t)d.B * d.C_in * k < kEarlyAlphaMinKept;
-  const bool early = quant && !given && list == kListSelect && k % 4 == 0 && n_top <= 8192 && !small_layer;
-  const bool codes_now = early || (given && k % 4 == 0);
+  const bool early = quant && !given && list == kListSelect && ks % 4 == 0 && n_top <= 8192 && !small_layer;
+  const bool codes_now = early || (given && ks % 4 == 0);
   float *tops = reinterpret_cast<float *>(ws + L.block_top);
   // the contraction finds alpha in the slots: as the largest of them, or (early) as the one
   // float the second pass left there after combining the selection's maxima
@@ -239,24 +248,24 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   // place (the dropped coefficients never reach memory)
   WCC_TRY(mark(WCC_T_GATHER, 0));
   if (src)
-    WCC_TRY(launch_chain_keep(d, k, *src, wdw, jmap, xc32, (quant && !given && !codes_now) ? slots : nullptr,
+    WCC_TRY(launch_chain_keep(d, ks, *src, wdw, jmap, xc32, (quant && !given && !codes_now) ? slots : nullptr,
                               (given && codes_now) ? alpha_in : 0.f, early ? tops : nullptr, n_top,
                               early ? slots : nullptr, s));
   else
-    WCC_TRY(launch_haar_keep(d, k, x, jmap, xc32, (quant && !given && !codes_now) ? slots : nullptr, wdw,
+    WCC_TRY(launch_haar_keep(d, ks, x, jmap, xc32, (quant && !given && !codes_now) ? slots : nullptr, wdw,
                              (given && codes_now) ? alpha_in : 0.f, early ? tops : nullptr, n_top,
                              early ? slots : nullptr, s));
   WCC_TRY(mark(WCC_T_GATHER, 1));
   // C: Y_wt = Conv(K_1x1, X_wt[I]) (kept coefficients still in fp32 are quantised as they are
   // loaded)
   WCC_TRY(mark(WCC_T_POINTWISE, 0));
-  WCC_TRY(pointwise_any(ws, L, d, k, w, w_scale, xc32, !codes_now, slots, n_alpha,
+  WCC_TRY(pointwise_any(ws, L, d, ks, w, w_scale, xc32, !codes_now, slots, n_alpha,
                         quant ? alpha_out_dev : nullptr, yc, s));
   WCC_TRY(mark(WCC_T_POINTWISE, 1));
   if (stop_before_inverse) return WCC_OK;
   // D + E: Y^0[I] = Y_wt, inverse levels
   WCC_TRY(mark(WCC_T_SCATTER_IHAAR, 0));
-  WCC_TRY(launch_scatter_ihaar(d, k, yc, jmap, y, reinterpret_cast<float *>(ws + L.scratch), residual, s));
+  WCC_TRY(launch_scatter_ihaar(d, ks, yc, jmap, y, reinterpret_cast<float *>(ws + L.scratch), residual, s));
   WCC_TRY(mark(WCC_T_SCATTER_IHAAR, 1));
   return WCC_OK;
 }
@@ -648,7 +657,7 @@ wcc_status wcc_block_forward(wcc_ctx *ctx, const wcc_block_desc *desc, const voi
                     nullptr, true);
     if (st != WCC_OK) return st;
     const ChainSrc src{reinterpret_cast<const float *>(ws + BL.layer1 + L1.yc),
-                       reinterpret_cast<const int32_t *>(ws + BL.layer1 + L1.jmap), k_of(d1)};
+                       reinterpret_cast<const int32_t *>(ws + BL.layer1 + L1.jmap), L1.ks};
     st = forward_on(ctx, ws + BL.layer3, L3, d3, nullptr, w3, w3_scale, 0.f, y, idx3_out, nullptr, x,
                     w_dw, prof && ctx->block_profile_layer == 1, s, kListSelect, nullptr, &src);
     if (st != WCC_OK) return st;

@@ -41,10 +41,11 @@ struct WsLayout {
   size_t alpha;       // kAlphaSlots floats: partial maxima of |kept coefficient|
   size_t block_top;   // [B, nblk] fp32: the same, one per workgroup of the selection's last kernel
   size_t scratch;     // kInvScratchBytes: sink for the stores of lanes outside the plane
-  size_t xc32;        // [B, C_in, k] fp32, or int8 codes in its first quarter
-  size_t yc;          // [B, C_out, k] fp32  (wcc_forward only)
+  size_t xc32;        // [B, C_in, ks] fp32, or int8 codes in its first quarter
+  size_t yc;          // [B, C_out, ks] fp32  (wcc_forward only)
   size_t w8;          // [C_out, C_in] int8: WCC_I4 weights widened (else empty)
   size_t total;
+  int64_t ks;         // row stride of xc32 and yc: k rounded up to 4 (fused calls)
   int G;              // channel groups of the forward transform
   int nblk;           // select workgroups per sample
   int sel_slots;      // 16-byte loads per thread in the select kernels: 1, 2 or 4
@@ -143,10 +144,13 @@ enum Front {
   kFrontDw = 1,     // K_dw x, convolved on the fly by both passes
   kFrontChain = 2   // K_dw iHWT(T^T Y_wt) of a producer layer, rebuilt from its compressed output
 };
-WsLayout ws_layout(const wcc_desc &d, int front = kFrontNone);
+// pad: see WsLayout::ks (without: ks = k; ws_layout takes that form by itself for a layer that fits
+// WCC_STATIC_SCRATCH_BYTES only so)
+WsLayout ws_layout(const wcc_desc &d, int front = kFrontNone, bool pad = true);
 int forward_groups(const wcc_desc &d, int front);
 
-// A producer layer's compressed output: t1 = iHWT(T^T yc), yc [B, C, k], jmap [B, N] its rank map
+// A producer layer's compressed output: t1 = iHWT(T^T yc), yc [B, C, k] (k: its row stride),
+// jmap [B, N] its rank map
 struct ChainSrc {
   const float *yc;
   const int32_t *jmap;
