@@ -412,72 +412,30 @@ __global__ __launch_bounds__(kThreads) void select_emit_kernel(const float *__re
 }
 
 // ---- small planes: the whole select of one sample in ONE workgroup -------------------------
-// For N <= 16384 the four kernels above are launch gaps and little else.  Here one workgroup of
+// For N <= 16384 the kernels above are launch gaps and little else.  Here one workgroup of
 // 1024 threads holds all keys of a sample in registers (slot s of thread t covers the four
-// positions from (s * 1024 + t) * 4 on: every load is one contiguous 16 KiB row), runs the
-// digit passes on an LDS histogram and emits idx and jmap in position order.  Same result,
-// bit for bit.
+// positions from (s * 1024 + t) * 4 on: every load is one contiguous 16 KiB row), finds the
+// threshold and emits idx and jmap in position order.  Same result, bit for bit.
 //
 // With all keys in one place the digits need not be raw bit fields: the passes work on
 // rel = key - min(keys), whose significant bits (those of max - min) are cut into fields of at
-// most 11 bits from the top.  Norms of one plane share their upper exponent bits, so the raw
+// most 13 bits from the top.  Norms of one plane share their upper exponent bits, so the raw
 // top field would put nearly all keys into a handful of bins and the LDS atomics of the 16
 // waves would serialise on them; the relative top field spreads them over the whole histogram.
-// Passes whose field is empty are skipped.
+// After a pass the keys that still matter are those of one bin.  They are few (a handful of 2048
+// keys in 8192 bins, or one class of equal keys): up to kSmallList of them go to a list in LDS, and
+// every entry counts the entries above it; only more than that take another pass.
+// Bound by its own chain: the loads, then a barrier behind every step.  Fields of 11 bits, always
+// as many passes as there are bits, and loads one slot after the other took 9.5-13 us on the eleven
+// small layers of the 16-layer stack (6-9.7 now) and 12.4 us on 16384 positions (10.5).
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / 64;
 constexpr int kSmallSlots = 4;  // 16-byte loads per thread at most (beyond that the one
-                                // workgroup is slower than the four spread-out kernels)
+                                // workgroup is slower than the spread-out kernels)
 constexpr int64_t kSmallMaxN = (int64_t)4 * kSmallSlots * kSmallThreads;
-
-// One pass over the field rel[hi-1 : lo] (hi - lo <= 11) of the keys that agree with `prefix`
-// above bit hi (FIRST: no bit is set above hi, all keys take part); then the digit that holds
-// the remaining rank is appended to prefix.
-template <bool FIRST>
-__device__ __forceinline__ void small_pass(const uint32_t (&rel)[4 * kSmallSlots], uint32_t vmask,
-                                           int slots, int hi, int lo, uint32_t &prefix,
-                                           uint32_t &remain, uint32_t *lh, uint32_t *tmp,
-                                           uint32_t *bcast) {
-  const int t = threadIdx.x;
-  const uint32_t fmask = (1u << (hi - lo)) - 1u;
-  for (int i = t; i < kRadixBins; i += kSmallThreads) lh[i] = 0;
-  if (t == 0) { bcast[0] = prefix; bcast[1] = remain; }  // rank beyond the data: unchanged
-  __syncthreads();
-#pragma unroll
-  for (int s = 0; s < kSmallSlots; ++s) {
-    if (s < slots) {  // uniform over the workgroup
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t r = rel[4 * s + e];
-        bool agrees = true;
-        if constexpr (!FIRST) agrees = (r >> hi) == (prefix >> hi);
-        hist_add_spread(lh, (r >> lo) & fmask, ((vmask >> s) & 1u) && agrees);
-      }
-    }
-  }
-  __syncthreads();
-  // two consecutive digits per thread, from the top
-  uint32_t cnt[2], sum = 0;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    cnt[i] = lh[kRadixBins - 1 - (t * 2 + i)];
-    sum += cnt[i];
-  }
-  uint32_t above = block_exclusive_scan<kSmallWaves>(sum, tmp);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    if (above < remain && remain <= above + cnt[i]) {
-      const uint32_t digit = kRadixBins - 1 - (t * 2 + i);
-      bcast[0] = prefix | (digit << lo);
-      bcast[1] = remain - above;
-    }
-    above += cnt[i];
-  }
-  __syncthreads();
-  prefix = bcast[0];
-  remain = bcast[1];
-  __syncthreads();
-}
+constexpr int kSmallBits = 13;  // bits of a field
+constexpr int kSmallBins = 1 << kSmallBits;
+constexpr uint32_t kSmallList = 512;
 
 // The G partial planes of a small map summed (and their maxima taken) by the whole chip before
 // the one-workgroup-a-sample kernel below: with many groups that kernel would otherwise read
@@ -493,81 +451,201 @@ __global__ __launch_bounds__(256) void combine_parts_kernel(const float *__restr
   if (top_part) *reinterpret_cast<float4 *>(top_part + at) = load_top(top_part, G, (int64_t)B * N, at);
 }
 
-// The partial planes are combined first from this many groups and this many values a sample on
-// (below that the extra launch costs more than the one workgroup's reads: the deep layers of the
-// 16-layer stack have 2048-8192 positions in up to 32 groups)
-constexpr int kCombineGroups = 4;
-constexpr int64_t kCombineValues = 1 << 18;
+// The partial planes (sums and maxima) are combined first from this many values a sample on: below
+// that the extra launch (5 us) costs more than the one workgroup's reads (16384 positions in 8
+// groups, 262144 values: 25 us alone, 5 + 12 us combined first)
+constexpr int64_t kCombineValues = 1 << 17;
 
-// grid = B, block = 1024.  REDUCE as in load_keys.
-template <bool REDUCE>
+// grid = B, block = 1024.  SLOTS: loads a thread (1, 2 or 4).  REDUCE as in load_keys.
+template <bool REDUCE, int SLOTS>
 __global__ __launch_bounds__(kSmallThreads) void select_small_kernel(
-    const float *__restrict__ src, float *__restrict__ norm, int G, int64_t N, int B, uint32_t k,
-    int slots, int32_t *__restrict__ idx, int32_t *__restrict__ jmap,
+    const float *__restrict__ src, int G, int64_t N, int B, uint32_t k,
+    int32_t *__restrict__ idx, int32_t *__restrict__ jmap,
     const float *__restrict__ top_part, float *block_top) {
-  __shared__ uint32_t lh[kRadixBins];
+  __shared__ __attribute__((aligned(16))) uint32_t lh[kSmallBins];
+  __shared__ __attribute__((aligned(16))) uint32_t list[kSmallList];
+  __shared__ uint32_t ends[2 * kSmallWaves];
   __shared__ uint32_t tmp[kSmallSlots * kSmallWaves];
-  __shared__ uint32_t bcast[2];
+  __shared__ uint32_t bcast[4];  // prefix, remaining rank, keys in the bin, entries in the list
   const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  uint32_t rel[4 * kSmallSlots];
-  float topv[4 * kSmallSlots];  // largest |coefficient| over the channels at the key's position
-  uint32_t vmask = 0;  // bit s: slot s of this thread lies inside the plane (N is a multiple of 4)
+  const int64_t BN = (int64_t)B * N;
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < kSmallBins / 4 / kSmallThreads; ++i)
+      reinterpret_cast<uint4 *>(lh)[i * kSmallThreads + t] = make_uint4(0, 0, 0, 0);
+    if (t == 0) bcast[3] = 0;
+  };
+
+  // All loads of all slots go out together, without a branch around any of them: a slot outside
+  // the plane (N is a multiple of 4: whole slots) reads the plane's last four values.
+  int64_t at[SLOTS];
+  uint32_t vmask = 0;  // bit s: slot s of this thread lies inside the plane
+  float4 v[SLOTS], m[SLOTS];
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s) {
+    const int64_t pos = ((int64_t)s * kSmallThreads + t) * 4;
+    vmask |= (pos < N ? 1u : 0u) << s;
+    at[s] = (int64_t)b * N + min(pos, N - 4);
+    v[s] = *reinterpret_cast<const float4 *>(src + at[s]);
+  }
+  if (top_part) {  // (uniform over the grid)
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) m[s] = *reinterpret_cast<const float4 *>(top_part + at[s]);
+  } else {
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) m[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  clear();
+  if constexpr (REDUCE) {
+    constexpr int PL = 4 / SLOTS;  // planes a round: four loads in flight of each kind
+    for (int g = 1; g < G; g += PL) {
+      float4 a[PL][SLOTS], c[PL][SLOTS];
+#pragma unroll
+      for (int i = 0; i < PL; ++i)
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s)
+          a[i][s] = *reinterpret_cast<const float4 *>(src + (int64_t)min(g + i, G - 1) * BN + at[s]);
+      if (top_part) {
+#pragma unroll
+        for (int i = 0; i < PL; ++i)
+#pragma unroll
+          for (int s = 0; s < SLOTS; ++s)
+            c[i][s] = *reinterpret_cast<const float4 *>(top_part + (int64_t)min(g + i, G - 1) * BN + at[s]);
+      }
+#pragma unroll
+      for (int i = 0; i < PL; ++i) {
+        if (g + i < G) {  // (uniform) added in increasing group order
+#pragma unroll
+          for (int s = 0; s < SLOTS; ++s) {
+            v[s].x += a[i][s].x; v[s].y += a[i][s].y; v[s].z += a[i][s].z; v[s].w += a[i][s].w;
+            if (top_part) {
+              m[s].x = fmaxf(m[s].x, c[i][s].x); m[s].y = fmaxf(m[s].y, c[i][s].y);
+              m[s].z = fmaxf(m[s].z, c[i][s].z); m[s].w = fmaxf(m[s].w, c[i][s].w);
+            }
+          }
+        }
+      }
+    }
+  }
+  uint32_t rel[4 * SLOTS];
+  float topv[4 * SLOTS];  // largest |coefficient| over the channels at the key's position
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
 #pragma unroll
-  for (int s = 0; s < kSmallSlots; ++s) {
-    const int64_t pos = ((int64_t)s * kSmallThreads + t) * 4;
-    uint4 k4 = make_uint4(0, 0, 0, 0);
-    float4 t4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (s < slots && pos < N) {
-      k4 = load_keys<REDUCE>(src, norm, G, (int64_t)B * N, (int64_t)b * N + pos);
-      if (top_part) t4 = load_top(top_part, G, (int64_t)B * N, (int64_t)b * N + pos);
-      vmask |= 1u << s;
-      kmin = min(kmin, min(min(k4.x, k4.y), min(k4.z, k4.w)));
-      kmax = max(kmax, max(max(k4.x, k4.y), max(k4.z, k4.w)));
+  for (int s = 0; s < SLOTS; ++s) {
+    const uint32_t k4[4] = {__float_as_uint(v[s].x), __float_as_uint(v[s].y), __float_as_uint(v[s].z),
+                            __float_as_uint(v[s].w)};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      rel[4 * s + e] = k4[e];
+      kmin = min(kmin, k4[e]);  // (the values a slot outside repeats are the plane's own)
+      kmax = max(kmax, k4[e]);
     }
-    rel[4 * s] = k4.x; rel[4 * s + 1] = k4.y; rel[4 * s + 2] = k4.z; rel[4 * s + 3] = k4.w;
-    topv[4 * s] = t4.x; topv[4 * s + 1] = t4.y; topv[4 * s + 2] = t4.z; topv[4 * s + 3] = t4.w;
+    topv[4 * s] = m[s].x; topv[4 * s + 1] = m[s].y; topv[4 * s + 2] = m[s].z; topv[4 * s + 3] = m[s].w;
   }
   // smallest and largest key of the sample
   kmin = wave_extreme<false>(kmin);
   kmax = wave_extreme<true>(kmax);
-  if (lane == 0) { tmp[wv] = kmin; tmp[kSmallWaves + wv] = kmax; }
-  __syncthreads();
+  if (lane == 0) { ends[wv] = kmin; ends[kSmallWaves + wv] = kmax; }
+  __syncthreads();  // (and the histogram is clear)
 #pragma unroll
   for (int i = 0; i < kSmallWaves; ++i) {
-    kmin = min(kmin, tmp[i]);
-    kmax = max(kmax, tmp[kSmallWaves + i]);
+    kmin = min(kmin, ends[i]);
+    kmax = max(kmax, ends[kSmallWaves + i]);
   }
 #pragma unroll
-  for (int i = 0; i < 4 * kSmallSlots; ++i) rel[i] -= kmin;  // slots outside the plane: unused
-  const int nbits = 32 - __clz((int)(kmax - kmin));  // 0 when all keys are equal (clz(0) = 32)
+  for (int i = 0; i < 4 * SLOTS; ++i) rel[i] -= kmin;
 
-  uint32_t T = 0, r_take = k;  // threshold (relative key) and how many keys equal to it to take
-  const int lo0 = max(nbits - 11, 0), lo1 = max(nbits - 22, 0);
-  small_pass<true>(rel, vmask, slots, nbits, lo0, T, r_take, lh, tmp, bcast);
-  if (lo0 > 0) small_pass<false>(rel, vmask, slots, lo0, lo1, T, r_take, lh, tmp, bcast);
-  if (lo1 > 0) small_pass<false>(rel, vmask, slots, lo1, 0, T, r_take, lh, tmp, bcast);
+  // T: the threshold (relative key); r_take: how many keys equal to it to take.  The bits of T from
+  // `hi` up are fixed.
+  uint32_t T = 0, r_take = k;
+  int hi = 32 - __clz((int)(kmax - kmin));  // 0 when all keys are equal (clz(0) = 32)
+  for (bool first = true; hi > 0; first = false) {
+    const int lo = max(hi - kSmallBits, 0);
+    const uint32_t fmask = (1u << (hi - lo)) - 1u;
+    if (!first) {
+      clear();
+      __syncthreads();
+    }
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t r = rel[4 * s + e];
+        // (bits above hi: none in the first pass; hi = 32 is a first pass too)
+        const bool agrees = first || (r >> hi) == (T >> hi);
+        hist_add_spread(lh, (r >> lo) & fmask, ((vmask >> s) & 1u) && agrees);
+      }
+    __syncthreads();
+    // eight consecutive bins per thread, from the top
+    constexpr int per = kSmallBins / kSmallThreads;
+    uint32_t cnt[per], sum = 0;
+    {
+      const uint4 *row = reinterpret_cast<const uint4 *>(lh) + (kSmallBins - (t + 1) * per) / 4;
+#pragma unroll
+      for (int i = 0; i < per / 4; ++i) {
+        const uint4 q = row[per / 4 - 1 - i];
+        cnt[4 * i] = q.w; cnt[4 * i + 1] = q.z; cnt[4 * i + 2] = q.y; cnt[4 * i + 3] = q.x;
+        sum += q.x + q.y + q.z + q.w;
+      }
+    }
+    uint32_t above = block_exclusive_scan<kSmallWaves>(sum, tmp);
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+      if (above < r_take && r_take <= above + cnt[i]) {  // (1 <= r_take <= keys that agree: one thread's bin)
+        bcast[0] = T | ((uint32_t)(kSmallBins - 1 - (t * per + i)) << lo);
+        bcast[1] = r_take - above;
+        bcast[2] = cnt[i];
+      }
+      above += cnt[i];
+    }
+    __syncthreads();
+    T = bcast[0];
+    r_take = bcast[1];
+    const uint32_t left = bcast[2];
+    hi = lo;
+    if (hi == 0) break;
+    if (left <= kSmallList) {  // (uniform)
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (((vmask >> s) & 1u) && (rel[4 * s + e] >> hi) == (T >> hi)) list[atomicAdd(&bcast[3], 1u)] = rel[4 * s + e];
+      __syncthreads();
+      if ((uint32_t)t < left) {
+        const uint32_t mine = list[t];
+        uint32_t gt = 0, ge = 0;
+        for (uint32_t i = 0; i < left; ++i) {
+          const uint32_t o = list[i];
+          gt += o > mine; ge += o >= mine;
+        }
+        if (gt < r_take && r_take <= ge) { bcast[0] = mine; bcast[1] = r_take - gt; }  // (equal entries write the same)
+      }
+      __syncthreads();
+      T = bcast[0];
+      r_take = bcast[1];
+      break;
+    }
+  }
 
   // Ordered compaction as in select_emit_kernel.  Position order is slot-major, then thread,
   // then the four keys of a slot: a wave scan per slot, then a scan over the 64 (slot, wave)
   // totals.  Counts (above T | equal to T) are packed 16 + 16 bits: N <= 16384.
-  uint32_t ex[kSmallSlots];
+  uint32_t ex[SLOTS];
 #pragma unroll
-  for (int s = 0; s < kSmallSlots; ++s) {
+  for (int s = 0; s < SLOTS; ++s) {
     uint32_t packed = 0;
     if ((vmask >> s) & 1u) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) packed += ((rel[4 * s + e] > T) << 16) + (rel[4 * s + e] == T);
     }
-    uint32_t inc = packed;
-    if (s < slots) inc = wave_inclusive_scan(packed);  // (uniform over the workgroup)
+    const uint32_t inc = wave_inclusive_scan(packed);
     ex[s] = inc - packed;
     if (lane == 63) tmp[s * kSmallWaves + wv] = inc;
   }
   __syncthreads();
   static_assert(kSmallSlots * kSmallWaves == 64, "one wave scans the totals");
-  if (t < 64) {  // wave 0: exclusive scan of the 64 totals
-    const uint32_t v = tmp[t];
+  if (t < 64) {  // wave 0: exclusive scan of the totals
+    const uint32_t v = t < SLOTS * kSmallWaves ? tmp[t] : 0u;
     tmp[t] = wave_inclusive_scan(v) - v;
   }
   __syncthreads();
@@ -575,7 +653,7 @@ __global__ __launch_bounds__(kSmallThreads) void select_small_kernel(
   int32_t *out = idx + (size_t)b * k;
   float kept_top = 0.f;  // largest |coefficient| over the channels at a kept position
 #pragma unroll
-  for (int s = 0; s < kSmallSlots; ++s) {
+  for (int s = 0; s < SLOTS; ++s) {
     if ((vmask >> s) & 1u) {
       const int e0 = s * kSmallWaves + wv;
       const uint32_t before = tmp[e0] + ex[s];
@@ -694,18 +772,27 @@ hipError_t launch_select(const wcc_desc &d, const float *norm_or_part, int G, fl
   const int nblk = L.nblk;
   const uint32_t k32 = (uint32_t)k;
   if (N <= kSmallMaxN) {
-    const int slots = (int)((N + 4 * kSmallThreads - 1) / (4 * kSmallThreads));
-    if (G >= kCombineGroups && (int64_t)G * N >= kCombineValues) {
+    const float *src = norm_or_part;
+    int planes = G;
+    if (G > 1 && (int64_t)G * N * (top_part ? 2 : 1) >= kCombineValues) {
       hipLaunchKernelGGL(combine_parts_kernel, dim3((unsigned)((N + 1023) / 1024), d.B), dim3(256), 0, s,
                          norm_or_part, norm_out, G, N, d.B, top_part);
-      hipLaunchKernelGGL((select_small_kernel<false>), dim3(d.B), dim3(kSmallThreads), 0, s, norm_out,
-                         nullptr, 1, N, d.B, k32, slots, idx, jmap, top_part, block_top);
-    } else if (G > 1)
-      hipLaunchKernelGGL((select_small_kernel<true>), dim3(d.B), dim3(kSmallThreads), 0, s,
-                         norm_or_part, norm_out, G, N, d.B, k32, slots, idx, jmap, top_part, block_top);
-    else
-      hipLaunchKernelGGL((select_small_kernel<false>), dim3(d.B), dim3(kSmallThreads), 0, s,
-                         norm_or_part, nullptr, 1, N, d.B, k32, slots, idx, jmap, top_part, block_top);
+      src = norm_out;
+      planes = 1;
+    }
+#define WCC_SMALL(SLOTS)                                                                               \
+  do {                                                                                                 \
+    if (planes > 1)                                                                                    \
+      hipLaunchKernelGGL((select_small_kernel<true, SLOTS>), dim3(d.B), dim3(kSmallThreads), 0, s,     \
+                         src, planes, N, d.B, k32, idx, jmap, top_part, block_top);                    \
+    else                                                                                               \
+      hipLaunchKernelGGL((select_small_kernel<false, SLOTS>), dim3(d.B), dim3(kSmallThreads), 0, s,    \
+                         src, 1, N, d.B, k32, idx, jmap, top_part, block_top);                         \
+  } while (0)
+    if (N <= 4 * kSmallThreads) WCC_SMALL(1);
+    else if (N <= 8 * kSmallThreads) WCC_SMALL(2);
+    else WCC_SMALL(4);
+#undef WCC_SMALL
     return hipGetLastError();
   }
   switch (L.sel_slots) {
