@@ -7,19 +7,19 @@ namespace {
 
 // x [B, C, H, W] -> coef [B, C, N]; partial norms over this block's channel group to
 // norm_part [G, B, N] (nullable); without STORE also the group's max |coefficient| per position
-// to max_part [G, B, N] (nullable).  block = 256.
-// SPLIT = false: grid = (ceil(units/4), G, B); each wave of a workgroup takes its own strip unit
-//                and walks all channels of the group.
-// SPLIT = true:  grid = (units, G, B); the four waves share one strip unit and take a quarter
-//                of the group's channels each (four times the waves in flight for the same
-//                number of partial-norm planes); their |coefficient| sums meet in LDS and are
-//                added in wave order.
+// to max_part [G, B, N] (nullable).
+// WPU = 1: block = 256, grid = (ceil(units/4), G, B); each wave of a workgroup takes its own strip
+//          unit and walks all channels of the group.
+// WPU > 1: block = 64 * WPU, grid = (units, G, B); the WPU waves of a workgroup share one strip
+//          unit and take a share of the group's channels each (WPU times the waves in flight for
+//          the same number of partial-norm planes); their |coefficient| sums meet in LDS and are
+//          added in wave order.
 // DWM: 0 = x is transformed as it is; 1, 2 = K_dw x is (wdw [C, 3, 3]; 2: the outside columns
 // of a wave row's first and last lane exist and are read).
 // XT: float or bf16_t, the storage type of x.  SQ: sums of squares instead of absolute values.
-template <int D, int V, bool SPLIT, bool STORE, int PF, int DWM, class XT, bool SQ = false,
+template <int D, int V, int WPU, bool STORE, int PF, int DWM, class XT, bool SQ = false,
           bool NT = false>
-__global__ __launch_bounds__(256) void haar_fwd_kernel(const XT *__restrict__ x,
+__global__ __launch_bounds__(WPU == 1 ? 256 : 64 * WPU) void haar_fwd_kernel(const XT *__restrict__ x,
                                                        float *__restrict__ coef,
                                                        float *__restrict__ norm_part,
                                                        float *__restrict__ max_part, Geo g,
@@ -28,17 +28,17 @@ __global__ __launch_bounds__(256) void haar_fwd_kernel(const XT *__restrict__ x,
                                                        const float *__restrict__ wdw) {
   constexpr int NS = slot_count(D, V);
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int unit = SPLIT ? (int)blockIdx.x : (int)blockIdx.x * 4 + wv;
+  const int unit = WPU > 1 ? (int)blockIdx.x : (int)blockIdx.x * 4 + wv;
   const int grp = blockIdx.y, b = blockIdx.z;
   // one workgroup per sample clears the state of the selection that follows this kernel
-  if (blockIdx.x == 0 && grp == 0) prep_sample(prep, b, threadIdx.x, 256);
+  if (blockIdx.x == 0 && grp == 0) prep_sample(prep, b, threadIdx.x, blockDim.x);
   LanePos<D> p;
   int row0, col0;
   locate<D, V>(m, g, unit, p, row0, col0);
   (void)coef;
   int c0 = grp * Cg, c1 = min(C, c0 + Cg);
-  if constexpr (SPLIT) {
-    const int Cw = (c1 - c0 + 3) / 4;
+  if constexpr (WPU > 1) {
+    const int Cw = (c1 - c0 + WPU - 1) / WPU;
     c0 = c0 + wv * Cw;
     c1 = min(c1, c0 + Cw);
   }
@@ -68,31 +68,36 @@ __global__ __launch_bounds__(256) void haar_fwd_kernel(const XT *__restrict__ x,
   }
 
   if (norm_part == nullptr) return;
-  if constexpr (SPLIT) {
-    __shared__ float comb[3][NS][kWave];
-    if (wv > 0) {
+  if constexpr (WPU > 1) {
+    // Every wave puts its values down, then adds up (takes the largest of) NS / WPU slots over all
+    // waves, in wave order; the first wave collects the results.
+    __shared__ float comb[WPU][NS][kWave];
+    constexpr int SW = (NS + WPU - 1) / WPU;
+    auto meet = [&](float (&v)[NS], auto &&join) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s) comb[wv - 1][s][lane] = sink.acc[s];
-    }
-    __syncthreads();
-    if (wv == 0) {
+      for (int s = 0; s < NS; ++s) comb[wv][s][lane] = v[s];
+      __syncthreads();
 #pragma unroll
-      for (int s = 0; s < NS; ++s)
-        sink.acc[s] = ((sink.acc[s] + comb[0][s][lane]) + comb[1][s][lane]) + comb[2][s][lane];
-    }
+      for (int i = 0; i < SW; ++i) {
+        const int s = wv * SW + i;
+        if (s < NS) {
+          float r = comb[0][s][lane];
+#pragma unroll
+          for (int u = 1; u < WPU; ++u) r = join(r, comb[u][s][lane]);
+          comb[0][s][lane] = r;
+        }
+      }
+      __syncthreads();
+      if (wv == 0) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) v[s] = comb[0][s][lane];
+      }
+    };
+    meet(sink.acc, [](float a, float c) { return a + c; });
     if constexpr (MX) {
-      if (max_part != nullptr) {  // (uniform over the grid) the maxima meet in the same buffer
+      if (max_part != nullptr) {  // (uniform over the grid)
         __syncthreads();
-        if (wv > 0) {
-#pragma unroll
-          for (int s = 0; s < NS; ++s) comb[wv - 1][s][lane] = sink.top[s];
-        }
-        __syncthreads();
-        if (wv == 0) {
-#pragma unroll
-          for (int s = 0; s < NS; ++s)
-            sink.top[s] = fmaxf(fmaxf(sink.top[s], comb[0][s][lane]), fmaxf(comb[1][s][lane], comb[2][s][lane]));
-        }
+        meet(sink.top, [](float a, float c) { return fmaxf(a, c); });
       }
     }
     if (wv > 0) return;
@@ -141,6 +146,12 @@ __global__ __launch_bounds__(256) void channel_norm_kernel(const float *__restri
   reinterpret_cast<float4 *>(norm + (size_t)b * N)[i4] = s;
 }
 
+// Most waves that can share a strip unit: the registers of a wave (d = 1: 48, 2: 88, 3: 176) times
+// their number fit a compute unit's.
+template <int D> constexpr int kMaxWpu = D <= 2 ? 16 : D == 3 ? 8 : 4;
+inline int max_wpu(int levels) { return levels <= 2 ? 16 : levels == 3 ? 8 : 4; }
+struct FwdShape { int G, wpu; };
+
 // x is fp32, or bf16 when the layer's activations are stored that way (fused calls only)
 template <int D, int V, bool STORE>
 hipError_t fwd_launch(const wcc_desc &d, const void *x, float *coef, float *norm_part,
@@ -153,69 +164,41 @@ hipError_t fwd_launch_t(const wcc_desc &d, const XT *x, float *coef, float *norm
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
   const StripMap m = make_map(d, V);
   const int Cg = (d.C_in + pl.G - 1) / pl.G;
-  const dim3 grid_split(m.units, pl.G, d.B), grid_flat((m.units + 3) / 4, pl.G, d.B), block(256);
-#define WCC_FWD(SPLIT, PF, DWM)                                                                       \
-  hipLaunchKernelGGL((haar_fwd_kernel<D, V, SPLIT, STORE, PF, DWM, XT>),                              \
-                     SPLIT ? grid_split : grid_flat, block, 0, s, x, coef, norm_part, max_part, g, m, d.C_in,   \
-                     Cg, d.B, prep, wdw)
-  if (d.norm == WCC_NORM_L2) {
-    // sums of squares: the norm-only pass over fp32 maps, prefetch depth 1
-    if constexpr (!STORE && std::is_same<XT, float>::value) {
-#define WCC_FWD_SQ(SPLIT, DWM)                                                                        \
-  hipLaunchKernelGGL((haar_fwd_kernel<D, V, SPLIT, false, 1, DWM, float, true>),                      \
-                     SPLIT ? grid_split : grid_flat, block, 0, s, x, coef, norm_part, max_part, g, m, d.C_in,   \
-                     Cg, d.B, prep, wdw)
-#define WCC_FWD_SQ_NT(DWM)                                                                            \
-  hipLaunchKernelGGL((haar_fwd_kernel<D, V, false, false, 1, DWM, float, true, true>), grid_flat,     \
-                     block, 0, s, x, coef, norm_part, max_part, g, m, d.C_in, Cg, d.B, prep, wdw)
-      const bool nt = pl.stream && !pl.split;  // (an input far larger than the memory-side cache)
-      if (wdw != nullptr) {
-        if constexpr (V == 4) {
-          const bool edges = dw_needs_edges(m);
-          if (nt)            { if (edges) WCC_FWD_SQ_NT(2); else WCC_FWD_SQ_NT(1); }
-          else if (pl.split) { if (edges) WCC_FWD_SQ(true, 2); else WCC_FWD_SQ(true, 1); }
-          else               { if (edges) WCC_FWD_SQ(false, 2); else WCC_FWD_SQ(false, 1); }
-          return hipGetLastError();
-        }
-        return hipErrorInvalidValue;
-      }
-      if (nt) WCC_FWD_SQ_NT(0); else if (pl.split) WCC_FWD_SQ(true, 0); else WCC_FWD_SQ(false, 0);
-#undef WCC_FWD_SQ_NT
-#undef WCC_FWD_SQ
-      return hipGetLastError();
+  // one launch: WPU waves a unit, DWM, and the sink's options
+  auto go = [&](auto wpu_c, auto dwm_c, auto sq_c, auto nt_c) {
+    constexpr int WPU = decltype(wpu_c)::value, DWM = decltype(dwm_c)::value;
+    constexpr bool SQ = decltype(sq_c)::value, NT = decltype(nt_c)::value;
+    hipLaunchKernelGGL((haar_fwd_kernel<D, V, WPU, STORE, 1, DWM, XT, SQ, NT>),
+                       dim3(WPU > 1 ? m.units : (m.units + 3) / 4, pl.G, d.B), dim3(WPU > 1 ? 64 * WPU : 256),
+                       0, s, x, coef, norm_part, max_part, g, m, d.C_in, Cg, d.B, prep, wdw);
+    return hipGetLastError();
+  };
+  // (a prefetch depth of two channels was measured on every workload and never paid)
+  using std::integral_constant;
+  auto with_waves = [&](auto dwm_c, auto sq_c) {
+    constexpr int DWM = decltype(dwm_c)::value;
+    if constexpr (!STORE) {  // an input far larger than the memory-side cache, read once
+      if (pl.stream && pl.wpu == 1) return go(integral_constant<int, 1>{}, dwm_c, sq_c, std::true_type{});
     }
+    if (pl.wpu == 1) return go(integral_constant<int, 1>{}, dwm_c, sq_c, std::false_type{});
+    if constexpr (DWM == 0 && kMaxWpu<D> > 4) {
+      if (pl.wpu > 4) return go(integral_constant<int, kMaxWpu<D>>{}, dwm_c, sq_c, std::false_type{});
+    }
+    return go(integral_constant<int, 4>{}, dwm_c, sq_c, std::false_type{});
+  };
+  auto with_sums = [&](auto dwm_c) {
+    if constexpr (!STORE && std::is_same<XT, float>::value) {
+      if (d.norm == WCC_NORM_L2) return with_waves(dwm_c, std::true_type{});
+    }
+    if (d.norm == WCC_NORM_L2) return hipErrorInvalidValue;  // fp32 maps, norm-only pass
+    return with_waves(dwm_c, std::false_type{});
+  };
+  if (wdw != nullptr) {  // K_dw in front of the transform (norm-only pass)
+    if constexpr (!STORE && (V == 4 || D == 4))
+      return dw_needs_edges(m) ? with_sums(integral_constant<int, 2>{}) : with_sums(integral_constant<int, 1>{});
     return hipErrorInvalidValue;
   }
-  if constexpr (!STORE) {
-    if (pl.stream && !pl.split) {  // an input far larger than the memory-side cache, read once
-#define WCC_FWD_NT(DWM)                                                                               \
-  hipLaunchKernelGGL((haar_fwd_kernel<D, V, false, false, 1, DWM, XT, false, true>), grid_flat,       \
-                     block, 0, s, x, coef, norm_part, max_part, g, m, d.C_in, Cg, d.B, prep, wdw)
-      if (wdw != nullptr) {
-        if constexpr (V == 4) {
-          if (dw_needs_edges(m)) WCC_FWD_NT(2); else WCC_FWD_NT(1);
-          return hipGetLastError();
-        }
-        return hipErrorInvalidValue;
-      }
-      WCC_FWD_NT(0);
-#undef WCC_FWD_NT
-      return hipGetLastError();
-    }
-  }
-  if constexpr (!STORE && V == 4) {
-    if (wdw != nullptr) {  // K_dw in front of the transform (norm-only pass)
-      const bool edges = dw_needs_edges(m);
-      if (pl.split) { if (edges) WCC_FWD(true, 1, 2); else WCC_FWD(true, 1, 1); }
-      else          { if (edges) WCC_FWD(false, 1, 2); else WCC_FWD(false, 1, 1); }
-      return hipGetLastError();
-    }
-  }
-  if (wdw != nullptr) return hipErrorInvalidValue;
-  // (a prefetch depth of two channels was measured on every workload and never paid)
-  if (pl.split) WCC_FWD(true, 1, 0); else WCC_FWD(false, 1, 0);
-#undef WCC_FWD
-  return hipGetLastError();
+  return with_sums(integral_constant<int, 0>{});
 }
 
 template <int D, int V, bool STORE>
@@ -230,48 +213,66 @@ hipError_t fwd_launch(const wcc_desc &d, const void *x, float *coef, float *norm
 
 }  // namespace
 
-// Every forward group costs one partial-norm plane (written once, read once): with >= 16
-// channels a group that is at most 1/16 of the transform's own traffic.  Measured on gfx950:
-// about a thousand waves, each walking as many channels as possible, stream best; more
-// groups only pay when a layer has fewer strips than that.
-int forward_groups(const wcc_desc &d, int front) {
-  const bool busy = front == kFrontChain || arithmetic_bound(d, front == kFrontDw);
-  return groups_for(d, d.C_in, busy ? 4096 : 1024, 4);
+// How the norm pass cuts a layer: wpu waves a strip unit and G channel groups (see the kernel).
+// About a thousand waves stream best, four thousand at d = 1, where a wave has only two rows of a
+// channel in flight.  What the strip units of the layer do not give is made up first by waves that
+// share a unit, whose sums meet in LDS, then by groups: every group is a plane of partial norms
+// (and one of maxima) that is written here and read by one of the selection's kernels, for a
+// small map through a single compute unit.  With groups alone and four waves a unit at most the
+// 16-layer stack took 852 us (820 now), 4 x 96 channels of 192 x 320 114 us (108), 2 x 144 of
+// 100 x 212 50.4 us (44.6), 8 x 128 of 192 x 640 311 us (305).
+static FwdShape fwd_shape(const wcc_desc &d, int front) {
+  const bool folded = front == kFrontDw;
+  if (front != kFrontNone) {
+    // K_dw in front: a wave holds two more rows and the taps; groups, and four waves a unit where
+    // there are still too few
+    FwdShape f{groups_for(d, d.C_in, front == kFrontChain || arithmetic_bound(d, folded) ? 4096 : 1024, 4), 1};
+    const StripMap m = make_map(d, lane_cols(d));
+    if (folded && (int64_t)m.units * d.B * f.G < 1024 && (d.C_in + f.G - 1) / f.G >= 8) f.wpu = 4;
+    return f;
+  }
+  const StripMap m = make_map(d, lane_cols(d));
+  const int64_t units = (int64_t)m.units * d.B;
+  const int64_t want = d.levels == 1 ? 4096 : 1024;
+  FwdShape f{1, 1};
+  if (units >= want) return f;  // enough strips: one wave walks all channels of its own
+  // (at least two channels a wave)
+  const int top = max_wpu(d.levels);
+  f.wpu = units * 4 < want && d.C_in >= 2 * top ? top : d.C_in >= 8 ? 4 : 1;
+  while (units * f.wpu * f.G < want && d.C_in / (f.G * 2 * f.wpu) >= 2) f.G *= 2;
+  return f;
 }
+
+int forward_groups(const wcc_desc &d, int front) { return fwd_shape(d, front).G; }
 
 template <bool STORE>
 hipError_t fwd_dispatch(const wcc_desc &d, const void *x, float *coef, float *norm_part,
                         float *max_part, Plan pl, const SelectPrep &prep, const float *wdw,
                         hipStream_t s) {
-  const bool v4 = d.W % 4 == 0;
+  const bool v4 = lane_cols(d) == 4;
   switch (d.levels) {
     case 1: return v4 ? fwd_launch<1, 4, STORE>(d, x, coef, norm_part, max_part, pl, prep, wdw, s)
                       : fwd_launch<1, 2, STORE>(d, x, coef, norm_part, max_part, pl, prep, wdw, s);
     case 2: return fwd_launch<2, 4, STORE>(d, x, coef, norm_part, max_part, pl, prep, wdw, s);
     case 3: return fwd_launch<3, 4, STORE>(d, x, coef, norm_part, max_part, pl, prep, wdw, s);
-    case 4: return fwd_launch<4, 4, STORE>(d, x, coef, norm_part, max_part, pl, prep, wdw, s);
+    case 4: return fwd_launch<4, 2, STORE>(d, x, coef, norm_part, max_part, pl, prep, wdw, s);
   }
   return hipErrorInvalidValue;
 }
 
-// G is fixed by the workspace layout (one partial-norm plane per group).  On small layers,
-// where even the groups leave fewer than 1024 waves, the four waves of a workgroup split a
-// group's channels (if each still gets >= 2).
-Plan fwd_plan(const wcc_desc &d, int G) {
-  const int Cg = (d.C_in + G - 1) / G;
-  const StripMap m = make_map(d, (d.W % 4 == 0) ? 4 : 2);
-  const int64_t waves = (int64_t)m.units * d.B * G;
-  return Plan{G, waves < 1024 && Cg >= 8, streams(d)};
+static Plan fwd_plan(const wcc_desc &d, int front) {
+  const FwdShape f = fwd_shape(d, front);
+  return Plan{f.G, f.wpu, streams(d)};
 }
 
-hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part, int G,
+hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part,
                            const SelectPrep &prep, hipStream_t s) {
-  return fwd_dispatch<true>(d, x, coef, norm_part, nullptr, fwd_plan(d, G), prep, nullptr, s);
+  return fwd_dispatch<true>(d, x, coef, norm_part, nullptr, fwd_plan(d, kFrontNone), prep, nullptr, s);
 }
 
 hipError_t launch_haar_norm(const wcc_desc &d, const void *x, float *norm_part, float *max_part,
-                            int G, const SelectPrep &prep, const float *wdw, hipStream_t s) {
-  const Plan pl = fwd_plan(d, G);
+                            const SelectPrep &prep, const float *wdw, hipStream_t s) {
+  const Plan pl = fwd_plan(d, wdw ? kFrontDw : kFrontNone);
   return fwd_dispatch<false>(d, x, nullptr, norm_part, max_part, pl, prep, wdw, s);
 }
 

@@ -20,7 +20,7 @@ namespace {
 // LDS tile laid out [lane][slot] whose other cells stay zero, and every lane reads its slots
 // back from there with 16-byte reads.  Lanes outside the plane take part in the list work; their
 // stores carry an offset beyond the plane, which the hardware drops.  Strips that keep more than kInvCap positions, layers with more than 2^20
-// kept positions, and d = 4 (whose tile would not fit) take the plain path: ranks in registers,
+// kept positions take the plain path: ranks in registers,
 // one conditional load per slot.
 // The channel walk of the staged path with NI dense fetches per channel.  mine[i]: the lane's
 // list entries.  PADDED: entries past the end of the list repeat its first entry (they fetch the
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
                                                             const YT *residual) {
   constexpr int R = 1 << D;
   constexpr int NS = slot_count(D, V);
-  constexpr bool kStaged = D <= 3;  // the [lane][slot] tiles of four waves fit in LDS
+  constexpr bool kStaged = D <= 3 || V == 2;  // the [lane][slot] tiles of four waves fit in LDS
   constexpr int CAP = NS * kWave < kInvCap ? NS * kWave : kInvCap;  // entries a wave can pack
   constexpr int STRIDE = tile_stride((NS + 3) / 4 * 4);  // words between two lanes' slots
   static_assert(NS <= 128, "slot mask is 128 bits wide");
@@ -281,13 +281,13 @@ hipError_t inv_launch(const wcc_desc &d, int64_t k, const float *yc, const int32
 
 hipError_t inv_dispatch(const wcc_desc &d, int64_t k, const float *yc, const int32_t *jmap, void *y,
                         int G, float *scratch, const void *residual, hipStream_t s) {
-  const bool v4 = d.W % 4 == 0;
+  const bool v4 = lane_cols(d) == 4;
   switch (d.levels) {
     case 1: return v4 ? inv_launch<1, 4>(d, k, yc, jmap, y, G, scratch, residual, s)
                       : inv_launch<1, 2>(d, k, yc, jmap, y, G, scratch, residual, s);
     case 2: return inv_launch<2, 4>(d, k, yc, jmap, y, G, scratch, residual, s);
     case 3: return inv_launch<3, 4>(d, k, yc, jmap, y, G, scratch, residual, s);
-    case 4: return inv_launch<4, 4>(d, k, yc, jmap, y, G, scratch, residual, s);
+    case 4: return inv_launch<4, 2>(d, k, yc, jmap, y, G, scratch, residual, s);
   }
   return hipErrorInvalidValue;
 }

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x
   // the maximum and the store offsets over the list rows instead of over every slot makes it
   // 20 % faster (block at keep 1/8: 375 -> 297 us).
   constexpr int NS = slot_count(D, V);
-  constexpr bool kStaged = V == 4 && (D == 2 || D == 3) && (DWM == 0 || sizeof(XT) == 2);
+  constexpr bool kStaged = ((V == 4 && (D == 2 || D == 3)) || D == 4) && (DWM == 0 || sizeof(XT) == 2);
   if constexpr (kStaged) {
     __shared__ uint32_t tiles[4][NS * kWave];
     constexpr int kRankBits = 20;  // list entry = rank | tile index << 20
@@ -210,7 +210,7 @@ hipError_t keep_launch_t(const wcc_desc &d, int64_t k, const XT *x, const int32_
       hipLaunchKernelGGL((haar_keep_kernel<D, V, PF, DWM, false, XT>), grid, dim3(256), 0, s, x,  \
                          jmap, xc, alpha_slots, g, m, d.C_in, Cg, cstep, k, wdw, 0.f, nullptr, 0, nullptr);                    \
   } while (0)
-  if constexpr (V == 4) {
+  if constexpr (V == 4 || D == 4) {
     if (wdw != nullptr) {  // K_dw in front of the transform
       if (dw_needs_edges(m)) WCC_KEEP(1, 2); else WCC_KEEP(1, 1);
       return hipGetLastError();
@@ -245,13 +245,13 @@ hipError_t keep_launch(const wcc_desc &d, int64_t k, const void *x, const int32_
 hipError_t keep_dispatch(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap, void *xc,
                          float *alpha_slots, Plan pl, const float *wdw, float q_alpha,
                          const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
-  const bool v4 = d.W % 4 == 0;
+  const bool v4 = lane_cols(d) == 4;
   switch (d.levels) {
     case 1: return v4 ? keep_launch<1, 4>(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s)
                       : keep_launch<1, 2>(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
     case 2: return keep_launch<2, 4>(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
     case 3: return keep_launch<3, 4>(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
-    case 4: return keep_launch<4, 4>(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+    case 4: return keep_launch<4, 2>(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
   }
   return hipErrorInvalidValue;
 }
@@ -259,7 +259,7 @@ hipError_t keep_dispatch(const wcc_desc &d, int64_t k, const void *x, const int3
 hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap,
                             void *xc, float *alpha_slots, const float *wdw, float q_alpha,
                             const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
-  const Plan pl{groups_for(d, d.C_in, arithmetic_bound(d, wdw != nullptr) ? 4096 : 1024, 4), false,
+  const Plan pl{groups_for(d, d.C_in, arithmetic_bound(d, wdw != nullptr) ? 4096 : 1024, 4), 1,
                 streams(d)};
   return keep_dispatch(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
 }

@@ -519,6 +519,13 @@ __device__ __forceinline__ void workgroup_lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Columns a lane owns: four, or two where four do not divide the width (possible at d = 1 only)
+// and at d = 4, whose 16 rows of four columns fill the register file (70 slots a lane) and leave
+// neither the packed lists of the keep pass and the inverse room in LDS nor a second wave a SIMD:
+// with four columns the keep pass and the inverse of 3 x 48 -> 96 channels of 16 x 64 (all kept) took
+// 28 and 24 us (14 and 15 now), the keep pass of 2 x 96 channels of 256 x 512 (1/8 kept) 34 us (24).
+__host__ __device__ inline int lane_cols(const wcc_desc &d) { return d.W % 4 != 0 || d.levels == 4 ? 2 : 4; }
+
 // A wave covers (64 / lpr) strips x (lpr lanes of V columns).  lpr is the power of two that
 // leaves the fewest lanes idle (ties: the wider one, for longer contiguous row segments);
 // rows narrower than 16 lanes are not split further.
@@ -547,7 +554,7 @@ inline StripMap make_map(const wcc_desc &d, int V) {
 // How a pass over the channels is cut into waves.
 struct Plan {
   int G;       // channel groups (grid.y)
-  bool split;  // forward/norm pass only: the 4 waves of a workgroup split a group's channels
+  int wpu;     // forward/norm pass only: waves of a workgroup that share a strip unit's channels
   bool stream; // x is read with streaming loads (maps far larger than the memory-side cache)
 };
 
@@ -558,8 +565,7 @@ inline bool dw_needs_edges(const StripMap &m) { return m.col_segs > 1 || m.lpr <
 // Channel groups: split the channels until the launch has `want_waves` waves to cover the
 // memory latency of 256 CUs, but keep at least `min_ch` channels in a group.
 inline int groups_for(const wcc_desc &d, int C, int64_t want_waves, int min_ch) {
-  const int V = (d.W % 4 == 0) ? 4 : 2;
-  const StripMap m = make_map(d, V);
+  const StripMap m = make_map(d, lane_cols(d));
   const int64_t waves = (int64_t)m.units * d.B;
   int G = 1;
   if (waves >= want_waves / 2) return G;  // already enough strips: keep the channel walk whole

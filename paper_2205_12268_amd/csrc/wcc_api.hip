@@ -54,9 +54,6 @@ namespace {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-constexpr int64_t kEarlyAlphaMinPositions = 16384;  // (the one-workgroup selection's limit)
-constexpr int64_t kEarlyAlphaMinKept = (int64_t)4 << 20;
-
 wcc_status check_desc(const wcc_desc *d) {
   if (!d) return WCC_ERR_NULL;
   if (d->B < 1 || d->C_in < 1 || d->C_out < 1 || d->H < 2 || d->W < 2) return WCC_ERR_SHAPE;
@@ -206,13 +203,12 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   //                    loader quantises.
   const bool given = quant && alpha_in > 0.f;
   const int n_top = select_top_count(d, L);
-  // (small layers -- a plane that the one-workgroup selection takes and a few million kept
-  // coefficients at most -- stay on the fp32 route: they are bound by launches, not bytes, and
-  // the extra loads of the maxima only lengthen them: measured on the 16-layer stack, 869 vs
-  // 851 us at keep 1/4)
-  const bool small_layer = (int64_t)d.H * d.W <= kEarlyAlphaMinPositions &&
-                           (int64_t)d.B * d.C_in * k < kEarlyAlphaMinKept;
-  const bool early = quant && !given && list == kListSelect && ks % 4 == 0 && n_top <= 8192 && !small_layer;
+  // (A small layer with K_dw in front -- a plane that the one-workgroup selection takes and a few
+  // million kept coefficients at most -- stays on the fp32 route: its passes run many channel
+  // groups, whose maxima the selection would have to read as well, and quantise slot by slot:
+  // 4 x 240 channels of 40 x 32, all kept: 96 us a block, 102 with the early alpha.)
+  const bool small_dw = wdw && (int64_t)d.H * d.W <= 16384 && (int64_t)d.B * d.C_in * k < ((int64_t)4 << 20);
+  const bool early = quant && !given && list == kListSelect && ks % 4 == 0 && n_top <= 8192 && !small_dw;
   const bool codes_now = early || (given && ks % 4 == 0);
   float *tops = reinterpret_cast<float *>(ws + L.block_top);
   // the contraction finds alpha in the slots: as the largest of them, or (early) as the one
@@ -227,7 +223,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
       WCC_TRY(launch_chain_norm(d, *src, wdw, L.G == 1 ? norm : part, top, L.G,
                                 make_prep(ws, L, slots, quant ? alpha_in : 0.f), s));
     else
-      WCC_TRY(launch_haar_norm(d, x, L.G == 1 ? norm : part, top, L.G,
+      WCC_TRY(launch_haar_norm(d, x, L.G == 1 ? norm : part, top,
                                make_prep(ws, L, slots, quant ? alpha_in : 0.f), wdw, s));
     WCC_TRY(mark(WCC_T_HAAR_FWD, 1));
     // B: norms, index set I (ascending), rank map for the inverse
@@ -421,7 +417,7 @@ wcc_status wcc_haar_fwd(wcc_ctx *ctx, const wcc_desc *desc, const float *x, floa
     // (sums of squares are taken from the stored coefficients in a pass of their own)
     wcc_desc plain = *desc;
     plain.norm = WCC_NORM_L1;
-    WCC_TRY(launch_haar_fwd(plain, x, coef, nullptr, L.G, no_prep, s));
+    WCC_TRY(launch_haar_fwd(plain, x, coef, nullptr, no_prep, s));
     if (norm)
       WCC_TRY(launch_channel_norm(coef, desc->B, desc->C_in, (int64_t)desc->H * desc->W, true, norm, s));
     return WCC_OK;
@@ -429,10 +425,10 @@ wcc_status wcc_haar_fwd(wcc_ctx *ctx, const wcc_desc *desc, const float *x, floa
   if ((st = need_ws(ctx, L)) != WCC_OK) return st;
   const int64_t BN = (int64_t)desc->B * desc->H * desc->W;
   if (L.G == 1) {
-    WCC_TRY(launch_haar_fwd(*desc, x, coef, norm, 1, no_prep, s));
+    WCC_TRY(launch_haar_fwd(*desc, x, coef, norm, no_prep, s));
   } else {
     float *part = reinterpret_cast<float *>(static_cast<char *>(ctx->ws) + L.norm_part);
-    WCC_TRY(launch_haar_fwd(*desc, x, coef, part, L.G, no_prep, s));
+    WCC_TRY(launch_haar_fwd(*desc, x, coef, part, no_prep, s));
     WCC_TRY(launch_norm_reduce(part, L.G, BN, norm, s));
   }
   return WCC_OK;

@@ -167,15 +167,16 @@ hipError_t launch_chain_keep(const wcc_desc &d, int64_t k, const ChainSrc &src, 
                              const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s);
 
 // launchers (each returns hipGetLastError() after its launches)
+// (norm_part, max_part: one plane for each of the forward_groups() channel groups)
 hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part,
-                           int G, const SelectPrep &prep, hipStream_t s);
+                           const SelectPrep &prep, hipStream_t s);
 // norm-only pass (no coefficient is written) and keep-only pass of the fused layer
 // wdw (nullable, [C_in, 3, 3]): the transform's input is the depthwise 3x3 convolution of x
 // with these kernels, computed on the fly; needs W % 4 == 0
 // (x: fp32, or bf16 if d.act_dtype says so; the same for y and residual further down)
 // max_part (nullable, [G, B, N]): also receives every group's largest |coefficient| per position
 hipError_t launch_haar_norm(const wcc_desc &d, const void *x, float *norm_part, float *max_part,
-                            int G, const SelectPrep &prep, const float *wdw, hipStream_t s);
+                            const SelectPrep &prep, const float *wdw, hipStream_t s);
 // q_alpha > 0, or alpha_src given (n_alpha floats whose largest is the clipping parameter,
 // read on the device): xc is int8 codes for that clipping parameter (alpha_slots unused); else
 // xc is fp32 and alpha_slots (nullable) is raised to max |kept coefficient|
