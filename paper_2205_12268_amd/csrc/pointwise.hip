@@ -539,6 +539,223 @@ __global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
   }
 }
 
+// ---- the same on weights in the order of the matrix instructions ------------------------------
+// What bounds the kernel above is LDS: with 64 x 64 wave tiles every matrix instruction needs one
+// 16-byte fragment read, and three workgroups a compute unit keep LDS busy all the time.  Here a
+// wave's tile is 64 rows x 128 (or 64) positions and only the activations go through LDS (four
+// reads for eight instructions); the weights come straight from memory into registers, reloaded a
+// stage ahead as each is used.  A lane's 16 bytes of a row are one of 32 rows' pieces, 32 bytes a
+// row and instruction, which cost the address unit as much as the matrix cores had to do
+// (1024 -> 256 channels: 110 us); so the weights are first brought into the order of the
+// instructions (PackJob), one contiguous KiB a load: 88 us.  The fused calls do that inside the
+// selection's first kernel, in memory that the codes leave free; the stage call, which has
+// no workspace, keeps the kernel above.
+// A workgroup's four waves take 64 * WM rows (WM waves) x 32 * CB * 4 / WM positions.  A stage is 128
+// bytes of K (64 channels of bf16, 128 of int8), two LDS buffers, one barrier a stage; the
+// activations of the stage after next are in flight under the matrix instructions.  The tiles are
+// dealt to the dies in contiguous chunks of the list, positions fastest (256 -> 1024 channels
+// 125 us, in the natural order 135).
+// Measured (8 x 16384 positions): 1024 -> 256 channels 120 -> 88 us with bf16 weights, 94 -> 70
+// with int8; 256 -> 1024 158 -> 125 and 142 -> 107; 1024 -> 4096 and back at 6 x 2304: 148 -> 109 and
+// 161 -> 107 us (1.08 PFLOP/s).
+__global__ __launch_bounds__(256) void pack_weights_kernel(PackJob job) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e < job.total) job.out[e] = pack_piece(job, e);
+}
+
+template <bool I8W, int WM, int CB>
+__global__ __launch_bounds__(256, CB == 4 ? 2 : 3) void pointwise_wide_kernel(
+    const uint4 *__restrict__ w, const float *__restrict__ w_scale, const int8_t *__restrict__ xq,
+    const float *__restrict__ alpha, int n_alpha, float *alpha_out, float *__restrict__ yc, int M,
+    int K, int64_t k, bool stream_out, int gx, int gy, int tiles) {
+  constexpr int ESZ = I8W ? 1 : 2;
+  constexpr int KB = 128, LDR = KB + 16;   // bytes of K a stage, LDS row bytes
+  constexpr int KC = KB / ESZ;             // channels a stage: 64 or 128
+  constexpr int WN = 4 / WM;               // waves along the positions
+  constexpr int TM = 64 * WM, TN = 32 * CB * WN;
+  constexpr int NG = TN / 4;               // groups of four positions
+  constexpr int DW = NG * KC / 256;        // activation words a thread and stage
+  constexpr int CPT = I8W ? (DW >= 16 ? 16 : 8) : (DW >= 8 ? 8 : 4);  // channels of a patch
+  constexpr int PT = DW / CPT;             // patches a thread
+  constexpr int KQ = KC / CPT;             // channel groups of a stage
+  static_assert(PT >= 1 && NG * KQ == 256 * PT, "patches cover the stage");
+  __shared__ __attribute__((aligned(16))) unsigned char Bs[2][TN * LDR];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int wm = wv % WM, wn = wv / WM;
+  const int tile = (blockIdx.x % kDies) * (gridDim.x / kDies) + blockIdx.x / kDies;
+  const float al = alpha_max(alpha, n_alpha);
+  if (alpha_out && tile == 0 && threadIdx.x == 0) alpha_out[0] = al;
+  if (tile >= tiles) return;
+  const int b = tile / (gx * gy);
+  const int by = (tile / gx) % gy, bx = tile % gx;
+  const int64_t n0 = (int64_t)bx * TN;
+  const int m0 = by * TM + wm * 64;
+  const int8_t *xb = xq + (size_t)b * K * k;
+  const int stages = (K + KC - 1) / KC;
+
+  using Acc = std::conditional_t<I8W, intx16, floatx16>;
+  Acc acc[2][CB];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < CB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  // (what lies outside returns zeros: blocks of rows past the last one, stages past the last one of
+  // the last block; a stage past the end of another block reads the next block's weights, which
+  // meet nothing that is used)
+  const __amdgpu_buffer_rsrc_t wdesc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint4 *>(w), 0, (int)(uint32_t)((int64_t)((M + 63) / 64 * 64) * stages * KB), 0x00020000);
+  const __amdgpu_buffer_rsrc_t xdesc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<int8_t *>(xb), 0, (int)(uint32_t)((int64_t)K * k), 0x00020000);
+  const int fr = lane & 31, half = lane >> 5;
+  // weights of step ks of a stage, for the wave's two blocks of 32 rows
+  u32x4 a[4][2];
+  const uint32_t wline = (uint32_t)(m0 / 32) * (uint32_t)(stages * 4) * 1024u + (uint32_t)lane * 16u;
+  auto load_a = [&](int st, int ks) {
+    const uint32_t at = wline + (uint32_t)(st * 4 + ks) * 1024u;
+    a[ks][0] = __builtin_amdgcn_raw_buffer_load_b128(wdesc, at, 0, 0);
+    a[ks][1] = __builtin_amdgcn_raw_buffer_load_b128(wdesc, at + (uint32_t)stages * 4096u, 0, 0);
+  };
+  // activations: CPT channels x 4 positions a patch
+  uint32_t x[PT][CPT];
+  uint32_t xcol[PT];
+#pragma unroll
+  for (int p = 0; p < PT; ++p) {
+    const int e = t + 256 * p, g = e % NG, kq = e / NG;
+    xcol[p] = (uint32_t)(n0 + 4 * g) + (uint32_t)(kq * CPT) * (uint32_t)k;
+  }
+  auto load_x = [&](int st) {
+#pragma unroll
+    for (int p = 0; p < PT; ++p)
+#pragma unroll
+      for (int c = 0; c < CPT; ++c)
+        x[p][c] = __builtin_amdgcn_raw_buffer_load_b32(xdesc, xcol[p] + (uint32_t)(st * KC + c) * (uint32_t)k, 0, 0);
+  };
+  auto stash = [&](int buf) {
+#pragma unroll
+    for (int p = 0; p < PT; ++p) {
+      const int e = t + 256 * p, g = e % NG, kq = e / NG;
+      uint32_t o[4][CPT * ESZ / 4];  // [position][words]
+      if constexpr (I8W) {
+#pragma unroll
+        for (int c = 0; c < CPT; c += 4) {
+          const uint32_t lo01 = __builtin_amdgcn_perm(x[p][c + 1], x[p][c], 0x05010400u);
+          const uint32_t lo23 = __builtin_amdgcn_perm(x[p][c + 3], x[p][c + 2], 0x05010400u);
+          const uint32_t hi01 = __builtin_amdgcn_perm(x[p][c + 1], x[p][c], 0x07030602u);
+          const uint32_t hi23 = __builtin_amdgcn_perm(x[p][c + 3], x[p][c + 2], 0x07030602u);
+          o[0][c / 4] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
+          o[1][c / 4] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+          o[2][c / 4] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
+          o[3][c / 4] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int c = 0; c < CPT; c += 2) {
+            const float f0 = (float)((int)(x[p][c] << (24 - 8 * i)) >> 24);
+            const float f1 = (float)((int)(x[p][c + 1] << (24 - 8 * i)) >> 24);
+            o[i][c / 2] = __builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0), 0x07060302u);
+          }
+      }
+      constexpr int WPN = 32 * CB;  // positions of a wave
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int nl = 4 * g + i;
+        const int row = (nl / WPN) * WPN + (nl % CB) * 32 + (nl % WPN) / CB;
+        unsigned char *dst = &Bs[buf][row * LDR + kq * CPT * ESZ];
+        if constexpr (CPT * ESZ == 16) *reinterpret_cast<uint4 *>(dst) = make_uint4(o[i][0], o[i][1], o[i][2], o[i][3]);
+        else *reinterpret_cast<uint2 *>(dst) = make_uint2(o[i][0], o[i][1]);
+      }
+    }
+  };
+
+  load_x(0);
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) load_a(0, ks);
+  stash(0);
+  load_x(1);
+  __syncthreads();
+  for (int s = 0; s < stages; ++s) {
+    const unsigned char *bs = &Bs[s & 1][(wn * 32 * CB + fr) * LDR + half * 16];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      uint4 bb[CB];
+#pragma unroll
+      for (int j = 0; j < CB; ++j) bb[j] = *reinterpret_cast<const uint4 *>(bs + j * 32 * LDR + ks * 32);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+          if constexpr (I8W)
+            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(intx4, a[ks][i]),
+                                                             __builtin_bit_cast(intx4, bb[j]), acc[i][j], 0, 0, 0);
+          else
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[ks][i]),
+                                                               __builtin_bit_cast(bf16x8, bb[j]), acc[i][j], 0, 0, 0);
+        }
+      load_a(s + 1, ks);
+    }
+    stash((s + 1) & 1);
+    load_x(s + 2);
+    __syncthreads();
+  }
+
+  const float sx = al / 127.f;
+  const int64_t n = n0 + wn * 32 * CB + CB * fr;
+  if (n < k) {
+    auto store_rows = [&](auto whole_c, auto stream_c) {
+      constexpr bool WHOLE = decltype(whole_c)::value, STREAM = decltype(stream_c)::value;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = m0 + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+          if (WHOLE || m < M) {
+            const float sc = I8W ? sx * w_scale[m] : sx;
+            float *dst = yc + ((size_t)b * M + m) * k + n;
+            if constexpr (CB == 4) {
+              floatx4 o = {(float)acc[i][0][r] * sc, (float)acc[i][1][r] * sc, (float)acc[i][2][r] * sc,
+                           (float)acc[i][3][r] * sc};
+              if constexpr (STREAM) __builtin_nontemporal_store(o, reinterpret_cast<floatx4 *>(dst));
+              else *reinterpret_cast<floatx4 *>(dst) = o;
+            } else {
+              floatx2 o = {(float)acc[i][0][r] * sc, (float)acc[i][1][r] * sc};
+              if constexpr (STREAM) __builtin_nontemporal_store(o, reinterpret_cast<floatx2 *>(dst));
+              else *reinterpret_cast<floatx2 *>(dst) = o;
+            }
+          }
+        }
+    };
+    const bool whole = m0 + 64 <= M;
+    if (whole) {
+      if (stream_out) store_rows(std::true_type{}, std::true_type{});
+      else store_rows(std::true_type{}, std::false_type{});
+    } else {
+      if (stream_out) store_rows(std::false_type{}, std::true_type{});
+      else store_rows(std::false_type{}, std::false_type{});
+    }
+  }
+}
+
+template <bool I8W, int WM, int CB>
+hipError_t wide_launch(const wcc_desc &d, int64_t k, const uint4 *packed, const float *w_scale, const void *xc,
+                       const float *alpha, int n_alpha, float *alpha_out, float *yc, hipStream_t s) {
+  constexpr int TM = 64 * WM, TN = 32 * CB * (4 / WM);
+  const int64_t gx = (k + TN - 1) / TN, gy = (d.C_out + TM - 1) / TM;
+  const int64_t tiles = gx * gy * d.B;
+  if (tiles > (int64_t)1 << 30) return hipErrorInvalidValue;
+  dim3 grid((unsigned)((tiles + kDies - 1) / kDies * kDies)), block(256);
+  const bool stream_out = (int64_t)d.B * d.C_out * k * 4 > ((int64_t)512 << 20);
+  hipLaunchKernelGGL((pointwise_wide_kernel<I8W, WM, CB>), grid, block, 0, s, packed, w_scale,
+                     static_cast<const int8_t *>(xc), alpha, n_alpha, alpha_out, yc, d.C_out, d.C_in, k,
+                     stream_out, (int)gx, (int)gy, (int)tiles);
+  return hipGetLastError();
+}
+
 template <bool I8W, int WM>
 hipError_t tile_launch(const wcc_desc &d, int64_t k, const void *w, const float *w_scale, const void *xc,
                        const float *alpha, int n_alpha, float *alpha_out, float *yc, hipStream_t s) {
@@ -810,6 +1027,43 @@ hipError_t f32_dispatch(const wcc_desc &d, int64_t k, const void *w, const float
 }
 
 }  // namespace
+
+// Layers for the kernel on packed weights: 256 channels and more (128 -> 128 measured 5 % slower than
+// the stream kernel, 64 -> 256 the same), more than one 64-row tile, rows of whole 16-byte pieces,
+// and byte offsets that fit 32 bits.
+PackJob pack_job(const wcc_desc &d, int64_t k, const void *w, void *room, size_t room_bytes) {
+  PackJob job{nullptr, nullptr, 0, 0, 0, 0, 0};
+  const bool i8 = d.w_dtype == WCC_I8 || d.w_dtype == WCC_I4;
+  if (d.act_quant_bits != 8 || k % 4 != 0 || (!i8 && d.w_dtype != WCC_BF16)) return job;
+  if (d.C_in < 256 || d.C_out <= 64 || d.C_in % (i8 ? 16 : 8) != 0) return job;
+  const int64_t limit = (int64_t)0xFFFFFFF0;
+  const int64_t steps = ((int64_t)d.C_in * (i8 ? 1 : 2) + 127) / 128 * 4, rows = ((int64_t)d.C_out + 63) / 64 * 64;
+  const int64_t bytes = rows * steps * 32;
+  if (bytes > ((int64_t)1 << 30) || (size_t)bytes > room_bytes || (int64_t)d.C_in * k > limit) return job;
+  if ((k + 63) / 64 * ((d.C_out + 127) / 128) * (int64_t)d.B > ((int64_t)1 << 30)) return job;
+  return PackJob{w, static_cast<uint4 *>(room), d.C_out, d.C_in, (int)steps, (int)(bytes / 16), d.w_dtype};
+}
+
+hipError_t launch_pack(const PackJob &job, hipStream_t s) {
+  hipLaunchKernelGGL(pack_weights_kernel, dim3((job.total + 255) / 256), dim3(256), 0, s, job);
+  return hipGetLastError();
+}
+
+hipError_t launch_pointwise_packed(const wcc_desc &d, int64_t k, const PackJob &job, const float *w_scale,
+                                   const void *xc, const float *alpha, int n_alpha, float *alpha_out,
+                                   float *yc, hipStream_t s) {
+  // The largest tile that still gives a compute unit two workgroups, else 256 x 64; layers of up to
+  // 128 rows do not fill a 256-row tile.
+  auto wgs = [&](int tm, int tn) { return (k + tn - 1) / tn * ((d.C_out + tm - 1) / tm) * (int64_t)d.B; };
+#define WCC_WIDE(WM, CB)                                                                                          \
+  return job.wt == WCC_BF16                                                                                       \
+             ? wide_launch<false, WM, CB>(d, k, job.out, w_scale, xc, alpha, n_alpha, alpha_out, yc, s)           \
+             : wide_launch<true, WM, CB>(d, k, job.out, w_scale, xc, alpha, n_alpha, alpha_out, yc, s)
+  if (d.C_out > 128 && wgs(256, 128) >= 512) WCC_WIDE(4, 4);
+  if (d.C_out <= 128 && wgs(128, 128) >= 512) WCC_WIDE(2, 2);
+  WCC_WIDE(4, 2);
+#undef WCC_WIDE
+}
 
 hipError_t launch_pointwise(const wcc_desc &d, int64_t k, const void *w, const float *w_scale,
                             const void *xc, bool xc_is_f32, const float *alpha, int n_alpha,

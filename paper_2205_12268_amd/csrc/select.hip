@@ -245,10 +245,24 @@ __device__ __forceinline__ void current_state(const uint32_t *hist_b, SelectStat
   }
 }
 
+// A job of moving 16-byte pieces done beside a kernel that is bound by its own latencies: the first
+// piece's load goes out early, its store and the few pieces after it follow at the end.
+struct PackOnTheSide {
+  uint4 v;
+  int e;
+  __device__ __forceinline__ PackOnTheSide(const PackJob &job, int first) : v(make_uint4(0, 0, 0, 0)), e(first) {
+    if (e < job.total) v = pack_piece(job, e);
+  }
+  __device__ __forceinline__ void finish(const PackJob &job, int threads) const {
+    if (e < job.total) job.out[e] = v;
+    for (int i = e + threads; i < job.total; i += threads) job.out[i] = pack_piece(job, i);
+  }
+};
+
 // One histogram pass.  grid = (nblk, B), block = 256.
 // PASS 0 with REDUCE reads partial norms `src` [G, B, N] and writes `norm`; otherwise src is
 // the norm array itself.  PASS 2 also writes this workgroup's suffix sums and its count of
-// keys above the 22-bit prefix.
+// keys above the 22-bit prefix.  PASS 0 also carries out `job`.
 // SLOTS: 16-byte loads per thread (a workgroup takes 1024 * SLOTS keys; slot s of thread t
 // covers the four positions from (s * 256 + t) * 4 on inside the workgroup's chunk).
 template <int PASS, bool REDUCE, int SLOTS>
@@ -258,7 +272,8 @@ __global__ __launch_bounds__(kThreads) void select_hist_kernel(const float *__re
                                                                uint32_t *hist, SelectState *st,
                                                                int nblk,
                                                                uint16_t *__restrict__ block_sfx,
-                                                               uint32_t *__restrict__ block_gthi) {
+                                                               uint32_t *__restrict__ block_gthi,
+                                                               PackJob job) {
   constexpr int bins = PASS == 2 ? 1024 : kRadixBins;
   __shared__ uint32_t lh[kRadixBins];
   __shared__ uint32_t tmp[kWaves];
@@ -277,6 +292,8 @@ __global__ __launch_bounds__(kThreads) void select_hist_kernel(const float *__re
     k4[sl] = make_uint4(0, 0, 0, 0);  // N is a multiple of 4: a slot's four keys are all in or all out
     if (q < N) k4[sl] = load_keys<REDUCE>(src, norm, G, (int64_t)B * N, (int64_t)b * N + q);
   }
+  const int first_piece = (int)((blockIdx.y * gridDim.x + blockIdx.x) * kThreads + t);
+  const PackOnTheSide side(job, PASS == 0 ? first_piece : job.total);
   uint32_t prefix, remain;
   current_state<PASS>(hist_b, st + b, k, prefix, remain, tmp, bcast, blockIdx.x == 0);
   __syncthreads();
@@ -296,6 +313,7 @@ __global__ __launch_bounds__(kThreads) void select_hist_kernel(const float *__re
     const uint32_t v = lh[i];
     if (v) atomicAdd(&gh[i], v);
   }
+  if constexpr (PASS == 0) side.finish(job, (int)(gridDim.x * gridDim.y * kThreads));
   if constexpr (PASS == 2) {
     // sfx[d] = number of this workgroup's matching keys with low digit >= d
     constexpr int per = bins / kThreads;  // 4 digits per thread, from the top
@@ -461,7 +479,7 @@ template <bool REDUCE, int SLOTS>
 __global__ __launch_bounds__(kSmallThreads) void select_small_kernel(
     const float *__restrict__ src, int G, int64_t N, int B, uint32_t k,
     int32_t *__restrict__ idx, int32_t *__restrict__ jmap,
-    const float *__restrict__ top_part, float *block_top) {
+    const float *__restrict__ top_part, float *block_top, PackJob job) {
   __shared__ __attribute__((aligned(16))) uint32_t lh[kSmallBins];
   __shared__ __attribute__((aligned(16))) uint32_t list[kSmallList];
   __shared__ uint32_t ends[2 * kSmallWaves];
@@ -495,6 +513,7 @@ __global__ __launch_bounds__(kSmallThreads) void select_small_kernel(
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) m[s] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
+  const PackOnTheSide side(job, (int)blockIdx.x * kSmallThreads + t);
   clear();
   if constexpr (REDUCE) {
     constexpr int PL = 4 / SLOTS;  // planes a round: four loads in flight of each kind
@@ -674,6 +693,7 @@ __global__ __launch_bounds__(kSmallThreads) void select_small_kernel(
       if (jmap) *reinterpret_cast<int4 *>(jmap + (size_t)b * N + pos) = make_int4(jm[0], jm[1], jm[2], jm[3]);
     }
   }
+  side.finish(job, (int)gridDim.x * kSmallThreads);
   if (top_part)  // (uniform over the grid)
     publish_top<kSmallWaves>(kept_top, block_top, (size_t)b, tmp);
 }
@@ -728,6 +748,14 @@ int select_top_count(const wcc_desc &d, const WsLayout &L) {
   return (int64_t)d.H * d.W <= kSmallMaxN ? d.B : d.B * L.nblk;
 }
 
+// Up to four pieces a thread of the first kernel: 16 KiB of weights a 256-thread workgroup.  A layer of
+// few select workgroups and many weights is better off with a launch over the whole chip (4 us).
+bool select_packs(const wcc_desc &d, const WsLayout &L, const PackJob &job) {
+  const int64_t threads = (int64_t)d.H * d.W <= kSmallMaxN ? (int64_t)d.B * kSmallThreads
+                                                           : (int64_t)d.B * L.nblk * kThreads;
+  return job.total > 0 && job.total <= 4 * threads;
+}
+
 hipError_t launch_select_init(const SelectPrep &p, int B, hipStream_t s) {
   hipLaunchKernelGGL(select_init_kernel, dim3(B), dim3(256), 0, s, p, B);
   return hipGetLastError();
@@ -738,23 +766,23 @@ template <int SLOTS>
 static hipError_t launch_passes(const wcc_desc &d, const float *norm_or_part, int G, float *norm_out,
                                 int64_t k, uint32_t *hist, SelectState *st, uint16_t *sfx,
                                 uint32_t *gthi, int nblk, int32_t *idx, int32_t *jmap,
-                                float *top_part, float *block_top, hipStream_t s) {
+                                float *top_part, float *block_top, const PackJob &job, hipStream_t s) {
   const int64_t N = (int64_t)d.H * d.W;
   const uint32_t k32 = (uint32_t)k;
   dim3 grid(nblk, d.B), block(kThreads);
   const float *norm = norm_or_part;
   if (G > 1) {
     hipLaunchKernelGGL((select_hist_kernel<0, true, SLOTS>), grid, block, 0, s, norm_or_part, norm_out,
-                       G, N, d.B, k32, hist, st, nblk, sfx, gthi);
+                       G, N, d.B, k32, hist, st, nblk, sfx, gthi, job);
     norm = norm_out;
   } else {
     hipLaunchKernelGGL((select_hist_kernel<0, false, SLOTS>), grid, block, 0, s, norm, nullptr, 1, N,
-                       d.B, k32, hist, st, nblk, sfx, gthi);
+                       d.B, k32, hist, st, nblk, sfx, gthi, job);
   }
   hipLaunchKernelGGL((select_hist_kernel<1, false, SLOTS>), grid, block, 0, s, norm, nullptr, 1, N, d.B,
-                     k32, hist, st, nblk, sfx, gthi);
+                     k32, hist, st, nblk, sfx, gthi, job);
   hipLaunchKernelGGL((select_hist_kernel<2, false, SLOTS>), grid, block, 0, s, norm, nullptr, 1, N, d.B,
-                     k32, hist, st, nblk, sfx, gthi);
+                     k32, hist, st, nblk, sfx, gthi, job);
   hipLaunchKernelGGL((select_emit_kernel<SLOTS>), grid, block, 0, s, norm, N, k, hist, st, sfx, gthi,
                      nblk, idx, jmap, top_part, G, d.B, block_top);
   return hipGetLastError();
@@ -762,7 +790,9 @@ static hipError_t launch_passes(const wcc_desc &d, const float *norm_or_part, in
 
 hipError_t launch_select(const wcc_desc &d, const float *norm_or_part, int G, float *norm_out,
                          int64_t k, void *ws_base, const WsLayout &L, int32_t *idx, int32_t *jmap,
-                         float *top_part, float *block_top, hipStream_t s) {
+                         float *top_part, float *block_top, const PackJob &wanted, hipStream_t s) {
+  PackJob job = wanted;
+  if (!select_packs(d, L, job)) job.total = 0;
   const int64_t N = (int64_t)d.H * d.W;
   char *ws = static_cast<char *>(ws_base);
   uint32_t *hist = reinterpret_cast<uint32_t *>(ws + L.hist);
@@ -784,10 +814,10 @@ hipError_t launch_select(const wcc_desc &d, const float *norm_or_part, int G, fl
   do {                                                                                                 \
     if (planes > 1)                                                                                    \
       hipLaunchKernelGGL((select_small_kernel<true, SLOTS>), dim3(d.B), dim3(kSmallThreads), 0, s,     \
-                         src, planes, N, d.B, k32, idx, jmap, top_part, block_top);                    \
+                         src, planes, N, d.B, k32, idx, jmap, top_part, block_top, job);                    \
     else                                                                                               \
       hipLaunchKernelGGL((select_small_kernel<false, SLOTS>), dim3(d.B), dim3(kSmallThreads), 0, s,    \
-                         src, 1, N, d.B, k32, idx, jmap, top_part, block_top);                         \
+                         src, 1, N, d.B, k32, idx, jmap, top_part, block_top, job);                         \
   } while (0)
     if (N <= 4 * kSmallThreads) WCC_SMALL(1);
     else if (N <= 8 * kSmallThreads) WCC_SMALL(2);
@@ -796,9 +826,9 @@ hipError_t launch_select(const wcc_desc &d, const float *norm_or_part, int G, fl
     return hipGetLastError();
   }
   switch (L.sel_slots) {
-    case 4: return launch_passes<4>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, s);
-    case 2: return launch_passes<2>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, s);
-    default: return launch_passes<1>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, s);
+    case 4: return launch_passes<4>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, job, s);
+    case 2: return launch_passes<2>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, job, s);
+    default: return launch_passes<1>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, job, s);
   }
 }
 

@@ -215,6 +215,15 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   // float the second pass left there after combining the selection's maxima
   const int n_alpha = early ? 1 : kAlphaSlots;
   float *top = early ? reinterpret_cast<float *>(ws + L.max_part) : nullptr;
+  // Packed weights go where the codes leave room: xc32 is sized for fp32.
+  const size_t codes_bytes = align256((size_t)d.B * d.C_in * ks), xc_bytes = (size_t)d.B * d.C_in * ks * 4;
+  PackJob pack{nullptr, nullptr, 0, 0, 0, 0, 0};
+  if (codes_now && xc_bytes > codes_bytes)
+    pack = pack_job(d, ks, w, ws + L.xc32 + codes_bytes, xc_bytes - codes_bytes);
+  const bool packed = list == kListSelect && select_packs(d, L, pack);
+  // (a launch of its own takes 4 us: 576 -> 160 channels at 4 x 512 positions, 2^27.5 multiply-adds, gain
+  // as much in the contraction, 320 -> 72 at 2048 lose 1 us)
+  if (!packed && (int64_t)d.B * d.C_in * d.C_out * ks < ((int64_t)1 << 27)) pack.total = 0;
   if (list == kListSelect) {
     // A: the transform, first pass: only the channel norms of X_wt leave the chip (the same
     // kernel clears the selection state)
@@ -228,7 +237,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
     WCC_TRY(mark(WCC_T_HAAR_FWD, 1));
     // B: norms, index set I (ascending), rank map for the inverse
     WCC_TRY(mark(WCC_T_NORM_SELECT, 0));
-    WCC_TRY(launch_select(d, L.G == 1 ? norm : part, L.G, norm, k, ws, L, idx, jmap, top, tops, s));
+    WCC_TRY(launch_select(d, L.G == 1 ? norm : part, L.G, norm, k, ws, L, idx, jmap, top, tops, pack, s));
     WCC_TRY(mark(WCC_T_NORM_SELECT, 1));
   } else {
     // a list that does not depend on the input: no norm pass, no selection
@@ -255,8 +264,13 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   // C: Y_wt = Conv(K_1x1, X_wt[I]) (kept coefficients still in fp32 are quantised as they are
   // loaded)
   WCC_TRY(mark(WCC_T_POINTWISE, 0));
-  WCC_TRY(pointwise_any(ws, L, d, ks, w, w_scale, xc32, !codes_now, slots, n_alpha,
-                        quant ? alpha_out_dev : nullptr, yc, s));
+  if (pack.total > 0) {
+    if (!packed) WCC_TRY(launch_pack(pack, s));
+    WCC_TRY(launch_pointwise_packed(d, ks, pack, w_scale, xc32, slots, n_alpha, alpha_out_dev, yc, s));
+  } else {
+    WCC_TRY(pointwise_any(ws, L, d, ks, w, w_scale, xc32, !codes_now, slots, n_alpha,
+                          quant ? alpha_out_dev : nullptr, yc, s));
+  }
   WCC_TRY(mark(WCC_T_POINTWISE, 1));
   if (stop_before_inverse) return WCC_OK;
   // D + E: Y^0[I] = Y_wt, inverse levels
@@ -452,7 +466,8 @@ wcc_status wcc_joint_topk(wcc_ctx *ctx, const wcc_desc *desc, const float *coef,
   }
   const int64_t k = k_of(*desc);
   WCC_TRY(launch_select_init(make_prep(ws, L, nullptr, 0.f), desc->B, s));
-  WCC_TRY(launch_select(*desc, norm, 1, nullptr, k, ws, L, idx, nullptr, nullptr, nullptr, s));
+  WCC_TRY(launch_select(*desc, norm, 1, nullptr, k, ws, L, idx, nullptr, nullptr, nullptr,
+                        PackJob{nullptr, nullptr, 0, 0, 0, 0, 0}, s));
   return WCC_OK;
 }
 

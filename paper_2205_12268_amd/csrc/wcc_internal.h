@@ -138,6 +138,43 @@ struct Quant {
   __device__ __forceinline__ int code(float v) const { return (int)level(v); }
 };
 
+// Weights brought into the order in which the matrix instructions take them: for every block of 32
+// rows and every 32 bytes of K one line of 64 x 16 bytes, lane l holding bytes (l / 32) * 16 on of
+// row l % 32; rows (up to a multiple of 64) and channels (up to 128 bytes) outside are zeros.
+// 4-bit codes are widened to int8.
+struct PackJob {
+  const void *w;
+  uint4 *out;
+  int M, K;
+  int steps;  // 32-byte steps a row
+  int total;  // 16-byte pieces; 0: nothing to do
+  int wt;     // WCC_BF16, WCC_I8 or WCC_I4
+};
+
+__device__ __forceinline__ uint4 pack_piece(const PackJob &job, int e) {
+  const int lane = e & 63, line = e >> 6, ks = line % job.steps, row = (line / job.steps) * 32 + (lane & 31);
+  const int piece = ks * 2 + (lane >> 5);  // of the row, in 16 bytes
+  uint4 v = make_uint4(0, 0, 0, 0);
+  if (job.wt == WCC_I4) {  // 16 codes from 8 bytes
+    if (row < job.M && piece * 16 < job.K) {
+      const uint2 q = *reinterpret_cast<const uint2 *>(static_cast<const uint8_t *>(job.w) +
+                                                       (size_t)row * (job.K / 2) + piece * 8);
+      auto widen = [](uint32_t h) {  // four codes in 16 bits -> four bytes
+        uint32_t r = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r |= ((uint32_t)((int)(h << (28 - 4 * i)) >> 28) & 0xFFu) << (8 * i);
+        return r;
+      };
+      v = make_uint4(widen(q.x & 0xFFFFu), widen(q.x >> 16), widen(q.y & 0xFFFFu), widen(q.y >> 16));
+    }
+  } else {
+    const int row_bytes = job.wt == WCC_BF16 ? job.K * 2 : job.K;
+    if (row < job.M && piece * 16 < row_bytes)
+      v = *reinterpret_cast<const uint4 *>(static_cast<const unsigned char *>(job.w) + (size_t)row * row_bytes + piece * 16);
+  }
+  return v;
+}
+
 // What stands in front of a layer's transform passes.
 enum Front {
   kFrontNone = 0,   // the layer's input is x as it is
@@ -200,7 +237,10 @@ hipError_t launch_select_init(const SelectPrep &p, int B, hipStream_t s);
 hipError_t launch_select(const wcc_desc &d, const float *norm_or_part, int G, float *norm_out,
                          int64_t k, void *ws_base, const WsLayout &L, int32_t *idx,
                          int32_t *jmap /*nullable*/, float *top_part, float *block_top,
-                         hipStream_t s);
+                         const PackJob &job, hipStream_t s);
+// Whether launch_select packs the weights on the side (job.total > 0 and few enough pieces for its
+// first kernel's threads); otherwise launch_pack has to.
+bool select_packs(const wcc_desc &d, const WsLayout &L, const PackJob &job);
 int select_top_count(const wcc_desc &d, const WsLayout &L);
 hipError_t launch_jmap_from_idx(const int32_t *idx, int B, int64_t N, int64_t k, int32_t *jmap,
                                 hipStream_t s);
@@ -220,6 +260,13 @@ hipError_t launch_quantize(const float *xc32, int64_t n, const float *alpha_slot
 hipError_t launch_pointwise(const wcc_desc &d, int64_t k, const void *w, const float *w_scale,
                             const void *xc, bool xc_is_f32, const float *alpha, int n_alpha,
                             float *alpha_out, float *yc, hipStream_t s);
+// The contraction on packed weights (int8 codes in): pack_job says whether the layer takes it (total
+// > 0) given `room` for them; launch_select or launch_pack carries the job out.
+PackJob pack_job(const wcc_desc &d, int64_t k, const void *w, void *room, size_t room_bytes);
+hipError_t launch_pack(const PackJob &job, hipStream_t s);
+hipError_t launch_pointwise_packed(const wcc_desc &d, int64_t k, const PackJob &job, const float *w_scale,
+                                   const void *xc, const float *alpha, int n_alpha, float *alpha_out,
+                                   float *yc, hipStream_t s);
 // scratch: kInvScratchBytes of device memory that the kernel may overwrite with anything
 // residual (nullable): [B, C_out, H, W] added to the result (may be y itself)
 hipError_t launch_scatter_ihaar(const wcc_desc &d, int64_t k, const float *yc, const int32_t *jmap,
