@@ -1,6 +1,8 @@
 // Shrinkage operator T applied with one index list to every channel (Eq. T, Alg. 1:
 // X_wt[I]), the layer-wide clipping parameter alpha = max |kept coefficient|, and the signed
 // uniform quantiser of Eq. (quantweights) with b = 8.
+#include <type_traits>
+
 #include "wcc_internal.h"
 
 namespace wcc {
@@ -21,18 +23,24 @@ constexpr int kGatherIters = 4;  // a workgroup covers 4 x 1024 consecutive j
 
 // xc[b, c, j] = coef[b, c, idx[b, j]].  grid = (ceil(k / 4096), C, B), block = 256, four
 // consecutive j per thread and iteration.  VEC: k is a multiple of 4 (16-byte idx loads and
-// xc stores).
-template <bool VEC>
+// xc stores).  Q8: alpha is known (the caller's q_alpha > 0), xc is int8 codes and alpha_out receives
+// q_alpha.  Otherwise the workgroup's largest |value| goes to wg_max[its number] (a plain store) or
+// raises one of the alpha slots (both nullable).
+template <bool VEC, bool Q8>
 __global__ __launch_bounds__(256) void gather_kernel(const float *__restrict__ coef,
                                                      const int32_t *__restrict__ idx, int C,
-                                                     int64_t N, int64_t k, float *__restrict__ xc,
-                                                     float *alpha_slots) {
+                                                     int64_t N, int64_t k, void *__restrict__ xc,
+                                                     float *alpha_slots, float *wg_max, float q_alpha,
+                                                     float *alpha_out) {
   __shared__ float wmax[4];
   const int c = blockIdx.y, b = blockIdx.z;
   const float *plane = coef + ((size_t)b * C + c) * N;
   const int32_t *ix = idx + (size_t)b * k;
-  float *out = xc + ((size_t)b * C + c) * k;
+  using Out = std::conditional_t<Q8, int8_t, float>;
+  Out *out = static_cast<Out *>(xc) + ((size_t)b * C + c) * k;
   float m = 0.f;
+  const Quant quant(Q8 ? q_alpha : 0.f);
+  if (Q8 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) alpha_out[0] = q_alpha;
   const int hi = (int)N - 1;  // an out-of-range index never leaves the plane
   if constexpr (VEC) {
     // all index loads first, then all gathers, then the stores: 16 independent loads in flight
@@ -54,7 +62,12 @@ __global__ __launch_bounds__(256) void gather_kernel(const float *__restrict__ c
     }
 #pragma unroll
     for (int it = 0; it < kGatherIters; ++it) {
-      if (j0[it] < k) {
+      if (j0[it] >= k) continue;
+      if constexpr (Q8) {
+        const uint32_t c0 = (uint32_t)quant.code(v[it].x) & 0xFFu, c1 = (uint32_t)quant.code(v[it].y) & 0xFFu;
+        const uint32_t c2 = (uint32_t)quant.code(v[it].z) & 0xFFu, c3 = (uint32_t)quant.code(v[it].w) & 0xFFu;
+        *reinterpret_cast<uint32_t *>(out + j0[it]) = c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
+      } else {
         *reinterpret_cast<float4 *>(out + j0[it]) = v[it];
         m = fmaxf(m, fmaxf(fmaxf(fabsf(v[it].x), fabsf(v[it].y)), fmaxf(fabsf(v[it].z), fabsf(v[it].w))));
       }
@@ -64,17 +77,22 @@ __global__ __launch_bounds__(256) void gather_kernel(const float *__restrict__ c
       const int64_t j0 = (((int64_t)blockIdx.x * kGatherIters + it) * 256 + threadIdx.x) * 4;
       for (int e = 0; e < 4 && j0 + e < k; ++e) {
         const float v = plane[min(max(ix[j0 + e], 0), hi)];
-        out[j0 + e] = v;
+        if constexpr (Q8) out[j0 + e] = (int8_t)quant.code(v);
+        else out[j0 + e] = v;
         m = fmaxf(m, fabsf(v));
       }
     }
   }
-  if (alpha_slots == nullptr) return;
+  if (Q8 || (alpha_slots == nullptr && wg_max == nullptr)) return;
   m = wave_max(m);
   if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
   __syncthreads();
   if (threadIdx.x == 0) {
     m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+    if (wg_max != nullptr) {
+      wg_max[((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = m;
+      return;
+    }
     // Non-negative floats order like their bit patterns: an integer max is exact and
     // independent of arrival order.  Atomics on one address serialise at the memory side, so
     // the workgroups spread over kAlphaSlots addresses; the consumer takes the max of the
@@ -88,10 +106,10 @@ __global__ __launch_bounds__(256) void gather_kernel(const float *__restrict__ c
 
 // codes[i] = q(xc32[i]); 16 values per thread when n is a multiple of 16
 __global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__ xc32, int64_t n,
-                                                       const float *__restrict__ alpha_slots,
+                                                       const float *__restrict__ alpha_src, int n_alpha,
                                                        float *__restrict__ alpha_out,
                                                        int8_t *__restrict__ codes) {
-  const float alpha = alpha_max(alpha_slots, kAlphaSlots);
+  const float alpha = alpha_max(alpha_src, n_alpha);
   if (blockIdx.x == 0 && threadIdx.x == 0) alpha_out[0] = alpha;
   const Quant a(alpha);
   const int64_t i0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 16;
@@ -135,22 +153,44 @@ hipError_t launch_alpha_init(float *alpha_slots, float alpha_in, hipStream_t s) 
   return hipGetLastError();
 }
 
+static dim3 gather_grid(int B, int C, int64_t k) {
+  return dim3((unsigned)((k + 1024 * kGatherIters - 1) / (1024 * kGatherIters)), C, B);
+}
+
+int64_t gather_workgroups(int B, int C, int64_t k) {
+  const dim3 g = gather_grid(B, C, k);
+  return (int64_t)g.x * g.y * g.z;
+}
+
 hipError_t launch_gather(const float *coef, const int32_t *idx, int B, int C, int64_t N, int64_t k,
-                         float *xc, float *alpha_slots, hipStream_t s) {
-  dim3 grid((unsigned)((k + 1024 * kGatherIters - 1) / (1024 * kGatherIters)), C, B);
+                         float *xc, float *alpha_slots, float *wg_max, hipStream_t s) {
+  const dim3 grid = gather_grid(B, C, k);
   if (k % 4 == 0)
-    hipLaunchKernelGGL(gather_kernel<true>, grid, dim3(256), 0, s, coef, idx, C, N, k, xc, alpha_slots);
+    hipLaunchKernelGGL((gather_kernel<true, false>), grid, dim3(256), 0, s, coef, idx, C, N, k, xc, alpha_slots,
+                       wg_max, 0.f, nullptr);
   else
-    hipLaunchKernelGGL(gather_kernel<false>, grid, dim3(256), 0, s, coef, idx, C, N, k, xc, alpha_slots);
+    hipLaunchKernelGGL((gather_kernel<false, false>), grid, dim3(256), 0, s, coef, idx, C, N, k, xc, alpha_slots,
+                       wg_max, 0.f, nullptr);
   return hipGetLastError();
 }
 
-hipError_t launch_quantize(const float *xc32, int64_t n, const float *alpha_slots, float *alpha_out,
+hipError_t launch_gather_codes(const float *coef, const int32_t *idx, int B, int C, int64_t N, int64_t k,
+                               int8_t *codes, float q_alpha, float *alpha_out, hipStream_t s) {
+  const dim3 grid = gather_grid(B, C, k);
+  if (k % 4 == 0)
+    hipLaunchKernelGGL((gather_kernel<true, true>), grid, dim3(256), 0, s, coef, idx, C, N, k, codes, nullptr,
+                       nullptr, q_alpha, alpha_out);
+  else
+    hipLaunchKernelGGL((gather_kernel<false, true>), grid, dim3(256), 0, s, coef, idx, C, N, k, codes, nullptr,
+                       nullptr, q_alpha, alpha_out);
+  return hipGetLastError();
+}
+
+hipError_t launch_quantize(const float *xc32, int64_t n, const float *alpha_src, int n_alpha, float *alpha_out,
                            int8_t *codes, hipStream_t s) {
   hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)((n + 4095) / 4096)), dim3(256), 0, s, xc32, n,
-                     alpha_slots, alpha_out, codes);
+                     alpha_src, n_alpha, alpha_out, codes);
   return hipGetLastError();
 }
-
 
 }  // namespace wcc

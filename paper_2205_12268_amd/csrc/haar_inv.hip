@@ -294,6 +294,8 @@ hipError_t inv_dispatch(const wcc_desc &d, int64_t k, const float *yc, const int
 
 hipError_t launch_scatter_ihaar(const wcc_desc &d, int64_t k, const float *yc, const int32_t *jmap,
                                 void *y, float *scratch, const void *residual, hipStream_t s) {
+  // (128 x 128, 1024 channels, 16 samples: 336 us with 4096 waves, 320 with 8192; two channels a wave at
+  // d <= 2 only, as in the keep pass)
   return inv_dispatch(d, k, yc, jmap, y, groups_for(d, d.C_out, 8192, d.levels <= 2 ? 2 : 4), scratch, residual, s);
 }
 

@@ -7,13 +7,14 @@ namespace {
 
 // grid = (ceil(units/4), G, B), block = 256.  DWM as in haar_fwd_kernel.  Q8: xc is int8 codes
 // for the clipping parameter q_alpha (> 0) or, if alpha_src is given, for the largest of its
-// n_alpha entries (what the selection found as max |kept coefficient|); alpha_slots must be
-// null then.
+// n_alpha entries (what the selection found as max |kept coefficient|); alpha_slots and wg_max must
+// be null then.  Otherwise the workgroup's max |kept coefficient| goes to wg_max[its number] (a plain
+// store, combined by the consumer) or raises one of the alpha slots (both nullable).
 template <int D, int V, int PF, int DWM, bool Q8, class XT, bool NT = false>
 __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x,
                                                         const int32_t *__restrict__ jmap,
                                                         void *__restrict__ xc, float *alpha_slots,
-                                                        Geo g, StripMap m, int C, int Cg, int cstep,
+                                                        float *wg_max, Geo g, StripMap m, int C, int Cg, int cstep,
                                                         int64_t k, const float *__restrict__ wdw,
                                                         float q_alpha,
                                                         const float *__restrict__ alpha_src,
@@ -171,13 +172,17 @@ __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x
       mx = walk(sink, next);
     }
   }
-  if (alpha_slots == nullptr) return;
+  if (alpha_slots == nullptr && wg_max == nullptr) return;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
   if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
   __syncthreads();
   if (threadIdx.x == 0) {
     mx = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+    if (wg_max != nullptr) {
+      wg_max[((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = mx;
+      return;
+    }
     // integer max on the bit pattern of a non-negative float: exact and order-independent;
     // workgroups spread over the slots because atomics on one address serialise
     unsigned int *a = reinterpret_cast<unsigned int *>(alpha_slots) +
@@ -189,7 +194,7 @@ __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x
 
 template <int D, int V, class XT>
 hipError_t keep_launch_t(const wcc_desc &d, int64_t k, const XT *x, const int32_t *jmap, void *xc,
-                         float *alpha_slots, Plan pl, const float *wdw, float q_alpha,
+                         float *alpha_slots, float *wg_max, Plan pl, const float *wdw, float q_alpha,
                          const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
   const StripMap m = make_map(d, V);
@@ -205,10 +210,10 @@ hipError_t keep_launch_t(const wcc_desc &d, int64_t k, const XT *x, const int32_
   do {                                                                                             \
     if (q8)                                                                                        \
       hipLaunchKernelGGL((haar_keep_kernel<D, V, PF, DWM, true, XT>), grid, dim3(256), 0, s, x,   \
-                         jmap, xc, nullptr, g, m, d.C_in, Cg, cstep, k, wdw, q_alpha, alpha_src, n_alpha, alpha_pub);                    \
+                         jmap, xc, nullptr, nullptr, g, m, d.C_in, Cg, cstep, k, wdw, q_alpha, alpha_src, n_alpha, alpha_pub);                    \
     else                                                                                           \
       hipLaunchKernelGGL((haar_keep_kernel<D, V, PF, DWM, false, XT>), grid, dim3(256), 0, s, x,  \
-                         jmap, xc, alpha_slots, g, m, d.C_in, Cg, cstep, k, wdw, 0.f, nullptr, 0, nullptr);                    \
+                         jmap, xc, alpha_slots, wg_max, g, m, d.C_in, Cg, cstep, k, wdw, 0.f, nullptr, 0, nullptr);                    \
   } while (0)
   if constexpr (V == 4 || D == 4) {
     if (wdw != nullptr) {  // K_dw in front of the transform
@@ -220,10 +225,10 @@ hipError_t keep_launch_t(const wcc_desc &d, int64_t k, const XT *x, const int32_
   if (pl.stream) {
     if (q8)
       hipLaunchKernelGGL((haar_keep_kernel<D, V, 1, 0, true, XT, true>), grid, dim3(256), 0, s, x,
-                         jmap, xc, nullptr, g, m, d.C_in, Cg, cstep, k, wdw, q_alpha, alpha_src, n_alpha, alpha_pub);
+                         jmap, xc, nullptr, nullptr, g, m, d.C_in, Cg, cstep, k, wdw, q_alpha, alpha_src, n_alpha, alpha_pub);
     else
       hipLaunchKernelGGL((haar_keep_kernel<D, V, 1, 0, false, XT, true>), grid, dim3(256), 0, s, x,
-                         jmap, xc, alpha_slots, g, m, d.C_in, Cg, cstep, k, wdw, 0.f, nullptr, 0, nullptr);
+                         jmap, xc, alpha_slots, wg_max, g, m, d.C_in, Cg, cstep, k, wdw, 0.f, nullptr, 0, nullptr);
     return hipGetLastError();
   }
   WCC_KEEP(1, 0);
@@ -233,36 +238,46 @@ hipError_t keep_launch_t(const wcc_desc &d, int64_t k, const XT *x, const int32_
 
 template <int D, int V>
 hipError_t keep_launch(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap, void *xc,
-                       float *alpha_slots, Plan pl, const float *wdw, float q_alpha,
+                       float *alpha_slots, float *wg_max, Plan pl, const float *wdw, float q_alpha,
                        const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
   if (d.act_dtype == WCC_BF16)
-    return keep_launch_t<D, V>(d, k, static_cast<const bf16_t *>(x), jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
-  return keep_launch_t<D, V>(d, k, static_cast<const float *>(x), jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+    return keep_launch_t<D, V>(d, k, static_cast<const bf16_t *>(x), jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+  return keep_launch_t<D, V>(d, k, static_cast<const float *>(x), jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
 }
 
 }  // namespace
 
 hipError_t keep_dispatch(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap, void *xc,
-                         float *alpha_slots, Plan pl, const float *wdw, float q_alpha,
+                         float *alpha_slots, float *wg_max, Plan pl, const float *wdw, float q_alpha,
                          const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
   const bool v4 = lane_cols(d) == 4;
   switch (d.levels) {
-    case 1: return v4 ? keep_launch<1, 4>(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s)
-                      : keep_launch<1, 2>(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
-    case 2: return keep_launch<2, 4>(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
-    case 3: return keep_launch<3, 4>(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
-    case 4: return keep_launch<4, 2>(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+    case 1: return v4 ? keep_launch<1, 4>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s)
+                      : keep_launch<1, 2>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+    case 2: return keep_launch<2, 4>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+    case 3: return keep_launch<3, 4>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+    case 4: return keep_launch<4, 2>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
   }
   return hipErrorInvalidValue;
 }
 
+static int keep_groups(const wcc_desc &d, bool folded) {
+  // About two thousand waves, down to two channels each at d <= 2, where a wave has few rows in flight
+  // (the 16-layer stack 792 -> 782 us against a thousand waves of four, 256 channels of 256 x 512
+  // 123.4 -> 121.3; two channels at d = 3 lose 1-3 %); with K_dw in front as measured there.
+  return groups_for(d, d.C_in, arithmetic_bound(d, folded) ? 4096 : folded ? 1024 : 2048,
+                    !folded && d.levels <= 2 ? 2 : 4);
+}
+
+int64_t keep_workgroups(const wcc_desc &d, bool folded) {
+  return (int64_t)((make_map(d, lane_cols(d)).units + 3) / 4) * keep_groups(d, folded) * d.B;
+}
+
 hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap,
-                            void *xc, float *alpha_slots, const float *wdw, float q_alpha,
+                            void *xc, float *alpha_slots, float *wg_max, const float *wdw, float q_alpha,
                             const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
-  const Plan pl{groups_for(d, d.C_in, arithmetic_bound(d, wdw != nullptr) ? 4096 : wdw != nullptr ? 1024 : 2048,
-                           wdw == nullptr && d.levels <= 2 ? 2 : 4), 1,
-                streams(d)};
-  return keep_dispatch(d, k, x, jmap, xc, alpha_slots, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+  const Plan pl{keep_groups(d, wdw != nullptr), 1, streams(d)};
+  return keep_dispatch(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
 }
 
 }  // namespace wcc

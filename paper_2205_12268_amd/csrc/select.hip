@@ -699,8 +699,10 @@ __global__ __launch_bounds__(kSmallThreads) void select_small_kernel(
 }
 
 // jmap from an arbitrary ascending index list: fill with -1, then jmap[b][idx[b][j]] = j
-__global__ __launch_bounds__(256) void fill_i32_kernel(int32_t *p, int64_t n, int32_t v) {
+__global__ __launch_bounds__(256) void fill_i32_kernel(int32_t *p, int64_t n, int32_t v, float *alpha,
+                                                       float alpha_in) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (alpha && i < kAlphaSlots) alpha[i] = alpha_in > 0.f ? alpha_in : 0.f;
   if (i < n) p[i] = v;
 }
 __global__ __launch_bounds__(256) void jmap_scatter_kernel(const int32_t *__restrict__ idx,
@@ -717,9 +719,11 @@ __global__ __launch_bounds__(256) void jmap_scatter_kernel(const int32_t *__rest
 // idx[b][j] = j (idx nullable)
 __global__ __launch_bounds__(256) void jmap_prefix_kernel(int64_t N, int64_t k,
                                                           int32_t *__restrict__ jmap,
-                                                          int32_t *__restrict__ idx) {
+                                                          int32_t *__restrict__ idx, float *alpha,
+                                                          float alpha_in) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int b = blockIdx.y;
+  if (alpha && b == 0 && q < kAlphaSlots) alpha[q] = alpha_in > 0.f ? alpha_in : 0.f;
   if (q >= N) return;
   jmap[(size_t)b * N + q] = q < k ? (int32_t)q : -1;
   if (idx && q < k) idx[(size_t)b * k + q] = (int32_t)q;
@@ -728,9 +732,9 @@ __global__ __launch_bounds__(256) void jmap_prefix_kernel(int64_t N, int64_t k,
 }  // namespace
 
 hipError_t launch_jmap_prefix(int B, int64_t N, int64_t k, int32_t *jmap, int32_t *idx,
-                              hipStream_t s) {
+                              float *alpha_slots, float alpha_in, hipStream_t s) {
   hipLaunchKernelGGL(jmap_prefix_kernel, dim3((unsigned)((N + 255) / 256), B), dim3(256), 0, s, N, k,
-                     jmap, idx);
+                     jmap, idx, alpha_slots, alpha_in);
   return hipGetLastError();
 }
 
@@ -833,9 +837,10 @@ hipError_t launch_select(const wcc_desc &d, const float *norm_or_part, int G, fl
 }
 
 hipError_t launch_jmap_from_idx(const int32_t *idx, int B, int64_t N, int64_t k, int32_t *jmap,
-                                hipStream_t s) {
+                                float *alpha_slots, float alpha_in, hipStream_t s) {
   const int64_t n = (int64_t)B * N;
-  hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, jmap, n, -1);
+  hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, jmap, n, -1,
+                     alpha_slots, alpha_in);
   dim3 grid((unsigned)((k + 255) / 256), B);
   hipLaunchKernelGGL(jmap_scatter_kernel, grid, dim3(256), 0, s, idx, N, k, jmap);
   return hipGetLastError();

@@ -54,6 +54,8 @@ namespace {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+constexpr int64_t kMaxWgMaxima = 1024;  // workgroup maxima that a consumer combines by itself
+
 wcc_status check_desc(const wcc_desc *d) {
   if (!d) return WCC_ERR_NULL;
   if (d->B < 1 || d->C_in < 1 || d->C_out < 1 || d->H < 2 || d->W < 2) return WCC_ERR_SHAPE;
@@ -213,7 +215,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   float *tops = reinterpret_cast<float *>(ws + L.block_top);
   // the contraction finds alpha in the slots: as the largest of them, or (early) as the one
   // float the second pass left there after combining the selection's maxima
-  const int n_alpha = early ? 1 : kAlphaSlots;
+  int n_alpha = early ? 1 : kAlphaSlots;
   float *top = early ? reinterpret_cast<float *>(ws + L.max_part) : nullptr;
   // Packed weights go where the codes leave room: xc32 is sized for fp32.
   const size_t codes_bytes = align256((size_t)d.B * d.C_in * ks), xc_bytes = (size_t)d.B * d.C_in * ks * 4;
@@ -242,22 +244,32 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   } else {
     // a list that does not depend on the input: no norm pass, no selection
     WCC_TRY(mark(WCC_T_NORM_SELECT, 0));
-    WCC_TRY(launch_alpha_init(slots, quant ? alpha_in : 0.f, s));
     if (list == kListPrefix)
-      WCC_TRY(launch_jmap_prefix(d.B, (int64_t)d.H * d.W, k, jmap, idx_out, s));
+      WCC_TRY(launch_jmap_prefix(d.B, (int64_t)d.H * d.W, k, jmap, idx_out, slots, quant ? alpha_in : 0.f, s));
     else
-      WCC_TRY(launch_jmap_from_idx(idx_given, d.B, (int64_t)d.H * d.W, k, jmap, s));
+      WCC_TRY(launch_jmap_from_idx(idx_given, d.B, (int64_t)d.H * d.W, k, jmap, slots, quant ? alpha_in : 0.f, s));
     WCC_TRY(mark(WCC_T_NORM_SELECT, 1));
   }
+  // alpha only after the second pass: its workgroups leave their maxima side by side for the
+  // contraction to combine (in the memory of the partial maxima, which this route does not use), or
+  // raise the slots where they are too many for every workgroup of the contraction to read.  (Raising
+  // slots, 64 words that share two lines of memory, and a launch to clear them: keep pass of 2 x 192
+  // channels of 400 x 56 23 us, 10 now; 2 x 176 of 204 x 144 25 and 15.)
+  const bool late = quant && !given && !codes_now;
+  const int64_t keep_wgs = src ? 0 : keep_workgroups(d, wdw != nullptr);
+  float *wg_max = late && !src && keep_wgs <= kMaxWgMaxima && (size_t)keep_wgs * 4 <= L.norm - L.max_part
+                      ? reinterpret_cast<float *>(ws + L.max_part)
+                      : nullptr;
+  if (wg_max) n_alpha = (int)keep_wgs;
   // A again + B': the transform, second pass: X_wt[I] is written straight into its compressed
   // place (the dropped coefficients never reach memory)
   WCC_TRY(mark(WCC_T_GATHER, 0));
   if (src)
-    WCC_TRY(launch_chain_keep(d, ks, *src, wdw, jmap, xc32, (quant && !given && !codes_now) ? slots : nullptr,
+    WCC_TRY(launch_chain_keep(d, ks, *src, wdw, jmap, xc32, late ? slots : nullptr,
                               (given && codes_now) ? alpha_in : 0.f, early ? tops : nullptr, n_top,
                               early ? slots : nullptr, s));
   else
-    WCC_TRY(launch_haar_keep(d, ks, x, jmap, xc32, (quant && !given && !codes_now) ? slots : nullptr, wdw,
+    WCC_TRY(launch_haar_keep(d, ks, x, jmap, xc32, (late && !wg_max) ? slots : nullptr, wg_max, wdw,
                              (given && codes_now) ? alpha_in : 0.f, early ? tops : nullptr, n_top,
                              early ? slots : nullptr, s));
   WCC_TRY(mark(WCC_T_GATHER, 1));
@@ -268,7 +280,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
     if (!packed) WCC_TRY(launch_pack(pack, s));
     WCC_TRY(launch_pointwise_packed(d, ks, pack, w_scale, xc32, slots, n_alpha, alpha_out_dev, yc, s));
   } else {
-    WCC_TRY(pointwise_any(ws, L, d, ks, w, w_scale, xc32, !codes_now, slots, n_alpha,
+    WCC_TRY(pointwise_any(ws, L, d, ks, w, w_scale, xc32, !codes_now, wg_max ? wg_max : slots, n_alpha,
                           quant ? alpha_out_dev : nullptr, yc, s));
   }
   WCC_TRY(mark(WCC_T_POINTWISE, 1));
@@ -483,18 +495,28 @@ wcc_status wcc_gather_quant(wcc_ctx *ctx, const wcc_desc *desc, const float *coe
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int64_t N = (int64_t)desc->H * desc->W, k = k_of(*desc);
   if (!quant) {
-    WCC_TRY(launch_gather(coef, idx, desc->B, desc->C_in, N, k, static_cast<float *>(xc), nullptr, s));
+    WCC_TRY(launch_gather(coef, idx, desc->B, desc->C_in, N, k, static_cast<float *>(xc), nullptr, nullptr, s));
     return WCC_OK;
   }
   const WsLayout L = ws_layout(*desc);
   if ((st = need_ws(ctx, L)) != WCC_OK) return st;
+  if (alpha_in > 0.f) {
+    WCC_TRY(launch_gather_codes(coef, idx, desc->B, desc->C_in, N, k, static_cast<int8_t *>(xc), alpha_in, alpha_dev, s));
+    return WCC_OK;
+  }
+  // alpha = the largest gathered value: the gather's workgroups leave their maxima side by side, or
+  // raise the slots where they are too many for every workgroup of the quantiser to read
   char *ws = static_cast<char *>(ctx->ws);
   float *xc32 = reinterpret_cast<float *>(ws + L.xc32);
   float *slots = reinterpret_cast<float *>(ws + L.alpha);
-  WCC_TRY(launch_alpha_init(slots, alpha_in, s));
-  WCC_TRY(launch_gather(coef, idx, desc->B, desc->C_in, N, k, xc32, alpha_in > 0.f ? nullptr : slots, s));
-  WCC_TRY(launch_quantize(xc32, (int64_t)desc->B * desc->C_in * k, slots, alpha_dev,
-                          static_cast<int8_t *>(xc), s));
+  const int64_t wgs = gather_workgroups(desc->B, desc->C_in, k);
+  float *wg_max = wgs <= kMaxWgMaxima && (size_t)wgs * 4 <= L.norm - L.max_part
+                      ? reinterpret_cast<float *>(ws + L.max_part)
+                      : nullptr;
+  if (!wg_max) WCC_TRY(launch_alpha_init(slots, 0.f, s));
+  WCC_TRY(launch_gather(coef, idx, desc->B, desc->C_in, N, k, xc32, wg_max ? nullptr : slots, wg_max, s));
+  WCC_TRY(launch_quantize(xc32, (int64_t)desc->B * desc->C_in * k, wg_max ? wg_max : slots,
+                          wg_max ? (int)wgs : kAlphaSlots, alpha_dev, static_cast<int8_t *>(xc), s));
   return WCC_OK;
 }
 
@@ -526,7 +548,7 @@ wcc_status wcc_scatter_ihaar(wcc_ctx *ctx, const wcc_desc *desc, const float *yc
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int64_t N = (int64_t)desc->H * desc->W, k = k_of(*desc);
   int32_t *jmap = reinterpret_cast<int32_t *>(static_cast<char *>(ctx->ws) + L.jmap);
-  WCC_TRY(launch_jmap_from_idx(idx, desc->B, N, k, jmap, s));
+  WCC_TRY(launch_jmap_from_idx(idx, desc->B, N, k, jmap, nullptr, 0.f, s));
   WCC_TRY(launch_scatter_ihaar(*desc, k, yc, jmap, y,
                                reinterpret_cast<float *>(static_cast<char *>(ctx->ws) + L.scratch),
                                nullptr, s));

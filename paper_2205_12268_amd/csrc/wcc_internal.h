@@ -216,9 +216,12 @@ hipError_t launch_haar_norm(const wcc_desc &d, const void *x, float *norm_part, 
                             const SelectPrep &prep, const float *wdw, hipStream_t s);
 // q_alpha > 0, or alpha_src given (n_alpha floats whose largest is the clipping parameter,
 // read on the device): xc is int8 codes for that clipping parameter (alpha_slots unused); else
-// xc is fp32 and alpha_slots (nullable) is raised to max |kept coefficient|
+// xc is fp32 and max |kept coefficient| goes to wg_max, one value for each of the keep_workgroups()
+// workgroups, or raises alpha_slots (both nullable)
+int64_t keep_workgroups(const wcc_desc &d, bool folded_dw);
 hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap,
-                            void *xc, float *alpha_slots /*nullable*/, const float *wdw /*nullable*/,
+                            void *xc, float *alpha_slots /*nullable*/, float *wg_max /*nullable*/,
+                            const float *wdw /*nullable*/,
                             float q_alpha, const float *alpha_src /*nullable*/, int n_alpha,
                             float *alpha_pub /*nullable: receives that largest value*/,
                             hipStream_t s);
@@ -242,16 +245,23 @@ hipError_t launch_select(const wcc_desc &d, const float *norm_or_part, int G, fl
 // first kernel's threads); otherwise launch_pack has to.
 bool select_packs(const wcc_desc &d, const WsLayout &L, const PackJob &job);
 int select_top_count(const wcc_desc &d, const WsLayout &L);
+// (both also set the alpha slots, where given, to alpha_in or 0)
 hipError_t launch_jmap_from_idx(const int32_t *idx, int B, int64_t N, int64_t k, int32_t *jmap,
-                                hipStream_t s);
+                                float *alpha_slots /*nullable*/, float alpha_in, hipStream_t s);
 // rank map (and index list, nullable) of "the first k positions of every sample"
-hipError_t launch_jmap_prefix(int B, int64_t N, int64_t k, int32_t *jmap, int32_t *idx, hipStream_t s);
+hipError_t launch_jmap_prefix(int B, int64_t N, int64_t k, int32_t *jmap, int32_t *idx,
+                              float *alpha_slots /*nullable*/, float alpha_in, hipStream_t s);
 hipError_t launch_alpha_init(float *alpha_slots, float alpha_in, hipStream_t s);
-// alpha_slots nullable: no maximum is taken
+// max |value| goes to wg_max, one value for each of the gather_workgroups() workgroups, or raises
+// alpha_slots (both nullable)
+int64_t gather_workgroups(int B, int C, int64_t k);
 hipError_t launch_gather(const float *coef, const int32_t *idx, int B, int C, int64_t N, int64_t k,
-                         float *xc, float *alpha_slots, hipStream_t s);
-// codes = q(xc32) with alpha = max(slots); also writes alpha to alpha_out[0]
-hipError_t launch_quantize(const float *xc32, int64_t n, const float *alpha_slots, float *alpha_out,
+                         float *xc, float *alpha_slots, float *wg_max, hipStream_t s);
+// the same straight to codes for a known alpha (q_alpha > 0, also written to alpha_out[0])
+hipError_t launch_gather_codes(const float *coef, const int32_t *idx, int B, int C, int64_t N, int64_t k,
+                               int8_t *codes, float q_alpha, float *alpha_out, hipStream_t s);
+// codes = q(xc32) with alpha = the largest of n_alpha values; also writes alpha to alpha_out[0]
+hipError_t launch_quantize(const float *xc32, int64_t n, const float *alpha_src, int n_alpha, float *alpha_out,
                            int8_t *codes, hipStream_t s);
 // xc_is_f32 with act_quant_bits = 8: xc holds the unquantised kept coefficients and the
 // kernel quantises them while loading (the fused path); otherwise xc is what the ABI says.
