@@ -756,7 +756,7 @@ hipError_t launch_chain_keep(const wcc_desc &d, int64_t k, const ChainSrc &src, 
                              const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
   const StripMap m = chain_map(d);
-  const int G = groups_for(d, d.C_in, 4096, 8);
+  const int G = groups_for(d, make_map(d, lane_cols(d)), d.C_in, 4096, 8);
   const int Cg = (d.C_in + G - 1) / G;
   const int segs = chain_segments(d), waves = chain_waves(segs);
   if (segs == 0) return hipErrorInvalidValue;

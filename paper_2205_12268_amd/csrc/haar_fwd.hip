@@ -162,7 +162,7 @@ hipError_t fwd_launch_t(const wcc_desc &d, const XT *x, float *coef, float *norm
                         float *max_part, Plan pl, const SelectPrep &prep, const float *wdw,
                         hipStream_t s) {
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
-  const StripMap m = make_map(d, V);
+  const StripMap m = wdw != nullptr ? make_map(d, V) : make_flat_map(d, V);
   const int Cg = (d.C_in + pl.G - 1) / pl.G;
   // one launch: WPU waves a unit, DWM, and the sink's options
   auto go = [&](auto wpu_c, auto dwm_c, auto sq_c, auto nt_c) {
@@ -177,14 +177,22 @@ hipError_t fwd_launch_t(const wcc_desc &d, const XT *x, float *coef, float *norm
   using std::integral_constant;
   auto with_waves = [&](auto dwm_c, auto sq_c) {
     constexpr int DWM = decltype(dwm_c)::value;
-    if constexpr (!STORE) {  // an input far larger than the memory-side cache, read once
-      if (pl.stream && pl.wpu == 1) return go(integral_constant<int, 1>{}, dwm_c, sq_c, std::true_type{});
+    auto with_hint = [&](auto nt_c) {
+      if (pl.wpu == 1) return go(integral_constant<int, 1>{}, dwm_c, sq_c, nt_c);
+      if constexpr (DWM == 0 && kMaxWpu<D> > 4) {
+        if (pl.wpu > 4) return go(integral_constant<int, kMaxWpu<D>>{}, dwm_c, sq_c, nt_c);
+      }
+      return go(integral_constant<int, 4>{}, dwm_c, sq_c, nt_c);
+    };
+    if constexpr (!STORE) {
+      // An input far larger than the memory-side cache is streamed past it.  Where waves share a unit,
+      // only if rows are whole 128-byte lines: otherwise the lines at a unit's ends are wanted by two
+      // workgroups (layers of 5, 7, 8 x 128 channels of 192 x 640: 209, 263, 295 us with the hint,
+      // 213, 270, 302 without; of 5, 6, 7 x 64 of 376 x 760: 417, 506, 560 with, 396, 482, 546 without).
+      const bool whole_lines = d.W * (int)sizeof(XT) % 128 == 0;
+      if (pl.stream && (pl.wpu == 1 || (DWM == 0 && whole_lines))) return with_hint(std::true_type{});
     }
-    if (pl.wpu == 1) return go(integral_constant<int, 1>{}, dwm_c, sq_c, std::false_type{});
-    if constexpr (DWM == 0 && kMaxWpu<D> > 4) {
-      if (pl.wpu > 4) return go(integral_constant<int, kMaxWpu<D>>{}, dwm_c, sq_c, std::false_type{});
-    }
-    return go(integral_constant<int, 4>{}, dwm_c, sq_c, std::false_type{});
+    return with_hint(std::false_type{});
   };
   auto with_sums = [&](auto dwm_c) {
     if constexpr (!STORE && std::is_same<XT, float>::value) {
@@ -226,12 +234,12 @@ static FwdShape fwd_shape(const wcc_desc &d, int front) {
   if (front != kFrontNone) {
     // K_dw in front: a wave holds two more rows and the taps; groups, and four waves a unit where
     // there are still too few
-    FwdShape f{groups_for(d, d.C_in, front == kFrontChain || arithmetic_bound(d, folded) ? 4096 : 1024, 4), 1};
     const StripMap m = make_map(d, lane_cols(d));
+    FwdShape f{groups_for(d, m, d.C_in, front == kFrontChain || arithmetic_bound(d, folded) ? 4096 : 1024, 4), 1};
     if (folded && (int64_t)m.units * d.B * f.G < 1024 && (d.C_in + f.G - 1) / f.G >= 8) f.wpu = 4;
     return f;
   }
-  const StripMap m = make_map(d, lane_cols(d));
+  const StripMap m = make_flat_map(d, lane_cols(d));
   const int64_t units = (int64_t)m.units * d.B;
   const int64_t want = d.levels == 1 ? 4096 : 1024;
   FwdShape f{1, 1};

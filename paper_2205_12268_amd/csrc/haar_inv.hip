@@ -265,7 +265,7 @@ template <int D, int V>
 hipError_t inv_launch(const wcc_desc &d, int64_t k, const float *yc, const int32_t *jmap, void *y,
                       int G, float *scratch, const void *residual, hipStream_t s) {
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
-  const StripMap m = make_map(d, V);
+  const StripMap m = make_flat_map(d, V);
   dim3 grid((m.units + 3) / 4, G, d.B);
 #define WCC_INV(RES, YT)                                                                          \
   hipLaunchKernelGGL((scatter_ihaar_kernel<D, V, RES, YT>), grid, dim3(256), 0, s, yc, jmap,      \
@@ -296,7 +296,7 @@ hipError_t launch_scatter_ihaar(const wcc_desc &d, int64_t k, const float *yc, c
                                 void *y, float *scratch, const void *residual, hipStream_t s) {
   // (128 x 128, 1024 channels, 16 samples: 336 us with 4096 waves, 320 with 8192; two channels a wave at
   // d <= 2 only, as in the keep pass)
-  return inv_dispatch(d, k, yc, jmap, y, groups_for(d, d.C_out, 8192, d.levels <= 2 ? 2 : 4), scratch, residual, s);
+  return inv_dispatch(d, k, yc, jmap, y, groups_for(d, make_flat_map(d, lane_cols(d)), d.C_out, 8192, d.levels <= 2 ? 2 : 4), scratch, residual, s);
 }
 
 }  // namespace wcc

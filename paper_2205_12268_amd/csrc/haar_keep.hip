@@ -21,7 +21,10 @@ __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x
                                                         int n_alpha, float *alpha_pub) {
   __shared__ float wmax[4];
   const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int grp = blockIdx.y, b = blockIdx.z;
+  const int grp = blockIdx.y;
+  // Samples are taken last to first: what the norm pass has left of x in the memory-side cache is its
+  // tail (2 x 128 bf16 channels of 256 x 512: layer 82.2 -> 81.1 us, the 16-layer stack 785 -> 782).
+  const int b = gridDim.z - 1 - blockIdx.z;
   LanePos<D> p;
   int row0, col0;
   const bool active = locate<D, V>(m, g, unit, p, row0, col0);
@@ -192,12 +195,24 @@ __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x
   }
 }
 
+inline StripMap keep_map(const wcc_desc &d, bool folded) {
+  return folded ? make_map(d, lane_cols(d)) : make_flat_map(d, lane_cols(d));
+}
+
+int keep_groups(const wcc_desc &d, bool folded) {
+  // About two thousand waves, down to two channels each at d <= 2, where a wave has few rows in flight
+  // (the 16-layer stack 792 -> 782 us against a thousand waves of four, 256 channels of 256 x 512
+  // 123.4 -> 121.3; two channels at d = 3 lose 1-3 %); with K_dw in front as measured there.
+  return groups_for(d, keep_map(d, folded), d.C_in, arithmetic_bound(d, folded) ? 4096 : folded ? 1024 : 2048,
+                    !folded && d.levels <= 2 ? 2 : 4);
+}
+
 template <int D, int V, class XT>
 hipError_t keep_launch_t(const wcc_desc &d, int64_t k, const XT *x, const int32_t *jmap, void *xc,
                          float *alpha_slots, float *wg_max, Plan pl, const float *wdw, float q_alpha,
                          const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
-  const StripMap m = make_map(d, V);
+  const StripMap m = keep_map(d, wdw != nullptr);
   const int Cg = (d.C_in + pl.G - 1) / pl.G;
   // Without K_dw in front, group g takes the channels g, g + G, ...: groups running side by
   // side then read neighbouring planes of x and write neighbouring planes of xc (keep pass of
@@ -261,16 +276,8 @@ hipError_t keep_dispatch(const wcc_desc &d, int64_t k, const void *x, const int3
   return hipErrorInvalidValue;
 }
 
-static int keep_groups(const wcc_desc &d, bool folded) {
-  // About two thousand waves, down to two channels each at d <= 2, where a wave has few rows in flight
-  // (the 16-layer stack 792 -> 782 us against a thousand waves of four, 256 channels of 256 x 512
-  // 123.4 -> 121.3; two channels at d = 3 lose 1-3 %); with K_dw in front as measured there.
-  return groups_for(d, d.C_in, arithmetic_bound(d, folded) ? 4096 : folded ? 1024 : 2048,
-                    !folded && d.levels <= 2 ? 2 : 4);
-}
-
 int64_t keep_workgroups(const wcc_desc &d, bool folded) {
-  return (int64_t)((make_map(d, lane_cols(d)).units + 3) / 4) * keep_groups(d, folded) * d.B;
+  return (int64_t)((keep_map(d, folded).units + 3) / 4) * keep_groups(d, folded) * d.B;
 }
 
 hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap,

@@ -321,17 +321,27 @@ struct StripMap {
   int lanes_w;    // W / V lanes needed per row
   int strips;     // H >> D
   int units;      // wave work items per plane
+  bool flat;      // the lanes of all strips follow each other (lpr, col_segs unused)
 };
 
 template <int D, int V>
 __device__ __forceinline__ bool locate(const StripMap &m, const Geo &g, int unit, LanePos<D> &p,
                                        int &row0, int &col0) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int sub = lane >> m.log_lpr;
-  p.lc = lane & (m.lpr - 1);
-  const int ru = unit / m.col_segs, cs = unit - ru * m.col_segs;
-  const int strip = ru * (kWave >> m.log_lpr) + sub;
-  const int col_lane = cs * m.lpr + p.lc;
+  int strip, col_lane;
+  if (m.flat) {  // (uniform)
+    // (lanes_w and 64 are multiples of the 2^D / V lanes that hold one coarsest value, so lane and
+    // column agree in the bits below that: partners are neighbours in the wave)
+    const int at = unit * kWave + lane;
+    strip = at / m.lanes_w;
+    col_lane = at - strip * m.lanes_w;
+    p.lc = lane;
+  } else {
+    p.lc = lane & (m.lpr - 1);
+    const int ru = unit / m.col_segs, cs = unit - ru * m.col_segs;
+    strip = ru * (kWave >> m.log_lpr) + (lane >> m.log_lpr);
+    col_lane = cs * m.lpr + p.lc;
+  }
   row0 = strip << D;
   col0 = col_lane * V;
 #pragma unroll
@@ -548,6 +558,22 @@ inline StripMap make_map(const wcc_desc &d, int V) {
   m.col_segs = (m.lanes_w + best - 1) / best;
   const int spw = kWave / best;
   m.units = ((m.strips + spw - 1) / spw) * m.col_segs;
+  m.flat = false;
+  return m;
+}
+
+// For passes that need no neighbour columns: a row longer than a wave that the map above cuts into
+// pieces of less than 64 lanes (640 columns into 512 bytes, 320 into 256) is not cut; the lanes of all
+// strips follow each other and a wave takes the next 64, wherever the strips end.  8 x 128 channels of
+// 192 x 640: norm, keep and inverse pass 87, 97 and 94 -> 80, 94 and 89 us; 5 x 144 of 240 x 608, bf16:
+// layer 129 -> 125 us.  (Not for rows of whole waves or less: pieces that start anywhere cost more
+// than the idle lanes there: 6 x 64 channels of 376 x 760, 190 lanes, layer 488 -> 516 us; 96 columns,
+// 24 of 32 lanes in use, block 1077 -> 1110 us.)
+inline StripMap make_flat_map(const wcc_desc &d, int V) {
+  StripMap m = make_map(d, V);
+  if (m.lanes_w <= kWave || m.lpr == kWave) return m;
+  m.flat = true;
+  m.units = (int)(((int64_t)m.strips * m.lanes_w + kWave - 1) / kWave);
   return m;
 }
 
@@ -564,8 +590,7 @@ inline bool dw_needs_edges(const StripMap &m) { return m.col_segs > 1 || m.lpr <
 
 // Channel groups: split the channels until the launch has `want_waves` waves to cover the
 // memory latency of 256 CUs, but keep at least `min_ch` channels in a group.
-inline int groups_for(const wcc_desc &d, int C, int64_t want_waves, int min_ch) {
-  const StripMap m = make_map(d, lane_cols(d));
+inline int groups_for(const wcc_desc &d, const StripMap &m, int C, int64_t want_waves, int min_ch) {
   const int64_t waves = (int64_t)m.units * d.B;
   int G = 1;
   if (waves >= want_waves / 2) return G;  // already enough strips: keep the channel walk whole
