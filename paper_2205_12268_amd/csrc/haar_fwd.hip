@@ -273,9 +273,25 @@ static Plan fwd_plan(const wcc_desc &d, int front) {
   return Plan{f.G, f.wpu, streams(d)};
 }
 
-hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part,
+// The storing pass writes every coefficient: waves that share a unit write 1 KiB pieces of as many planes
+// where the waves of a workgroup otherwise write one run of 4 KiB.  On large maps that costs more
+// than the planes of partial norms (6 x 432 channels of 56 x 504, 293 MB: 155 against 143 us, the sum over
+// 16 instead of 2 planes 9 against 5); on small ones the launch that sums planes does.
+int store_groups(const wcc_desc &d, int64_t planes) {
+  const FwdShape f = fwd_shape(d, kFrontNone);
+  if ((int64_t)d.B * d.C_in * d.H * d.W * 4 <= ((int64_t)128 << 20) || f.wpu == 1) return f.G;
+  return (int)std::min<int64_t>(groups_for(d, make_flat_map(d, lane_cols(d)), d.C_in, 1024, 4), planes);
+}
+
+hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part, int G,
                            const SelectPrep &prep, hipStream_t s) {
-  return fwd_dispatch<true>(d, x, coef, norm_part, nullptr, fwd_plan(d, kFrontNone), prep, nullptr, s);
+  Plan pl = fwd_plan(d, kFrontNone);
+  if (G != pl.G) {
+    const int64_t waves = (int64_t)make_flat_map(d, lane_cols(d)).units * d.B * G;
+    pl.G = G;
+    pl.wpu = waves < 1024 && (d.C_in + G - 1) / G >= 8 ? 4 : 1;
+  }
+  return fwd_dispatch<true>(d, x, coef, norm_part, nullptr, pl, prep, nullptr, s);
 }
 
 hipError_t launch_haar_norm(const wcc_desc &d, const void *x, float *norm_part, float *max_part,

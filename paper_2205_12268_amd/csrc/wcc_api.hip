@@ -439,23 +439,25 @@ wcc_status wcc_haar_fwd(wcc_ctx *ctx, const wcc_desc *desc, const float *x, floa
   hipStream_t s = static_cast<hipStream_t>(stream);
   const WsLayout L = ws_layout(*desc);
   const SelectPrep no_prep{nullptr, nullptr, 0.f};
+  const int64_t BN = (int64_t)desc->B * desc->H * desc->W;
+  // (the whole workspace is free for the planes of partial norms)
+  const int G = store_groups(*desc, (int64_t)(L.total / ((size_t)BN * 4)));
   if (!norm || desc->norm == WCC_NORM_L2) {
     // (sums of squares are taken from the stored coefficients in a pass of their own)
     wcc_desc plain = *desc;
     plain.norm = WCC_NORM_L1;
-    WCC_TRY(launch_haar_fwd(plain, x, coef, nullptr, no_prep, s));
+    WCC_TRY(launch_haar_fwd(plain, x, coef, nullptr, G, no_prep, s));
     if (norm)
       WCC_TRY(launch_channel_norm(coef, desc->B, desc->C_in, (int64_t)desc->H * desc->W, true, norm, s));
     return WCC_OK;
   }
   if ((st = need_ws(ctx, L)) != WCC_OK) return st;
-  const int64_t BN = (int64_t)desc->B * desc->H * desc->W;
-  if (L.G == 1) {
-    WCC_TRY(launch_haar_fwd(*desc, x, coef, norm, no_prep, s));
+  if (G == 1) {
+    WCC_TRY(launch_haar_fwd(*desc, x, coef, norm, 1, no_prep, s));
   } else {
-    float *part = reinterpret_cast<float *>(static_cast<char *>(ctx->ws) + L.norm_part);
-    WCC_TRY(launch_haar_fwd(*desc, x, coef, part, no_prep, s));
-    WCC_TRY(launch_norm_reduce(part, L.G, BN, norm, s));
+    float *part = static_cast<float *>(ctx->ws);
+    WCC_TRY(launch_haar_fwd(*desc, x, coef, part, G, no_prep, s));
+    WCC_TRY(launch_norm_reduce(part, G, BN, norm, s));
   }
   return WCC_OK;
 }

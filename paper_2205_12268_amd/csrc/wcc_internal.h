@@ -204,8 +204,10 @@ hipError_t launch_chain_keep(const wcc_desc &d, int64_t k, const ChainSrc &src, 
                              const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s);
 
 // launchers (each returns hipGetLastError() after its launches)
-// (norm_part, max_part: one plane for each of the forward_groups() channel groups)
-hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part,
+// (norm_part, max_part: one plane for each channel group: forward_groups() of them in the fused layer's
+// pass, store_groups() in the storing one, which has memory for `planes` at most)
+int store_groups(const wcc_desc &d, int64_t planes);
+hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part, int G,
                            const SelectPrep &prep, hipStream_t s);
 // norm-only pass (no coefficient is written) and keep-only pass of the fused layer
 // wdw (nullable, [C_in, 3, 3]): the transform's input is the depthwise 3x3 convolution of x
