@@ -247,7 +247,12 @@ static FwdShape fwd_shape(const wcc_desc &d, int front) {
   // (at least two channels a wave)
   const int top = max_wpu(d.levels);
   f.wpu = units * 4 < want && d.C_in >= 2 * top ? top : d.C_in >= 8 ? 4 : 1;
-  while (units * f.wpu * f.G < want && d.C_in / (f.G * 2 * f.wpu) >= 2) f.G *= 2;
+  // (no more groups than a pass without shared units would take: the planes are the caller's memory, and
+  // wcc_forward_static's array holds only so many.  Two groups of a few channels on layers that have the
+  // strips for a thousand waves cost more than they gave: 4 -> 32 channels, 4 x 512 x 512, d = 1, layer
+  // 84.2 -> 79.8 us without; 2 x 16 -> 96 of 436 x 576 90.8 -> 89.3)
+  const int most = groups_for(d, make_map(d, lane_cols(d)), d.C_in, 1024, 4);
+  while (units * f.wpu * f.G < want && f.G * 2 <= most && d.C_in / (f.G * 2 * f.wpu) >= 2) f.G *= 2;
   return f;
 }
 
