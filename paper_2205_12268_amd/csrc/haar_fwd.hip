@@ -14,6 +14,9 @@ namespace {
 //          unit and take a share of the group's channels each (WPU times the waves in flight for
 //          the same number of partial-norm planes); their |coefficient| sums meet in LDS and are
 //          added in wave order.
+// split:   STORE with WPU = 1 only; grid.y = G * split.  A group's channels are cut as split waves that
+//          share a unit would cut them, each part being a launch row with a plane of partial norms of its
+//          own (norm_part [G * split, B, N]), which norm_reduce adds in the order of the shared form.
 // DWM: 0 = x is transformed as it is; 1, 2 = K_dw x is (wdw [C, 3, 3]; 2: the outside columns
 // of a wave row's first and last lane exist and are read).
 // XT: float or bf16_t, the storage type of x.  SQ: sums of squares instead of absolute values.
@@ -25,21 +28,24 @@ __global__ __launch_bounds__(WPU == 1 ? 256 : 64 * WPU) void haar_fwd_kernel(con
                                                        float *__restrict__ max_part, Geo g,
                                                        StripMap m, int C, int Cg, int B,
                                                        SelectPrep prep,
-                                                       const float *__restrict__ wdw) {
+                                                       const float *__restrict__ wdw, int split) {
   constexpr int NS = slot_count(D, V);
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int unit = WPU > 1 ? (int)blockIdx.x : (int)blockIdx.x * 4 + wv;
-  const int grp = blockIdx.y, b = blockIdx.z;
+  constexpr bool kSplit = STORE && WPU == 1;
+  const int plane = blockIdx.y, b = blockIdx.z;
+  const int grp = kSplit ? plane / split : plane;
   // one workgroup per sample clears the state of the selection that follows this kernel
-  if (blockIdx.x == 0 && grp == 0) prep_sample(prep, b, threadIdx.x, blockDim.x);
+  if (blockIdx.x == 0 && plane == 0) prep_sample(prep, b, threadIdx.x, blockDim.x);
   LanePos<D> p;
   int row0, col0;
   locate<D, V>(m, g, unit, p, row0, col0);
   (void)coef;
   int c0 = grp * Cg, c1 = min(C, c0 + Cg);
-  if constexpr (WPU > 1) {
-    const int Cw = (c1 - c0 + WPU - 1) / WPU;
-    c0 = c0 + wv * Cw;
+  if constexpr (WPU > 1 || kSplit) {
+    const int parts = kSplit ? split : WPU, part = kSplit ? plane - grp * split : wv;
+    const int Cw = (c1 - c0 + parts - 1) / parts;
+    c0 = c0 + part * Cw;
     c1 = min(c1, c0 + Cw);
   }
 
@@ -103,23 +109,38 @@ __global__ __launch_bounds__(WPU == 1 ? 256 : 64 * WPU) void haar_fwd_kernel(con
     if (wv > 0) return;
   }
   if (!p.active) return;
-  write_slots<D, V>(norm_part + ((size_t)grp * B + b) * g.N, sink.acc, p);
+  write_slots<D, V>(norm_part + ((size_t)plane * B + b) * g.N, sink.acc, p);
   if constexpr (MX) {
-    if (max_part != nullptr) write_slots<D, V>(max_part + ((size_t)grp * B + b) * g.N, sink.top, p);
+    if (max_part != nullptr) write_slots<D, V>(max_part + ((size_t)plane * B + b) * g.N, sink.top, p);
   }
 }
 
 // ---- small helpers ----------------------------------------------------------------------------
-// norm[i] = sum_g part[g][i], groups added in increasing order (fixed order: reproducible).
-__global__ __launch_bounds__(256) void norm_reduce_kernel(const float *__restrict__ part, int G,
+// norm[i] = sum_g sum_u part[g][u][i], the parts of a group first, then the groups, both in increasing
+// order: the order in which the norm-only pass (waves of a unit in LDS) and the selection (groups) add,
+// so that the two ways to a layer's norms agree bit for bit.
+__global__ __launch_bounds__(256) void norm_reduce_kernel(const float *__restrict__ part, int G, int split,
                                                           int64_t BN4, float4 *__restrict__ norm) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= BN4) return;
-  const float4 *p = reinterpret_cast<const float4 *>(part);
-  float4 s = p[i];
-  for (int gi = 1; gi < G; ++gi) {
-    const float4 t = p[(int64_t)gi * BN4 + i];
-    s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+  const float4 *p = reinterpret_cast<const float4 *>(part) + i;
+  const int planes = G * split;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f), r = s;  // (0 + a sum of |values| is that sum)
+  int left = split;
+  for (int p0 = 0; p0 < planes; p0 += 8) {  // eight loads in flight (past the last plane: it again, unused)
+    float4 t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = p[(int64_t)min(p0 + u, planes - 1) * BN4];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (p0 + u >= planes) break;
+      r.x += t[u].x; r.y += t[u].y; r.z += t[u].z; r.w += t[u].w;
+      if (--left == 0) {
+        s.x += r.x; s.y += r.y; s.z += r.z; s.w += r.w;
+        r = make_float4(0.f, 0.f, 0.f, 0.f);
+        left = split;
+      }
+    }
   }
   norm[i] = s;
 }
@@ -169,8 +190,9 @@ hipError_t fwd_launch_t(const wcc_desc &d, const XT *x, float *coef, float *norm
     constexpr int WPU = decltype(wpu_c)::value, DWM = decltype(dwm_c)::value;
     constexpr bool SQ = decltype(sq_c)::value, NT = decltype(nt_c)::value;
     hipLaunchKernelGGL((haar_fwd_kernel<D, V, WPU, STORE, 1, DWM, XT, SQ, NT>),
-                       dim3(WPU > 1 ? m.units : (m.units + 3) / 4, pl.G, d.B), dim3(WPU > 1 ? 64 * WPU : 256),
-                       0, s, x, coef, norm_part, max_part, g, m, d.C_in, Cg, d.B, prep, wdw);
+                       dim3(WPU > 1 ? m.units : (m.units + 3) / 4, pl.G * (WPU > 1 ? 1 : pl.split), d.B),
+                       dim3(WPU > 1 ? 64 * WPU : 256), 0, s, x, coef, norm_part, max_part, g, m, d.C_in, Cg, d.B,
+                       prep, wdw, pl.split);
     return hipGetLastError();
   };
   // (a prefetch depth of two channels was measured on every workload and never paid)
@@ -275,27 +297,30 @@ hipError_t fwd_dispatch(const wcc_desc &d, const void *x, float *coef, float *no
 
 static Plan fwd_plan(const wcc_desc &d, int front) {
   const FwdShape f = fwd_shape(d, front);
-  return Plan{f.G, f.wpu, streams(d)};
+  return Plan{f.G, f.wpu, streams(d), 1};
 }
 
 // The storing pass writes every coefficient: waves that share a unit write 1 KiB pieces of as many planes
-// where the waves of a workgroup otherwise write one run of 4 KiB.  On large maps that costs more
-// than the planes of partial norms (6 x 432 channels of 56 x 504, 293 MB: 155 against 143 us, the sum over
-// 16 instead of 2 planes 9 against 5); on small ones the launch that sums planes does.
-int store_groups(const wcc_desc &d, int64_t planes) {
+// where the waves of a workgroup otherwise write one run of 4 KiB.  On large maps, above all where a
+// plane is a power of two, that costs more than the waves' sums as planes of their own (16 x 640 channels of
+// 64 x 64, d = 2, 160 MB: 145 us shared, 75 apart, the sum over the planes included; 1 x 1024 of 192 x 256
+// 120 and 88; 6 x 432 of 56 x 504, d = 3, 165 and 154), so there the parts of a group become launch
+// rows of the same channels, and norm_reduce adds them as the waves would have: the norms are those of
+// the norm-only pass bit for bit.  Not where the planes are more than a sixteenth of the channels
+// (4 x 96 of 384 x 320: 79 us shared, 85 apart), nor on maps up to 128 MB (2 x 432 of 56 x 504, 93 MB:
+// 39 and 46; 8 x 640 of 64 x 64, 80 MB, the other way round: 37 and 32).
+StorePlan store_plan(const wcc_desc &d, int64_t planes) {
   const FwdShape f = fwd_shape(d, kFrontNone);
-  if ((int64_t)d.B * d.C_in * d.H * d.W * 4 <= ((int64_t)128 << 20) || f.wpu == 1) return f.G;
-  return (int)std::min<int64_t>(groups_for(d, make_flat_map(d, lane_cols(d)), d.C_in, 1024, 4), planes);
+  const int64_t parts = (int64_t)f.G * f.wpu;
+  const bool apart = f.wpu > 1 && (int64_t)d.B * d.C_in * d.H * d.W * 4 > ((int64_t)128 << 20) &&
+                     parts <= planes && parts * 16 <= d.C_in;
+  return StorePlan{f.G, apart ? f.wpu : 1};
 }
 
-hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part, int G,
+hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part, const StorePlan &sp,
                            const SelectPrep &prep, hipStream_t s) {
   Plan pl = fwd_plan(d, kFrontNone);
-  if (G != pl.G) {
-    const int64_t waves = (int64_t)make_flat_map(d, lane_cols(d)).units * d.B * G;
-    pl.G = G;
-    pl.wpu = waves < 1024 && (d.C_in + G - 1) / G >= 8 ? 4 : 1;
-  }
+  if (sp.split > 1) { pl.split = sp.split; pl.wpu = 1; }
   return fwd_dispatch<true>(d, x, coef, norm_part, nullptr, pl, prep, nullptr, s);
 }
 
@@ -305,10 +330,10 @@ hipError_t launch_haar_norm(const wcc_desc &d, const void *x, float *norm_part, 
   return fwd_dispatch<false>(d, x, nullptr, norm_part, max_part, pl, prep, wdw, s);
 }
 
-hipError_t launch_norm_reduce(const float *norm_part, int G, int64_t BN, float *norm, hipStream_t s) {
+hipError_t launch_norm_reduce(const float *norm_part, const StorePlan &sp, int64_t BN, float *norm, hipStream_t s) {
   const int64_t n4 = BN / 4;
   hipLaunchKernelGGL(norm_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s,
-                     norm_part, G, n4, reinterpret_cast<float4 *>(norm));
+                     norm_part, sp.G, sp.split, n4, reinterpret_cast<float4 *>(norm));
   return hipGetLastError();
 }
 

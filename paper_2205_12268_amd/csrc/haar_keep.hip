@@ -283,7 +283,7 @@ int64_t keep_workgroups(const wcc_desc &d, bool folded) {
 hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap,
                             void *xc, float *alpha_slots, float *wg_max, const float *wdw, float q_alpha,
                             const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
-  const Plan pl{keep_groups(d, wdw != nullptr), 1, streams(d)};
+  const Plan pl{keep_groups(d, wdw != nullptr), 1, streams(d), 1};
   return keep_dispatch(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
 }
 

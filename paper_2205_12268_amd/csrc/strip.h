@@ -582,6 +582,7 @@ struct Plan {
   int G;       // channel groups (grid.y)
   int wpu;     // forward/norm pass only: waves of a workgroup that share a strip unit's channels
   bool stream; // x is read with streaming loads (maps far larger than the memory-side cache)
+  int split;   // storing pass with wpu = 1 only: launch rows that share a group's channels (1: none)
 };
 
 // does a wave row span less than the plane's width (so that its end lanes have neighbours

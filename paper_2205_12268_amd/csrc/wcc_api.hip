@@ -441,23 +441,23 @@ wcc_status wcc_haar_fwd(wcc_ctx *ctx, const wcc_desc *desc, const float *x, floa
   const SelectPrep no_prep{nullptr, nullptr, 0.f};
   const int64_t BN = (int64_t)desc->B * desc->H * desc->W;
   // (the whole workspace is free for the planes of partial norms)
-  const int G = store_groups(*desc, (int64_t)(L.total / ((size_t)BN * 4)));
+  const StorePlan sp = store_plan(*desc, (int64_t)(L.total / ((size_t)BN * 4)));
   if (!norm || desc->norm == WCC_NORM_L2) {
     // (sums of squares are taken from the stored coefficients in a pass of their own)
     wcc_desc plain = *desc;
     plain.norm = WCC_NORM_L1;
-    WCC_TRY(launch_haar_fwd(plain, x, coef, nullptr, G, no_prep, s));
+    WCC_TRY(launch_haar_fwd(plain, x, coef, nullptr, sp, no_prep, s));
     if (norm)
       WCC_TRY(launch_channel_norm(coef, desc->B, desc->C_in, (int64_t)desc->H * desc->W, true, norm, s));
     return WCC_OK;
   }
   if ((st = need_ws(ctx, L)) != WCC_OK) return st;
-  if (G == 1) {
-    WCC_TRY(launch_haar_fwd(*desc, x, coef, norm, 1, no_prep, s));
+  if (sp.G * sp.split == 1) {
+    WCC_TRY(launch_haar_fwd(*desc, x, coef, norm, sp, no_prep, s));
   } else {
     float *part = static_cast<float *>(ctx->ws);
-    WCC_TRY(launch_haar_fwd(*desc, x, coef, part, G, no_prep, s));
-    WCC_TRY(launch_norm_reduce(part, G, BN, norm, s));
+    WCC_TRY(launch_haar_fwd(*desc, x, coef, part, sp, no_prep, s));
+    WCC_TRY(launch_norm_reduce(part, sp, BN, norm, s));
   }
   return WCC_OK;
 }

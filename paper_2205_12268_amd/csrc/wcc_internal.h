@@ -205,9 +205,10 @@ hipError_t launch_chain_keep(const wcc_desc &d, int64_t k, const ChainSrc &src, 
 
 // launchers (each returns hipGetLastError() after its launches)
 // (norm_part, max_part: one plane for each channel group: forward_groups() of them in the fused layer's
-// pass, store_groups() in the storing one, which has memory for `planes` at most)
-int store_groups(const wcc_desc &d, int64_t planes);
-hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part, int G,
+// pass, G * split in the storing one, which has memory for `planes` at most)
+struct StorePlan { int G, split; };
+StorePlan store_plan(const wcc_desc &d, int64_t planes);
+hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part, const StorePlan &sp,
                            const SelectPrep &prep, hipStream_t s);
 // norm-only pass (no coefficient is written) and keep-only pass of the fused layer
 // wdw (nullable, [C_in, 3, 3]): the transform's input is the depthwise 3x3 convolution of x
@@ -227,7 +228,7 @@ hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const i
                             float q_alpha, const float *alpha_src /*nullable*/, int n_alpha,
                             float *alpha_pub /*nullable: receives that largest value*/,
                             hipStream_t s);
-hipError_t launch_norm_reduce(const float *norm_part, int G, int64_t BN, float *norm, hipStream_t s);
+hipError_t launch_norm_reduce(const float *norm_part, const StorePlan &sp, int64_t BN, float *norm, hipStream_t s);
 hipError_t launch_channel_norm(const float *coef, int B, int C, int64_t N, bool squares, float *norm,
                                hipStream_t s);
 SelectPrep make_prep(void *ws_base, const WsLayout &L, float *alpha_slots, float alpha_in);
