@@ -495,7 +495,7 @@ __global__ __launch_bounds__(chain_waves(SEGS) * kWave, 4 / chain_waves(SEGS)) v
   const int c0 = grp * Cg, n_ch = min(C, c0 + Cg) - c0;
   // whole waves leave (SEGS > 1: the waves of a workgroup share their strip, and every segment
   // has lanes inside the plane, so they leave or stay together)
-  if (__ballot(active) == 0 || n_ch <= 0) return;
+  if (__ballot(active) == 0) return;
 
   const int32_t *jm1 = jmap1 + (size_t)b * g.N;
   const bool up_in = row0 > 0, dn_in = row0 + (1 << D) < g.H;
@@ -509,9 +509,12 @@ __global__ __launch_bounds__(chain_waves(SEGS) * kWave, 4 / chain_waves(SEGS)) v
     for (int s = 0; s < NS; ++s) sink.top[s] = 0.f;
   }
   sink.plane = nullptr;
-  chain_walk<D, SEGS>(yc1 + ((size_t)b * C + c0) * k1, k1, n_ch, wdw + (size_t)c0 * 9, cg, tiles[wv], p,
-                      p.lc == 0, p.lc == m.lpr - 1 || col0 + V4 >= g.W, xchg, wv, sink,
-                      [](FwdSink<D, V4, false, SQ> &) {});
+  // (the last groups have no channels where C does not fill them -- 42 channels in 8 groups of 6 --; their
+  // planes are zeros: the selection adds the planes of all groups)
+  if (n_ch > 0)
+    chain_walk<D, SEGS>(yc1 + ((size_t)b * C + c0) * k1, k1, n_ch, wdw + (size_t)c0 * 9, cg, tiles[wv], p,
+                        p.lc == 0, p.lc == m.lpr - 1 || col0 + V4 >= g.W, xchg, wv, sink,
+                        [](FwdSink<D, V4, false, SQ> &) {});
   if (!active) return;
   write_slots<D, V4>(norm_part + ((size_t)grp * B + b) * g.N, sink.acc, p);
   if constexpr (FwdSink<D, V4, false, SQ>::MX) {
