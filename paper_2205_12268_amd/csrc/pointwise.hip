@@ -827,7 +827,11 @@ hipError_t mfma_dispatch(const wcc_desc &d, int64_t k, const void *w, const floa
 // lane): 96 -> 96 channels at 4 x 15360 positions 37.5 -> 19.6 us, 32 -> 32 at 2048 8.2 -> 4.3 us;
 // 87 TFLOP/s at 358 -> 570 channels x 38528.
 // One LDS stage is filled while the other is multiplied, one barrier a stage; the loads of the
-// stage after next travel under the matrix instructions.
+// stage after next travel under the matrix instructions.  With few channels the chain of latencies counts:
+// no load is issued past the last stage, the row scales come in with the first loads, and where rows of yc
+// are not whole words a store's lanes lie side by side.  (Loads past the end, a scale load in front of every store
+// and stores of every other position: 2 -> 79 channels, int8, 3 x 45526 positions 31.4 us, 18.2 now and 19.4 with the
+// vector-unit kernel; 8 -> 544, 6 x 5814 44.9, 23.9 and 23.7; 200 -> 544, fp32, 4 x 31103 327, 312 and 544.)
 template <int DT> struct WLoad;
 template <> struct WLoad<WCC_F32> {
   using T = float;
@@ -859,16 +863,21 @@ __global__ __launch_bounds__(256) void pointwise_f32_kernel(const void *__restri
                                                             float *__restrict__ yc, int M, int K,
                                                             int64_t k) {
   constexpr int TM = 32 * WVM * MB, TN = 32 * (4 / WVM) * NB;
-  constexpr int LDA = FK + 1, LDB = TN + 32;  // LDS row words: the 64 lanes of a read hit 64 banks
+    constexpr int LDA = FK + 1, LDB = TN + 32;  // LDS row words: the 64 lanes of a read of Bs hit 64 banks
+                                              // (of As 47; FK + 2, which makes that 64, measured the same)
   constexpr int NA = TM * FK / 256;           // weights a thread and stage
   constexpr int XV = VEC ? 4 : 1;             // positions a load
   constexpr int NX = TN * FK / 256 / XV;      // loads of activations a thread and stage
+  // Where a lane stores words of two positions the two column blocks of a wave take the even and the
+  // odd positions of its 64; else they lie side by side, so that the lanes of a store do.
+  constexpr int STEP = VEC ? NB : 1;
   static_assert(TM * FK % 256 == 0 && TN * FK % (256 * XV) == 0, "whole loads");
   using WT = typename WLoad<WDT>::T;
   using XT = std::conditional_t<XM == 1, std::conditional_t<VEC, uint32_t, int8_t>,
                                 std::conditional_t<VEC, float4, float>>;
   __shared__ float As[2][TM * LDA];
   __shared__ __attribute__((aligned(16))) float Bs[2][FK * LDB];
+  __shared__ __attribute__((aligned(16))) float scales[WDT == WCC_I8 ? TM : 4];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int wm = wv % WVM, wn = wv / WVM;
   const int b = blockIdx.z, m0 = blockIdx.y * TM;
@@ -940,14 +949,13 @@ __global__ __launch_bounds__(256) void pointwise_f32_kernel(const void *__restri
       float a[MB], x[NB];
 #pragma unroll
       for (int i = 0; i < MB; ++i) a[i] = As[buf][(wm * 32 * MB + i * 32 + fr) * LDA + ks + half];
-      // the two column blocks of a wave take the even and the odd positions of its 64, so that a
-      // lane ends up with two neighbours
-      const float *row = &Bs[buf][(ks + half) * LDB + wn * 32 * NB + NB * fr];
-      if constexpr (NB == 2) {
+      const float *row = &Bs[buf][(ks + half) * LDB + wn * 32 * NB + STEP * fr];
+      if constexpr (STEP == 2) {
         const float2 v = *reinterpret_cast<const float2 *>(row);
         x[0] = v.x; x[1] = v.y;
       } else {
-        x[0] = row[0];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) x[j] = row[32 * j];
       }
 #pragma unroll
       for (int i = 0; i < MB; ++i)
@@ -959,33 +967,43 @@ __global__ __launch_bounds__(256) void pointwise_f32_kernel(const void *__restri
 
   const int stages = (K + FK - 1) / FK;
   load(0);
+  if constexpr (WDT == WCC_I8) {  // (read behind the barriers below)
+    if (t < TM) scales[t] = w_scale[min(m0 + t, M - 1)];
+  }
   stash(0, 0);
-  load(FK);
+  if (stages > 1) load(FK);
   __syncthreads();
   for (int s = 0; s < stages; ++s) {
     multiply(s & 1);
     stash((s + 1) * FK, (s + 1) & 1);  // (every wave left that buffer at the last barrier)
-    load((s + 2) * FK);
+    if (s + 2 < stages) load((s + 2) * FK);
     __syncthreads();
   }
 
-  // acc[i][j][r]: row wm*32*MB + i*32 + (r/4)*8 + (lane/32)*4 + r%4, position wn*32*NB + NB*(lane%32) + j
+  // acc[i][j][r]: row wm*32*MB + i*32 + (r/4)*8 + (lane/32)*4 + r%4, position wn*32*NB + (STEP == 2 ? 2*(lane%32) + j : 32*j + lane%32)
   const float sx = XM != 0 ? al / 127.f : 1.f;
-  const int64_t n = n0 + wn * 32 * NB + NB * fr;
+  const int64_t n = n0 + wn * 32 * NB + STEP * fr;
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int m = m0 + wm * 32 * MB + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-      if (m >= M || n >= k) continue;
-      const float sc = sx * (WDT == WCC_I8 ? w_scale[m] : 1.f);
-      float *dst = yc + ((size_t)b * M + m) * k + n;
-      if constexpr (VEC && NB == 2) {
-        *reinterpret_cast<float2 *>(dst) = make_float2(acc[i][0][r] * sc, acc[i][1][r] * sc);
-      } else {
+    for (int q = 0; q < 4; ++q) {
+      const int row = wm * 32 * MB + i * 32 + q * 8 + half * 4;  // four rows of the lane
+      float4 s4 = make_float4(1.f, 1.f, 1.f, 1.f);
+      if constexpr (WDT == WCC_I8) s4 = *reinterpret_cast<const float4 *>(&scales[row]);
+      const float sw[4] = {s4.x, s4.y, s4.z, s4.w};
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
-          if (n + j < k) dst[j] = acc[i][j][r] * sc;
+      for (int e = 0; e < 4; ++e) {
+        const int m = m0 + row + e, r = 4 * q + e;
+        if (m >= M || n >= k) continue;
+        const float sc = sx * sw[e];
+        float *dst = yc + ((size_t)b * M + m) * k + n;
+        if constexpr (STEP == 2) {
+          *reinterpret_cast<float2 *>(dst) = make_float2(acc[i][0][r] * sc, acc[i][1][r] * sc);
+        } else {
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            if (n + 32 * j < k) dst[32 * j] = acc[i][j][r] * sc;
+        }
       }
     }
 }
@@ -1074,7 +1092,12 @@ hipError_t launch_pointwise(const wcc_desc &d, int64_t k, const void *w, const f
   // (4 GB of weights or of one sample's compressed signal take the plain kernel below)
   const int64_t limit = (int64_t)0xFFFFFFF0;
   const bool narrow = (int64_t)(d.C_out + 256) * K * 2 <= limit && (int64_t)K * k * (xc_is_f32 ? 4 : 1) <= limit;
-  if (narrow && quant && k % 4 == 0) {
+  // (Few channels into few rows leave the stream kernel's tile of 64 rows x 64 channels and more mostly empty: the
+  // fp32 kernel's 32 rows x 16 channels fit them.  8 -> 8 channels, int8 weights, 15 x 265760 positions: 205 us
+  // there, 94 here; 32 -> 16, 8 x 100000: 52 and 32; 40 -> 32, bf16, 4 x 60000: 17.1 and 16.8; 64 -> 32: 17.9 and
+  // 21.7.  The sums of int8 codes are exact either way: 32 * 127 * 127 < 2^24.)
+  const bool few = K <= 32 && d.C_out <= 32;
+  if (narrow && quant && k % 4 == 0 && !few) {
     // (rows of the weights start at whole dwords)
     if (d.w_dtype == WCC_BF16 && K % 2 == 0)
       return mfma_dispatch<false>(d, k, w, w_scale, xc, xc_is_f32, alpha, n_alpha, alpha_out, yc, s);
