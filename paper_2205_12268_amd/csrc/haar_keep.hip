@@ -199,12 +199,20 @@ inline StripMap keep_map(const wcc_desc &d, bool folded) {
   return folded ? make_map(d, lane_cols(d)) : make_flat_map(d, lane_cols(d));
 }
 
-int keep_groups(const wcc_desc &d, bool folded) {
+int keep_groups(const wcc_desc &d, bool folded, bool late) {
   // About two thousand waves, down to two channels each at d <= 2, where a wave has few rows in flight
   // (the 16-layer stack 792 -> 782 us against a thousand waves of four, 256 channels of 256 x 512
   // 123.4 -> 121.3; two channels at d = 3 lose 1-3 %); with K_dw in front as measured there.
-  return groups_for(d, keep_map(d, folded), d.C_in, arithmetic_bound(d, folded) ? 4096 : folded ? 1024 : 2048,
-                    !folded && d.levels <= 2 ? 2 : 4);
+  const StripMap m = keep_map(d, folded);
+  int G = groups_for(d, m, d.C_in, arithmetic_bound(d, folded) ? 4096 : folded ? 1024 : 2048,
+                     !folded && d.levels <= 2 ? 2 : 4);
+  // Planes of one to three strip units leave waves of a workgroup idle, so that two thousand waves are as many
+  // workgroups: too many to leave a maximum each where alpha is found here, and raising slots costs more than
+  // the second thousand gains (15 x 400 bf16 channels of 14 x 10, a fifth kept: 15 us with 960 workgroups, 23 with
+  // 1920).
+  if (late && (int64_t)((m.units + 3) / 4) * G * d.B > kMaxWgMaxima)
+    G = std::min(G, groups_for(d, m, d.C_in, arithmetic_bound(d, folded) ? 4096 : 1024, 4));
+  return G;
 }
 
 template <int D, int V, class XT>
@@ -277,13 +285,14 @@ hipError_t keep_dispatch(const wcc_desc &d, int64_t k, const void *x, const int3
 }
 
 int64_t keep_workgroups(const wcc_desc &d, bool folded) {
-  return (int64_t)((keep_map(d, folded).units + 3) / 4) * keep_groups(d, folded) * d.B;
+  return (int64_t)((keep_map(d, folded).units + 3) / 4) * keep_groups(d, folded, true) * d.B;
 }
 
 hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap,
                             void *xc, float *alpha_slots, float *wg_max, const float *wdw, float q_alpha,
                             const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
-  const Plan pl{keep_groups(d, wdw != nullptr), 1, streams(d), 1};
+  const bool late = alpha_slots != nullptr || wg_max != nullptr;
+  const Plan pl{keep_groups(d, wdw != nullptr, late), 1, streams(d), 1};
   return keep_dispatch(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
 }
 

@@ -54,8 +54,6 @@ namespace {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-constexpr int64_t kMaxWgMaxima = 1024;  // workgroup maxima that a consumer combines by itself
-
 wcc_status check_desc(const wcc_desc *d) {
   if (!d) return WCC_ERR_NULL;
   if (d->B < 1 || d->C_in < 1 || d->C_out < 1 || d->H < 2 || d->W < 2) return WCC_ERR_SHAPE;

@@ -221,7 +221,8 @@ hipError_t launch_haar_norm(const wcc_desc &d, const void *x, float *norm_part, 
 // read on the device): xc is int8 codes for that clipping parameter (alpha_slots unused); else
 // xc is fp32 and max |kept coefficient| goes to wg_max, one value for each of the keep_workgroups()
 // workgroups, or raises alpha_slots (both nullable)
-int64_t keep_workgroups(const wcc_desc &d, bool folded_dw);
+constexpr int64_t kMaxWgMaxima = 1024;  // workgroup maxima that a consumer combines by itself
+int64_t keep_workgroups(const wcc_desc &d, bool folded_dw);  // (when asked for the maxima)
 hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap,
                             void *xc, float *alpha_slots /*nullable*/, float *wg_max /*nullable*/,
                             const float *wdw /*nullable*/,

@@ -17,6 +17,8 @@ SHAPES = [
     (2, 40, 32, 48, 2, 1, 5),       # k = 308
     (3, 30, 64, 72, 3, 1, 7),       # k = 659
     (2, 700, 16, 24, 2, 1, 3),      # over 1024 gather workgroups: the slots
+    (15, 400, 14, 10, 1, 1, 5),     # planes of one strip unit: fewer channel groups, so that the maxima fit
+    (40, 64, 16, 16, 2, 1, 4),      # the same with whole words; more samples than keep workgroups for the maxima
 ]
 
 
