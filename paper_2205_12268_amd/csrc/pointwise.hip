@@ -337,9 +337,12 @@ constexpr int kDies = 8;
 constexpr int kTileM = 128, kTileN = 128, kTileKB = 64, kTileLDR = kTileKB + 16;
 constexpr int kTileMinChannels = 256;
 
-// WM: 32-row blocks of a wave tile, 2 (workgroup tile 128 rows) or 4 (256 rows)
-template <bool I8W, int WM>
-__global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
+// (256-row tiles with 128 x 64 wave tiles, two workgroups a compute unit: measured slower on every layer
+// tried, 176 vs 147 us at 1024 -> 4096 channels; three resident workgroups hide more than the halved
+// conversion work saves)
+// Reached by the stage call, and by fused layers whose compressed signal leaves no room for packed weights.
+template <bool I8W>
+__global__ __launch_bounds__(256, 3) void pointwise_tile_kernel(
     const void *__restrict__ w, const float *__restrict__ w_scale, const int8_t *__restrict__ xq,
     const float *__restrict__ alpha, int n_alpha, float *alpha_out, float *__restrict__ yc, int M,
     int K, int64_t k, bool stream_out, int gx, int gy, int tiles, int dies) {
@@ -347,9 +350,7 @@ __global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
   constexpr int KC = kTileKB / ESZ;       // channels a stage: 64 or 32
   constexpr int CPT = KC / 8;             // channels a thread converts: 8 or 4
   constexpr int LDR = kTileLDR;
-  constexpr int TM = 64 * WM;             // rows of the workgroup tile
-  constexpr int WQ = WM / 2;              // 16-byte weight loads a thread and stage: half a row, or a whole one
-  __shared__ __attribute__((aligned(16))) unsigned char As[2][TM * LDR];
+  __shared__ __attribute__((aligned(16))) unsigned char As[2][kTileM * LDR];
   __shared__ __attribute__((aligned(16))) unsigned char Bs[2][kTileN * LDR];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int wm = wv >> 1, wn = wv & 1;    // the wave's place in the 2 x 2 arrangement
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
   const int tile = (blockIdx.x % dies) * (gridDim.x / dies) + blockIdx.x / dies;
   const int b = tile / (gx * gy), by = (tile / gx) % gy, bx = tile % gx;
   const int64_t n0 = (int64_t)bx * kTileN;
-  const int m0 = by * TM;
+  const int m0 = by * kTileM;
   const int8_t *xb = xq + (size_t)b * K * k;
   const unsigned char *wb = static_cast<const unsigned char *>(w);
   // activation loader: group of four positions, channel group.  A wave takes 8 position groups
@@ -374,9 +375,9 @@ __global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
   if (tile >= tiles) return;  // the workgroups that pad the grid to a multiple of 8
 
   using Acc = std::conditional_t<I8W, intx16, floatx16>;
-  Acc acc[WM][2];
+  Acc acc[2][2];
 #pragma unroll
-  for (int i = 0; i < WM; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -394,7 +395,7 @@ __global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
   // no other.
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   struct Regs {
-    u32x4 w[2 * WQ];
+    u32x4 w[2];
     uint32_t x[CPT];
   };
   const __amdgpu_buffer_rsrc_t wdesc = __builtin_amdgcn_make_buffer_rsrc(
@@ -405,12 +406,12 @@ __global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
   // (two lanes a row: their 16-byte LDS writes collide pairwise with those of other rows, but a
   // row per lane -- conflict-free in LDS -- makes every load touch 64 cache lines instead of 32
   // and was measured slower, 175 vs 147 us)
-  const int a_row = WM == 2 ? t >> 1 : t, a_half = WM == 2 ? t & 1 : 0;
+  const int a_row = t >> 1, a_half = t & 1;
   const uint32_t wrow = (uint32_t)(m0 + a_row) * (uint32_t)(K * ESZ);
   const uint32_t xcol = (uint32_t)(n0 + 4 * g) + (uint32_t)(kq * CPT) * (uint32_t)k;
   auto fetch = [&](Regs &r, int st) {
 #pragma unroll
-    for (int q = 0; q < 2 * WQ; ++q) {
+    for (int q = 0; q < 2; ++q) {
       // first channel of the 16-byte load; a stage is whole or empty in K (C_in is a multiple of
       // what 16 bytes hold), but its two halves may differ: the choice is the lane's
       const int kk = st * KC + (a_half * 2 + q) * (16 / ESZ);
@@ -425,7 +426,7 @@ __global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
   // high half), 8 bytes of K for each of the four positions
   auto stash = [&](const Regs &r, int buf) {
 #pragma unroll
-    for (int q = 0; q < 2 * WQ; ++q)
+    for (int q = 0; q < 2; ++q)
       *reinterpret_cast<u32x4 *>(&As[buf][a_row * LDR + (a_half * 2 + q) * 16]) = r.w[q];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -455,15 +456,15 @@ __global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
   auto multiply = [&](int buf) {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      uint4 a[WM], bb[2];
+      uint4 a[2], bb[2];
 #pragma unroll
-      for (int i = 0; i < WM; ++i)
-        a[i] = *reinterpret_cast<const uint4 *>(&As[buf][(wm * (32 * WM) + i * 32 + fr) * LDR + ks * 32 + half * 16]);
+      for (int i = 0; i < 2; ++i)
+        a[i] = *reinterpret_cast<const uint4 *>(&As[buf][(wm * 64 + i * 32 + fr) * LDR + ks * 32 + half * 16]);
 #pragma unroll
       for (int j = 0; j < 2; ++j)
         bb[j] = *reinterpret_cast<const uint4 *>(&Bs[buf][(wn * 64 + j * 32 + fr) * LDR + ks * 32 + half * 16]);
 #pragma unroll
-      for (int i = 0; i < WM; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           if constexpr (I8W)
@@ -511,10 +512,10 @@ __global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
     auto store_rows = [&](auto whole_c, auto stream_c) {
       constexpr bool WHOLE = decltype(whole_c)::value, STREAM = decltype(stream_c)::value;
 #pragma unroll
-      for (int i = 0; i < WM; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int m = m0 + wm * (32 * WM) + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+          const int m = m0 + wm * 64 + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
           if (WHOLE || m < M) {
             const float sc = I8W ? sx * w_scale[m] : sx;
             const float v0 = (float)acc[i][0][r] * sc, v1 = (float)acc[i][1][r] * sc;
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
           }
         }
     };
-    const bool whole = m0 + wm * (32 * WM) + 32 * WM <= M;
+    const bool whole = m0 + wm * 64 + 64 <= M;
     if (whole) {
       if (stream_out) store_rows(std::true_type{}, std::true_type{});
       else store_rows(std::true_type{}, std::false_type{});
@@ -548,8 +549,8 @@ __global__ __launch_bounds__(256, WM == 2 ? 3 : 2) void pointwise_tile_kernel(
 // row and instruction, which cost the address unit as much as the matrix cores had to do
 // (1024 -> 256 channels: 110 us); so the weights are first brought into the order of the
 // instructions (PackJob), one contiguous KiB a load: 88 us.  The fused calls do that inside the
-// selection's first kernel, in memory that the codes leave free; the stage call, which has
-// no workspace, keeps the kernel above.
+// selection's first kernel, in memory that the codes leave free; the stage call, which needs no
+// workspace unless weights are 4-bit, keeps the kernel above.
 // A workgroup's four waves take 64 * WM rows (WM waves) x 32 * CB * 4 / WM positions.  A stage is 128
 // bytes of K (64 channels of bf16, 128 of int8), two LDS buffers, one barrier a stage; the
 // activations of the stage after next are in flight under the matrix instructions.  The tiles are
@@ -756,16 +757,15 @@ hipError_t wide_launch(const wcc_desc &d, int64_t k, const uint4 *packed, const 
   return hipGetLastError();
 }
 
-template <bool I8W, int WM>
+template <bool I8W>
 hipError_t tile_launch(const wcc_desc &d, int64_t k, const void *w, const float *w_scale, const void *xc,
                        const float *alpha, int n_alpha, float *alpha_out, float *yc, hipStream_t s) {
-  constexpr int TM = 64 * WM;
-  const int64_t gx = (k + kTileN - 1) / kTileN, gy = (d.C_out + TM - 1) / TM;
+  const int64_t gx = (k + kTileN - 1) / kTileN, gy = (d.C_out + kTileM - 1) / kTileM;
   const int64_t tiles = gx * gy * d.B;
   if (tiles > (int64_t)1 << 30) return hipErrorInvalidValue;
   dim3 grid((unsigned)((tiles + kDies - 1) / kDies * kDies)), block(256);
   const bool stream_out = (int64_t)d.B * d.C_out * k * 4 > ((int64_t)512 << 20);
-  hipLaunchKernelGGL((pointwise_tile_kernel<I8W, WM>), grid, block, 0, s, w, w_scale,
+  hipLaunchKernelGGL((pointwise_tile_kernel<I8W>), grid, block, 0, s, w, w_scale,
                      static_cast<const int8_t *>(xc), alpha, n_alpha, alpha_out, yc, d.C_out, d.C_in, k,
                      stream_out, (int)gx, (int)gy, (int)tiles,
                      (int64_t)d.C_out * d.C_in * (I8W ? 1 : 2) >= ((int64_t)1 << 20) ? kDies : 1);
@@ -796,11 +796,8 @@ hipError_t mfma_dispatch(const wcc_desc &d, int64_t k, const void *w, const floa
                          float *yc, hipStream_t s) {
 #define WCC_MFMA(BM_, BN_) \
   return mfma_launch<BM_, BN_, I8W>(d, k, w, w_scale, xc, f32, alpha, n_alpha, alpha_out, yc, s)
-  // (WM = 4, 256-row tiles with 128 x 64 wave tiles, two workgroups a compute unit: measured
-  // slower on every layer tried, 176 vs 147 us at 1024 -> 4096 channels; three resident
-  // workgroups hide more than the halved conversion work saves)
   if (wants_tile_kernel(d, k, f32))
-    return tile_launch<I8W, 2>(d, k, w, w_scale, xc, alpha, n_alpha, alpha_out, yc, s);
+    return tile_launch<I8W>(d, k, w, w_scale, xc, alpha, n_alpha, alpha_out, yc, s);
   const int64_t want = 256;  // compute units
   auto wgs = [&](int bm, int bn) {
     return ((k + bn - 1) / bn) * ((d.C_out + bm - 1) / bm) * (int64_t)d.B;
@@ -1070,8 +1067,10 @@ hipError_t launch_pack(const PackJob &job, hipStream_t s) {
 hipError_t launch_pointwise_packed(const wcc_desc &d, int64_t k, const PackJob &job, const float *w_scale,
                                    const void *xc, const float *alpha, int n_alpha, float *alpha_out,
                                    float *yc, hipStream_t s) {
-  // The largest tile that still gives a compute unit two workgroups, else 256 x 64; layers of up to
-  // 128 rows do not fill a 256-row tile.
+  // The largest tile that still gives a compute unit two workgroups: 256 x 128, or 128 x 128 for layers of up
+  // to 128 rows; else 256 x 64, also for those: half its waves then multiply zeros, but it makes twice the
+  // workgroups of 128 x 128 (384 -> 96 channels, bf16, 4 x 512 positions: 7.6 us and 9.0; 512 -> 128, 4 x 1024: 8.6
+  // and 9.7; 256 -> 80, 8 x 2048: 6.8 and 8.6; 512 -> 96, int8, 4 x 4096: 10.0 and 9.9).
   auto wgs = [&](int tm, int tn) { return (k + tn - 1) / tn * ((d.C_out + tm - 1) / tm) * (int64_t)d.B; };
 #define WCC_WIDE(WM, CB)                                                                                          \
   return job.wt == WCC_BF16                                                                                       \

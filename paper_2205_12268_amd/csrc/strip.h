@@ -534,6 +534,8 @@ __device__ __forceinline__ void workgroup_lds_barrier() {
 // neither the packed lists of the keep pass and the inverse room in LDS nor a second wave a SIMD:
 // with four columns the keep pass and the inverse of 3 x 48 -> 96 channels of 16 x 64 (all kept) took
 // 28 and 24 us (14 and 15 now), the keep pass of 2 x 96 channels of 256 x 512 (1/8 kept) 34 us (24).
+// Bf16 maps, whose loads are then 4 bytes a lane, unquantised and half kept, gain least: keep pass of the same
+// shape 27.5 -> 26.7 us, layer to 96 channels 148 -> 113.
 __host__ __device__ inline int lane_cols(const wcc_desc &d) { return d.W % 4 != 0 || d.levels == 4 ? 2 : 4; }
 
 // A wave covers (64 / lpr) strips x (lpr lanes of V columns).  lpr is the power of two that

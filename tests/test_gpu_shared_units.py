@@ -63,7 +63,8 @@ def test_norms_and_index_sets(ref, shape):
         ctx.wcc_forward(dd, dev(xx).to(t), wd, None, 0.0, y, idx, alpha)
         np.testing.assert_array_equal(idx.cpu().numpy().astype(np.int64), o_idx)
         assert float(alpha.item()) == o_alpha
-        assert rel_l2(y.float().cpu().numpy(), want) <= 1e-2
+        # fp32 maps: exact products, at most 200 additions of 2^-24 each, then the inverse; bf16: one rounding of y
+        assert rel_l2(y.float().cpu().numpy(), want) <= (1e-5 if act == wcc.F32 else 1e-2)
     ctx.close()
 
 
