@@ -301,20 +301,24 @@ static Plan fwd_plan(const wcc_desc &d, int front) {
 }
 
 // The storing pass writes every coefficient: waves that share a unit write 1 KiB pieces of as many planes
-// where the waves of a workgroup otherwise write one run of 4 KiB.  On large maps, above all where a
-// plane is a power of two, that costs more than the waves' sums as planes of their own (16 x 640 channels of
-// 64 x 64, d = 2, 160 MB: 145 us shared, 75 apart, the sum over the planes included; 1 x 1024 of 192 x 256
-// 120 and 88; 6 x 432 of 56 x 504, d = 3, 165 and 154), so there the parts of a group become launch
-// rows of the same channels, and norm_reduce adds them as the waves would have: the norms are those of
-// the norm-only pass bit for bit.  Not where the planes are more than a sixteenth of the channels
-// (4 x 96 of 384 x 320: 79 us shared, 85 apart), nor on maps up to 128 MB (2 x 432 of 56 x 504, 93 MB:
-// 39 and 46; 8 x 640 of 64 x 64, 80 MB, the other way round: 37 and 32).
+// where the waves of a workgroup otherwise write one run of 4 KiB, and sixteen of them on few units keep as
+// few compute units busy.  Where that costs more than the waves' sums as planes of their own, the parts of
+// a group become launch rows of the same channels, and norm_reduce adds them as the waves would have: the
+// norms are those of the norm-only pass bit for bit.  Measured, shared and apart, the sum over the planes
+// included (us; in brackets inputs that are in no cache):
+//   large maps, planes at most a sixteenth of the channels: 6 x 432 channels of 56 x 504, d = 3, 293 MB, 165 and 154;
+//   1 x 1024 of 192 x 256, d = 2, 201 MB, 120 and 88; with more planes 4 x 96 of 384 x 320, 189 MB, 79 and 85;
+//   sixteen waves on fewer than 128 units from 32 MB on, planes at most an eighth: 16 x 512 of 64 x 64, d = 2, 134 MB,
+//   63 and 52 (136 and 85); 2 x 512 of 128 x 128, 67 MB, 31 and 27 (76 and 45); 2 x 256, 34 MB, 20 and 17 (39 and 30);
+//   with more planes 1 x 400 of 100 x 212, 34 MB, 17 and 21 (35 and 34); on more units 2 x 256 of 128 x 128, d = 1,
+//   15 and 20 (25 and 31); on smaller maps 2 x 512 of 64 x 64, 17 MB, 13 and 19 (23 and 26).
 StorePlan store_plan(const wcc_desc &d, int64_t planes) {
   const FwdShape f = fwd_shape(d, kFrontNone);
-  const int64_t parts = (int64_t)f.G * f.wpu;
-  const bool apart = f.wpu > 1 && (int64_t)d.B * d.C_in * d.H * d.W * 4 > ((int64_t)128 << 20) &&
-                     parts <= planes && parts * 16 <= d.C_in;
-  return StorePlan{f.G, apart ? f.wpu : 1};
+  const int64_t bytes = (int64_t)d.B * d.C_in * d.H * d.W * 4, parts = (int64_t)f.G * f.wpu;
+  const int64_t shared_wgs = (int64_t)make_flat_map(d, lane_cols(d)).units * d.B * f.G;
+  const bool large = bytes > ((int64_t)128 << 20) && parts * 16 <= d.C_in;
+  const bool few = f.wpu == 16 && shared_wgs < 128 && bytes >= ((int64_t)32 << 20) && parts * 8 <= d.C_in;
+  return StorePlan{f.G, f.wpu > 1 && parts <= planes && (large || few) ? f.wpu : 1};
 }
 
 hipError_t launch_haar_fwd(const wcc_desc &d, const float *x, float *coef, float *norm_part, const StorePlan &sp,

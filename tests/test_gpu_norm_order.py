@@ -1,6 +1,6 @@
 """The two ways to a layer's channel norms (needs an MI355X): the norm-only pass of wcc_forward and the storing
-pass of wcc_haar_fwd, which on maps over 128 MB gives the parts of a channel group launch rows and
-planes of their own.  Both add in one order, so the index sets agree on any input; the storing pass stays
+pass of wcc_haar_fwd, which on large maps, and on middling ones of few strip units, gives the parts of a
+channel group launch rows and planes of their own.  Both add in one order, so the index sets agree on any input; the storing pass stays
 inside its buffers; the norm-only pass reads inputs over 256 MB past the cache, with 8 and 16 waves a unit."""
 import numpy as np
 import pytest
@@ -15,6 +15,7 @@ SHAPES = [
     (6, 432, 56, 504, 3),    # 293 MB: two groups of eight parts
     (1, 1030, 72, 504, 3),   # 150 MB: eight groups, the last one short, of eight ragged parts
     (1, 1024, 96, 352, 2),   # 138 MB: sixteen parts, rows that run on from strip to strip
+    (2, 260, 128, 128, 2),   # 34 MB in 32 units: two groups of sixteen parts, the last ones short
     (4, 96, 384, 320, 3),    # 189 MB, too few channels for planes of their own: waves share a unit
     (2, 100, 32, 64, 1),     # small: shared units, several groups
     (2, 200, 24, 40, 3),
@@ -71,7 +72,7 @@ def dyadic(shape, seed):
 
 
 @pytest.mark.parametrize("keep", [(1, 4), (1, 1024)])
-@pytest.mark.parametrize("shape", SHAPES[:3], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", SHAPES[:4], ids=lambda s: "x".join(map(str, s)))
 def test_storing_pass_stays_inside_its_buffers(shape, keep):
     """A workspace of exactly the bytes asked for: with a quarter kept it holds the planes of the parts, with
     1/1024 kept it does not (and waves share a unit again)."""
