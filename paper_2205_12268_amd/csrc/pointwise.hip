@@ -1091,11 +1091,12 @@ hipError_t launch_pointwise(const wcc_desc &d, int64_t k, const void *w, const f
   // (4 GB of weights or of one sample's compressed signal take the plain kernel below)
   const int64_t limit = (int64_t)0xFFFFFFF0;
   const bool narrow = (int64_t)(d.C_out + 256) * K * 2 <= limit && (int64_t)K * k * (xc_is_f32 ? 4 : 1) <= limit;
-  // (Few channels into few rows leave the stream kernel's tile of 64 rows x 64 channels and more mostly empty: the
+  // (Few channels into few rows leave the stream kernel's large tile, 128 rows x 64 channels, mostly empty: the
   // fp32 kernel's 32 rows x 16 channels fit them.  8 -> 8 channels, int8 weights, 15 x 265760 positions: 205 us
   // there, 94 here; 32 -> 16, 8 x 100000: 52 and 32; 40 -> 32, bf16, 4 x 60000: 17.1 and 16.8; 64 -> 32: 17.9 and
-  // 21.7.  The sums of int8 codes are exact either way: 32 * 127 * 127 < 2^24.)
-  const bool few = K <= 32 && d.C_out <= 32;
+  // 21.7.  The sums of int8 codes are exact either way: 32 * 127 * 127 < 2^24.  Signals too short for that tile stay
+  // with the 64 x 64 one: 24 -> 4, quantised on load, 8 x 2688, 5.0 us there and 5.7; 32 -> 16, 4 x 3840, 5.7 and 5.3.)
+  const bool few = K <= 32 && d.C_out <= 32 && (k + 127) / 128 * (int64_t)d.B >= 256;
   if (narrow && quant && k % 4 == 0 && !few) {
     // (rows of the weights start at whole dwords)
     if (d.w_dtype == WCC_BF16 && K % 2 == 0)

@@ -1,5 +1,5 @@
 """The contraction of few channels (needs an MI355X): up to 32 channels into up to 32 rows of 8-bit codes take the fp32
-matrix kernel, beyond that the 8-bit one; one, two and three stages of 16 channels; rows of the compressed
+matrix kernel where the signal is long, beyond that the 8-bit one; one, two and three stages of 16 channels; rows of the compressed
 signal of whole words and not.  int8 weights bit for bit (every sum is an exact integer), bf16 within the
 rounding of the additions."""
 import numpy as np
@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("wt", [wcc.I8, wcc.BF16])
-@pytest.mark.parametrize("B,H,W", [(1, 2, 6), (2, 30, 34), (3, 64, 132)])     # k = 3, 255 and 2112
+@pytest.mark.parametrize("B,H,W", [(1, 2, 6), (2, 30, 34), (3, 64, 132), (16, 64, 132)])     # k = 3, 255, 2112 and, enough
+# workgroups for the large tiles, 2112 again
 @pytest.mark.parametrize("K,M", [(1, 1), (8, 8), (12, 32), (16, 33), (32, 32), (33, 32), (32, 33), (36, 20), (48, 130)])
 def test_few_channels(ref, K, M, B, H, W, wt):
     k = -(-H * W // 4)
