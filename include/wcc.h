@@ -47,7 +47,8 @@
  *   WCC_I4 weights          uint8  [C_out, C_in/2]: two signed 4-bit codes (two's complement,
  *                                  -7..7) a byte, channel 2i in the low nibble, 2i+1 in the
  *                                  high one; C_in must be even.  The codes are widened to int8
- *                                  by a small kernel into the workspace and then take the int8
+ *                                  in the workspace (by a small kernel, or on the way into the
+ *                                  packed order of the contraction) and then take the int8
  *                                  path (the paper's tables use 4-bit weights with 8-bit
  *                                  activations).
  */
@@ -107,7 +108,8 @@ enum {
   WCC_T_HAAR_FWD = 0,  /* first transform pass (channel norms), one kernel            */
   WCC_T_NORM_SELECT,   /* norm reduction + radix select + index emission               */
   WCC_T_GATHER,        /* second transform pass: kept coefficients + max|c|, one kernel */
-  WCC_T_POINTWISE,     /* quantise + contraction + dequantise, one kernel              */
+  WCC_T_POINTWISE,     /* quantise + contraction + dequantise (and, on some layers of many
+                          channels, the packing of the weights in front)               */
   WCC_T_SCATTER_IHAAR, /* scatter + inverse Haar, one kernel                           */
   WCC_T_EVENT_PAIR,    /* an empty bracket: what two event records cost by themselves  */
   WCC_T_DEPTHWISE,     /* wcc_block_forward only: the depthwise 3x3 kernel             */
@@ -173,9 +175,10 @@ wcc_status wcc_gather_quant(wcc_ctx *ctx, const wcc_desc *desc, const float *coe
 /* ---- C: the 1x1 convolution on the compressed signal,  y_i = sum_j k_ij x_j --------------
  * yc[b,o,j] = s_x * s_w[o] * sum_c w[o,c] * xc[b,c,j]  with s_x = alpha/127 for int8 codes
  * (alpha read from alpha_dev on the device) and 1 for fp32 xc; s_w = w_scale for int8
- * weights (required then), else 1.  Arithmetic: bf16 or int8 weights with int8 codes run on
- * the matrix cores (bf16 x bf16 -> fp32, int8 x int8 -> int32); every other combination
- * is computed with fp32 FMAs on the weights widened to fp32. */
+ * weights (required then), else 1.  Everything runs on the matrix cores: bf16 or int8 weights
+ * with int8 codes as bf16 x bf16 -> fp32 or int8 x int8 -> int32 where rows are whole words and
+ * the shape fills their tiles; every other combination as fp32 x fp32 -> fp32 on operands
+ * widened to fp32 (int8 x int8 sums are exact there while they stay below 2^24). */
 wcc_status wcc_pointwise(wcc_ctx *ctx, const wcc_desc *desc, const void *w,
                          const float *w_scale /*nullable unless w_dtype = I8*/, const void *xc,
                          const float *alpha_dev /*nullable unless act_quant_bits = 8*/,
@@ -191,7 +194,10 @@ wcc_status wcc_scatter_ihaar(wcc_ctx *ctx, const wcc_desc *desc, const float *yc
 
 /* ---- the whole layer (Alg. 1 with the quantiser between shrinkage and convolution) ------
  * y = H^T T^T K T H x.  Intermediates live in the workspace.  Results are those of the five
- * calls above run in sequence.  idx_out ([B,k]) and alpha_out_dev (1 float) are optional. */
+ * calls above run in sequence: the same index set (with WCC_NORM_L1, whose norms are the same
+ * bits both ways; the two sums of squares of WCC_NORM_L2 differ in their order of summation) and
+ * the same codes; the contraction may add its products in another order (fp32 rounding).
+ * idx_out ([B,k]) and alpha_out_dev (1 float) are optional. */
 wcc_status wcc_forward(wcc_ctx *ctx, const wcc_desc *desc, const void *x, const void *w,
                        const float *w_scale /*nullable unless I8*/, float alpha_in, void *y,
                        int32_t *idx_out /*nullable*/, float *alpha_out_dev /*nullable*/,
