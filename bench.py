@@ -71,8 +71,8 @@ def read_profile_column(profile_dir: str, prefix: str, workload: str, kernel: st
 
 def profiled_kernel_name(profile_dir: str, workload: str, prefix: str, default: str) -> str:
     """Name (without template arguments) of the first kernel starting with `prefix` in the
-    committed `kernel_stats_<workload>.txt`: the library picks between two contraction
-    kernels by shape, and the profile says which one ran."""
+    committed `kernel_stats_<workload>.txt`: the library picks among four contraction
+    kernels by shape and type, and the profile says which one ran."""
     path = os.path.join(profile_dir, f"kernel_stats_{workload}.txt")
     if os.path.exists(path):
         for line in open(path):
@@ -646,8 +646,8 @@ def main() -> int:
         # the contraction against the matrix-core peak of its operand type, and the counter's
         # own reading of how busy the matrix cores were (profiles/sq_counters_*.txt); the stage
         # is bound by HBM at these shapes, so its HBM fraction stands beside it
-        "mfma": {"kernel": profiled_kernel_name(prof, cfg.name, "pointwise_",
-                                                "pointwise_mfma_kernel"), "flops": flops,
+        "mfma": {"kernel": profiled_kernel_name(prof, cfg.name, "pointwise_", "pointwise_mfma_kernel"
+                                                if cfg.act_bits else "pointwise_f32_kernel"), "flops": flops,
                  "achieved_tflops": round(gemm_tflops, 2), "peak_tflops": MFMA_PEAK_TFLOPS[wname],
                  "frac": round(gemm_tflops / MFMA_PEAK_TFLOPS[wname], 4),
                  "busy_frac_counter": read_profile_column(prof, "sq_counters", cfg.name,
