@@ -110,7 +110,8 @@ enum {
   WCC_T_GATHER,        /* second transform pass: kept coefficients + max|c|, one kernel */
   WCC_T_POINTWISE,     /* quantise + contraction + dequantise (and, on some layers of many
                           channels, the packing of the weights in front)               */
-  WCC_T_SCATTER_IHAAR, /* scatter + inverse Haar, one kernel                           */
+  WCC_T_SCATTER_IHAAR, /* scatter + inverse Haar, one kernel; on layers of few channels and
+                          a long kept signal the contraction too (WCC_T_POINTWISE is 0) */
   WCC_T_EVENT_PAIR,    /* an empty bracket: what two event records cost by themselves  */
   WCC_T_DEPTHWISE,     /* wcc_block_forward only: the depthwise 3x3 kernel             */
   WCC_T_COUNT

@@ -195,6 +195,264 @@ __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x
   }
 }
 
+
+// ---- the same into words ---------------------------------------------------------------------------
+// Every lane's coefficients of a channel go into an LDS tile [slot][lane]; the wave picks its kept positions,
+// unit by unit (four units a wave, consecutive in the compressed signal), NI rows of 64.  8-bit codes of
+// four channels make a word, so that a row of 64 positions and four channels is one store of 256 contiguous bytes.
+// Stores of a channel group of four are issued behind the first transform of the next one: between a load and the
+// wait for it every path has the same number of memory instructions.
+// Bound by its reads of x: 4 x 64 channels of 512 x 1024, an eighth kept, 99 us, where a byte store a code, in short runs
+// of lines that several dies write, takes the kernel above 114 (the norm pass reads the same x in 82).
+// grid = (ceil(wave units / 4), G, B), block = 256; group y takes the quads of channels y, y + G, ...
+template <int D, int V>
+struct WordSink {
+  uint32_t *tile;  // this lane's column of [slot][lane]
+  template <int L, int J>
+  __device__ __forceinline__ void put_row(const LanePos<D> &, int i, const float (&v)[cols_at(V, L)], bool) {
+    constexpr int CV = cols_at(V, L), base = slot_base(D, V, L, J);
+#pragma unroll
+    for (int e = 0; e < CV; ++e) tile[(base + i * CV + e) * kWave] = __float_as_uint(v[e]);
+  }
+};
+
+template <int D, int V, bool Q8, class XT, bool NT>
+__global__ __launch_bounds__(256) void haar_keep_words_kernel(const XT *__restrict__ x, const int32_t *__restrict__ jmap,
+                                                              const uint32_t *__restrict__ ucount, int upad,
+                                                              uint32_t *__restrict__ xw, float *alpha_slots,
+                                                              float *wg_max, Geo g, StripMap m, int C, int64_t ks,
+                                                              float q_alpha, const float *__restrict__ alpha_src,
+                                                              int n_alpha, float *alpha_pub) {
+  constexpr int NS = slot_count(D, V), R = 1 << D;
+  __shared__ float wmax[4];
+  __shared__ uint32_t tiles[4][NS * kWave];
+  const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int unit = blockIdx.x * 4 + wv, grp = blockIdx.y, G = gridDim.y;
+  const int b = gridDim.z - 1 - blockIdx.z;  // (last to first: what the norm pass left in the cache is the tail)
+  LanePos<D> p;
+  int row0, col0;
+  const bool active = locate<D, V>(m, g, unit, p, row0, col0);
+  const int quads = (C + 3) / 4, nq = grp < quads ? (quads - grp + G - 1) / G : 0;
+
+  const int32_t *jm = jmap + (size_t)b * g.N;
+  int at[NS];
+  auto fetch = [&](auto Lc, auto Jc) {
+    constexpr int L = decltype(Lc)::value, J = decltype(Jc)::value;
+    constexpr int CV = cols_at(V, L), S2 = span_at(V, L);
+    const bool owner = (S2 == 1) || ((p.lc & (S2 - 1)) == 0);
+#pragma unroll
+    for (int i = 0; i < rows_at(D, L); ++i)
+#pragma unroll
+      for (int e = 0; e < CV; ++e) {
+        constexpr int base = slot_base(D, V, L, J);
+        int j = -1;
+        if (active && owner) j = jm[J * p.nl[L] + p.off[L] + i * p.rowlen[L] + e];
+        at[base + i * CV + e] = j;
+      }
+  };
+  auto each_level = [&](auto Lc) {
+    constexpr int L = decltype(Lc)::value;
+    fetch(Lc, std::integral_constant<int, 1>{});
+    fetch(Lc, std::integral_constant<int, 2>{});
+    fetch(Lc, std::integral_constant<int, 3>{});
+    if constexpr (L == D) fetch(Lc, std::integral_constant<int, 0>{});
+  };
+  each_level(std::integral_constant<int, 1>{});
+  if constexpr (D >= 2) each_level(std::integral_constant<int, 2>{});
+  if constexpr (D >= 3) each_level(std::integral_constant<int, 3>{});
+  if constexpr (D >= 4) each_level(std::integral_constant<int, 4>{});
+  // kept positions in front of this wave's units
+  uint32_t before = 0;
+  {
+    const uint4 *uc = reinterpret_cast<const uint4 *>(ucount + (size_t)b * upad);  // four units: one wave's
+    const int n = min(unit, upad / 4);
+    for (int i = lane; i < n; i += kWave) {
+      const uint4 v = uc[i];
+      before += v.x + v.y + v.z + v.w;
+    }
+  }
+  if constexpr (Q8) {
+    if (alpha_src != nullptr) {  // (uniform over the grid)
+      q_alpha = alpha_max(alpha_src, n_alpha);
+      if (alpha_pub != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0)
+        alpha_pub[0] = q_alpha;
+    }
+  }
+  const Quant quant(Q8 ? q_alpha : 0.f);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, kWave);
+  before = (uint32_t)__builtin_amdgcn_readfirstlane((int)before);
+
+  // the wave's list: unit by unit, slot by slot, lane by lane
+  uint32_t *tile = tiles[wv];
+  const int shift = lane & 16;
+  auto mine16 = [&](uint64_t kept) {  // the votes of this lane's unit
+    return ((lane & 32 ? (uint32_t)(kept >> 32) : (uint32_t)kept) >> shift) & 0xFFFFu;
+  };
+  int total = 0;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) total += __popc(mine16(__ballot(at[s] >= 0)));
+  const int t0 = __builtin_amdgcn_readlane(total, 0), t1 = __builtin_amdgcn_readlane(total, 16);
+  const int t2 = __builtin_amdgcn_readlane(total, 32), count = t0 + t1 + t2 + __builtin_amdgcn_readlane(total, 48);
+  float mx = 0.f;
+  if (count > 0 && nq > 0) {
+    int running = lane < 16 ? 0 : lane < 32 ? t0 : lane < 48 ? t0 + t1 : t0 + t1 + t2;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const uint32_t kept = mine16(__ballot(at[s] >= 0));
+      if (at[s] >= 0) tile[running + __popc(kept & ((1u << (lane & 15)) - 1u))] = (uint32_t)(s * kWave + lane);
+      running += __popc(kept);
+    }
+    wave_lds_fence();
+    const int ni = (count + kWave - 1) / kWave;
+    // Sixteen rows a walk over the channels at most: 32 rows take the registers of a second wave.  The cells of
+    // the second walk wait two to a register.
+    constexpr int kRows = 16;
+    constexpr bool kTwo = (V << D) > kRows;
+    auto entry = [&](int i) { return tile[min(lane + kWave * i, count - 1)]; };
+    uint32_t later[kTwo ? kRows / 2 : 1];
+    if constexpr (kTwo) {
+#pragma unroll
+      for (int i = 0; i < kRows / 2; ++i) later[i] = entry(kRows + 2 * i) | entry(kRows + 2 * i + 1) << 16;
+    }
+    // (lanes outside the plane read the plane's first rows; their values are in no list)
+    const XT *src = x + (size_t)b * C * g.N + (active ? (size_t)row0 * g.W + col0 : (size_t)0);
+    uint32_t *out = xw + (size_t)b * (Q8 ? quads : C) * ks + before;
+    // cell: past the end of the list its last entry again (the stores there are dropped); left: entries
+    auto walk = [&](auto ni_c, const uint32_t (&cell)[decltype(ni_c)::value], uint32_t *out, int left) {
+      constexpr int NI = decltype(ni_c)::value;
+      wave_lds_fence();
+      WordSink<D, V> sink{tile + lane};
+      uint32_t word[NI];
+#pragma unroll
+      for (int i = 0; i < NI; ++i) word[i] = 0;
+      // row of the signal, -1: nothing yet
+      auto store = [&](int row) {
+        const bool in = row >= 0 && (Q8 || row < C);
+        const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc(out + (size_t)(in ? row : 0) * ks, 0,
+                                                                           in ? left * 4 : 0, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) __builtin_amdgcn_raw_buffer_store_b32(word[i], to, (lane + kWave * i) * 4, 0, 0);
+      };
+      auto channel = [&](int i) { return min((grp + (i >> 2) * G) * 4 + (i & 3), C - 1); };
+      Row<V, XT> buf[2][R];
+      auto load = [&](Row<V, XT> (&to)[R], int i) {
+        const XT *nx = src + (size_t)channel(min(i, 4 * nq - 1)) * g.N;
+#pragma unroll
+        for (int r = 0; r < R; ++r) to[r].template load<NT>(nx + (size_t)r * g.W);
+      };
+      load(buf[0], 0);
+      int pending = -1;
+      for (int qd = 0; qd < nq; ++qd) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          load(buf[(u + 1) & 1], 4 * qd + u + 1);
+          __builtin_amdgcn_sched_barrier(0);
+          float in[R][V];
+#pragma unroll
+          for (int r = 0; r < R; ++r) buf[u & 1][r].get(in[r]);
+          fwd_levels<D, V, 1>(in, p, sink);
+          if (!Q8 || u == 0) store(pending);
+          wave_lds_fence();
+          if constexpr (Q8) {
+            float v[NI];
+#pragma unroll
+            for (int i = 0; i < NI; ++i) v[i] = __uint_as_float(tile[cell[i]]);
+            auto code = [&](auto fast_c) {  // the new code comes in at the top, the oldest leaves at the bottom
+              constexpr bool FAST = decltype(fast_c)::value;
+#pragma unroll
+              for (int i = 0; i < NI; ++i)
+                word[i] = __builtin_amdgcn_alignbyte((uint32_t)(int)quant.template level_as<FAST>(v[i]), word[i], 1);
+            };
+            if (quant.fast) code(std::true_type{}); else code(std::false_type{});
+            if (u == 3) pending = grp + qd * G;
+          } else {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+              word[i] = tile[cell[i]];
+              mx = fmaxf(mx, fabsf(__uint_as_float(word[i])));
+            }
+            pending = (grp + qd * G) * 4 + u;  // (channels past the last repeat it, and are not stored)
+          }
+          wave_lds_fence();
+        }
+      }
+      store(pending);
+    };
+    auto first = [&](auto ni_c) {
+      constexpr int NI = decltype(ni_c)::value;
+      uint32_t cell[NI];
+#pragma unroll
+      for (int i = 0; i < NI; ++i) cell[i] = entry(i);
+      walk(ni_c, cell, out, count);
+    };
+    using std::integral_constant;
+    if ((V << D) == 4 || ni <= 4) first(integral_constant<int, 4>{});
+    else if constexpr ((V << D) >= 8) {
+      if ((V << D) == 8 || ni <= 8) first(integral_constant<int, 8>{});
+      else if constexpr ((V << D) >= 16) {
+        first(integral_constant<int, 16>{});
+        if constexpr (kTwo) {
+          if (ni > kRows) {
+            uint32_t cell[kRows];
+#pragma unroll
+            for (int i = 0; i < kRows; ++i) cell[i] = i & 1 ? later[i / 2] >> 16 : later[i / 2] & 0xFFFFu;
+            walk(integral_constant<int, kRows>{}, cell, out + kRows * kWave, count - kRows * kWave);
+          }
+        }
+      }
+    }
+  }
+  if (alpha_slots == nullptr && wg_max == nullptr) return;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+  if (lane == 0) wmax[wv] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    mx = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+    if (wg_max != nullptr) {
+      wg_max[((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = mx;
+      return;
+    }
+    unsigned int *a = reinterpret_cast<unsigned int *>(alpha_slots) +
+                      ((blockIdx.x + 3u * blockIdx.y + 11u * blockIdx.z) & (kAlphaSlots - 1));
+    const unsigned int top = __float_as_uint(mx);
+    if (top > __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(a, top);
+  }
+}
+
+// the lanes of all strips follow each other, 64 a wave: four units
+inline StripMap words_map(const wcc_desc &d) {
+  StripMap m = make_map(d, lane_cols(d));
+  m.flat = true;
+  m.units = (int)(((int64_t)m.strips * m.lanes_w + kWave - 1) / kWave);
+  return m;
+}
+
+int words_groups(const wcc_desc &d, bool late) {
+  const StripMap m = words_map(d);
+  int G = groups_for(d, m, d.C_in, 2048, 4);
+  if (late && (int64_t)((m.units + 3) / 4) * G * d.B > kMaxWgMaxima) G = std::min(G, groups_for(d, m, d.C_in, 1024, 4));
+  return G;
+}
+
+template <int D, int V, class XT>
+hipError_t words_launch(const wcc_desc &d, int64_t ks, const XT *x, const int32_t *jmap, const uint32_t *ucount,
+                        uint32_t *xw, float *alpha_slots, float *wg_max, float q_alpha, const float *alpha_src,
+                        int n_alpha, float *alpha_pub, hipStream_t s) {
+  const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
+  const StripMap m = words_map(d);
+  const int upad = unit_pad(unit_map(d));
+  const dim3 grid((m.units + 3) / 4, words_groups(d, alpha_slots != nullptr || wg_max != nullptr), d.B);
+#define WCC_WORDS(Q8, NT)                                                                                          \
+  hipLaunchKernelGGL((haar_keep_words_kernel<D, V, Q8, XT, NT>), grid, dim3(256), 0, s, x, jmap, ucount, upad, xw, \
+                     alpha_slots, wg_max, g, m, d.C_in, ks, q_alpha, alpha_src, n_alpha, alpha_pub)
+  if (q_alpha > 0.f || alpha_src != nullptr) { if (streams(d)) WCC_WORDS(true, true); else WCC_WORDS(true, false); }
+  else                                       { if (streams(d)) WCC_WORDS(false, true); else WCC_WORDS(false, false); }
+#undef WCC_WORDS
+  return hipGetLastError();
+}
+
 inline StripMap keep_map(const wcc_desc &d, bool folded) {
   return folded ? make_map(d, lane_cols(d)) : make_flat_map(d, lane_cols(d));
 }
@@ -294,6 +552,24 @@ hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const i
   const bool late = alpha_slots != nullptr || wg_max != nullptr;
   const Plan pl{keep_groups(d, wdw != nullptr, late), 1, streams(d), 1};
   return keep_dispatch(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+}
+
+int64_t keep_words_workgroups(const wcc_desc &d) {
+  return (int64_t)((words_map(d).units + 3) / 4) * words_groups(d, true) * d.B;
+}
+
+hipError_t launch_haar_keep_words(const wcc_desc &d, int64_t ks, const void *x, const int32_t *jmap,
+                                  const uint32_t *ucount, uint32_t *xw, float *alpha_slots, float *wg_max,
+                                  float q_alpha, const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
+#define WCC_GO(D, V)                                                                                               \
+  return d.act_dtype == WCC_BF16                                                                                   \
+             ? words_launch<D, V>(d, ks, static_cast<const bf16_t *>(x), jmap, ucount, xw, alpha_slots, wg_max,    \
+                                  q_alpha, alpha_src, n_alpha, alpha_pub, s)                                       \
+             : words_launch<D, V>(d, ks, static_cast<const float *>(x), jmap, ucount, xw, alpha_slots, wg_max,     \
+                                  q_alpha, alpha_src, n_alpha, alpha_pub, s)
+  if (d.levels == 3) WCC_GO(3, 4);  // (the last kernel's)
+#undef WCC_GO
+  return hipErrorInvalidValue;
 }
 
 }  // namespace wcc

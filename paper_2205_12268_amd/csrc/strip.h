@@ -231,24 +231,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const YT *plane, in
 }
 template <int V>
 __device__ __forceinline__ void store_row_buf(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
-                                              const float (&src)[V], float) {
+                                              const float (&src)[V], float, uint32_t uniform = 0) {
   if constexpr (V == 4) {
     buf_u4 t = {__float_as_uint(src[0]), __float_as_uint(src[1]), __float_as_uint(src[2]), __float_as_uint(src[3])};
-    __builtin_amdgcn_raw_buffer_store_b128(t, rsrc, off, 0, kBufStream);
+    __builtin_amdgcn_raw_buffer_store_b128(t, rsrc, off, uniform, kBufStream);
   } else {
     buf_u2 t = {__float_as_uint(src[0]), __float_as_uint(src[1])};
-    __builtin_amdgcn_raw_buffer_store_b64(t, rsrc, off, 0, kBufStream);
+    __builtin_amdgcn_raw_buffer_store_b64(t, rsrc, off, uniform, kBufStream);
   }
 }
 template <int V>
 __device__ __forceinline__ void store_row_buf(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
-                                              const float (&src)[V], bf16_t) {
+                                              const float (&src)[V], bf16_t, uint32_t uniform = 0) {
   const uint32_t a = pack_bf16(src[0], src[1]);
   if constexpr (V == 4) {
     buf_u2 t = {a, pack_bf16(src[2], src[3])};
-    __builtin_amdgcn_raw_buffer_store_b64(t, rsrc, off, 0, kBufStream);
+    __builtin_amdgcn_raw_buffer_store_b64(t, rsrc, off, uniform, kBufStream);
   } else {
-    __builtin_amdgcn_raw_buffer_store_b32(a, rsrc, off, 0, kBufStream);
+    __builtin_amdgcn_raw_buffer_store_b32(a, rsrc, off, uniform, kBufStream);
   }
 }
 template <int V>

@@ -166,13 +166,13 @@ enum { kListSelect = 0,  // joint shrinkage: top-k channel norms (Alg. 1)
 // [C_in, 3, 3]): the layer's input is K_dw x, convolved on the fly by both transform passes; with
 // src given (x unused) it is K_dw t1, t1 rebuilt from a producer layer's compressed output.
 // stop_before_inverse: the layer ends with Y_wt in its workspace (y unused), for a consumer that
-// takes it from there.  prof: bracket the stages with the context's events.
+// takes it from there.  may_tail: contraction and inverse may be one kernel.  prof: bracket the stages with the context's events.
 wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc &d, const void *x,
                       const void *w, const float *w_scale, float alpha_in, void *y,
                       int32_t *idx_out, float *alpha_out_dev, const void *residual,
                       const float *wdw, bool prof, hipStream_t s, int list = kListSelect,
                       const int32_t *idx_given = nullptr, const ChainSrc *src = nullptr,
-                      bool stop_before_inverse = false) {
+                      bool stop_before_inverse = false, bool may_tail = false) {
   const int64_t k = k_of(d);
   const int64_t ks = L.ks;  // row stride of the compressed signals in the workspace
   const bool quant = d.act_quant_bits == 8;
@@ -210,6 +210,10 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   const bool small_dw = wdw && (int64_t)d.H * d.W <= 16384 && (int64_t)d.B * d.C_in * k < ((int64_t)4 << 20);
   const bool early = quant && !given && list == kListSelect && ks % 4 == 0 && n_top <= 8192 && !small_dw;
   const bool codes_now = early || (given && ks % 4 == 0);
+  // One kernel for the contraction and the inverse: the counts of kept positions of its units lie where Y_wt
+  // would.
+  const bool tail = may_tail && tail_takes(d, ks, (size_t)d.B * d.C_out * ks * 4);
+  uint32_t *ucount = reinterpret_cast<uint32_t *>(yc);
   float *tops = reinterpret_cast<float *>(ws + L.block_top);
   // the contraction finds alpha in the slots: as the largest of them, or (early) as the one
   // float the second pass left there after combining the selection's maxima
@@ -218,7 +222,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   // Packed weights go where the codes leave room: xc32 is sized for fp32.
   const size_t codes_bytes = align256((size_t)d.B * d.C_in * ks), xc_bytes = (size_t)d.B * d.C_in * ks * 4;
   PackJob pack{nullptr, nullptr, 0, 0, 0, 0, 0};
-  if (codes_now && xc_bytes > codes_bytes)
+  if (!tail && codes_now && xc_bytes > codes_bytes)
     pack = pack_job(d, ks, w, ws + L.xc32 + codes_bytes, xc_bytes - codes_bytes);
   const bool packed = list == kListSelect && select_packs(d, L, pack);
   // (a launch of its own takes 4 us: 576 -> 160 channels at 4 x 512 positions, 2^27.5 multiply-adds, gain
@@ -254,7 +258,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   // slots, 64 words that share two lines of memory, and a launch to clear them: keep pass of 2 x 192
   // channels of 400 x 56 23 us, 10 now; 2 x 176 of 204 x 144 25 and 15.)
   const bool late = quant && !given && !codes_now;
-  const int64_t keep_wgs = src ? 0 : keep_workgroups(d, wdw != nullptr);
+  const int64_t keep_wgs = src ? 0 : tail ? keep_words_workgroups(d) : keep_workgroups(d, wdw != nullptr);
   float *wg_max = late && !src && keep_wgs <= kMaxWgMaxima && (size_t)keep_wgs * 4 <= L.norm - L.max_part
                       ? reinterpret_cast<float *>(ws + L.max_part)
                       : nullptr;
@@ -262,7 +266,12 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   // A again + B': the transform, second pass: X_wt[I] is written straight into its compressed
   // place (the dropped coefficients never reach memory)
   WCC_TRY(mark(WCC_T_GATHER, 0));
-  if (src)
+  if (tail) {
+    WCC_TRY(launch_unit_count(d, jmap, ucount, s));
+    WCC_TRY(launch_haar_keep_words(d, ks, x, jmap, ucount, reinterpret_cast<uint32_t *>(xc32),
+                                   (late && !wg_max) ? slots : nullptr, wg_max, (given && codes_now) ? alpha_in : 0.f,
+                                   early ? tops : nullptr, n_top, early ? slots : nullptr, s));
+  } else if (src)
     WCC_TRY(launch_chain_keep(d, ks, *src, wdw, jmap, xc32, late ? slots : nullptr,
                               (given && codes_now) ? alpha_in : 0.f, early ? tops : nullptr, n_top,
                               early ? slots : nullptr, s));
@@ -271,6 +280,16 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
                              (given && codes_now) ? alpha_in : 0.f, early ? tops : nullptr, n_top,
                              early ? slots : nullptr, s));
   WCC_TRY(mark(WCC_T_GATHER, 1));
+  if (tail) {
+    // C, D, E in one
+    WCC_TRY(mark(WCC_T_SCATTER_IHAAR, 0));
+    const TailArgs a{w, w_scale, reinterpret_cast<const uint32_t *>(xc32), !codes_now,
+                     quant ? (wg_max ? wg_max : slots) : nullptr, n_alpha, quant ? alpha_out_dev : nullptr, jmap, ucount,
+                     unit_pad(unit_map(d)), y, ks};
+    WCC_TRY(launch_layer_tail(d, a, s));
+    WCC_TRY(mark(WCC_T_SCATTER_IHAAR, 1));
+    return WCC_OK;
+  }
   // C: Y_wt = Conv(K_1x1, X_wt[I]) (kept coefficients still in fp32 are quantised as they are
   // loaded)
   WCC_TRY(mark(WCC_T_POINTWISE, 0));
@@ -568,7 +587,7 @@ wcc_status wcc_forward(wcc_ctx *ctx, const wcc_desc *desc, const void *x, const 
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool prof = ctx->profiling && ctx->ev_ok;
   st = forward_on(ctx, static_cast<char *>(ctx->ws), L, *desc, x, w, w_scale, alpha_in, y, idx_out,
-                  alpha_out_dev, nullptr, nullptr, prof, s);
+                  alpha_out_dev, nullptr, nullptr, prof, s, kListSelect, nullptr, nullptr, false, true);
   if (st != WCC_OK) return st;
   if (prof) {
     WCC_TRY(hipEventRecord(ctx->ev[WCC_T_EVENT_PAIR][0], s));
@@ -597,7 +616,7 @@ wcc_status wcc_forward_static(wcc_ctx *ctx, const wcc_desc *desc, const void *x,
   // every buffer that has to start at a known value (histograms, alpha slots) is cleared by the
   // first kernel of the layer itself, as with a caller's workspace of unknown content
   return forward_on(ctx, static_cast<char *>(ctx->static_ws), L, *desc, x, w, w_scale, alpha_in, y,
-                    idx_out, alpha_out_dev, nullptr, nullptr, false, s);
+                    idx_out, alpha_out_dev, nullptr, nullptr, false, s, kListSelect, nullptr, nullptr, false, true);
 }
 
 wcc_status wcc_forward_fixed(wcc_ctx *ctx, const wcc_desc *desc, const void *x, const void *w,
@@ -613,7 +632,7 @@ wcc_status wcc_forward_fixed(wcc_ctx *ctx, const wcc_desc *desc, const void *x, 
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool prof = ctx->profiling && ctx->ev_ok;
   st = forward_on(ctx, static_cast<char *>(ctx->ws), L, *desc, x, w, w_scale, alpha_in, y, nullptr,
-                  alpha_out_dev, nullptr, nullptr, prof, s, idx ? kListGiven : kListPrefix, idx);
+                  alpha_out_dev, nullptr, nullptr, prof, s, idx ? kListGiven : kListPrefix, idx, nullptr, false, true);
   if (st != WCC_OK) return st;
   if (prof) {
     WCC_TRY(hipEventRecord(ctx->ev[WCC_T_EVENT_PAIR][0], s));
@@ -698,8 +717,11 @@ wcc_status wcc_block_forward(wcc_ctx *ctx, const wcc_block_desc *desc, const voi
     void *t1 = t1_out ? t1_out : static_cast<void *>(ws + BL.t1);
     float *t2 = t2_out ? t2_out : reinterpret_cast<float *>(ws + BL.t2);
     // K1 (expand), K_dw, K3 (project) with the skip connection added by the last kernel
+    // (where such a block may also run chained, the middle tensor a caller asks for is the sums of the chained
+    // call's own kernel, bit for bit)
     st = forward_on(ctx, ws + BL.layer1, L1, d1, x, w1, w1_scale, 0.f, t1, idx1_out, nullptr,
-                    nullptr, nullptr, prof && ctx->block_profile_layer == 0, s);
+                    nullptr, nullptr, prof && ctx->block_profile_layer == 0, s, kListSelect, nullptr, nullptr, false,
+                    block_front(*desc, d3, false) != kFrontChain);
     if (st != WCC_OK) return st;
     if (!fold || t2_out) {
       if (prof) WCC_TRY(hipEventRecord(ctx->ev[WCC_T_DEPTHWISE][0], s));

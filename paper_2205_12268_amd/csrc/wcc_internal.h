@@ -203,6 +203,43 @@ hipError_t launch_chain_keep(const wcc_desc &d, int64_t k, const ChainSrc &src, 
                              const int32_t *jmap, void *xc, float *alpha_slots, float q_alpha,
                              const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s);
 
+// ---- the fused layer's own form of the compressed signal --------------------------------------------
+// A unit is 16 lanes of the strip transform (lane_cols() columns each) of one strip, or of two where a strip
+// ends inside it: lane f = strip * lanes_w + column lane, unit f / 16.  Inside a call whose last two steps run in
+// one kernel (launch_layer_tail) kept positions are numbered unit by unit, inside a unit slot by slot of the
+// lane's tile, then lane by lane; the rank map only says which are kept, and ucount how many there are in
+// every unit.  The signal is words: [B, ceil(C_in / 4), ks] of four channels' 8-bit codes, or [B, C_in, ks] fp32.
+constexpr int kUnitLanes = 16;
+struct UnitMap {
+  int lanes_w;  // lanes a strip
+  int lanes;    // lanes of the plane
+  int units;
+};
+UnitMap unit_map(const wcc_desc &d);
+inline int unit_pad(const UnitMap &m) { return (m.units + 15) / 16 * 16; }  // entries of ucount a sample
+struct TailArgs {
+  const void *w;
+  const float *w_scale;
+  const uint32_t *xw;  // words
+  bool words_f32;      // fp32 words (with act_quant_bits = 8: quantised on the way into LDS)
+  const float *alpha;  // n_alpha partial maxima, nullptr without quantisation
+  int n_alpha;
+  float *alpha_out;    // nullable
+  const int32_t *jmap;
+  const uint32_t *ucount;
+  int upad;
+  void *y;
+  int64_t ks;
+};
+bool tail_takes(const wcc_desc &d, int64_t ks, size_t count_room);
+hipError_t launch_unit_count(const wcc_desc &d, const int32_t *jmap, uint32_t *ucount, hipStream_t s);
+hipError_t launch_layer_tail(const wcc_desc &d, const TailArgs &a, hipStream_t s);
+// the second transform pass, writing such words (see launch_haar_keep for the rest)
+int64_t keep_words_workgroups(const wcc_desc &d);
+hipError_t launch_haar_keep_words(const wcc_desc &d, int64_t ks, const void *x, const int32_t *jmap,
+                                  const uint32_t *ucount, uint32_t *xw, float *alpha_slots, float *wg_max,
+                                  float q_alpha, const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s);
+
 // launchers (each returns hipGetLastError() after its launches)
 // (norm_part, max_part: one plane for each channel group: forward_groups() of them in the fused layer's
 // pass, G * split in the storing one, which has memory for `planes` at most)

@@ -1,0 +1,103 @@
+"""The kernel that takes contraction and inverse in one (needs an MI355X): layers of few channels, three levels and
+a long kept signal, at the edges of what it takes.  Every operand type, one step of channels and two, rows of
+weights that end inside a 16-byte load, output channels that are no multiple of 16, units that keep nothing, units
+that keep everything (more than the LDS holds of two steps), a last unit that is not full, each way to the index list and
+to alpha, and both storage types."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2205_12268_amd import synth, wcc
+from tests.util import dev, rel_l2, tol_for, upload_weights
+
+pytestmark = pytest.mark.gpu
+
+# B, C_in, C_out, H, W, keep, weights, bits: at least 48 MiB of output coefficients and 900 units of 512 positions
+CASES = [
+    (4, 64, 36, 264, 512, (3, 4), synth.W_BF16, 8),   # a whole step; 4 channels in the last block
+    (8, 10, 34, 256, 256, (3, 4), synth.W_BF16, 8),   # a row of 20 bytes
+    (7, 128, 36, 256, 320, (2, 3), synth.W_I8, 8),    # two steps; units that the LDS does not hold
+    (4, 68, 40, 264, 480, (2, 3), synth.W_I8, 8),     # one channel quad in the second step
+    (4, 24, 33, 256, 512, (3, 4), synth.W_I4, 8),
+    (4, 32, 36, 264, 512, (2, 3), synth.W_F32, 0),    # two steps of fp32
+    (9, 5, 64, 152, 352, (1, 2), synth.W_F32, 0),     # W: 88 lanes a strip, units across strips, a last one of 8 lanes
+    (4, 20, 40, 256, 512, (2, 3), synth.W_F32, 8),
+    (4, 8, 184, 256, 360, (1, 1), synth.W_I8, 8),     # all kept: rows that are not whole lines
+]
+
+
+def _input(cfg, maps):
+    x, w = synth.make_inputs(cfg)
+    # a part of every plane is zero: with three quarters kept its units hold nothing but ties, which go to the lower
+    # positions; another is loud, and keeps everything
+    x[:, :, :64, :128] = 0.0
+    x[:, :, 128:192, :64] *= 8.0
+    if maps == wcc.BF16:
+        x = np.rint(x * 8.0).astype(np.float32) / 8.0      # below 32: exact in bf16
+    return x, w
+
+
+@pytest.mark.parametrize("maps", [wcc.F32, wcc.BF16])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_layer(ref, case, maps):
+    B, Ci, Co, H, W, (num, den), wt, bits = case
+    cfg = synth.LayerCfg("tail", B, Ci, Co, H, W, 3, num, den, wt, bits, sigma=1.0, clip_hi=3.0,
+                         seed=synth.SEED_BASE + 0x1500 + Ci)
+    print(cfg, flush=True)
+    x, w = _input(cfg, maps)
+    d = wcc.make_desc(B, Ci, Co, H, W, 3, num, den, wt, bits, maps)
+    ctx = wcc.Context(0)
+    need = wcc.workspace_bytes(d)
+    ws = torch.full((need + 4096,), 255, dtype=torch.uint8, device="cuda")  # NaN patterns, a guard band behind
+    ctx.set_workspace(ws[:need])
+    wd, wsd = upload_weights(w)
+    t = torch.bfloat16 if maps == wcc.BF16 else torch.float32
+    tol = 1e-2 if maps == wcc.BF16 else tol_for(cfg)
+    flat = torch.full((B * Co * H * W + 4096,), float("nan"), dtype=t, device="cuda")
+    y = flat[:B * Co * H * W].view(B, Co, H, W)
+    idx = torch.full((B, cfg.k), -7, dtype=torch.int32, device="cuda")
+    alpha = torch.zeros(1, device="cuda")
+    xd = dev(x).to(t)
+    ctx.wcc_forward(d, xd, wd, wsd, 0.0, y, idx, alpha if bits else None)
+    want, o_idx, o_alpha = ref.forward(x, w.values, w.scale, 3, num, den, act_bits=bits)
+    np.testing.assert_array_equal(idx.cpu().numpy().astype(np.int64), o_idx)
+    if bits:
+        assert float(alpha.item()) == np.float32(o_alpha)
+    assert rel_l2(y.float().cpu().numpy(), want) <= tol
+    first = y.clone()
+    # the same list given, and the list "first k": alpha is found in the second pass, which leaves fp32
+    y.fill_(float("nan"))
+    ctx.wcc_forward_fixed(d, xd, wd, wsd, 0.0, idx, y)
+    assert torch.equal(y, first)
+    y.fill_(float("nan"))
+    ctx.wcc_forward_fixed(d, xd, wd, wsd, 0.0, None, y)
+    lists = np.broadcast_to(np.arange(cfg.k), (B, cfg.k)).copy()
+    want, _ = ref.forward_with_list(x, w.values, w.scale, 3, lists, act_bits=bits)[:2]
+    assert rel_l2(y.float().cpu().numpy(), want) <= tol
+    if bits:  # a given alpha
+        y.fill_(float("nan"))
+        ctx.wcc_forward(d, xd, wd, wsd, 2.5, y)
+        want, _, _ = ref.forward(x, w.values, w.scale, 3, num, den, act_bits=bits, alpha_in=2.5)
+        assert rel_l2(y.float().cpu().numpy(), want) <= tol
+    assert bool(torch.isnan(flat[B * Co * H * W:]).all()) and bool((ws[need:] == 255).all())
+    ctx.close()
+
+
+def test_a_row_of_weights_does_not_reach_into_the_row_before():
+    """20 channels: the last 16-byte load of a row of 40 bytes brings in the next row's first weights."""
+    cfg = synth.LayerCfg("tail_rows", 4, 20, 36, 264, 512, 3, 3, 4, synth.W_BF16, 8, sigma=1.0, seed=synth.SEED_BASE + 0x1580)
+    x, w = synth.make_inputs(cfg)
+    d = wcc.make_desc(4, 20, 36, 264, 512, 3, 3, 4, synth.W_BF16, 8)
+    ctx = wcc.Context(0)
+    ctx.ensure_workspace(d)
+    got = []
+    for bad in (False, True):
+        stored = w.stored.copy()
+        if bad:
+            stored[7] = 0x7FC0  # NaN
+        y = torch.empty((4, 36, 264, 512), dtype=torch.float32, device="cuda")
+        ctx.wcc_forward(d, dev(x), dev(stored), None, 0.0, y)
+        got.append(y)
+    keep = [c for c in range(36) if c != 7]
+    assert torch.equal(got[0][:, keep], got[1][:, keep])
+    ctx.close()
