@@ -111,7 +111,9 @@ __device__ __forceinline__ void inv_staged_walk(const float *__restrict__ plane,
 // scratch: unused (kept for the launcher's signature).  RES: y = residual + (the above),
 // residual [B, C, H, W] (the skip connection of Eq. (inverted)); it may be y itself.
 // YT: float or bf16_t, the storage type of y and of the residual.
-template <int D, int V, bool RES, class YT>
+// SHARE: grid = (units, G / 4, B); the four waves of a workgroup stand on one strip unit, each with a channel group of its
+// own; they look up a quarter of the unit's ranks each and pack one list together.
+template <int D, int V, bool RES, class YT, bool SHARE>
 __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restrict__ yc,
                                                             const int32_t *__restrict__ jmap,
                                                             YT *y, Geo g, StripMap m, int C,
@@ -125,12 +127,15 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
   static_assert(NS <= 128, "slot mask is 128 bits wide");
   static_assert(!kStaged || STRIDE * kWave <= (1 << (32 - kInvRankBits)), "cell index fits above the rank");
   __shared__ __attribute__((aligned(16))) uint32_t tiles[kStaged ? 4 : 1][kStaged ? STRIDE * kWave : 1];
+  __shared__ uint32_t shared_list[SHARE ? CAP : 1];
+  __shared__ int shared_count[4];
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int unit = blockIdx.x * 4 + wv;
+  const int unit = SHARE ? (int)blockIdx.x : (int)blockIdx.x * 4 + wv;
   // Samples are taken last to first: the contraction wrote yc first to last, so what is still
   // in the memory-side cache when this kernel starts is the tail, and it is read before the
   // rest of the reads push it out.
-  const int grp = blockIdx.y, b = gridDim.z - 1 - blockIdx.z;
+  const int b = gridDim.z - 1 - blockIdx.z;
+  const int grp = SHARE ? (int)blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(wv) : (int)blockIdx.y;
   LanePos<D> p;
   int row0, col0;
   const bool active = locate<D, V>(m, g, unit, p, row0, col0);
@@ -140,7 +145,7 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
   // block's expand layer 503 -> 478 us).
   const int c0 = grp;
   const int n_ch = c0 >= C ? 0 : (C - c0 + G - 1) / G;
-  if (__ballot(active) == 0 || n_ch <= 0) return;  // whole waves leave
+  if (!SHARE && (__ballot(active) == 0 || n_ch <= 0)) return;  // whole waves leave
   const int64_t kstep = (int64_t)G * k, nstep = (int64_t)G * g.N;
 
   const int32_t *jm = jmap + (size_t)b * g.N;
@@ -152,62 +157,112 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
   InvDirect<D, V> src;
   src.any[0] = src.any[1] = 0;
   int count = 0;  // kept positions of this wave's strip (wave-uniform)
-  auto fetch = [&](auto Lc, auto Jc) {
-    constexpr int L = decltype(Lc)::value, J = decltype(Jc)::value;
-    constexpr int CV = cols_at(V, L);
+  // slots [FIRST, LAST)
+  auto fetch_slots = [&](auto first_c, auto last_c) {
+    constexpr int FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
+    auto fetch = [&](auto Lc, auto Jc) {
+      constexpr int L = decltype(Lc)::value, J = decltype(Jc)::value;
+      constexpr int CV = cols_at(V, L);
 #pragma unroll
-    for (int i = 0; i < rows_at(D, L); ++i)
+      for (int i = 0; i < rows_at(D, L); ++i)
 #pragma unroll
-      for (int e = 0; e < CV; ++e) {
-        constexpr int base = slot_base(D, V, L, J);
-        int j = -1;
-        if (active) j = jm[J * p.nl[L] + p.off[L] + i * p.rowlen[L] + e];
-        src.jj[base + i * CV + e] = j;
-      }
+        for (int e = 0; e < CV; ++e) {
+          constexpr int base = slot_base(D, V, L, J);
+          const int s = base + i * CV + e;
+          if (s < FIRST || s >= LAST) continue;
+          int j = -1;
+          if (active) j = jm[J * p.nl[L] + p.off[L] + i * p.rowlen[L] + e];
+          src.jj[s] = j;
+        }
+    };
+    auto each_level = [&](auto Lc) {
+      constexpr int L = decltype(Lc)::value;
+      fetch(Lc, std::integral_constant<int, 1>{});
+      fetch(Lc, std::integral_constant<int, 2>{});
+      fetch(Lc, std::integral_constant<int, 3>{});
+      if constexpr (L == D) fetch(Lc, std::integral_constant<int, 0>{});
+    };
+    each_level(std::integral_constant<int, 1>{});
+    if constexpr (D >= 2) each_level(std::integral_constant<int, 2>{});
+    if constexpr (D >= 3) each_level(std::integral_constant<int, 3>{});
+    if constexpr (D >= 4) each_level(std::integral_constant<int, 4>{});
   };
-  auto each_level = [&](auto Lc) {
-    constexpr int L = decltype(Lc)::value;
-    fetch(Lc, std::integral_constant<int, 1>{});
-    fetch(Lc, std::integral_constant<int, 2>{});
-    fetch(Lc, std::integral_constant<int, 3>{});
-    if constexpr (L == D) fetch(Lc, std::integral_constant<int, 0>{});
-  };
-  each_level(std::integral_constant<int, 1>{});
-  if constexpr (D >= 2) each_level(std::integral_constant<int, 2>{});
-  if constexpr (D >= 3) each_level(std::integral_constant<int, 3>{});
-  if constexpr (D >= 4) each_level(std::integral_constant<int, 4>{});
-  // (all map loads are in flight before the first vote waits for one)
+  // puts the list entries of slots [FIRST, LAST) from `at` on down: rank, cell, slot-major, then lane
+  auto pack_slots = [&](auto first_c, auto last_c, uint32_t *list, int at0) {
+    constexpr int FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
+    int running = at0;
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    const uint64_t kept = __ballot(src.jj[s] >= 0);
-    if (kept != 0) src.any[s >> 6] |= (uint64_t)1 << (s & 63);
-    count += __popcll(kept);
+    for (int s = FIRST; s < LAST; ++s) {
+      if (!SHARE && !((src.any[s >> 6] >> (s & 63)) & 1)) continue;
+      const int j = src.jj[s];
+      const uint64_t kept = __ballot(j >= 0);
+      const int at = running + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(kept >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)kept, 0u));
+      if (j >= 0) list[at] = (uint32_t)j | ((uint32_t)(lane * STRIDE + s) << kInvRankBits);
+      running += __popcll(kept);
+    }
+  };
+  using Zero = std::integral_constant<int, 0>;
+  using All = std::integral_constant<int, NS>;
+  bool packed = kStaged && k <= ((int64_t)1 << kInvRankBits);  // (uniform over the grid)
+  if constexpr (SHARE) {
+    // a quarter of the slots a wave (the branch is uniform, and no barrier stands in it)
+    const int part = __builtin_amdgcn_readfirstlane(wv);
+    auto quarter = [&](auto &&f) {
+      using std::integral_constant;
+      constexpr int Q = (NS + 3) / 4, Q2 = 2 * Q < NS ? 2 * Q : NS, Q3 = 3 * Q < NS ? 3 * Q : NS;
+      if (part == 0) f(Zero{}, integral_constant<int, Q>{});
+      else if (part == 1) f(integral_constant<int, Q>{}, integral_constant<int, Q2>{});
+      else if (part == 2) f(integral_constant<int, Q2>{}, integral_constant<int, Q3>{});
+      else f(integral_constant<int, Q3>{}, All{});
+    };
+    int own = 0;
+    quarter([&](auto first_c, auto last_c) {
+      fetch_slots(first_c, last_c);
+#pragma unroll
+      for (int s = decltype(first_c)::value; s < decltype(last_c)::value; ++s) own += __popcll(__ballot(src.jj[s] >= 0));
+    });
+    if (lane == 0) shared_count[wv] = own;
+    __syncthreads();
+    int in_front = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int n = __builtin_amdgcn_readfirstlane(shared_count[i]);
+      in_front += i < part ? n : 0;
+      count += n;
+    }
+    packed = packed && count <= CAP;
+    if (packed) quarter([&](auto first_c, auto last_c) { pack_slots(first_c, last_c, shared_list, in_front); });
+    __syncthreads();
+    if (__ballot(active) == 0 || n_ch <= 0) return;  // whole waves leave
+  } else {
+    fetch_slots(Zero{}, All{});
+    // (all map loads are in flight before the first vote waits for one)
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const uint64_t kept = __ballot(src.jj[s] >= 0);
+      if (kept != 0) src.any[s >> 6] |= (uint64_t)1 << (s & 63);
+      count += __popcll(kept);
+    }
+    packed = packed && count <= CAP;
   }
 
   if constexpr (kStaged) {
-    if (count <= CAP && k <= ((int64_t)1 << kInvRankBits)) {
-      // pack (rank, cell): slot-major, then lane (a band row's kept positions have consecutive
-      // j).  The tile serves as scratch for the list before it becomes the staging area.
+    if (packed) {
+      // The tile serves as scratch for the list before it becomes the staging area.  (A band row's kept positions have
+      // consecutive ranks.)
       uint32_t *tile = tiles[wv];
-      int running = 0;
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        if ((src.any[s >> 6] >> (s & 63)) & 1) {
-          const int j = src.jj[s];
-          const uint64_t kept = __ballot(j >= 0);
-          const int at = running + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(kept >> 32),
-                                       __builtin_amdgcn_mbcnt_lo((uint32_t)kept, 0u));
-          if (j >= 0) tile[at] = (uint32_t)j | ((uint32_t)(lane * STRIDE + s) << kInvRankBits);
-          running += __popcll(kept);
-        }
+      const uint32_t *list = SHARE ? shared_list : tile;
+      if constexpr (!SHARE) {
+        pack_slots(Zero{}, All{}, tile, 0);
+        wave_lds_fence();
       }
-      wave_lds_fence();
       uint32_t mine[kInvCap / kWave];  // this lane's share of the list: entries lane + 64 i
-      const uint32_t pad = count > 0 ? tile[0] : kInvNone;  // (see inv_staged_walk: PADDED)
+      const uint32_t pad = count > 0 ? list[0] : kInvNone;  // (see inv_staged_walk: PADDED)
 #pragma unroll
       for (int i = 0; i < kInvCap / kWave; ++i) {
         const int e = lane + 64 * i;
-        mine[i] = (i < CAP / kWave && e < count) ? tile[e] : pad;
+        mine[i] = (i < CAP / kWave && e < count) ? list[e] : pad;
       }
       wave_lds_fence();
       uint32_t *row = tile + lane * STRIDE;  // this lane's slots
@@ -238,6 +293,12 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
   }
 
   // plain path
+  if constexpr (SHARE) {
+    fetch_slots(Zero{}, All{});
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (__ballot(src.jj[s] >= 0) != 0) src.any[s >> 6] |= (uint64_t)1 << (s & 63);
+  }
   if (!active) return;
   src.plane = plane;
   const YT *res = RES ? residual + first : nullptr;
@@ -261,19 +322,40 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
   }
 }
 
+// Whether the four waves of a workgroup share a strip unit.  Sharing takes three quarters of a wave's rank lookups and votes
+// off, which are what a wave starts with; four waves on four neighbouring units write runs four times as long, which counts
+// once memory is the bound.  At 1 and 2 levels a strip has few slots and sharing measured 0.92..1.27 of the time.  At 3
+// levels, apart -> shared: 1x256x128x128 at 1/4 9.8 -> 8.4 us, 1x32x256x512 at 1/4 9.6 -> 7.9, 16x512x64x64 at 1/8
+// 34.6 -> 28.5; up to 16 MB of kept values 0.78..1.02 of the time, with 24 to 64 MB 1.00..1.12.  At 4 levels the line lies at
+// 8 MB: 4x96x128x128 at 1/3 17.4 -> 16.2, but 4x96x96x320 at 1/4 (11 MB) 18.8 -> 20.0.  Above a third kept many units
+// overflow the list and look their ranks up twice: 0.94..1.19.  With the residual added sharing pays there all the same
+// (16x256x128x128 at 1/2 123 -> 108 us, 8x128x192x320 131 -> 114); under 8 units (64x64 and smaller) that kernel measured
+// 0.92..1.10 at 1/4 and 0.75..1.15 at 1/2.
+bool shares_units(const wcc_desc &d, const StripMap &m, int64_t k, bool residual) {
+  if (d.levels < 3) return false;
+  const bool few = k * 3 <= (int64_t)d.H * d.W + 2;
+  if (residual && m.units < 8) return false;
+  if (residual && !few) return true;
+  return few && (int64_t)d.B * d.C_out * k * 4 <= ((int64_t)(d.levels == 3 ? 16 : 8) << 20);
+}
+
 template <int D, int V>
 hipError_t inv_launch(const wcc_desc &d, int64_t k, const float *yc, const int32_t *jmap, void *y,
                       int G, float *scratch, const void *residual, hipStream_t s) {
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
   const StripMap m = make_flat_map(d, V);
-  dim3 grid((m.units + 3) / 4, G, d.B);
-#define WCC_INV(RES, YT)                                                                          \
-  hipLaunchKernelGGL((scatter_ihaar_kernel<D, V, RES, YT>), grid, dim3(256), 0, s, yc, jmap,      \
+  const bool share = G >= 4 && shares_units(d, m, k, residual != nullptr);
+  const dim3 grid(share ? m.units : (m.units + 3) / 4, share ? G / 4 : G, d.B);
+  constexpr bool kShares = D >= 3;  // (the rule takes no others)
+#define WCC_INV_T(RES, YT, SHARE)                                                                 \
+  hipLaunchKernelGGL((scatter_ihaar_kernel<D, V, RES, YT, SHARE && kShares>), grid, dim3(256), 0, s, yc, jmap, \
                      static_cast<YT *>(y), g, m, d.C_out, G, k, scratch,                          \
                      static_cast<const YT *>(residual))
+#define WCC_INV(RES, YT) do { if (share) WCC_INV_T(RES, YT, true); else WCC_INV_T(RES, YT, false); } while (0)
   if (d.act_dtype == WCC_BF16) { if (residual) WCC_INV(true, bf16_t); else WCC_INV(false, bf16_t); }
   else                         { if (residual) WCC_INV(true, float); else WCC_INV(false, float); }
 #undef WCC_INV
+#undef WCC_INV_T
   return hipGetLastError();
 }
 
