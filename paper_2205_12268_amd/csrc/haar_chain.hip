@@ -630,8 +630,12 @@ __global__ __launch_bounds__(chain_waves(SEGS) * kWave, 4 / chain_waves(SEGS)) v
     const float *kw = wdw + (size_t)c0 * 9;
     const bool first_lane = p.lc == 0, last_lane = p.lc == m.lpr - 1 || col0 + V4 >= g.W;
     // Both lists short enough: dense stores of the consumer's list (NI3 rows), producer's list
-    // walked with NI1 rows.  The two go together (both layers keep the same fraction), so three
-    // pairs cover the cases instead of every combination.
+    // walked with NI1 rows.  The two go together (both layers keep the same fraction; the producer's holds the rows
+    // above and below as well, and is about twice as long), so four pairs cover the cases instead of every combination.
+    // Kept at a quarter, 256 columns, three levels, lists of 8 and 17 rows are the rule, just above a power of two: with 12
+    // and 24 rows between 8/16 and 16/32 the pass takes 455-473 us (8x1024 channels, before 476-481), and 4/12 instead of
+    // 4/8 takes 3 % off blocks kept at an eighth (at two levels, where 4/8 holds the lists, it costs 1.6 %).  20 rows
+    // in place of 16 or 24 were slower, 467-482 us, and so is the norm pass with 24 or 20 (368-381 against 361-368).
     auto staged = [&](auto ni3_c, auto ni1_c) {
       constexpr int NI3 = decltype(ni3_c)::value, NI1 = decltype(ni1_c)::value;
       ChainStagedSink<D, Q8, NI3> st(Q8 ? q_alpha : 0.f);
@@ -649,11 +653,14 @@ __global__ __launch_bounds__(chain_waves(SEGS) * kWave, 4 / chain_waves(SEGS)) v
                          });
       mx = st.vmax;
     };
+    constexpr int kShort = D == 3 ? 12 : 8;
     const int ni3 = (count3 + kWave - 1) >> 6, ni1 = (cg.count + kWave - 1) >> 6;
-    if (listed3 && cg.packed && cg.count > 0 && ni3 <= 4 && ni1 <= 8) {
-      staged(std::integral_constant<int, 4>{}, std::integral_constant<int, 8>{});
+    if (listed3 && cg.packed && cg.count > 0 && ni3 <= 4 && ni1 <= kShort) {
+      staged(std::integral_constant<int, 4>{}, std::integral_constant<int, kShort>{});
     } else if (listed3 && cg.packed && cg.count > 0 && ni3 <= 8 && ni1 <= 16) {
       staged(std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{});
+    } else if (listed3 && cg.packed && cg.count > 0 && ni3 <= 12 && ni1 <= 24) {
+      staged(std::integral_constant<int, 12>{}, std::integral_constant<int, 24>{});
     } else if (listed3 && cg.packed && cg.count > 0 && ni3 <= 16 && ni1 <= 32) {
       staged(std::integral_constant<int, 16>{}, std::integral_constant<int, 32>{});
     } else {
