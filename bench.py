@@ -143,7 +143,7 @@ def bench_stack(args, synth, run_layer, ctx) -> int:
         total_alg += sum(alg.values())
         per_layer.append({"layer": cfg.name, "us": round(dt * 1e6, 2), "levels": cfg.levels,
                           "stages_us": {n: round(v, 2) for n, v in stage_us.items()}})
-        dom = max(kernel_of, key=lambda n: stage_us[n])
+        dom = max(STAGE_KERNEL, key=lambda n: stage_us[n])
         if worst is None or stage_us[dom] > worst[0]:
             worst = (stage_us[dom], dom, alg[dom], cfg.name)
     achieved = worst[2] / (worst[0] * 1e-6) / 1e9
