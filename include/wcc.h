@@ -135,9 +135,9 @@ int64_t wcc_k(const wcc_desc *desc /*[host]*/);
 
 const char *wcc_status_string(wcc_status s);
 
-/* When enabled, wcc_forward brackets each stage with HIP events on `stream`.
- * wcc_stage_times() waits for the last profiled wcc_forward and writes the
- * WCC_T_COUNT stage durations in milliseconds to ms [host]. */
+/* When enabled, wcc_forward, wcc_forward_fixed and wcc_block_forward bracket each stage with
+ * HIP events on `stream`.  wcc_stage_times() waits for the last profiled call and writes its
+ * WCC_T_COUNT stage durations in milliseconds to ms [host], 0 for a stage it did not run. */
 wcc_status wcc_set_profiling(wcc_ctx *ctx, int enabled);
 wcc_status wcc_stage_times(wcc_ctx *ctx, float *ms /*[host], WCC_T_COUNT floats*/);
 

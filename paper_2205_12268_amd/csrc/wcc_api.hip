@@ -40,7 +40,7 @@ struct wcc_ctx {
   bool have_times = false;
   hipEvent_t ev[WCC_T_COUNT][2] = {};
   bool ev_ok = false;
-  bool marked[WCC_T_COUNT] = {};  // stage bracket recorded since profiling was switched on
+  bool marked[WCC_T_COUNT] = {};  // stage bracket recorded by the last profiled call
   int block_profile_layer = 1;  // which layer of wcc_block_forward the stage events bracket
 };
 
@@ -89,6 +89,14 @@ int64_t k_of(const wcc_desc &d) {
 bool coded(int w_dtype) { return w_dtype == WCC_I8 || w_dtype == WCC_I4; }
 
 bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) != 0; }
+
+// Whether the call that starts here records its stages.  Which of them it runs depends on its route (a fixed list has no
+// norm pass, some layers no contraction of their own), so the brackets of the call before are forgotten.
+bool start_profile(wcc_ctx *ctx) {
+  if (!ctx->profiling || !ctx->ev_ok) return false;
+  for (bool &m : ctx->marked) m = false;
+  return true;
+}
 
 wcc_status need_ws(const wcc_ctx *ctx, const WsLayout &L) {
   if (!ctx->ws || ctx->ws_bytes < L.total) return WCC_ERR_WORKSPACE;
@@ -439,7 +447,7 @@ wcc_status wcc_stage_times(wcc_ctx *ctx, float *ms) {
   if (!ctx->have_times) return WCC_ERR_UNSUPPORTED;
   for (int i = 0; i < WCC_T_COUNT; ++i) {
     ms[i] = 0.f;
-    if (!ctx->marked[i]) continue;  // a stage the last calls did not run
+    if (!ctx->marked[i]) continue;  // a stage the last call did not run
     if (hipEventSynchronize(ctx->ev[i][1]) != hipSuccess) return WCC_ERR_HIP;
     if (hipEventElapsedTime(&ms[i], ctx->ev[i][0], ctx->ev[i][1]) != hipSuccess) return WCC_ERR_HIP;
   }
@@ -585,7 +593,7 @@ wcc_status wcc_forward(wcc_ctx *ctx, const wcc_desc *desc, const void *x, const 
   const WsLayout L = ws_layout(*desc);
   if ((st = need_ws(ctx, L)) != WCC_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const bool prof = ctx->profiling && ctx->ev_ok;
+  const bool prof = start_profile(ctx);
   st = forward_on(ctx, static_cast<char *>(ctx->ws), L, *desc, x, w, w_scale, alpha_in, y, idx_out,
                   alpha_out_dev, nullptr, nullptr, prof, s, kListSelect, nullptr, nullptr, false, true);
   if (st != WCC_OK) return st;
@@ -630,7 +638,7 @@ wcc_status wcc_forward_fixed(wcc_ctx *ctx, const wcc_desc *desc, const void *x, 
   const WsLayout L = ws_layout(*desc);
   if ((st = need_ws(ctx, L)) != WCC_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const bool prof = ctx->profiling && ctx->ev_ok;
+  const bool prof = start_profile(ctx);
   st = forward_on(ctx, static_cast<char *>(ctx->ws), L, *desc, x, w, w_scale, alpha_in, y, nullptr,
                   alpha_out_dev, nullptr, nullptr, prof, s, idx ? kListGiven : kListPrefix, idx, nullptr, false, true);
   if (st != WCC_OK) return st;
@@ -696,7 +704,7 @@ wcc_status wcc_block_forward(wcc_ctx *ctx, const wcc_block_desc *desc, const voi
   if (!ctx->ws || ctx->ws_bytes < BL.total) return WCC_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   char *ws = static_cast<char *>(ctx->ws);
-  const bool prof = ctx->profiling && ctx->ev_ok;
+  const bool prof = start_profile(ctx);
   const int front = block_front(*desc, d3, t1_out != nullptr || t2_out != nullptr);
   const WsLayout L1 = ws_layout(d1), L3 = ws_layout(d3, front);
 
