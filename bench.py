@@ -29,7 +29,8 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "int8": 5000.0, "f32": 157.3}
 CACHE_BYTES = 256 << 20  # memory-side cache
 
 
-# stage of wcc_forward -> the one kernel it launches (norm_select is four small kernels)
+# stage of wcc_forward -> the kernel that takes its time (norm_select is four small kernels; where contraction and
+# inverse are one kernel, see fold_tail, a small one that counts kept positions stands in front of the gather's)
 STAGE_KERNEL = {"haar_fwd": "haar_fwd_kernel", "gather": "haar_keep_kernel",
                 "pointwise": "pointwise", "scatter_ihaar": "scatter_ihaar_kernel"}
 
@@ -50,6 +51,19 @@ def algorithmic_bytes(cfg, act_bytes: int = 4, xc_bytes: int | None = None) -> d
         "pointwise": xc_bytes * B * Ci * k + bw * Ci * Co + 4 * B * Co * k,
         "scatter_ihaar": 4 * B * Co * k + 4 * B * k + a * B * Co * N,
     }
+
+
+def fold_tail(alg: dict, kernel_of: dict, cfg, stage_us: dict, prefix: str = "") -> bool:
+    """Adjusts `alg` and `kernel_of` of the layer `cfg` (stages named with `prefix`) if its contraction and inverse
+    ran as one kernel: Y_wt is then neither written nor read, and the contraction's bracket was not recorded (it is
+    exactly 0 in `stage_us`, the brackets as the library gives them).  Returns whether they did."""
+    pointwise, inverse = prefix + "pointwise", prefix + "scatter_ihaar"
+    if stage_us[pointwise] != 0 or stage_us[inverse] == 0:
+        return False
+    alg[inverse] += alg[pointwise] - 2 * 4 * cfg.B * cfg.C_out * cfg.k
+    alg[pointwise] = 0
+    kernel_of.update({prefix + "gather": "haar_keep_words_kernel", inverse: "layer_tail_kernel"})
+    return True
 
 
 def read_profile_column(profile_dir: str, prefix: str, workload: str, kernel: str, column: int):
@@ -136,16 +150,17 @@ def bench_stack(args, synth, run_layer, ctx) -> int:
     per_layer, total_s, total_pix, total_alg = [], 0.0, 0, 0
     worst = None
     for cfg in layers:
-        dt, stage_us, _, _, _ = run_layer(cfg, ctx)
-        alg = algorithmic_bytes(cfg, 2 if args.act == "bf16" else 4)
+        dt, stage_us, _, _, _, raw_us = run_layer(cfg, ctx)
+        alg, kernel_of = algorithmic_bytes(cfg, 2 if args.act == "bf16" else 4), dict(STAGE_KERNEL)
+        fold_tail(alg, kernel_of, cfg, raw_us)
         total_s += dt
         total_pix += cfg.B * cfg.H * cfg.W * cfg.C_in
         total_alg += sum(alg.values())
         per_layer.append({"layer": cfg.name, "us": round(dt * 1e6, 2), "levels": cfg.levels,
                           "stages_us": {n: round(v, 2) for n, v in stage_us.items()}})
-        dom = max(STAGE_KERNEL, key=lambda n: stage_us[n])
+        dom = max(kernel_of, key=lambda n: stage_us[n])
         if worst is None or stage_us[dom] > worst[0]:
-            worst = (stage_us[dom], dom, alg[dom], cfg.name)
+            worst = (stage_us[dom], kernel_of[dom], alg[dom], cfg.name)
     achieved = worst[2] / (worst[0] * 1e-6) / 1e9
     out = {
         "metric": "WCC layer forward throughput", "value": round(total_pix / total_s / 1e9, 3),
@@ -153,7 +168,7 @@ def bench_stack(args, synth, run_layer, ctx) -> int:
         "ms_per_step": round(total_s * 1e3, 5), "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "bf16", "data": "synthetic", "launch": args.launch,
         "config": {"workload": f"stack16_B4_keep{num}/{den}", "layers": len(layers), "act_bits": 8},
-        "roofline": {"bound": "hbm", "kernel": STAGE_KERNEL[worst[1]], "layer": worst[3],
+        "roofline": {"bound": "hbm", "kernel": worst[1], "layer": worst[3],
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
                      "algorithmic_bytes": worst[2], "kernel_us": round(worst[0], 2)},
@@ -330,6 +345,8 @@ def bench_block(args, synth, wcc, torch, np) -> int:
             kernel_of[f"l{layer}_{name}"] = kname
     if chained:
         kernel_of["l1_haar_fwd"], kernel_of["l1_gather"] = "chain_norm_kernel", "chain_keep_kernel"
+    else:
+        fold_tail(alg, kernel_of, cfg.layer(0), stage_us, "l0_")
     dom = max(kernel_of, key=lambda n: stage_us[n])
     prof = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles")
     traffic = read_traffic(prof, cfg.name, kernel_of[dom])
@@ -483,7 +500,8 @@ def main() -> int:
     wcc.lib()  # fails loudly if the HIP library is missing
 
     def run_layer(cfg, ctx):
-        """Times args.steps forwards of one layer; returns (seconds per step, stage us, event pair us, x, w)."""
+        """Times args.steps forwards of one layer; returns (seconds per step, stage us, event pair us, x, w, stage us as
+        recorded, the event pair included)."""
         x, w = synth.make_inputs(cfg)
         bf16 = args.act == "bf16"
         if bf16:
@@ -572,8 +590,9 @@ def main() -> int:
         # an empty event bracket measures what the two records cost by themselves; take it off
         acc.pop("depthwise", None)  # a stage of the block workload only
         pair_us = 1e3 * acc.pop("event_pair") / args.steps
-        stage_us = {n: max(1e3 * v / args.steps - pair_us, 0.0) for n, v in acc.items()}
-        return dt, stage_us, pair_us, x, w
+        raw_us = {n: 1e3 * v / args.steps for n, v in acc.items()}
+        stage_us = {n: max(v - pair_us, 0.0) for n, v in raw_us.items()}
+        return dt, stage_us, pair_us, x, w, raw_us
 
     if args.table:
         return bench_table(args, synth, wcc, torch, np)
@@ -583,7 +602,7 @@ def main() -> int:
     if args.config == 5:
         return bench_stack(args, synth, run_layer, ctx)
     cfg = synth.config(args.config)
-    dt, stage_us, pair_us, x, w = run_layer(cfg, ctx)
+    dt, stage_us, pair_us, x, w, raw_us = run_layer(cfg, ctx)
 
     pix_ch = cfg.B * cfg.H * cfg.W * cfg.C_in
     value = pix_ch / dt / 1e9
@@ -594,12 +613,8 @@ def main() -> int:
     alg = algorithmic_bytes(cfg, act_bytes, 1 if codes else 4)
     if args.index_list == "prefix":  # no norm pass, no selection: only the rank map is written
         alg["haar_fwd"], alg["norm_select"] = 0, 4 * cfg.B * cfg.N
-    kernel_of, contraction = dict(STAGE_KERNEL), "pointwise"
-    if stage_us["pointwise"] == 0:  # contraction and inverse were one kernel: Y_wt is neither written nor read
-        alg["scatter_ihaar"] += alg["pointwise"] - 2 * 4 * cfg.B * cfg.C_out * cfg.k
-        alg["pointwise"] = 0
-        kernel_of.update(gather="haar_keep_words_kernel", scatter_ihaar="layer_tail_kernel")
-        contraction = "scatter_ihaar"
+    kernel_of = dict(STAGE_KERNEL)
+    contraction = "scatter_ihaar" if fold_tail(alg, kernel_of, cfg, raw_us) else "pointwise"
     # stage_us is the HIP-event bracket around each stage as recorded (it holds the kernel and its
     # launch gap); the roofline figures use it as it is, so they err on the low side, and the
     # bracket less the cost of the two event records is reported beside it

@@ -107,7 +107,9 @@ typedef struct {
 enum {
   WCC_T_HAAR_FWD = 0,  /* first transform pass (channel norms), one kernel            */
   WCC_T_NORM_SELECT,   /* norm reduction + radix select + index emission               */
-  WCC_T_GATHER,        /* second transform pass: kept coefficients + max|c|, one kernel */
+  WCC_T_GATHER,        /* second transform pass: kept coefficients + max|c|, one kernel;
+                          with a small one in front, which counts the kept positions, where
+                          WCC_T_SCATTER_IHAAR holds the contraction                    */
   WCC_T_POINTWISE,     /* quantise + contraction + dequantise (and, on some layers of many
                           channels, the packing of the weights in front)               */
   WCC_T_SCATTER_IHAAR, /* scatter + inverse Haar, one kernel; on layers of few channels and

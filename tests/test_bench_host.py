@@ -138,3 +138,64 @@ def test_timing_table_rows_are_the_papers():
     assert rect.w_dtype == synth.W_BF16 and synth.block_config(1, 4).name == "block_256x256_c256_e4_b8_keep1of4"
     w8 = bench.block_from_shape(synth, "256,256,4,8", 1, 4, "i8")       # --weights i8
     assert w8.w_dtype == synth.W_I8 and w8.layer(1).w_dtype == synth.W_I8 and w8.name.endswith("_w8")
+
+
+def test_bytes_and_kernels_where_contraction_and_inverse_are_one_kernel():
+    """Y_wt is then neither written nor read, X_wt and the weights are read by the last kernel: by hand for the first layer
+    of the stack (16 -> 96 channels of 256 x 512, a quarter kept) and for the longest single-layer workload."""
+    cfg = synth.stack_layers(1, 4, B=4)[0]
+    B, N, k = cfg.B, cfg.N, cfg.k
+    assert (B, cfg.C_in, cfg.C_out, N, k) == (4, 16, 96, 131_072, 32_768)
+    alg, kernels = bench.algorithmic_bytes(cfg), dict(bench.STAGE_KERNEL)
+    total = sum(alg.values())
+    ran = {"haar_fwd": 21.0, "norm_select": 34.0, "gather": 25.0, "pointwise": 0.0, "scatter_ihaar": 47.0}
+    assert bench.fold_tail(alg, kernels, cfg, ran)
+    assert kernels["scatter_ihaar"] == "layer_tail_kernel" and kernels["gather"] == "haar_keep_words_kernel"
+    y_wt = 4 * B * 96 * k
+    assert alg["pointwise"] == 0
+    assert alg["scatter_ihaar"] == B * 16 * k + 2 * 16 * 96 + 4 * B * k + 4 * B * 96 * N == 203_951_104
+    assert sum(alg.values()) == total - 2 * y_wt
+    # a bracket of its own, however short, is a contraction of its own; a stage that ends before the inverse is no tail
+    for stages in (dict(ran, pointwise=0.4), dict(ran, scatter_ihaar=0.0)):
+        alg, kernels = bench.algorithmic_bytes(cfg), dict(bench.STAGE_KERNEL)
+        assert not bench.fold_tail(alg, kernels, cfg, stages)
+        assert alg == bench.algorithmic_bytes(cfg) and kernels == bench.STAGE_KERNEL
+    # the block's expand layer
+    bcfg = synth.block_shape(256, 512, 32, 4, 4, 1, 2, synth.W_BF16)
+    alg = bench.block_algorithmic_bytes(bcfg, 4, chained=False)
+    kernels, before = {}, dict(alg)
+    assert bench.fold_tail(alg, kernels, bcfg.layer(0), {"l0_pointwise": 0.0, "l0_scatter_ihaar": 9.0}, "l0_")
+    assert alg["l0_scatter_ihaar"] == before["l0_scatter_ihaar"] + before["l0_pointwise"] - 8 * 4 * 128 * bcfg.k
+    assert set(kernels) == {"l0_gather", "l0_scatter_ihaar"} and alg["l1_scatter_ihaar"] == before["l1_scatter_ihaar"]
+
+
+def test_stack_line_names_the_kernels_that_ran(capsys):
+    """The stack's roofline takes its layers' own kernels and bytes (its first layer here: one kernel at the end)."""
+    import argparse
+    import json
+
+    layers = synth.stack_layers(1, 4, B=4)
+
+    def run_layer(cfg, ctx):
+        one = cfg is run_layer.first
+        raw = {"haar_fwd": 20.0, "norm_select": 20.0, "gather": 20.0, "pointwise": 0.0 if one else 14.0,
+               "scatter_ihaar": 50.0 if one else 24.0}
+        return 1e-4, {n: max(v - 4.0, 0.0) for n, v in raw.items()}, 4.0, None, None, raw
+
+    class Ctx:
+        def close(self):
+            pass
+
+    class Layers:
+        @staticmethod
+        def stack_layers(num, den, B):
+            run_layer.first = layers[0]
+            return layers
+
+    args = argparse.Namespace(keep="1/4", act="f32", steps=1, warmup=0, launch="eager")
+    bench.bench_stack(args, Layers, run_layer, Ctx())
+    line = json.loads(capsys.readouterr().out)
+    assert line["roofline"]["kernel"] == "layer_tail_kernel"
+    assert line["roofline"]["algorithmic_bytes"] == 203_951_104
+    total = sum(sum(bench.algorithmic_bytes(c).values()) for c in layers) - 8 * 4 * 96 * layers[0].k
+    assert line["layer_alg_GBs"] == round(total / (len(layers) * 1e-4) / 1e9, 1)
