@@ -500,9 +500,16 @@ bool tail_takes(const wcc_desc &d, int64_t ks, size_t count_room) {
   const bool whole_lines = (int64_t)d.W * (d.act_dtype == WCC_BF16 ? 2 : 4) % 128 == 0;
   const bool all_kept = ks * 10 >= (int64_t)d.H * d.W * 9;
   if (!(mb >= 48 && units >= 900 && whole_lines) && !(mb >= 256 && units >= 640 && all_kept)) return false;
+  // A workgroup's start is paid once a unit, whatever C_out is, and a block of 16 channels costs the same whether all 16
+  // are there.  Without and with the one kernel: 8 x 16 -> 4 of 512 x 2048, half kept 427 and 659; 4 x 64 -> 8 of
+  // 512 x 1024, all kept 381 and 457; 64 -> 17, half kept 339 and 382; 64 -> 32 375 and 386; 1 x 6 -> 32 of 680 x 1344 112
+  // and 128.  Three blocks pay where the unit's share of Y_wt is long enough: 5 x 32 -> 41 of 432 x 608, 1/4 kept 179 and
+  // 182, but 13 x 8 -> 35 of 760 x 352, 1/3 kept (154 MB) 306 and 248.
+  const int64_t N = (int64_t)d.H * d.W, k = kept_count(d);
+  if (d.C_out <= 32 || (d.C_out < 48 && d.C_out * k < 16 * N && mb < 96)) return false;
   // byte offsets of 32 bits: sixteen planes of the output, the weights, a sample's compressed signal; and the
   // counts that every workgroup adds up
-  const int64_t N = (int64_t)d.H * d.W, limit = (int64_t)0xFFFFFFF0 - 16;
+  const int64_t limit = (int64_t)0xFFFFFFF0 - 16;
   if (16 * N * 4 > limit || (int64_t)(d.C_out + 48) * row > limit || (int64_t)(K + 3) * ks * 4 > limit) return false;
   return um.units <= 8192 && (size_t)d.B * unit_pad(um) * 4 <= count_room;
 }

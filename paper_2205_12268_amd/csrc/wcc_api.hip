@@ -80,11 +80,6 @@ wcc_status check_desc(const wcc_desc *d) {
   return WCC_OK;
 }
 
-int64_t k_of(const wcc_desc &d) {
-  const int64_t N = (int64_t)d.H * d.W;
-  return (d.keep_num * N + d.keep_den - 1) / d.keep_den;
-}
-
 // integer weight codes with a per-output-channel scale
 bool coded(int w_dtype) { return w_dtype == WCC_I8 || w_dtype == WCC_I4; }
 
@@ -111,7 +106,7 @@ constexpr size_t kSelectMinBlocks = 512;
 
 WsLayout ws_layout(const wcc_desc &d, int front, bool pad) {
   WsLayout L{};
-  const size_t N = (size_t)d.H * d.W, B = d.B, k = (size_t)k_of(d);
+  const size_t N = (size_t)d.H * d.W, B = d.B, k = (size_t)kept_count(d);
   // Rows of the compressed signals are whole words of four positions, so that the contraction can
   // load and store them whatever k is (the padding holds anything: it is never scattered).
   L.ks = pad ? ((int64_t)k + 3) & ~(int64_t)3 : (int64_t)k;
@@ -181,7 +176,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
                       const float *wdw, bool prof, hipStream_t s, int list = kListSelect,
                       const int32_t *idx_given = nullptr, const ChainSrc *src = nullptr,
                       bool stop_before_inverse = false, bool may_tail = false) {
-  const int64_t k = k_of(d);
+  const int64_t k = kept_count(d);
   const int64_t ks = L.ks;  // row stride of the compressed signals in the workspace
   const bool quant = d.act_quant_bits == 8;
 
@@ -338,7 +333,7 @@ int block_front(const wcc_block_desc &bd, const wcc_desc &d3, bool wants_middle)
   // Chained, a pass costs arithmetic and a gather per kept coefficient instead of bytes per
   // pixel: it wins while at most a third of the coefficients is kept (measured on the 256 x 256
   // block: 1.54 vs 1.93 ms at keep 1/8, 1.61 vs 2.25 ms at 1/4, 3.2 vs 2.8 ms at 1/2).
-  const bool sparse = k_of(d3) * 3 <= (int64_t)d3.H * d3.W;
+  const bool sparse = kept_count(d3) * 3 <= (int64_t)d3.H * d3.W;
   return (!wants_middle && sparse && chain_supported(d3)) ? kFrontChain : kFrontDw;
 }
 
@@ -426,7 +421,7 @@ wcc_status wcc_set_workspace(wcc_ctx *ctx, void *dev_ptr, size_t bytes) {
 
 int64_t wcc_k(const wcc_desc *desc) {
   if (check_desc(desc) != WCC_OK) return -1;
-  return k_of(*desc);
+  return kept_count(*desc);
 }
 
 wcc_status wcc_set_profiling(wcc_ctx *ctx, int enabled) {
@@ -503,7 +498,7 @@ wcc_status wcc_joint_topk(wcc_ctx *ctx, const wcc_desc *desc, const float *coef,
                                 desc->norm == WCC_NORM_L2, nw, s));
     norm = nw;
   }
-  const int64_t k = k_of(*desc);
+  const int64_t k = kept_count(*desc);
   WCC_TRY(launch_select_init(make_prep(ws, L, nullptr, 0.f), desc->B, s));
   WCC_TRY(launch_select(*desc, norm, 1, nullptr, k, ws, L, idx, nullptr, nullptr, nullptr,
                         PackJob{nullptr, nullptr, 0, 0, 0, 0, 0}, s));
@@ -520,7 +515,7 @@ wcc_status wcc_gather_quant(wcc_ctx *ctx, const wcc_desc *desc, const float *coe
   if (quant && !alpha_dev) return WCC_ERR_NULL;
   if (misaligned(coef) || misaligned(idx) || misaligned(xc)) return WCC_ERR_ALIGN;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int64_t N = (int64_t)desc->H * desc->W, k = k_of(*desc);
+  const int64_t N = (int64_t)desc->H * desc->W, k = kept_count(*desc);
   if (!quant) {
     WCC_TRY(launch_gather(coef, idx, desc->B, desc->C_in, N, k, static_cast<float *>(xc), nullptr, nullptr, s));
     return WCC_OK;
@@ -557,7 +552,7 @@ wcc_status wcc_pointwise(wcc_ctx *ctx, const wcc_desc *desc, const void *w, cons
   if (misaligned(w) || misaligned(xc) || misaligned(yc)) return WCC_ERR_ALIGN;
   const WsLayout L = ws_layout(*desc);
   if (desc->w_dtype == WCC_I4 && (st = need_ws(ctx, L)) != WCC_OK) return st;
-  WCC_TRY(pointwise_any(static_cast<char *>(ctx->ws), L, *desc, k_of(*desc), w, w_scale, xc,
+  WCC_TRY(pointwise_any(static_cast<char *>(ctx->ws), L, *desc, kept_count(*desc), w, w_scale, xc,
                         desc->act_quant_bits == 0, alpha_dev, 1, nullptr, yc,
                         static_cast<hipStream_t>(stream)));
   return WCC_OK;
@@ -573,7 +568,7 @@ wcc_status wcc_scatter_ihaar(wcc_ctx *ctx, const wcc_desc *desc, const float *yc
   const WsLayout L = ws_layout(*desc);
   if ((st = need_ws(ctx, L)) != WCC_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int64_t N = (int64_t)desc->H * desc->W, k = k_of(*desc);
+  const int64_t N = (int64_t)desc->H * desc->W, k = kept_count(*desc);
   int32_t *jmap = reinterpret_cast<int32_t *>(static_cast<char *>(ctx->ws) + L.jmap);
   WCC_TRY(launch_jmap_from_idx(idx, desc->B, N, k, jmap, nullptr, 0.f, s));
   WCC_TRY(launch_scatter_ihaar(*desc, k, yc, jmap, y,

@@ -27,6 +27,12 @@ struct Geo {
   __host__ __device__ int64_t band(int l, int j) const { return (int64_t)j * n(l); }
 };
 
+// positions that a checked layer keeps: k of Alg. 1
+inline int64_t kept_count(const wcc_desc &d) {
+  const int64_t N = (int64_t)d.H * d.W;
+  return (d.keep_num * N + d.keep_den - 1) / d.keep_den;
+}
+
 // How the workspace is carved up for one layer (offsets in bytes, all multiples of 256).
 struct WsLayout {
   size_t norm_part;   // [G, B, N] fp32 partial channel norms

@@ -1,0 +1,40 @@
+"""Which layers run contraction and inverse as one kernel (needs an MI355X): both sides of every line of the rule, each at a
+shape where the other route was measured the slower one.  The stage times say which ran: the contraction's bracket is
+exactly 0 where it has no kernel of its own."""
+import pytest
+import torch
+
+from paper_2205_12268_amd import wcc
+
+pytestmark = pytest.mark.gpu
+
+# one kernel?, B, C_in, C_out, H, W, keep, weights, bits, maps
+FEW_OUT = [
+    (False, 8, 16, 4, 512, 2048, (1, 2), wcc.BF16, 8, wcc.F32),
+    (False, 4, 64, 8, 512, 1024, (1, 1), wcc.BF16, 8, wcc.F32),
+    (False, 4, 64, 17, 512, 1024, (1, 2), wcc.BF16, 8, wcc.F32),
+    (False, 4, 64, 32, 512, 1024, (1, 2), wcc.BF16, 8, wcc.F32),
+    (False, 5, 32, 41, 432, 608, (1, 4), wcc.BF16, 8, wcc.F32),
+    (True, 7, 32, 33, 424, 576, (1, 1), wcc.BF16, 8, wcc.F32),
+    (True, 13, 8, 35, 760, 352, (1, 3), wcc.I4, 8, wcc.F32),
+    (True, 9, 16, 48, 184, 576, (1, 2), wcc.I4, 8, wcc.F32),
+    (True, 4, 16, 96, 256, 512, (1, 4), wcc.BF16, 8, wcc.F32),
+    (True, 4, 64, 256, 512, 1024, (1, 8), wcc.BF16, 8, wcc.F32),
+]
+
+
+@pytest.mark.parametrize("case", FEW_OUT, ids=lambda c: "x".join(map(str, c)))
+def test_route(case):
+    one, B, ci, co, H, W, (num, den), wt, bits, maps = case
+    d = wcc.make_desc(B, ci, co, H, W, 3, num, den, wt, bits, maps)
+    ctx = wcc.Context(0)
+    ctx.ensure_workspace(d)
+    t = torch.bfloat16 if maps == wcc.BF16 else torch.float32
+    x, y = (torch.zeros((B, c, H, W), dtype=t, device="cuda") for c in (ci, co))
+    wd = {wcc.F32: torch.float32, wcc.BF16: torch.bfloat16}.get(wt, torch.int8)
+    w = torch.zeros((co, ci // 2 if wt == wcc.I4 else ci), dtype=wd, device="cuda")
+    ctx.set_profiling(True)
+    ctx.wcc_forward(d, x, w, torch.ones(co, device="cuda") if wt in (wcc.I8, wcc.I4) else None, 0.0, y)
+    ms = ctx.stage_times()
+    assert ms["scatter_ihaar"] > 0 and (ms["pointwise"] == 0) == one
+    ctx.close()
