@@ -507,6 +507,14 @@ bool tail_takes(const wcc_desc &d, int64_t ks, size_t count_room) {
   // 182, but 13 x 8 -> 35 of 760 x 352, 1/3 kept (154 MB) 306 and 248.
   const int64_t N = (int64_t)d.H * d.W, k = kept_count(d);
   if (d.C_out <= 32 || (d.C_out < 48 && d.C_out * k < 16 * N && mb < 96)) return false;
+  // Where the channels take two steps the LDS holds X of 320 of a unit's 512 positions (kBlocks); a unit that keeps more
+  // stages X again for every block of channels.  More than half kept: 3 x 80 -> 160 of 376 x 640, the first 3/5 323 us without
+  // and 879 with; 10 x 128 -> 224 of 600 x 128, 3/4 576 and 656; 4 x 20 fp32 -> 128 of 256 x 512, 3/4 176 and 215.  Between a
+  // third and a half some units do where what is kept stands close together, against which codes need many blocks
+  // (15 x 128 -> 66 of 312 x 256 432 and 476, but 8 x 128 -> 404 of 216 x 768 984 and 693); the fp32 contraction that they
+  // would take otherwise costs more (5 x 30 -> 61 of 400 x 352 151 and 132).
+  const bool two_steps = d.w_dtype != WCC_BF16 && row > 64;
+  if (two_steps && (k * 2 > N || (k * 3 > N + 2 && d.w_dtype != WCC_F32 && d.C_out < 96))) return false;
   // byte offsets of 32 bits: sixteen planes of the output, the weights, a sample's compressed signal; and the
   // counts that every workgroup adds up
   const int64_t limit = (int64_t)0xFFFFFFF0 - 16;

@@ -2,7 +2,7 @@
 a long kept signal, at the edges of what it takes.  Every operand type, one step of channels and two, rows of
 weights that end inside a 16-byte load, output channels that are no multiple of 16, units that keep nothing, units
 that keep everything (more than the LDS holds of two steps), a last unit that is not full, each way to the index list and
-to alpha, and both storage types."""
+to alpha, and both storage types; the stage times say that the one kernel ran."""
 import numpy as np
 import pytest
 import torch
@@ -12,17 +12,26 @@ from tests.util import dev, rel_l2, tol_for, upload_weights
 
 pytestmark = pytest.mark.gpu
 
-# B, C_in, C_out, H, W, keep, weights, bits: at least 48 MiB of output coefficients and 900 units of 512 positions
+# B, C_in, C_out, H, W, keep, weights, bits, the maps' types with which the layer runs contraction and inverse as one kernel:
+# at least 48 MiB of output coefficients and 900 units of 512 positions
+F32, BF16 = wcc.F32, wcc.BF16
 CASES = [
-    (4, 64, 36, 264, 512, (3, 4), synth.W_BF16, 8),   # a whole step; 4 channels in the last block
-    (8, 10, 34, 256, 256, (3, 4), synth.W_BF16, 8),   # a row of 20 bytes
-    (7, 128, 36, 256, 320, (2, 3), synth.W_I8, 8),    # two steps; units that the LDS does not hold
-    (4, 68, 40, 264, 480, (2, 3), synth.W_I8, 8),     # one channel quad in the second step
-    (4, 24, 33, 256, 512, (3, 4), synth.W_I4, 8),
-    (4, 32, 36, 264, 512, (2, 3), synth.W_F32, 0),    # two steps of fp32
-    (9, 5, 64, 152, 352, (1, 2), synth.W_F32, 0),     # W: 88 lanes a strip, units across strips, a last one of 8 lanes
-    (4, 20, 40, 256, 512, (2, 3), synth.W_F32, 8),
-    (4, 8, 184, 256, 360, (1, 1), synth.W_I8, 8),     # all kept: rows that are not whole lines
+    (4, 64, 36, 264, 512, (3, 4), synth.W_BF16, 8, {F32, BF16}),   # a whole step; 4 channels in the last block
+    (8, 10, 34, 256, 256, (3, 4), synth.W_BF16, 8, {F32, BF16}),   # a row of 20 bytes
+    (4, 24, 33, 256, 512, (3, 4), synth.W_I4, 8, {F32, BF16}),     # one channel in the last block
+    (9, 5, 64, 152, 352, (1, 2), synth.W_F32, 0, {F32}),     # 88 lanes a strip, units across strips, a last one of 8 lanes
+    (4, 8, 184, 256, 360, (1, 1), synth.W_I8, 8, {F32, BF16}),     # all kept: rows that are not whole lines
+    (4, 8, 184, 264, 360, (1, 1), synth.W_I8, 8, {F32, BF16}),     # the same, units across strips, a last one of 10 lanes
+    (6, 128, 100, 256, 320, (1, 2), synth.W_I8, 8, {F32, BF16}),   # two steps; units that the LDS does not hold
+    (4, 68, 100, 264, 448, (1, 2), synth.W_I8, 8, {F32, BF16}),    # one channel quad in the second step
+    (4, 72, 104, 264, 448, (2, 5), synth.W_I4, 8, {F32, BF16}),
+    (4, 32, 68, 264, 512, (1, 2), synth.W_F32, 0, {F32, BF16}),    # two steps of fp32
+    (4, 20, 72, 256, 512, (1, 2), synth.W_F32, 8, {F32, BF16}),
+    # next to them, in the two kernels: two steps and more than half kept
+    (7, 128, 36, 256, 320, (2, 3), synth.W_I8, 8, set()),
+    (4, 68, 40, 264, 480, (2, 3), synth.W_I8, 8, set()),
+    (4, 32, 36, 264, 512, (2, 3), synth.W_F32, 0, set()),
+    (4, 20, 40, 256, 512, (2, 3), synth.W_F32, 8, set()),
 ]
 
 
@@ -38,9 +47,9 @@ def _input(cfg, maps):
 
 
 @pytest.mark.parametrize("maps", [wcc.F32, wcc.BF16])
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c[:-1])))
 def test_layer(ref, case, maps):
-    B, Ci, Co, H, W, (num, den), wt, bits = case
+    B, Ci, Co, H, W, (num, den), wt, bits, one_kernel = case
     cfg = synth.LayerCfg("tail", B, Ci, Co, H, W, 3, num, den, wt, bits, sigma=1.0, clip_hi=3.0,
                          seed=synth.SEED_BASE + 0x1500 + Ci)
     print(cfg, flush=True)
@@ -58,7 +67,11 @@ def test_layer(ref, case, maps):
     idx = torch.full((B, cfg.k), -7, dtype=torch.int32, device="cuda")
     alpha = torch.zeros(1, device="cuda")
     xd = dev(x).to(t)
+    ctx.set_profiling(True)
     ctx.wcc_forward(d, xd, wd, wsd, 0.0, y, idx, alpha if bits else None)
+    ms = ctx.stage_times()
+    ctx.set_profiling(False)
+    assert ms["scatter_ihaar"] > 0 and (ms["pointwise"] == 0) == (maps in one_kernel)
     want, o_idx, o_alpha = ref.forward(x, w.values, w.scale, 3, num, den, act_bits=bits)
     np.testing.assert_array_equal(idx.cpu().numpy().astype(np.int64), o_idx)
     if bits:

@@ -21,9 +21,22 @@ FEW_OUT = [
     (True, 4, 16, 96, 256, 512, (1, 4), wcc.BF16, 8, wcc.F32),
     (True, 4, 64, 256, 512, 1024, (1, 8), wcc.BF16, 8, wcc.F32),
 ]
+# X in two steps: a unit that keeps more than the LDS holds stages it again for every block
+TWO_STEPS = [
+    (False, 3, 80, 160, 376, 640, (3, 5), wcc.I4, 8, wcc.F32),
+    (False, 10, 128, 224, 600, 128, (3, 4), wcc.I8, 8, wcc.F32),
+    (False, 4, 20, 128, 256, 512, (3, 4), wcc.F32, 8, wcc.F32),
+    (False, 15, 128, 66, 312, 256, (1, 2), wcc.I8, 8, wcc.F32),
+    (False, 3, 128, 66, 616, 736, (1, 1), wcc.I8, 8, wcc.F32),    # all kept, rows that are not whole lines
+    (True, 3, 64, 369, 752, 288, (3, 4), wcc.BF16, 8, wcc.F32),    # one step
+    (True, 6, 88, 335, 152, 1024, (1, 2), wcc.I4, 8, wcc.F32),
+    (True, 5, 30, 61, 400, 352, (1, 2), wcc.F32, 0, wcc.F32),
+    (True, 5, 64, 48, 592, 832, (1, 3), wcc.I8, 8, wcc.F32),
+    (True, 4, 80, 48, 768, 416, (1, 4), wcc.I4, 8, wcc.F32),
+]
 
 
-@pytest.mark.parametrize("case", FEW_OUT, ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("case", FEW_OUT + TWO_STEPS, ids=lambda c: "x".join(map(str, c)))
 def test_route(case):
     one, B, ci, co, H, W, (num, den), wt, bits, maps = case
     d = wcc.make_desc(B, ci, co, H, W, 3, num, den, wt, bits, maps)
