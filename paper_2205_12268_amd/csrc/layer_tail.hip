@@ -504,7 +504,7 @@ bool tail_takes(const wcc_desc &d, int64_t ks, size_t count_room) {
   // are there.  Without and with the one kernel: 8 x 16 -> 4 of 512 x 2048, half kept 427 and 659; 4 x 64 -> 8 of
   // 512 x 1024, all kept 381 and 457; 64 -> 17, half kept 339 and 382; 64 -> 32 375 and 386; 1 x 6 -> 32 of 680 x 1344 112
   // and 128.  Three blocks pay where the unit's share of Y_wt is long enough: 5 x 32 -> 41 of 432 x 608, 1/4 kept 179 and
-  // 182, but 13 x 8 -> 35 of 760 x 352, 1/3 kept (154 MB) 306 and 248.
+  // 182, but 13 x 8 -> 35 of 760 x 352, 1/3 kept (154 MB) 305 and 247.
   const int64_t N = (int64_t)d.H * d.W, k = kept_count(d);
   if (d.C_out <= 32 || (d.C_out < 48 && d.C_out * k < 16 * N && mb < 96)) return false;
   // Where the channels take two steps the LDS holds X of 320 of a unit's 512 positions (kBlocks); a unit that keeps more
@@ -515,6 +515,12 @@ bool tail_takes(const wcc_desc &d, int64_t ks, size_t count_room) {
   // would take otherwise costs more (5 x 30 -> 61 of 400 x 352 151 and 132).
   const bool two_steps = d.w_dtype != WCC_BF16 && row > 64;
   if (two_steps && (k * 2 > N || (k * 3 > N + 2 && d.w_dtype != WCC_F32 && d.C_out < 96))) return false;
+  // Little kept: bf16 maps, whose rows are half as long to write, need a longer Y_wt or more of it a unit (5 x 12 -> 272 of
+  // 232 x 768, 1/16 kept 146 without and 151 us with; 2 x 6 -> 89 of 712 x 960, the first sixth 92 and 112; but
+  // 6 x 52 -> 144 of 136 x 960, 1/5 166 and 123), and the keep pass into words transforms whole quads of channels
+  // (6 x 1 -> 170 of 304 x 480, 1/10 161 and 167; 2 x 6 -> 248 of 456 x 928 227 and 232).
+  if (d.act_dtype == WCC_BF16 && mb < 96 && (mb < 64 || d.C_out * k < 24 * N)) return false;
+  if (K < 8 && k * 8 < N) return false;
   // byte offsets of 32 bits: sixteen planes of the output, the weights, a sample's compressed signal; and the
   // counts that every workgroup adds up
   const int64_t limit = (int64_t)0xFFFFFFF0 - 16;

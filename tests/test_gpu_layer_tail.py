@@ -16,9 +16,9 @@ pytestmark = pytest.mark.gpu
 # at least 48 MiB of output coefficients and 900 units of 512 positions
 F32, BF16 = wcc.F32, wcc.BF16
 CASES = [
-    (4, 64, 36, 264, 512, (3, 4), synth.W_BF16, 8, {F32, BF16}),   # a whole step; 4 channels in the last block
-    (8, 10, 34, 256, 256, (3, 4), synth.W_BF16, 8, {F32, BF16}),   # a row of 20 bytes
-    (4, 24, 33, 256, 512, (3, 4), synth.W_I4, 8, {F32, BF16}),     # one channel in the last block
+    (4, 64, 52, 264, 512, (3, 4), synth.W_BF16, 8, {F32, BF16}),   # a whole step; 4 channels in the last block
+    (8, 10, 50, 256, 256, (3, 4), synth.W_BF16, 8, {F32, BF16}),   # a row of 20 bytes
+    (4, 24, 49, 256, 512, (3, 4), synth.W_I4, 8, {F32, BF16}),     # one channel in the last block
     (9, 5, 64, 152, 352, (1, 2), synth.W_F32, 0, {F32}),     # 88 lanes a strip, units across strips, a last one of 8 lanes
     (4, 8, 184, 256, 360, (1, 1), synth.W_I8, 8, {F32, BF16}),     # all kept: rows that are not whole lines
     (4, 8, 184, 264, 360, (1, 1), synth.W_I8, 8, {F32, BF16}),     # the same, units across strips, a last one of 10 lanes

@@ -34,9 +34,21 @@ TWO_STEPS = [
     (True, 5, 64, 48, 592, 832, (1, 3), wcc.I8, 8, wcc.F32),
     (True, 4, 80, 48, 768, 416, (1, 4), wcc.I4, 8, wcc.F32),
 ]
+# little kept: bf16 maps, and fewer than eight channels
+LITTLE = [
+    (False, 5, 12, 272, 232, 768, (1, 16), wcc.I8, 8, wcc.BF16),
+    (False, 2, 6, 89, 712, 960, (1, 6), wcc.BF16, 8, wcc.BF16),
+    (False, 11, 128, 128, 392, 256, (1, 8), wcc.I4, 8, wcc.BF16),
+    (False, 6, 1, 170, 304, 480, (1, 10), wcc.F32, 0, wcc.F32),
+    (False, 2, 6, 248, 456, 928, (1, 10), wcc.F32, 0, wcc.F32),
+    (True, 6, 52, 144, 136, 960, (1, 5), wcc.I8, 8, wcc.BF16),
+    (True, 7, 112, 69, 280, 576, (1, 3), wcc.I4, 8, wcc.BF16),
+    (True, 5, 64, 147, 552, 896, (1, 16), wcc.BF16, 8, wcc.F32),
+    (True, 1, 4, 77, 864, 1120, (1, 3), wcc.BF16, 8, wcc.F32),
+]
 
 
-@pytest.mark.parametrize("case", FEW_OUT + TWO_STEPS, ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("case", FEW_OUT + TWO_STEPS + LITTLE, ids=lambda c: "x".join(map(str, c)))
 def test_route(case):
     one, B, ci, co, H, W, (num, den), wt, bits, maps = case
     d = wcc.make_desc(B, ci, co, H, W, 3, num, den, wt, bits, maps)
