@@ -1,5 +1,6 @@
 // Zero filling and the inverse transform (the decompression step after Eq. wavelet_transform;
 // the last loop of Alg. 1), with the skip connection of the inverted residual block.
+#include "rules.h"
 #include "strip_io.h"
 
 namespace wcc {
@@ -322,31 +323,12 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
   }
 }
 
-// Whether the four waves of a workgroup share a strip unit.  Sharing takes three quarters of a wave's rank lookups and votes
-// off, which are what a wave starts with; four waves on four neighbouring units write runs four times as long, which counts
-// once memory is the bound.  At 1 and 2 levels a strip has few slots and sharing measured 0.92..1.27 of the time.  At 3
-// levels, apart -> shared: 1x256x128x128 at 1/4 9.8 -> 8.4 us, 1x32x256x512 at 1/4 9.6 -> 7.9, 16x512x64x64 at 1/8
-// 34.6 -> 28.5; up to 16 MB of kept values 0.78..1.02 of the time, from there to 24 MB 0.85..1.01 with
-// up to 512 columns (4x96x192x320 at 1/4 25.1 -> 23.1 in the layer) but 39.1 -> 41.2 with 1024, with 24 to 64 MB 1.00..1.12.  At 4 levels the line lies at
-// 8 MB: 4x96x128x128 at 1/3 17.4 -> 16.2, but 4x96x96x320 at 1/4 (11 MB) 18.8 -> 20.0.  Above a third kept many units
-// overflow the list and look their ranks up twice: 0.94..1.19.  With the residual added sharing pays there all the same
-// (16x256x128x128 at 1/2 123 -> 108 us, 8x128x192x320 131 -> 114); under 8 units (64x64 and smaller) that kernel measured
-// 0.92..1.10 at 1/4 and 0.75..1.15 at 1/2.
-bool shares_units(const wcc_desc &d, const StripMap &m, int64_t k, bool residual) {
-  if (d.levels < 3) return false;
-  const bool few = k * 3 <= (int64_t)d.H * d.W + 2;
-  if (residual && m.units < 8) return false;
-  if (residual && !few) return true;
-  const int most = d.levels == 4 ? 8 : d.W <= 512 ? 24 : 16;  // MB
-  return few && (int64_t)d.B * d.C_out * k * 4 <= (int64_t)most << 20;
-}
-
 template <int D, int V>
 hipError_t inv_launch(const wcc_desc &d, int64_t k, const float *yc, const int32_t *jmap, void *y,
                       int G, float *scratch, const void *residual, hipStream_t s) {
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
   const StripMap m = make_flat_map(d, V);
-  const bool share = G >= 4 && shares_units(d, m, k, residual != nullptr);
+  const bool share = G >= 4 && shares_units(d, m.units, k, residual != nullptr);
   const dim3 grid(share ? m.units : (m.units + 3) / 4, share ? G / 4 : G, d.B);
   constexpr bool kShares = D >= 3;  // (the rule takes no others)
 #define WCC_INV_T(RES, YT, SHARE)                                                                 \

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2205_12268_amd import synth, wcc
-from tests.util import dev, rel_l2
+from tests.util import dev, layer_with_index_set, rel_l2, upload_weights
 
 pytestmark = pytest.mark.gpu
 
@@ -19,6 +19,9 @@ CASES = [
     (1, 18, 48, 40, 3, (1, 1920)),  # one position kept
     (2, 19, 64, 48, 4, (1, 3)),
     (1, 64, 48, 1040, 4, (1, 5)),
+    (2, 19, 64, 48, 4, (1, 6)),     # four levels share up to a sixth kept
+    (1, 64, 48, 1040, 4, (1, 8)),   # strips of several units
+    (2, 18, 16, 16, 4, (1, 256)),   # one position kept, one unit mostly outside the plane
 ]
 
 
@@ -80,3 +83,37 @@ def test_with_skip_connection(shape, keep):
     branch = torch.full_like(x, float("nan"))
     ctx3.wcc_forward(d3, t2, w3, None, 0.0, branch)
     assert torch.equal(y, branch + x)
+
+
+# levels, B, C, H, W, keep: shared at three levels, at four up to a quarter kept; last units that are not full
+BLOCKS = [(3, 2, 16, 128, 128, (1, 2)), (3, 1, 20, 72, 264, (1, 1)), (3, 1, 32, 136, 96, (1, 5)),
+          (4, 2, 16, 128, 128, (1, 4)), (4, 1, 20, 144, 272, (1, 8)), (4, 1, 32, 128, 128, (1, 2))]
+
+
+@pytest.mark.parametrize("maps", [wcc.F32, wcc.BF16])
+@pytest.mark.parametrize("shape", BLOCKS, ids=lambda c: "x".join(map(str, c)))
+def test_skip_connection_against_oracle(ref, shape, maps):
+    """The block's second layer in 64 bits from the first one's output as the call gives it and the call's own index set.
+    fp32 maps: sums of 32 bits.  bf16 maps: each value is rounded once, by 2^-9 of it at most."""
+    levels, B, C, H, W, keep = shape
+    cfg = synth.BlockCfg("shared", B, C, 2, H, W, levels, *keep, synth.W_F32, 0, sigma=1.0,
+                         seed=synth.SEED_BASE + 0x1780 + 16 * levels + C)
+    print(cfg, maps, flush=True)
+    x, w1, w_dw, w3 = synth.make_block_inputs(cfg)
+    t = torch.bfloat16 if maps == wcc.BF16 else torch.float32
+    xd = dev(x).to(t)
+    d = wcc.make_block_desc(B, C, 2, H, W, levels, *keep, cfg.w_dtype, 0, maps)
+    ctx = wcc.Context(0)
+    ctx.ensure_workspace(d)
+    flat = torch.full((x.size + 4096,), float("nan"), dtype=t, device="cuda")
+    y = flat[:x.size].view(x.shape)
+    t1 = torch.empty((B, 2 * C, H, W), dtype=t, device="cuda")
+    idx3 = torch.empty((B, cfg.k), dtype=torch.int32, device="cuda")
+    (w1d, _), (w3d, _) = upload_weights(w1), upload_weights(w3)
+    ctx.wcc_block_forward(d, xd, w1d, None, dev(w_dw), w3d, None, y, t1, None, None, idx3)
+    t2 = ref.depthwise3x3(t1.float().cpu().numpy().astype(np.float64), w_dw)
+    branch, _ = layer_with_index_set(ref, cfg.layer(1), w3, t2, idx3.cpu().numpy().astype(np.int64))
+    want = xd.float().cpu().numpy().astype(np.float64) + branch
+    assert rel_l2(y.float().cpu().numpy(), want) <= (2.0 ** -9 + 1e-5 if maps == wcc.BF16 else 1e-5)
+    assert torch.isnan(flat[x.size:].float()).all()
+    ctx.close()
