@@ -518,9 +518,11 @@ bool tail_takes(const wcc_desc &d, int64_t ks, size_t count_room) {
   // Little kept: bf16 maps, whose rows are half as long to write, need a longer Y_wt or more of it a unit (5 x 12 -> 272 of
   // 232 x 768, 1/16 kept 146 without and 151 us with; 2 x 6 -> 89 of 712 x 960, the first sixth 92 and 112; but
   // 6 x 52 -> 144 of 136 x 960, 1/5 166 and 123), and the keep pass into words transforms whole quads of channels
-  // (6 x 1 -> 170 of 304 x 480, 1/10 161 and 167; 2 x 6 -> 248 of 456 x 928 227 and 232).
+  // (6 x 1 -> 170 of 304 x 480, 1/10 161 and 167; 2 x 6 -> 248 of 456 x 928 227 and 232), which
+  // below a twelfth of few channels is not made good either (4 x 8 -> 112 of 624 x 736, 1/16 229 and 235; 14 x 16 -> 373 fp32
+  // channels of 360 x 128 238 and 244; but 5 x 38 -> 240 of 344 x 736 312 and 299).
   if (d.act_dtype == WCC_BF16 && mb < 96 && (mb < 64 || d.C_out * k < 24 * N)) return false;
-  if (K < 8 && k * 8 < N) return false;
+  if (k * 8 < N && K < (k * 12 < N ? 24 : 8)) return false;
   // byte offsets of 32 bits: sixteen planes of the output, the weights, a sample's compressed signal; and the
   // counts that every workgroup adds up
   const int64_t limit = (int64_t)0xFFFFFFF0 - 16;

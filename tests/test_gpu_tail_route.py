@@ -41,6 +41,9 @@ LITTLE = [
     (False, 11, 128, 128, 392, 256, (1, 8), wcc.I4, 8, wcc.BF16),
     (False, 6, 1, 170, 304, 480, (1, 10), wcc.F32, 0, wcc.F32),
     (False, 2, 6, 248, 456, 928, (1, 10), wcc.F32, 0, wcc.F32),
+    (False, 4, 8, 112, 624, 736, (1, 16), wcc.I4, 8, wcc.F32),
+    (False, 14, 16, 373, 360, 128, (1, 16), wcc.F32, 0, wcc.F32),
+    (True, 5, 8, 198, 336, 992, (1, 10), wcc.I8, 8, wcc.F32),
     (True, 6, 52, 144, 136, 960, (1, 5), wcc.I8, 8, wcc.BF16),
     (True, 7, 112, 69, 280, 576, (1, 3), wcc.I4, 8, wcc.BF16),
     (True, 5, 64, 147, 552, 896, (1, 16), wcc.BF16, 8, wcc.F32),
