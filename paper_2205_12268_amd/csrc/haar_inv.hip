@@ -1,6 +1,5 @@
 // Zero filling and the inverse transform (the decompression step after Eq. wavelet_transform;
 // the last loop of Alg. 1), with the skip connection of the inverted residual block.
-#include "rules.h"
 #include "strip_io.h"
 
 namespace wcc {
@@ -328,7 +327,7 @@ hipError_t inv_launch(const wcc_desc &d, int64_t k, const float *yc, const int32
                       int G, float *scratch, const void *residual, hipStream_t s) {
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
   const StripMap m = make_flat_map(d, V);
-  const bool share = G >= 4 && shares_units(d, m.units, k, residual != nullptr);
+  const bool share = G >= 4 && shares_units(d, m.units, residual != nullptr);
   const dim3 grid(share ? m.units : (m.units + 3) / 4, share ? G / 4 : G, d.B);
   constexpr bool kShares = D >= 3;  // (the rule takes no others)
 #define WCC_INV_T(RES, YT, SHARE)                                                                 \

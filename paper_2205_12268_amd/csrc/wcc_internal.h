@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <algorithm>
 
+#include "rules.h"
 #include "wcc.h"
 
 namespace wcc {
@@ -26,12 +27,6 @@ struct Geo {
   // offset of band j (0 = y1, only for l = d; 1..3 = y2..y4) of level l
   __host__ __device__ int64_t band(int l, int j) const { return (int64_t)j * n(l); }
 };
-
-// positions that a checked layer keeps: k of Alg. 1
-inline int64_t kept_count(const wcc_desc &d) {
-  const int64_t N = (int64_t)d.H * d.W;
-  return (d.keep_num * N + d.keep_den - 1) / d.keep_den;
-}
 
 // How the workspace is carved up for one layer (offsets in bytes, all multiples of 256).
 struct WsLayout {

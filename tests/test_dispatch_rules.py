@@ -11,8 +11,8 @@ from paper_2205_12268_amd import wcc
 CSRC = os.path.join(os.path.dirname(os.path.abspath(wcc.__file__)), "csrc")
 SHIM = """
 #include "rules.h"
-extern "C" int shares(const wcc_desc *d, int units, int64_t k, int residual) {
-  return wcc::shares_units(*d, units, k, residual != 0);
+extern "C" int shares(const wcc_desc *d, int units, int residual) {
+  return wcc::shares_units(*d, units, residual != 0);
 }
 """
 
@@ -25,14 +25,13 @@ def rules(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + CSRC,
                     "-I" + os.path.join(os.path.dirname(os.path.dirname(CSRC)), "include"), "-o", str(lib), str(src)], check=True)
     L = C.CDLL(str(lib))
-    L.shares.argtypes = [C.POINTER(wcc.Desc), C.c_int, C.c_int64, C.c_int]
+    L.shares.argtypes = [C.POINTER(wcc.Desc), C.c_int, C.c_int]
     return L
 
 
 def shares(rules, B, co, H, W, levels, keep, units, residual):
     d = wcc.make_desc(B, 32, co, H, W, levels, *keep, wcc.F32, 0)
-    k = -(-keep[0] * H * W // keep[1])
-    return bool(rules.shares(C.byref(d), units, k, int(residual)))
+    return bool(rules.shares(C.byref(d), units, int(residual)))
 
 
 # shared?, B, C, H, W, keep, strip units of a plane, skip connection
@@ -58,6 +57,9 @@ THREE_LEVELS = [
     (True, 4, 96, 192, 320, (1, 4), 30, False), (False, 16, 256, 128, 128, (1, 2), 8, False),
     (False, 4, 96, 136, 1024, (1, 8), 68, False),
     (True, 8, 128, 128, 128, (1, 2), 8, True), (True, 4, 16, 192, 320, (1, 1), 30, True),
+    # a third kept: the same for a layer, whose rows are rounded up to whole words, as for a stage call
+    (True, 2, 17, 64, 64, (1, 3), 2, False), (True, 2, 512, 128, 128, (1, 3), 8, False),
+    (True, 1, 16, 8, 16, (1, 3), 1, False), (True, 16, 128, 128, 128, (1, 3), 8, True),
     (False, 4, 64, 64, 64, (1, 2), 2, True), (False, 8, 128, 192, 320, (1, 4), 30, True),
 ]
 
