@@ -19,8 +19,9 @@ inline int64_t kept_count(const wcc_desc &d) {
 // neighbouring units write runs four times as long, which counts once memory is the bound.  At 1 and 2 levels a strip has
 // few slots and sharing measured 0.92..1.27 of the time.
 // At 3 levels, apart -> shared: 1x256x128x128 at 1/4 9.8 -> 8.4 us, 1x32x256x512 at 1/4 9.6 -> 7.9, 16x512x64x64 at 1/8
-// 34.6 -> 28.5; up to 16 MB of kept values 0.78..1.02 of the time, from there to 24 MB 0.85..1.01 with up to 512 columns
-// (4x96x192x320 at 1/4 25.1 -> 23.1 in the layer) but 39.1 -> 41.2 with 1024, with 24 to 64 MB 1.00..1.12.  Above a third
+// 34.6 -> 28.5; up to 16 MB of kept values 0.78..1.02 of the time.  From there to 24 MB 0.85..1.01 with up to 512 columns and
+// up to 160 MB to be stored (4x96x192x320 at 1/4 25.1 -> 23.1 in the layer), but 39.1 -> 41.2 with 1024 columns and, of 192 MB
+// to be stored, 38.8 -> 39.5 and 38.8 -> 40.6 (4x96x256x512 at 1/10 and 1/8); from 24 to 64 MB 1.00..1.12.  Above a third
 // kept many units overflow the list and look their ranks up twice: 0.94..1.19; with the residual added sharing pays there
 // all the same (8x128x128x128 at 1/2 36.9 -> 34.5, 4x16x192x320 18.0 -> 12.5; at 3/4 38.0 -> 35.0 and 19.2 -> 13.3; all
 // kept 0.67..1.01), and from a third on (16x128x128x128, 43 MB, 60.0 -> 55.9; 8x128x192x320, 80 MB, 108.3 -> 109.1).  Below
@@ -37,7 +38,8 @@ inline bool shares_units(const wcc_desc &d, int units, bool residual) {
     return (k * 8 <= N && kept <= 8 * MB) || (k * 6 <= N + 5 && kept <= 4 * MB);
   }
   if (residual && k * 3 >= N) return true;
-  return k * 3 <= N + 2 && kept <= (d.W <= 512 ? 24 : 16) * MB;
+  const bool long_store = (int64_t)d.B * d.C_out * N > 40 * MB;  // y of more than 160 MB in fp32
+  return k * 3 <= N + 2 && kept <= (d.W <= 512 && !long_store ? 24 : 16) * MB;
 }
 
 }  // namespace wcc

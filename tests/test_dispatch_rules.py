@@ -56,6 +56,8 @@ THREE_LEVELS = [
     (True, 1, 256, 128, 128, (1, 4), 8, False), (True, 16, 512, 64, 64, (1, 8), 2, False),
     (True, 4, 96, 192, 320, (1, 4), 30, False), (False, 16, 256, 128, 128, (1, 2), 8, False),
     (False, 4, 96, 136, 1024, (1, 8), 68, False),
+    (False, 4, 96, 256, 512, (1, 8), 64, False), (False, 4, 96, 256, 512, (1, 10), 64, False),  # 192 MB to be stored
+    (True, 4, 96, 256, 512, (1, 16), 64, False), (True, 16, 64, 128, 128, (1, 3), 8, False),
     (True, 8, 128, 128, 128, (1, 2), 8, True), (True, 4, 16, 192, 320, (1, 1), 30, True),
     # a third kept: the same for a layer, whose rows are rounded up to whole words, as for a stage call
     (True, 2, 17, 64, 64, (1, 3), 2, False), (True, 2, 512, 128, 128, (1, 3), 8, False),
