@@ -16,12 +16,15 @@ from tests.util import desc_of, dev, upload_weights
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("which", ["small_plane", "large_plane"])
+@pytest.mark.parametrize("which", ["small_plane", "large_plane", "one_kernel_tail"])
 def test_graph_replays_match_eager(which):
     base = synth.config(2)
     if which == "small_plane":   # one-workgroup select, 64x64 contraction tiles
         cfg = synth.small(base, name="graph_small", B=2, C_in=64, C_out=96, H=64, W=128, levels=2,
                           keep_num=1, keep_den=4, seed=synth.SEED_BASE + 0x700)
+    elif which == "one_kernel_tail":  # contraction and inverse in one kernel; channels in two steps, some staged block by block
+        cfg = synth.small(base, name="graph_tail", B=4, C_in=72, C_out=104, H=264, W=448, levels=3, keep_num=1,
+                          keep_den=2, seed=synth.SEED_BASE + 0x702, w_dtype=synth.W_I8, sigma=2.0)
     else:                        # multi-kernel select, partial-norm groups
         cfg = synth.small(base, name="graph_large", B=1, C_in=32, C_out=32, H=128, W=256, levels=3,
                           keep_num=1, keep_den=8, seed=synth.SEED_BASE + 0x701)
@@ -34,6 +37,11 @@ def test_graph_replays_match_eager(which):
         wd, wsd = upload_weights(w)
         xs = [dev(x1), dev(x2)]
         shape = (cfg.B, cfg.C_out, cfg.H, cfg.W)
+        if which == "one_kernel_tail":
+            ctx.set_profiling(True)
+            ctx.wcc_forward(d, xs[0], wd, wsd, 0.0, torch.empty(shape, device="cuda"))
+            assert ctx.stage_times()["pointwise"] == 0
+            ctx.set_profiling(False)
 
         def eager(xd):
             y = torch.empty(shape, dtype=torch.float32, device="cuda")
@@ -129,4 +137,39 @@ def test_block_graph_replays_match_eager(which):
             assert torch.equal(idx3, want[sel][1]), f"replay {rep}: index list differs"
             assert torch.equal(y, want[sel][0]), f"replay {rep}: output differs"
     finally:
+        ctx.close()
+
+
+def test_one_kernel_tail_on_a_second_stream():
+    """Two contexts with the tail in one kernel, on two streams at once, with work of their own in between: each result is
+    the one that the call gives by itself."""
+    cfg = synth.LayerCfg("stream_tail", 4, 16, 96, 256, 512, 3, 1, 4, synth.W_BF16, 8, sigma=2.0,
+                         seed=synth.SEED_BASE + 0x703)
+    x1, w = synth.make_inputs(cfg)
+    d = desc_of(cfg)
+    wd, _ = upload_weights(w)
+    xs = [dev(x1), dev(np.ascontiguousarray(x1[:, ::-1, :, ::-1]))]
+    ctxs = [wcc.Context(0) for _ in xs]
+    shape = (cfg.B, cfg.C_out, cfg.H, cfg.W)
+    want = []
+    for ctx, xd in zip(ctxs, xs):
+        ctx.ensure_workspace(d)
+        ctx.set_profiling(True)
+        want.append(torch.empty(shape, device="cuda"))
+        ctx.wcc_forward(d, xd, wd, None, 0.0, want[-1])
+        assert ctx.stage_times()["pointwise"] == 0
+        ctx.set_profiling(False)
+    assert not torch.equal(*want)
+    streams = [torch.cuda.Stream() for _ in xs]
+    got = [torch.full(shape, float("nan"), device="cuda") for _ in xs]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for s, ctx, xd, y in zip(streams, ctxs, xs, got):
+            with torch.cuda.stream(s):
+                y.fill_(float("nan"))
+                ctx.wcc_forward(d, xd, wd, None, 0.0, y)
+    torch.cuda.synchronize()
+    for y, ref_y in zip(got, want):
+        assert torch.equal(y, ref_y)
+    for ctx in ctxs:
         ctx.close()

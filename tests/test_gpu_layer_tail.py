@@ -114,3 +114,25 @@ def test_a_row_of_weights_does_not_reach_into_the_row_before():
     keep = [c for c in range(36) if c != 7]
     assert torch.equal(got[0][:, keep], got[1][:, keep])
     ctx.close()
+
+
+def test_in_the_static_scratch_memory(ref):
+    """A layer with the tail in one kernel whose intermediates fit wcc_forward_static: the same bits, and the oracle's."""
+    cfg = synth.LayerCfg("tail_static", 4, 8, 104, 256, 480, 3, 1, 4, synth.W_F32, 0, sigma=1.0, seed=synth.SEED_BASE + 0x1590)
+    x, w = synth.make_inputs(cfg)
+    d = wcc.make_desc(4, 8, 104, 256, 480, 3, 1, 4, wcc.F32, 0)
+    assert wcc.workspace_bytes(d) <= 64 << 20
+    ctx = wcc.Context(0)
+    ctx.ensure_workspace(d)
+    xd, (wd, _) = dev(x), upload_weights(w)
+    y, y_static = (torch.full((4, 104, 256, 480), float("nan"), device="cuda") for _ in range(2))
+    idx, idx_static = (torch.full((4, cfg.k), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+    ctx.set_profiling(True)
+    ctx.wcc_forward(d, xd, wd, None, 0.0, y, idx)
+    assert ctx.stage_times()["pointwise"] == 0
+    ctx.wcc_forward_static(d, xd, wd, None, 0.0, y_static, idx_static)
+    assert torch.equal(y, y_static) and torch.equal(idx, idx_static)
+    want, o_idx, _ = ref.forward(x, w.values, w.scale, 3, 1, 4, act_bits=0)
+    np.testing.assert_array_equal(idx.cpu().numpy().astype(np.int64), o_idx)
+    assert rel_l2(y.cpu().numpy(), want) <= tol_for(cfg)
+    ctx.close()
