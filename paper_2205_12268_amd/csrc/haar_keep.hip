@@ -204,9 +204,10 @@ __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x
 // wait for it every path has the same number of memory instructions.
 // Bound by its reads of x: 4 x 64 channels of 512 x 1024, an eighth kept, 99 us, where a byte store a code, in short runs
 // of lines that several dies write, takes the kernel above 114 (the norm pass reads the same x in 82).
+// Three levels, four columns a lane (the last kernel's).
 // grid = (ceil(wave units / 4), G, B), block = 256; group y takes the quads of channels y, y + G, ...
-template <int D, int V>
 struct WordSink {
+  static constexpr int D = 3, V = 4;
   uint32_t *tile;  // this lane's column of [slot][lane]
   template <int L, int J>
   __device__ __forceinline__ void put_row(const LanePos<D> &, int i, const float (&v)[cols_at(V, L)], bool) {
@@ -216,14 +217,14 @@ struct WordSink {
   }
 };
 
-template <int D, int V, bool Q8, class XT, bool NT>
+template <bool Q8, class XT, bool NT>
 __global__ __launch_bounds__(256) void haar_keep_words_kernel(const XT *__restrict__ x, const int32_t *__restrict__ jmap,
                                                               const uint32_t *__restrict__ ucount, int upad,
                                                               uint32_t *__restrict__ xw, float *alpha_slots,
                                                               float *wg_max, Geo g, StripMap m, int C, int64_t ks,
                                                               float q_alpha, const float *__restrict__ alpha_src,
                                                               int n_alpha, float *alpha_pub) {
-  constexpr int NS = slot_count(D, V), R = 1 << D;
+  constexpr int D = WordSink::D, V = WordSink::V, NS = slot_count(D, V), R = 1 << D;
   __shared__ float wmax[4];
   __shared__ uint32_t tiles[4][NS * kWave];
   const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -258,9 +259,8 @@ __global__ __launch_bounds__(256) void haar_keep_words_kernel(const XT *__restri
     if constexpr (L == D) fetch(Lc, std::integral_constant<int, 0>{});
   };
   each_level(std::integral_constant<int, 1>{});
-  if constexpr (D >= 2) each_level(std::integral_constant<int, 2>{});
-  if constexpr (D >= 3) each_level(std::integral_constant<int, 3>{});
-  if constexpr (D >= 4) each_level(std::integral_constant<int, 4>{});
+  each_level(std::integral_constant<int, 2>{});
+  each_level(std::integral_constant<int, 3>{});
   // kept positions in front of this wave's units
   uint32_t before = 0;
   {
@@ -305,16 +305,14 @@ __global__ __launch_bounds__(256) void haar_keep_words_kernel(const XT *__restri
     }
     wave_lds_fence();
     const int ni = (count + kWave - 1) / kWave;
-    // Sixteen rows a walk over the channels at most: 32 rows take the registers of a second wave.  The cells of
+    // Sixteen of 32 rows a walk over the channels at most: 32 rows take the registers of a second wave.  The cells of
     // the second walk wait two to a register.
     constexpr int kRows = 16;
-    constexpr bool kTwo = (V << D) > kRows;
+    static_assert(2 * kRows == V << D, "two walks hold every position of the wave's units");
     auto entry = [&](int i) { return tile[min(lane + kWave * i, count - 1)]; };
-    uint32_t later[kTwo ? kRows / 2 : 1];
-    if constexpr (kTwo) {
+    uint32_t later[kRows / 2];
 #pragma unroll
-      for (int i = 0; i < kRows / 2; ++i) later[i] = entry(kRows + 2 * i) | entry(kRows + 2 * i + 1) << 16;
-    }
+    for (int i = 0; i < kRows / 2; ++i) later[i] = entry(kRows + 2 * i) | entry(kRows + 2 * i + 1) << 16;
     // (lanes outside the plane read the plane's first rows; their values are in no list)
     const XT *src = x + (size_t)b * C * g.N + (active ? (size_t)row0 * g.W + col0 : (size_t)0);
     uint32_t *out = xw + (size_t)b * (Q8 ? quads : C) * ks + before;
@@ -322,7 +320,7 @@ __global__ __launch_bounds__(256) void haar_keep_words_kernel(const XT *__restri
     auto walk = [&](auto ni_c, const uint32_t (&cell)[decltype(ni_c)::value], uint32_t *out, int left) {
       constexpr int NI = decltype(ni_c)::value;
       wave_lds_fence();
-      WordSink<D, V> sink{tile + lane};
+      WordSink sink{tile + lane};
       uint32_t word[NI];
 #pragma unroll
       for (int i = 0; i < NI; ++i) word[i] = 0;
@@ -387,19 +385,15 @@ __global__ __launch_bounds__(256) void haar_keep_words_kernel(const XT *__restri
       walk(ni_c, cell, out, count);
     };
     using std::integral_constant;
-    if ((V << D) == 4 || ni <= 4) first(integral_constant<int, 4>{});
-    else if constexpr ((V << D) >= 8) {
-      if ((V << D) == 8 || ni <= 8) first(integral_constant<int, 8>{});
-      else if constexpr ((V << D) >= 16) {
-        first(integral_constant<int, 16>{});
-        if constexpr (kTwo) {
-          if (ni > kRows) {
-            uint32_t cell[kRows];
+    if (ni <= 4) first(integral_constant<int, 4>{});
+    else if (ni <= 8) first(integral_constant<int, 8>{});
+    else {
+      first(integral_constant<int, kRows>{});
+      if (ni > kRows) {
+        uint32_t cell[kRows];
 #pragma unroll
-            for (int i = 0; i < kRows; ++i) cell[i] = i & 1 ? later[i / 2] >> 16 : later[i / 2] & 0xFFFFu;
-            walk(integral_constant<int, kRows>{}, cell, out + kRows * kWave, count - kRows * kWave);
-          }
-        }
+        for (int i = 0; i < kRows; ++i) cell[i] = i & 1 ? later[i / 2] >> 16 : later[i / 2] & 0xFFFFu;
+        walk(integral_constant<int, kRows>{}, cell, out + kRows * kWave, count - kRows * kWave);
       }
     }
   }
@@ -436,7 +430,7 @@ int words_groups(const wcc_desc &d, bool late) {
   return G;
 }
 
-template <int D, int V, class XT>
+template <class XT>
 hipError_t words_launch(const wcc_desc &d, int64_t ks, const XT *x, const int32_t *jmap, const uint32_t *ucount,
                         uint32_t *xw, float *alpha_slots, float *wg_max, float q_alpha, const float *alpha_src,
                         int n_alpha, float *alpha_pub, hipStream_t s) {
@@ -445,7 +439,7 @@ hipError_t words_launch(const wcc_desc &d, int64_t ks, const XT *x, const int32_
   const int upad = unit_pad(unit_map(d));
   const dim3 grid((m.units + 3) / 4, words_groups(d, alpha_slots != nullptr || wg_max != nullptr), d.B);
 #define WCC_WORDS(Q8, NT)                                                                                          \
-  hipLaunchKernelGGL((haar_keep_words_kernel<D, V, Q8, XT, NT>), grid, dim3(256), 0, s, x, jmap, ucount, upad, xw, \
+  hipLaunchKernelGGL((haar_keep_words_kernel<Q8, XT, NT>), grid, dim3(256), 0, s, x, jmap, ucount, upad, xw, \
                      alpha_slots, wg_max, g, m, d.C_in, ks, q_alpha, alpha_src, n_alpha, alpha_pub)
   if (q_alpha > 0.f || alpha_src != nullptr) { if (streams(d)) WCC_WORDS(true, true); else WCC_WORDS(true, false); }
   else                                       { if (streams(d)) WCC_WORDS(false, true); else WCC_WORDS(false, false); }
@@ -561,15 +555,12 @@ int64_t keep_words_workgroups(const wcc_desc &d) {
 hipError_t launch_haar_keep_words(const wcc_desc &d, int64_t ks, const void *x, const int32_t *jmap,
                                   const uint32_t *ucount, uint32_t *xw, float *alpha_slots, float *wg_max,
                                   float q_alpha, const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
-#define WCC_GO(D, V)                                                                                               \
-  return d.act_dtype == WCC_BF16                                                                                   \
-             ? words_launch<D, V>(d, ks, static_cast<const bf16_t *>(x), jmap, ucount, xw, alpha_slots, wg_max,    \
-                                  q_alpha, alpha_src, n_alpha, alpha_pub, s)                                       \
-             : words_launch<D, V>(d, ks, static_cast<const float *>(x), jmap, ucount, xw, alpha_slots, wg_max,     \
-                                  q_alpha, alpha_src, n_alpha, alpha_pub, s)
-  if (d.levels == 3) WCC_GO(3, 4);  // (the last kernel's)
-#undef WCC_GO
-  return hipErrorInvalidValue;
+  if (d.levels != WordSink::D) return hipErrorInvalidValue;
+  return d.act_dtype == WCC_BF16
+             ? words_launch(d, ks, static_cast<const bf16_t *>(x), jmap, ucount, xw, alpha_slots, wg_max, q_alpha,
+                            alpha_src, n_alpha, alpha_pub, s)
+             : words_launch(d, ks, static_cast<const float *>(x), jmap, ucount, xw, alpha_slots, wg_max, q_alpha,
+                            alpha_src, n_alpha, alpha_pub, s);
 }
 
 }  // namespace wcc
