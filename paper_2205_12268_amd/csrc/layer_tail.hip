@@ -490,12 +490,18 @@ bool tail_takes(const wcc_desc &d, int64_t ks, size_t count_room) {
   // row; where nearly everything is kept, which the inverse on its own takes value by value, any rows.  Layers without and
   // with it, us (X: left to them):
   //   4 x 64 -> 256 channels of 512 x 1024, 1/8 kept, 268 MB of Y_wt, 4096 units: 720 and 617;
-  //   53 MB, 416 columns, 1131 units: 117 and 107; 92 MB, 512, 976: 179 and 149; 126 MB, 224, 1344: 137 and 103;
-  //   126 MB, 192, 1152: 190 and 138; all kept: 368 MB, 792, 693: 301 and 223; 759 MB, 280, 945: 576 and 359;
-  //   X shorter: 20 MB, 640, 2520: 132 and 143; 26 MB, 688, 1354: 157 and 164; X ragged lines: 69 MB, 728, 1024: 117 and
-  //   141; 82 MB, 744, 1232: 200 and 233; X few units: 39 MB, 200, 188: 58 and 85; 93 MB, 88, 319: 135 and 200;
+  //   48 MB, 512 columns, 1024 units (4 x 16 -> 96): 96 and 94; 53 MB, 416, 1131: 117 and 107; 92 MB, 512, 976: 179 and 149;
+  //   126 MB, 224, 1344: 137 and 103; 126 MB, 192, 1152: 190 and 138; all kept: 368 MB, 792, 693: 301 and 223; 759 MB, 280, 945:
+  //   576 and 359;
+  //   X shorter: 20 MB, 640, 2520: 132 and 143; 26 MB, 688, 1354: 157 and 164; X ragged lines: 186 MB, 744, 1488: 272 and 289;
+  //   65 MB, 520, 1040: 155 and 188; 136 MB, 728, 2912: 322 and 360; 106 MB, 424, 1696: 271 and 307; X few units, whole lines:
+  //   64 MB, 256, 128: 105 and 134 at 1/4, 83 and 117 at 1/2; 39 MB, 200 (ragged), 188: 58 and 85;
   //   X more channels: 16 x 256 -> 1024 of 128 x 128, half kept: 465 without, 1170 with (conversions of X for every
   //   block of channels); 144 fp32 channels of half kept 192 x 320 maps: 422 and 1400 (X staged again for every block).
+  // The line of 900 units is on the safe side: with whole lines 512 to 768 of them measured 0.76..0.97 of the time (2 x 64 ->
+  // 256 of 256 x 512, 1/4 kept 123 and 115), with x out of the cache 0.83..1.04.
+  // 203 layers drawn from all that the rule takes, lines below included: 0.51..1.01 of the time, 0.78 in the mean; with x out
+  // of the cache 0.49..1.03, 0.81.
   const int64_t mb = ((int64_t)d.B * d.C_out * ks * 4) >> 20, units = (int64_t)um.units * d.B;
   const bool whole_lines = (int64_t)d.W * (d.act_dtype == WCC_BF16 ? 2 : 4) % 128 == 0;
   const bool all_kept = ks * 10 >= (int64_t)d.H * d.W * 9;
