@@ -28,14 +28,16 @@ inline int64_t kept_count(const wcc_desc &d) {
 // 0.71..1.01, at a quarter and more than 24 MB 1.00..1.01, under 8 units (64x64 and smaller) 0.92..1.10.
 // At 4 levels the list takes a third workgroup off a compute unit (57 of 160 KiB of LDS), which only the shortest lists make
 // good: up to 1/8 kept 0.72..1.00 of the time, at 1/6 0.78..0.97 up to 4 MB but 4x96x96x320 (7.5 MB) 15.0 -> 17.4, at 1/5 and
-// above 0.93..1.16.  With the residual up to 1/4 0.72..0.97, then 0.98..1.21 (4x64x256x512 at 1/2 58.8 -> 71.2, at 1/3
-// 58.4 -> 67.0, all kept 68.8 -> 72.2).
+// above 0.93..1.16, but on planes of half a unit (1024 positions), whose lists are as short, 0.44..0.90 up to a third
+// (6x480x16x16 12.4 -> 10.8, 16x256x32x32 20.7 -> 9.3; a whole unit, 8x128x32x64, 11.5 -> 12.0).  With the residual up
+// to 1/4 0.72..0.97, then 0.98..1.21 (4x64x256x512 at 1/2 58.8 -> 71.2, at 1/3 58.4 -> 67.0, all kept 68.8 -> 72.2).
 inline bool shares_units(const wcc_desc &d, int units, bool residual) {
   if (d.levels < 3 || (residual && units < 8)) return false;
   const int64_t N = (int64_t)d.H * d.W, k = kept_count(d), kept = (int64_t)d.B * d.C_out * k * 4, MB = 1 << 20;
   if (d.levels == 4) {
     if (residual) return k * 4 <= N && kept <= 8 * MB;
-    return (k * 8 <= N && kept <= 8 * MB) || (k * 6 <= N + 5 && kept <= 4 * MB);
+    if (kept > 8 * MB) return false;
+    return k * 8 <= N || (k * 6 <= N + 5 && kept <= 4 * MB) || (k * 3 <= N + 2 && N <= 1024);
   }
   if (residual && k * 3 >= N) return true;
   const bool long_store = (int64_t)d.B * d.C_out * N > 40 * MB;  // y of more than 160 MB in fp32

@@ -43,6 +43,8 @@ FOUR_LEVELS = [
     (True, 1, 256, 128, 128, (1, 4), 8, True), (True, 4, 16, 256, 512, (1, 4), 64, True),
     (True, 4, 96, 128, 128, (1, 8), 8, False), (True, 2, 512, 64, 64, (1, 6), 2, False),
     (True, 1, 256, 256, 512, (1, 16), 64, False),
+    (True, 6, 480, 16, 16, (1, 3), 1, False), (True, 16, 256, 32, 32, (3, 10), 1, False),  # planes of half a unit
+    (False, 8, 128, 32, 64, (1, 4), 1, False),
 ]
 
 

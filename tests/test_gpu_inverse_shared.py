@@ -21,6 +21,7 @@ CASES = [
     (1, 64, 48, 1040, 4, (1, 5)),
     (2, 19, 64, 48, 4, (1, 6)),     # four levels share up to a sixth kept
     (1, 64, 48, 1040, 4, (1, 8)),   # strips of several units
+    (2, 17, 32, 32, 4, (1, 3)),     # half a unit, four levels
     (2, 18, 16, 16, 4, (1, 256)),   # one position kept, one unit mostly outside the plane
 ]
 
