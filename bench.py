@@ -23,8 +23,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
-# dense matrix-core peaks (published) by the contraction's operand type, TFLOP/s (TOP/s for int8);
-# fp32 weights or unquantised activations run on the vector ALUs (fp32 vector peak)
+# dense matrix-core peaks (published) by the contraction's operand type, TFLOP/s (TOP/s for int8); fp32 weights or
+# unquantised activations run on its fp32 instructions
 MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "int8": 5000.0, "f32": 157.3}
 CACHE_BYTES = 256 << 20  # memory-side cache
 
