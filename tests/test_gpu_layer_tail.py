@@ -8,7 +8,7 @@ import pytest
 import torch
 
 from paper_2205_12268_amd import synth, wcc
-from tests.util import dev, rel_l2, tol_for, upload_weights
+from tests.util import check_block_without_middle_outputs, dev, layer_with_index_set, rel_l2, tol_for, upload_weights
 
 pytestmark = pytest.mark.gpu
 
@@ -135,4 +135,61 @@ def test_in_the_static_scratch_memory(ref):
     want, o_idx, _ = ref.forward(x, w.values, w.scale, 3, 1, 4, act_bits=0)
     np.testing.assert_array_equal(idx.cpu().numpy().astype(np.int64), o_idx)
     assert rel_l2(y.cpu().numpy(), want) <= tol_for(cfg)
+    ctx.close()
+
+
+@pytest.mark.parametrize("maps", [wcc.F32, wcc.BF16])
+def test_expand_layer_of_a_block(ref, maps):
+    """Half kept, so that the block forms its middle tensor: the expand layer ends in the one kernel, the project layer in
+    the two.  bf16 maps round the middle tensor and y once each."""
+    cfg = synth.BlockCfg("tail_block", 8, 16, 6, 256, 256, 3, 1, 2, synth.W_BF16, 8, sigma=1.0, seed=synth.SEED_BASE + 0x15A0)
+    x, w1, w_dw, w3 = synth.make_block_inputs(cfg)
+    if maps == wcc.BF16:
+        x = synth.round_to_bf16(x)
+    t = torch.bfloat16 if maps == wcc.BF16 else torch.float32
+    d = wcc.make_block_desc(cfg.B, cfg.C, cfg.expansion, cfg.H, cfg.W, 3, 1, 2, cfg.w_dtype, 8, maps)
+    assert not wcc.block_is_chained(d)
+    ctx = wcc.Context(0)
+    ctx.ensure_workspace(d)
+    ctx.set_block_profile_layer(0)
+    ctx.set_profiling(True)
+    xd, (w1d, _), (w3d, _) = dev(x).to(t), upload_weights(w1), upload_weights(w3)
+    y, t1 = torch.full_like(xd, float("nan")), torch.empty((cfg.B, cfg.C_mid, cfg.H, cfg.W), dtype=t, device="cuda")
+    idx1, idx3 = (torch.empty((cfg.B, cfg.k), dtype=torch.int32, device="cuda") for _ in range(2))
+    ctx.wcc_block_forward(d, xd, w1d, None, dev(w_dw), w3d, None, y, t1, None, idx1, idx3)
+    assert ctx.stage_times()["pointwise"] == 0
+    want, o_idx, _ = ref.forward(x, w1.values, w1.scale, 3, 1, 2, act_bits=8)
+    np.testing.assert_array_equal(idx1.cpu().numpy().astype(np.int64), o_idx)
+    got_t1 = t1.float().cpu().numpy().astype(np.float64)
+    assert rel_l2(got_t1, want) <= 1e-2
+    branch, _ = layer_with_index_set(ref, cfg.layer(1), w3, ref.depthwise3x3(got_t1, w_dw),
+                                     idx3.cpu().numpy().astype(np.int64))
+    assert rel_l2(y.float().cpu().numpy(), x.astype(np.float64) + branch) <= 1e-2
+    ctx.close()
+
+
+def test_expand_layer_of_a_block_that_may_run_chained(ref):
+    """A quarter kept: the middle tensor that a caller asks for comes from the contraction that the chained call runs, so that
+    both calls give the same bits, although the layer by itself would take the one kernel."""
+    cfg = synth.BlockCfg("tail_chain", 8, 16, 8, 256, 256, 3, 1, 4, synth.W_BF16, 8, sigma=1.0, seed=synth.SEED_BASE + 0x15A1)
+    x, w1, w_dw, w3 = synth.make_block_inputs(cfg)
+    d = wcc.make_block_desc(cfg.B, cfg.C, cfg.expansion, cfg.H, cfg.W, 3, 1, 4, cfg.w_dtype, 8)
+    assert wcc.block_is_chained(d)
+    ctx = wcc.Context(0)
+    ctx.ensure_workspace(d)
+    ctx.set_block_profile_layer(0)
+    ctx.set_profiling(True)
+    xd, wdd, (w1d, _), (w3d, _) = dev(x), dev(w_dw), upload_weights(w1), upload_weights(w3)
+    y = torch.full_like(xd, float("nan"))
+    t1, t2 = (torch.empty((cfg.B, cfg.C_mid, cfg.H, cfg.W), device="cuda") for _ in range(2))
+    idx3 = torch.empty((cfg.B, cfg.k), dtype=torch.int32, device="cuda")
+    ctx.wcc_block_forward(d, xd, w1d, None, wdd, w3d, None, y, t1, t2, None, idx3)
+    assert ctx.stage_times()["pointwise"] > 0
+    ctx.set_profiling(False)
+    check_block_without_middle_outputs(ref, ctx, cfg, d, xd, x.astype(np.float64), w1d, None, wdd, w3d, None, w3,
+                                       t2.cpu().numpy(), y, idx3, 1e-2)
+    lone = wcc.make_desc(cfg.B, cfg.C, cfg.C_mid, cfg.H, cfg.W, 3, 1, 4, cfg.w_dtype, 8)
+    ctx.set_profiling(True)
+    ctx.wcc_forward(lone, xd, w1d, None, 0.0, t2)
+    assert ctx.stage_times()["pointwise"] == 0 and rel_l2(t2.cpu().numpy(), t1.double().cpu().numpy()) <= 1e-6
     ctx.close()
