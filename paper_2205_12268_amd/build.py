@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(CSRC, "libwcc.so")
 PROBE_LIB = os.path.join(CSRC, "libwcc_probe.so")
-SOURCES = ["haar_fwd.hip", "haar_keep.hip", "haar_inv.hip", "layer_tail.hip", "select.hip", "gather.hip", "pointwise.hip",
+SOURCES = ["haar_fwd.hip", "haar_keep.hip", "haar_inv.hip", "layer_tail.hip", "select.hip", "select_two.hip", "gather.hip", "pointwise.hip",
            "depthwise.hip", "haar_chain.hip", "wcc_api.hip"]
 PROBE_SOURCES = ["stream_probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE,

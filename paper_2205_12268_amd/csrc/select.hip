@@ -17,7 +17,8 @@
 // never from the arrival order of atomics, so the result is the same on every run.
 // The first pass can take the channel-group partial norms of the forward transform and
 // reduce them on the fly (fixed order), writing the final norms as a by-product.
-#include "wcc_internal.h"
+// Planes of middling size take the two launches of select_two.hip instead (the rule is in ws_layout).
+#include "select_dev.h"
 
 namespace wcc {
 namespace {
@@ -35,161 +36,8 @@ __device__ __forceinline__ bool matches(uint32_t key, uint32_t prefix, int pass)
   return pass == 0 ? true : pass == 1 ? (key >> 21) == (prefix >> 21) : (key >> 10) == (prefix >> 10);
 }
 
-// lh[digit] += 1 for every valid lane; lanes of a wave that share a digit are counted by one
-// LDS atomic (two leader rounds catch the big tie classes, the rest goes lane by lane)
-__device__ __forceinline__ void hist_add(uint32_t *lh, uint32_t digit, bool valid) {
-  const int lane = threadIdx.x & 63;
-  uint64_t todo = __ballot(valid);
-#pragma unroll
-  for (int round = 0; round < 2; ++round) {
-    if (todo == 0) break;
-    const int leader = __ffsll((unsigned long long)todo) - 1;
-    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)digit, leader);  // leader is wave-uniform
-    const uint64_t same = __ballot(valid && digit == d0);
-    if (lane == leader) atomicAdd(&lh[d0], (uint32_t)__popcll(same));
-    if (digit == d0) valid = false;
-    todo &= ~same;
-  }
-  if (valid) atomicAdd(&lh[digit], 1u);
-}
-
-// The same for a workgroup whose digits are spread out: one round, the class of the first
-// valid lane is counted by one atomic, every other lane adds for itself.
-__device__ __forceinline__ void hist_add_spread(uint32_t *lh, uint32_t digit, bool valid) {
-  if (valid) {
-    const uint32_t d0 = __builtin_amdgcn_readfirstlane(digit);
-    const uint64_t same = __ballot(digit == d0);
-    const int first = __ffsll((unsigned long long)same) - 1;
-    const uint32_t val = digit != d0 ? 1u : ((int)(threadIdx.x & 63) == first ? (uint32_t)__popcll(same) : 0u);
-    if (val) atomicAdd(&lh[digit], val);
-  }
-}
-
-// Inclusive prefix sum over the 64 lanes of a wave (all of them active), on the data-parallel
-// shifts of the vector unit instead of six round trips through the LDS crossbar: shifts by
-// 1, 2, 4, 8 inside rows of 16 lanes (a lane shifted in from outside its row adds 0), then lane
-// 15 of rows 0 and 2 into rows 1 and 3, then lane 31 into rows 2 and 3.
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
-  uint32_t v = x;
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-  return v;
-}
-
-// Smallest / largest value over the 64 lanes (all active), every lane gets it: the moves of the
-// scan with the operation's identity shifted in; lane 63 ends up with the whole wave's result.
-template <bool MAX>
-__device__ __forceinline__ uint32_t wave_extreme(uint32_t x) {
-  constexpr int id = MAX ? 0 : -1;
-  uint32_t v = x;
-  auto join = [](uint32_t a, uint32_t b) { return MAX ? max(a, b) : min(a, b); };
-  v = join(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x111, 0xf, 0xf, false));
-  v = join(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x112, 0xf, 0xf, false));
-  v = join(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x114, 0xf, 0xf, false));
-  v = join(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x118, 0xf, 0xf, false));
-  v = join(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x142, 0xa, 0xf, false));
-  v = join(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x143, 0xc, 0xf, false));
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-// block-wide sum of v (all threads get it); `tmp` has NW (waves per workgroup) entries
-template <int NW = kWaves>
-__device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t *tmp) {
-  v = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(v), 63);
-  __syncthreads();  // tmp may still be read from a previous use
-  if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = v;
-  __syncthreads();
-  uint32_t s = 0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) s += tmp[i];
-  return s;
-}
-
-// block-wide exclusive scan in thread order; `tmp` has NW (waves per workgroup) entries
-template <int NW = kWaves>
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *tmp) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint32_t inc = wave_inclusive_scan(v);
-  __syncthreads();
-  if (lane == 63) tmp[wv] = inc;
-  __syncthreads();
-  uint32_t before = 0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i)
-    if (i < wv) before += tmp[i];
-  return before + inc - v;
-}
-
 __global__ __launch_bounds__(256) void select_init_kernel(SelectPrep p, int B) {
   if ((int)blockIdx.x < B) prep_sample(p, blockIdx.x, threadIdx.x, blockDim.x);
-}
-
-// Four keys of this thread.  REDUCE: keys are sums of G partial-norm planes (added in
-// increasing group order), and the sums are written to norm.
-template <bool REDUCE>
-__device__ __forceinline__ uint4 load_keys(const float *__restrict__ src, float *__restrict__ norm,
-                                           int G, int64_t BN, int64_t at) {
-  float4 v = *reinterpret_cast<const float4 *>(src + at);
-  if constexpr (REDUCE) {
-    int g = 1;
-    for (; g + 4 <= G; g += 4) {  // four loads in flight, added in increasing group order
-      float4 t[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) t[i] = *reinterpret_cast<const float4 *>(src + (int64_t)(g + i) * BN + at);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { v.x += t[i].x; v.y += t[i].y; v.z += t[i].z; v.w += t[i].w; }
-    }
-    for (; g < G; ++g) {
-      const float4 t = *reinterpret_cast<const float4 *>(src + (int64_t)g * BN + at);
-      v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
-    }
-    *reinterpret_cast<float4 *>(norm + at) = v;
-  }
-  return make_uint4(__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z),
-                    __float_as_uint(v.w));
-}
-
-// max over the G channel groups of their largest |coefficient| at this thread's four positions
-// (top_part [G, B, N], written by the norm-only transform pass)
-__device__ __forceinline__ float4 load_top(const float *__restrict__ top_part, int G, int64_t BN,
-                                           int64_t at) {
-  float4 m = *reinterpret_cast<const float4 *>(top_part + at);
-  int g = 1;
-  for (; g + 4 <= G; g += 4) {  // four loads in flight
-    float4 t[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) t[i] = *reinterpret_cast<const float4 *>(top_part + (int64_t)(g + i) * BN + at);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      m.x = fmaxf(m.x, t[i].x); m.y = fmaxf(m.y, t[i].y); m.z = fmaxf(m.z, t[i].z); m.w = fmaxf(m.w, t[i].w);
-    }
-  }
-  for (; g < G; ++g) {
-    const float4 t = *reinterpret_cast<const float4 *>(top_part + (int64_t)g * BN + at);
-    m.x = fmaxf(m.x, t.x); m.y = fmaxf(m.y, t.y); m.z = fmaxf(m.z, t.z); m.w = fmaxf(m.w, t.w);
-  }
-  return m;
-}
-
-// block_top[slot] = the workgroup's largest kept |coefficient| (v >= 0 in every thread, all
-// threads of the workgroup call; `tmp` has NW entries).  A plain store per workgroup: the
-// consumers take the maximum over all of them.
-template <int NW>
-__device__ __forceinline__ void publish_top(float v, float *block_top, size_t slot, uint32_t *tmp) {
-  const uint32_t w = wave_extreme<true>(__float_as_uint(v));  // (>= 0: floats order like their bits)
-  __syncthreads();  // tmp may still be read from a previous use
-  if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = w;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t mine = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) mine = max(mine, tmp[i]);
-    block_top[slot] = __uint_as_float(mine);
-  }
 }
 
 // Turns the finished histogram of pass P into the digit that holds the remaining rank:
@@ -244,20 +92,6 @@ __device__ __forceinline__ void current_state(const uint32_t *hist_b, SelectStat
     s->remain[UPTO - 1] = remain;
   }
 }
-
-// A job of moving 16-byte pieces done beside a kernel that is bound by its own latencies: the first
-// piece's load goes out early, its store and the few pieces after it follow at the end.
-struct PackOnTheSide {
-  uint4 v;
-  int e;
-  __device__ __forceinline__ PackOnTheSide(const PackJob &job, int first) : v(make_uint4(0, 0, 0, 0)), e(first) {
-    if (e < job.total) v = pack_piece(job, e);
-  }
-  __device__ __forceinline__ void finish(const PackJob &job, int threads) const {
-    if (e < job.total) job.out[e] = v;
-    for (int i = e + threads; i < job.total; i += threads) job.out[i] = pack_piece(job, i);
-  }
-};
 
 // One histogram pass.  grid = (nblk, B), block = 256.
 // PASS 0 with REDUCE reads partial norms `src` [G, B, N] and writes `norm`; otherwise src is
@@ -323,14 +157,14 @@ __global__ __launch_bounds__(kThreads) void select_hist_kernel(const float *__re
       c[i] = lh[bins - 1 - (t * per + i)];
       sum += c[i];
     }
-    uint32_t run = block_exclusive_scan(sum, tmp);
+    uint32_t run = block_exclusive_scan<kWaves>(sum, tmp);
     const size_t blk = (size_t)b * nblk + blockIdx.x;
 #pragma unroll
     for (int i = 0; i < per; ++i) {
       run += c[i];
       block_sfx[blk * kSfxStride + (bins - 1 - (t * per + i))] = (uint16_t)run;
     }
-    const uint32_t tot_above = block_sum(above, tmp);
+    const uint32_t tot_above = block_sum<kWaves>(above, tmp);
     if (t == 0) block_gthi[blk] = tot_above;
   }
 }
@@ -383,8 +217,8 @@ __global__ __launch_bounds__(kThreads) void select_emit_kernel(const float *__re
     gt0 += block_gthi[blk] + gtl;
     eq0 += ge - gtl;
   }
-  gt0 = block_sum(gt0, tmp);
-  eq0 = block_sum(eq0, tmp);
+  gt0 = block_sum<kWaves>(gt0, tmp);
+  eq0 = block_sum<kWaves>(eq0, tmp);
 
   // Position order inside the workgroup's chunk is slot by slot, thread by thread: one block
   // scan a slot, on top of the totals of the slots before it.  Counts are packed
@@ -400,7 +234,7 @@ __global__ __launch_bounds__(kThreads) void select_emit_kernel(const float *__re
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (in) packed += ((key[e] > T) << 16) + (key[e] == T);
-    const uint32_t ex = block_exclusive_scan(packed, tmp);
+    const uint32_t ex = block_exclusive_scan<kWaves>(packed, tmp);
     uint32_t gt = gt0 + (ex >> 16), eq = eq0 + (ex & 0xFFFFu);
     if (SLOTS > 1) {  // the slot's totals (tmp holds the waves' inclusive sums until the next scan)
       uint32_t tot = 0;
@@ -450,7 +284,7 @@ constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / 64;
 constexpr int kSmallSlots = 4;  // 16-byte loads per thread at most (beyond that the one
                                 // workgroup is slower than the spread-out kernels)
-constexpr int64_t kSmallMaxN = (int64_t)4 * kSmallSlots * kSmallThreads;
+static_assert(kSmallMaxN == (int64_t)4 * kSmallSlots * kSmallThreads, "one workgroup's keys");
 constexpr int kSmallBits = 13;  // bits of a field
 constexpr int kSmallBins = 1 << kSmallBits;
 constexpr uint32_t kSmallList = 512;
@@ -738,6 +572,9 @@ hipError_t launch_jmap_prefix(int B, int64_t N, int64_t k, int32_t *jmap, int32_
   return hipGetLastError();
 }
 
+// Whether the selection merges histograms (select_hist_kernel), which have to be clear before it.
+bool select_counts(const WsLayout &L) { return !L.one_wg && L.two_nblk == 0; }
+
 SelectPrep make_prep(void *ws_base, const WsLayout &L, float *alpha_slots, float alpha_in) {
   char *ws = static_cast<char *>(ws_base);
   SelectPrep p;
@@ -749,14 +586,15 @@ SelectPrep make_prep(void *ws_base, const WsLayout &L, float *alpha_slots, float
 
 // how many partial maxima launch_select leaves in block_top: one per workgroup of its last kernel
 int select_top_count(const wcc_desc &d, const WsLayout &L) {
-  return (int64_t)d.H * d.W <= kSmallMaxN ? d.B : d.B * L.nblk;
+  return L.one_wg ? d.B : d.B * (L.two_nblk > 0 ? L.two_nblk : L.nblk);
 }
 
 // Up to four pieces a thread of the first kernel: 16 KiB of weights a 256-thread workgroup.  A layer of
 // few select workgroups and many weights is better off with a launch over the whole chip (4 us).
 bool select_packs(const wcc_desc &d, const WsLayout &L, const PackJob &job) {
-  const int64_t threads = (int64_t)d.H * d.W <= kSmallMaxN ? (int64_t)d.B * kSmallThreads
-                                                           : (int64_t)d.B * L.nblk * kThreads;
+  const int64_t threads = L.one_wg          ? (int64_t)d.B * kSmallThreads
+                          : L.two_nblk > 0 ? (int64_t)d.B * L.two_nblk * 1024
+                                           : (int64_t)d.B * L.nblk * kThreads;
   return job.total > 0 && job.total <= 4 * threads;
 }
 
@@ -805,7 +643,7 @@ hipError_t launch_select(const wcc_desc &d, const float *norm_or_part, int G, fl
   uint32_t *gthi = reinterpret_cast<uint32_t *>(ws + L.block_gthi);
   const int nblk = L.nblk;
   const uint32_t k32 = (uint32_t)k;
-  if (N <= kSmallMaxN) {
+  if (L.one_wg) {
     const float *src = norm_or_part;
     int planes = G;
     if (G > 1 && (int64_t)G * N * (top_part ? 2 : 1) >= kCombineValues) {
@@ -829,6 +667,9 @@ hipError_t launch_select(const wcc_desc &d, const float *norm_or_part, int G, fl
 #undef WCC_SMALL
     return hipGetLastError();
   }
+  if (L.two_nblk > 0)
+    return launch_select_two(d, norm_or_part, G, norm_out, k, ws + L.two_tables,
+                             reinterpret_cast<uint32_t *>(ws + L.norm_part), L.two_slots, L.two_nblk, idx, jmap, top_part, block_top, job, s);
   switch (L.sel_slots) {
     case 4: return launch_passes<4>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, job, s);
     case 2: return launch_passes<2>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, job, s);

@@ -104,6 +104,15 @@ wcc_status need_ws(const wcc_ctx *ctx, const WsLayout &L) {
 // get slower again: measured at 256 and 480 workgroups)
 constexpr size_t kSelectMinBlocks = 512;
 
+// Two-launch selection: workgroups at most, one a compute unit, in chunks as small as that allows.  With two a unit
+// 4 x 512 x 1024 positions take 30 us in chunks of 4096 and 23 in chunks of 8192 (30 in the four launches); beyond the
+// largest chunk the four launches are quicker (16 x 512 x 1024 positions: 62 us, 63 in two launches; 16 x 1024 x 1024 110
+// and 122, 256 x 256 x 256 113 and 106).
+constexpr size_t kSelectTwoWorkgroups = 256;
+// ... and positions a sample at most: from there on the keys of one digit begin to leave LDS (1024 x 1024: 22.7 us, 30 in
+// four launches; 1024 x 2048: 42 and 38.5).
+constexpr size_t kSelectTwoMaxN = 1 << 20;
+
 WsLayout ws_layout(const wcc_desc &d, int front, bool pad) {
   WsLayout L{};
   const size_t N = (size_t)d.H * d.W, B = d.B, k = (size_t)kept_count(d);
@@ -134,8 +143,23 @@ WsLayout ws_layout(const wcc_desc &d, int front, bool pad) {
   L.scratch = take(kInvScratchBytes);
   L.xc32 = take(B * (size_t)d.C_in * L.ks * 4);
   L.yc = take(B * (size_t)d.C_out * L.ks * 4);
+  const size_t yc_end = off;
   L.w8 = take(d.w_dtype == WCC_I4 ? (size_t)d.C_out * d.C_in : 0);
   L.total = off;
+  // The selection: one workgroup a sample on small planes, else two launches on planes of middling size where its tables
+  // have room, in the memory of the histograms or of Y_wt.
+  L.one_wg = (int64_t)N <= kSmallMaxN;
+  for (int sl = 1; sl <= 4 && !L.one_wg && N <= kSelectTwoMaxN; sl *= 2) {
+    const size_t chunk = (size_t)select_two_chunk(sl), chunks = (N + chunk - 1) / chunk;
+    if (chunks * B > kSelectTwoWorkgroups) continue;
+    const size_t bytes = select_two_bytes(d.B, (int)chunks);
+    const bool at_hist = bytes <= L.jmap - L.hist;
+    if (!at_hist && bytes > yc_end - L.yc) continue;
+    L.two_nblk = (int)chunks;
+    L.two_slots = sl;
+    L.two_tables = at_hist ? L.hist : L.yc;
+    break;
+  }
   // (a layer that fits the static scratch array only without the padding goes without it)
   if (pad && L.total > (size_t)WCC_STATIC_SCRATCH_BYTES) {
     const WsLayout bare = ws_layout(d, front, false);
@@ -499,7 +523,7 @@ wcc_status wcc_joint_topk(wcc_ctx *ctx, const wcc_desc *desc, const float *coef,
     norm = nw;
   }
   const int64_t k = kept_count(*desc);
-  WCC_TRY(launch_select_init(make_prep(ws, L, nullptr, 0.f), desc->B, s));
+  if (select_counts(L)) WCC_TRY(launch_select_init(make_prep(ws, L, nullptr, 0.f), desc->B, s));
   WCC_TRY(launch_select(*desc, norm, 1, nullptr, k, ws, L, idx, nullptr, nullptr, nullptr,
                         PackJob{nullptr, nullptr, 0, 0, 0, 0, 0}, s));
   return WCC_OK;

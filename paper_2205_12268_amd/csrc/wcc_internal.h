@@ -16,6 +16,8 @@ constexpr int kMaxLevels = 4;      // register-resident strip transform up to 16
 constexpr int kRadixBins = 2048;   // 11 + 11 + 10 bit radix select
 constexpr int kSelectChunk = 1024; // keys a select workgroup takes with one 16-byte load a thread
 constexpr int kSfxStride = 1024;   // per-workgroup suffix sums of the low-digit histogram
+constexpr int64_t kSmallMaxN = 16384;    // positions up to which one workgroup selects a sample's (select.hip)
+constexpr int kSelectTwoBlocks = 256;    // chunks a sample at most in the two-launch selection (select_two.hip)
 constexpr int kAlphaSlots = 64;    // max|kept c| is reduced into this many slots, then combined
 constexpr int kInvScratchBytes = 1024;  // one 16-byte line per lane for stores that must go nowhere
 
@@ -50,6 +52,10 @@ struct WsLayout {
   int G;              // channel groups of the forward transform
   int nblk;           // select workgroups per sample
   int sel_slots;      // 16-byte loads per thread in the select kernels: 1, 2 or 4
+  bool one_wg;        // one workgroup selects a sample's positions
+  int two_nblk;       // chunks per sample of the two-launch selection; 0: not taken
+  int two_slots;      // 16-byte loads per thread there: 1, 2 or 4
+  size_t two_tables;  // its tables: in the memory of the histograms, or of yc
 };
 
 struct SelectState {
@@ -270,6 +276,14 @@ hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const i
 hipError_t launch_norm_reduce(const float *norm_part, const StorePlan &sp, int64_t BN, float *norm, hipStream_t s);
 hipError_t launch_channel_norm(const float *coef, int B, int C, int64_t N, bool squares, float *norm,
                                hipStream_t s);
+// Selection in two launches (select_two.hip): bytes of its tables, positions a chunk (slots: 16-byte loads a
+// thread).  grouped: [B, N] words of scratch memory, may be plane 0 of norm_or_part where G > 1.
+size_t select_two_bytes(int B, int nblk);
+int select_two_chunk(int slots);
+hipError_t launch_select_two(const wcc_desc &d, const float *norm_or_part, int G, float *norm_out, int64_t k,
+                             void *tables, uint32_t *grouped, int slots, int nblk, int32_t *idx, int32_t *jmap,
+                             const float *top_part, float *block_top, const PackJob &job, hipStream_t s);
+bool select_counts(const WsLayout &L);
 SelectPrep make_prep(void *ws_base, const WsLayout &L, float *alpha_slots, float alpha_in);
 hipError_t launch_select_init(const SelectPrep &p, int B, hipStream_t s);
 // G > 1: norm_or_part is [G, B, N] partial norms, reduced into norm_out on the fly;
