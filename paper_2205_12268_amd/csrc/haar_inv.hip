@@ -108,6 +108,7 @@ __device__ __forceinline__ void inv_staged_walk(const float *__restrict__ plane,
 }
 
 // yc [B, C, k] + jmap [B, N] -> y [B, C, H, W].  grid = (ceil(units/4), G, B), block = 256.
+// jmap null: the first `prefix` positions are kept, each its own rank.
 // scratch: unused (kept for the launcher's signature).  RES: y = residual + (the above),
 // residual [B, C, H, W] (the skip connection of Eq. (inverted)); it may be y itself.
 // YT: float or bf16_t, the storage type of y and of the residual.
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
                                                             const int32_t *__restrict__ jmap,
                                                             YT *y, Geo g, StripMap m, int C,
                                                             int G, int64_t k, float *scratch,
-                                                            const YT *residual) {
+                                                            const YT *residual, int64_t prefix) {
   constexpr int R = 1 << D;
   constexpr int NS = slot_count(D, V);
   constexpr bool kStaged = D <= 3 || V == 2;  // the [lane][slot] tiles of four waves fit in LDS
@@ -148,7 +149,6 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
   if (!SHARE && (__ballot(active) == 0 || n_ch <= 0)) return;  // whole waves leave
   const int64_t kstep = (int64_t)G * k, nstep = (int64_t)G * g.N;
 
-  const int32_t *jm = jmap + (size_t)b * g.N;
   const float *plane = yc + ((size_t)b * C + c0) * k;
   const size_t first = ((size_t)b * C + c0) * g.N + (size_t)row0 * g.W + col0;
   YT *dst = y + first;
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
   src.any[0] = src.any[1] = 0;
   int count = 0;  // kept positions of this wave's strip (wave-uniform)
   // slots [FIRST, LAST)
-  auto fetch_slots = [&](auto first_c, auto last_c) {
+  auto fetch_slots_of = [&](auto first_c, auto last_c, auto &&rank_of) {
     constexpr int FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
     auto fetch = [&](auto Lc, auto Jc) {
       constexpr int L = decltype(Lc)::value, J = decltype(Jc)::value;
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
           const int s = base + i * CV + e;
           if (s < FIRST || s >= LAST) continue;
           int j = -1;
-          if (active) j = jm[J * p.nl[L] + p.off[L] + i * p.rowlen[L] + e];
+          if (active) j = rank_of(J * p.nl[L] + p.off[L] + i * p.rowlen[L] + e);
           src.jj[s] = j;
         }
     };
@@ -186,6 +186,15 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
     if constexpr (D >= 2) each_level(std::integral_constant<int, 2>{});
     if constexpr (D >= 3) each_level(std::integral_constant<int, 3>{});
     if constexpr (D >= 4) each_level(std::integral_constant<int, 4>{});
+  };
+  auto fetch_slots = [&](auto first_c, auto last_c) {
+    if (jmap != nullptr) {  // (uniform over the grid)
+      const int32_t *jm = jmap + (size_t)b * g.N;
+      fetch_slots_of(first_c, last_c, [&](int at) { return jm[at]; });
+    } else {
+      const int first = (int)prefix;
+      fetch_slots_of(first_c, last_c, [&](int at) { return at < first ? at : -1; });
+    }
   };
   // puts the list entries of slots [FIRST, LAST) from `at` on down: rank, cell, slot-major, then lane
   auto pack_slots = [&](auto first_c, auto last_c, uint32_t *list, int at0) {
@@ -324,7 +333,7 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
 
 template <int D, int V>
 hipError_t inv_launch(const wcc_desc &d, int64_t k, const float *yc, const int32_t *jmap, void *y,
-                      int G, float *scratch, const void *residual, hipStream_t s) {
+                      int G, float *scratch, const void *residual, int64_t prefix, hipStream_t s) {
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
   const StripMap m = make_flat_map(d, V);
   const bool share = G >= 4 && shares_units(d, m.units, residual != nullptr);
@@ -333,7 +342,7 @@ hipError_t inv_launch(const wcc_desc &d, int64_t k, const float *yc, const int32
 #define WCC_INV_T(RES, YT, SHARE)                                                                 \
   hipLaunchKernelGGL((scatter_ihaar_kernel<D, V, RES, YT, SHARE && kShares>), grid, dim3(256), 0, s, yc, jmap, \
                      static_cast<YT *>(y), g, m, d.C_out, G, k, scratch,                          \
-                     static_cast<const YT *>(residual))
+                     static_cast<const YT *>(residual), prefix)
 #define WCC_INV(RES, YT) do { if (share) WCC_INV_T(RES, YT, true); else WCC_INV_T(RES, YT, false); } while (0)
   if (d.act_dtype == WCC_BF16) { if (residual) WCC_INV(true, bf16_t); else WCC_INV(false, bf16_t); }
   else                         { if (residual) WCC_INV(true, float); else WCC_INV(false, float); }
@@ -345,23 +354,23 @@ hipError_t inv_launch(const wcc_desc &d, int64_t k, const float *yc, const int32
 }  // namespace
 
 hipError_t inv_dispatch(const wcc_desc &d, int64_t k, const float *yc, const int32_t *jmap, void *y,
-                        int G, float *scratch, const void *residual, hipStream_t s) {
+                        int G, float *scratch, const void *residual, int64_t prefix, hipStream_t s) {
   const bool v4 = lane_cols(d) == 4;
   switch (d.levels) {
-    case 1: return v4 ? inv_launch<1, 4>(d, k, yc, jmap, y, G, scratch, residual, s)
-                      : inv_launch<1, 2>(d, k, yc, jmap, y, G, scratch, residual, s);
-    case 2: return inv_launch<2, 4>(d, k, yc, jmap, y, G, scratch, residual, s);
-    case 3: return inv_launch<3, 4>(d, k, yc, jmap, y, G, scratch, residual, s);
-    case 4: return inv_launch<4, 2>(d, k, yc, jmap, y, G, scratch, residual, s);
+    case 1: return v4 ? inv_launch<1, 4>(d, k, yc, jmap, y, G, scratch, residual, prefix, s)
+                      : inv_launch<1, 2>(d, k, yc, jmap, y, G, scratch, residual, prefix, s);
+    case 2: return inv_launch<2, 4>(d, k, yc, jmap, y, G, scratch, residual, prefix, s);
+    case 3: return inv_launch<3, 4>(d, k, yc, jmap, y, G, scratch, residual, prefix, s);
+    case 4: return inv_launch<4, 2>(d, k, yc, jmap, y, G, scratch, residual, prefix, s);
   }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_scatter_ihaar(const wcc_desc &d, int64_t k, const float *yc, const int32_t *jmap,
-                                void *y, float *scratch, const void *residual, hipStream_t s) {
+                                void *y, float *scratch, const void *residual, int64_t prefix, hipStream_t s) {
   // (128 x 128, 1024 channels, 16 samples: 336 us with 4096 waves, 320 with 8192; two channels a wave at
   // d <= 2 only, as in the keep pass)
-  return inv_dispatch(d, k, yc, jmap, y, groups_for(d, make_flat_map(d, lane_cols(d)), d.C_out, 8192, d.levels <= 2 ? 2 : 4), scratch, residual, s);
+  return inv_dispatch(d, k, yc, jmap, y, groups_for(d, make_flat_map(d, lane_cols(d)), d.C_out, 8192, d.levels <= 2 ? 2 : 4), scratch, residual, prefix, s);
 }
 
 }  // namespace wcc

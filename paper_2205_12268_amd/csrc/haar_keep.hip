@@ -10,6 +10,7 @@ namespace {
 // n_alpha entries (what the selection found as max |kept coefficient|); alpha_slots and wg_max must
 // be null then.  Otherwise the workgroup's max |kept coefficient| goes to wg_max[its number] (a plain
 // store, combined by the consumer) or raises one of the alpha slots (both nullable).
+// jmap null: the first `prefix` positions are kept, each its own rank.
 template <int D, int V, int PF, int DWM, bool Q8, class XT, bool NT = false>
 __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x,
                                                         const int32_t *__restrict__ jmap,
@@ -18,7 +19,7 @@ __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x
                                                         int64_t k, const float *__restrict__ wdw,
                                                         float q_alpha,
                                                         const float *__restrict__ alpha_src,
-                                                        int n_alpha, float *alpha_pub) {
+                                                        int n_alpha, float *alpha_pub, int64_t prefix) {
   __shared__ float wmax[4];
   const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int grp = blockIdx.y;
@@ -36,33 +37,41 @@ __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x
 
   using Sink = KeepSink<D, V, Q8>;
   Sink sink(0.f);
-  const int32_t *jm = jmap + (size_t)b * g.N;
-  auto fetch = [&](auto Lc, auto Jc) {
-    constexpr int L = decltype(Lc)::value, J = decltype(Jc)::value;
-    constexpr int CV = cols_at(V, L), S2 = span_at(V, L);
-    const bool owner = (S2 == 1) || ((p.lc & (S2 - 1)) == 0);
+  auto ranks = [&](auto &&rank_of) {
+    auto fetch = [&](auto Lc, auto Jc) {
+      constexpr int L = decltype(Lc)::value, J = decltype(Jc)::value;
+      constexpr int CV = cols_at(V, L), S2 = span_at(V, L);
+      const bool owner = (S2 == 1) || ((p.lc & (S2 - 1)) == 0);
 #pragma unroll
-    for (int i = 0; i < rows_at(D, L); ++i)
+      for (int i = 0; i < rows_at(D, L); ++i)
 #pragma unroll
-      for (int e = 0; e < CV; ++e) {
-        constexpr int base = slot_base(D, V, L, J);
-        const int s = base + i * CV + e;
-        int j = -1;
-        if (active && owner) j = jm[J * p.nl[L] + p.off[L] + i * p.rowlen[L] + e];
-        sink.at[s] = (uint32_t)j;  // (turned into a byte offset below, once all loads are out)
-      }
+        for (int e = 0; e < CV; ++e) {
+          constexpr int base = slot_base(D, V, L, J);
+          const int s = base + i * CV + e;
+          int j = -1;
+          if (active && owner) j = rank_of(J * p.nl[L] + p.off[L] + i * p.rowlen[L] + e);
+          sink.at[s] = (uint32_t)j;  // (turned into a byte offset below, once all loads are out)
+        }
+    };
+    auto each_level = [&](auto Lc) {
+      constexpr int L = decltype(Lc)::value;
+      fetch(Lc, std::integral_constant<int, 1>{});
+      fetch(Lc, std::integral_constant<int, 2>{});
+      fetch(Lc, std::integral_constant<int, 3>{});
+      if constexpr (L == D) fetch(Lc, std::integral_constant<int, 0>{});
+    };
+    each_level(std::integral_constant<int, 1>{});
+    if constexpr (D >= 2) each_level(std::integral_constant<int, 2>{});
+    if constexpr (D >= 3) each_level(std::integral_constant<int, 3>{});
+    if constexpr (D >= 4) each_level(std::integral_constant<int, 4>{});
   };
-  auto each_level = [&](auto Lc) {
-    constexpr int L = decltype(Lc)::value;
-    fetch(Lc, std::integral_constant<int, 1>{});
-    fetch(Lc, std::integral_constant<int, 2>{});
-    fetch(Lc, std::integral_constant<int, 3>{});
-    if constexpr (L == D) fetch(Lc, std::integral_constant<int, 0>{});
-  };
-  each_level(std::integral_constant<int, 1>{});
-  if constexpr (D >= 2) each_level(std::integral_constant<int, 2>{});
-  if constexpr (D >= 3) each_level(std::integral_constant<int, 3>{});
-  if constexpr (D >= 4) each_level(std::integral_constant<int, 4>{});
+  if (jmap != nullptr) {  // (uniform over the grid)
+    const int32_t *jm = jmap + (size_t)b * g.N;
+    ranks([&](int at) { return jm[at]; });
+  } else {
+    const int first = (int)prefix;
+    ranks([&](int at) { return at < first ? at : -1; });
+  }
   if constexpr (Q8) {
     // The clipping parameter the selection found: the largest of its workgroups' maxima.  Taken
     // here, behind the rank loads, so that the two round trips to memory overlap.  The first
@@ -470,7 +479,7 @@ int keep_groups(const wcc_desc &d, bool folded, bool late) {
 template <int D, int V, class XT>
 hipError_t keep_launch_t(const wcc_desc &d, int64_t k, const XT *x, const int32_t *jmap, void *xc,
                          float *alpha_slots, float *wg_max, Plan pl, const float *wdw, float q_alpha,
-                         const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
+                         const float *alpha_src, int n_alpha, float *alpha_pub, int64_t prefix, hipStream_t s) {
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
   const StripMap m = keep_map(d, wdw != nullptr);
   const int Cg = (d.C_in + pl.G - 1) / pl.G;
@@ -485,10 +494,10 @@ hipError_t keep_launch_t(const wcc_desc &d, int64_t k, const XT *x, const int32_
   do {                                                                                             \
     if (q8)                                                                                        \
       hipLaunchKernelGGL((haar_keep_kernel<D, V, PF, DWM, true, XT>), grid, dim3(256), 0, s, x,   \
-                         jmap, xc, nullptr, nullptr, g, m, d.C_in, Cg, cstep, k, wdw, q_alpha, alpha_src, n_alpha, alpha_pub);                    \
+                         jmap, xc, nullptr, nullptr, g, m, d.C_in, Cg, cstep, k, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix);                    \
     else                                                                                           \
       hipLaunchKernelGGL((haar_keep_kernel<D, V, PF, DWM, false, XT>), grid, dim3(256), 0, s, x,  \
-                         jmap, xc, alpha_slots, wg_max, g, m, d.C_in, Cg, cstep, k, wdw, 0.f, nullptr, 0, nullptr);                    \
+                         jmap, xc, alpha_slots, wg_max, g, m, d.C_in, Cg, cstep, k, wdw, 0.f, nullptr, 0, nullptr, prefix);                    \
   } while (0)
   if constexpr (V == 4 || D == 4) {
     if (wdw != nullptr) {  // K_dw in front of the transform
@@ -500,10 +509,10 @@ hipError_t keep_launch_t(const wcc_desc &d, int64_t k, const XT *x, const int32_
   if (pl.stream) {
     if (q8)
       hipLaunchKernelGGL((haar_keep_kernel<D, V, 1, 0, true, XT, true>), grid, dim3(256), 0, s, x,
-                         jmap, xc, nullptr, nullptr, g, m, d.C_in, Cg, cstep, k, wdw, q_alpha, alpha_src, n_alpha, alpha_pub);
+                         jmap, xc, nullptr, nullptr, g, m, d.C_in, Cg, cstep, k, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix);
     else
       hipLaunchKernelGGL((haar_keep_kernel<D, V, 1, 0, false, XT, true>), grid, dim3(256), 0, s, x,
-                         jmap, xc, alpha_slots, wg_max, g, m, d.C_in, Cg, cstep, k, wdw, 0.f, nullptr, 0, nullptr);
+                         jmap, xc, alpha_slots, wg_max, g, m, d.C_in, Cg, cstep, k, wdw, 0.f, nullptr, 0, nullptr, prefix);
     return hipGetLastError();
   }
   WCC_KEEP(1, 0);
@@ -514,24 +523,24 @@ hipError_t keep_launch_t(const wcc_desc &d, int64_t k, const XT *x, const int32_
 template <int D, int V>
 hipError_t keep_launch(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap, void *xc,
                        float *alpha_slots, float *wg_max, Plan pl, const float *wdw, float q_alpha,
-                       const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
+                       const float *alpha_src, int n_alpha, float *alpha_pub, int64_t prefix, hipStream_t s) {
   if (d.act_dtype == WCC_BF16)
-    return keep_launch_t<D, V>(d, k, static_cast<const bf16_t *>(x), jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
-  return keep_launch_t<D, V>(d, k, static_cast<const float *>(x), jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+    return keep_launch_t<D, V>(d, k, static_cast<const bf16_t *>(x), jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s);
+  return keep_launch_t<D, V>(d, k, static_cast<const float *>(x), jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s);
 }
 
 }  // namespace
 
 hipError_t keep_dispatch(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap, void *xc,
                          float *alpha_slots, float *wg_max, Plan pl, const float *wdw, float q_alpha,
-                         const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
+                         const float *alpha_src, int n_alpha, float *alpha_pub, int64_t prefix, hipStream_t s) {
   const bool v4 = lane_cols(d) == 4;
   switch (d.levels) {
-    case 1: return v4 ? keep_launch<1, 4>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s)
-                      : keep_launch<1, 2>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
-    case 2: return keep_launch<2, 4>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
-    case 3: return keep_launch<3, 4>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
-    case 4: return keep_launch<4, 2>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+    case 1: return v4 ? keep_launch<1, 4>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s)
+                      : keep_launch<1, 2>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s);
+    case 2: return keep_launch<2, 4>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s);
+    case 3: return keep_launch<3, 4>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s);
+    case 4: return keep_launch<4, 2>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s);
   }
   return hipErrorInvalidValue;
 }
@@ -542,10 +551,10 @@ int64_t keep_workgroups(const wcc_desc &d, bool folded) {
 
 hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const int32_t *jmap,
                             void *xc, float *alpha_slots, float *wg_max, const float *wdw, float q_alpha,
-                            const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
+                            const float *alpha_src, int n_alpha, float *alpha_pub, int64_t prefix, hipStream_t s) {
   const bool late = alpha_slots != nullptr || wg_max != nullptr;
   const Plan pl{keep_groups(d, wdw != nullptr, late), 1, streams(d), 1};
-  return keep_dispatch(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, s);
+  return keep_dispatch(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s);
 }
 
 int64_t keep_words_workgroups(const wcc_desc &d) {

@@ -255,6 +255,21 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   // (a launch of its own takes 4 us: 576 -> 160 channels at 4 x 512 positions, 2^27.5 multiply-adds, gain
   // as much in the contraction, 320 -> 72 at 2048 lose 1 us)
   if (!packed && (int64_t)d.B * d.C_in * d.C_out * ks < ((int64_t)1 << 27)) pack.total = 0;
+  // alpha only after the second pass: its workgroups leave their maxima side by side for the
+  // contraction to combine (in the memory of the partial maxima, which this route does not use), or
+  // raise the slots where they are too many for every workgroup of the contraction to read.  (Raising
+  // slots, 64 words that share two lines of memory, and a launch to clear them: keep pass of 2 x 192
+  // channels of 400 x 56 23 us, 10 now; 2 x 176 of 204 x 144 25 and 15.)
+  const bool late = quant && !given && !codes_now;
+  const int64_t keep_wgs = src ? 0 : tail ? keep_words_workgroups(d) : keep_workgroups(d, wdw != nullptr);
+  float *wg_max = late && !src && keep_wgs <= kMaxWgMaxima && (size_t)keep_wgs * 4 <= L.norm - L.max_part
+                      ? reinterpret_cast<float *>(ws + L.max_part)
+                      : nullptr;
+  if (wg_max) n_alpha = (int)keep_wgs;
+  // The first k positions need no rank map: a position is its own rank (2 x 96 -> 192 channels of 128 x 256: four launches
+  // 33.5 us, three 31.6).  The launch stays where it has something else to write: the caller's copy of the list, the
+  // caller's alpha or the cleared slots.
+  if (list == kListPrefix && !tail && idx_out == nullptr && (!quant || wg_max)) jmap = nullptr;
   if (list == kListSelect) {
     // A: the transform, first pass: only the channel norms of X_wt leave the chip (the same
     // kernel clears the selection state)
@@ -273,23 +288,12 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   } else {
     // a list that does not depend on the input: no norm pass, no selection
     WCC_TRY(mark(WCC_T_NORM_SELECT, 0));
-    if (list == kListPrefix)
+    if (list == kListPrefix && jmap != nullptr)
       WCC_TRY(launch_jmap_prefix(d.B, (int64_t)d.H * d.W, k, jmap, idx_out, slots, quant ? alpha_in : 0.f, s));
-    else
+    else if (list == kListGiven)
       WCC_TRY(launch_jmap_from_idx(idx_given, d.B, (int64_t)d.H * d.W, k, jmap, slots, quant ? alpha_in : 0.f, s));
     WCC_TRY(mark(WCC_T_NORM_SELECT, 1));
   }
-  // alpha only after the second pass: its workgroups leave their maxima side by side for the
-  // contraction to combine (in the memory of the partial maxima, which this route does not use), or
-  // raise the slots where they are too many for every workgroup of the contraction to read.  (Raising
-  // slots, 64 words that share two lines of memory, and a launch to clear them: keep pass of 2 x 192
-  // channels of 400 x 56 23 us, 10 now; 2 x 176 of 204 x 144 25 and 15.)
-  const bool late = quant && !given && !codes_now;
-  const int64_t keep_wgs = src ? 0 : tail ? keep_words_workgroups(d) : keep_workgroups(d, wdw != nullptr);
-  float *wg_max = late && !src && keep_wgs <= kMaxWgMaxima && (size_t)keep_wgs * 4 <= L.norm - L.max_part
-                      ? reinterpret_cast<float *>(ws + L.max_part)
-                      : nullptr;
-  if (wg_max) n_alpha = (int)keep_wgs;
   // A again + B': the transform, second pass: X_wt[I] is written straight into its compressed
   // place (the dropped coefficients never reach memory)
   WCC_TRY(mark(WCC_T_GATHER, 0));
@@ -305,7 +309,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   else
     WCC_TRY(launch_haar_keep(d, ks, x, jmap, xc32, (late && !wg_max) ? slots : nullptr, wg_max, wdw,
                              (given && codes_now) ? alpha_in : 0.f, early ? tops : nullptr, n_top,
-                             early ? slots : nullptr, s));
+                             early ? slots : nullptr, k, s));
   WCC_TRY(mark(WCC_T_GATHER, 1));
   if (tail) {
     // C, D, E in one
@@ -331,7 +335,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   if (stop_before_inverse) return WCC_OK;
   // D + E: Y^0[I] = Y_wt, inverse levels
   WCC_TRY(mark(WCC_T_SCATTER_IHAAR, 0));
-  WCC_TRY(launch_scatter_ihaar(d, ks, yc, jmap, y, reinterpret_cast<float *>(ws + L.scratch), residual, s));
+  WCC_TRY(launch_scatter_ihaar(d, ks, yc, jmap, y, reinterpret_cast<float *>(ws + L.scratch), residual, k, s));
   WCC_TRY(mark(WCC_T_SCATTER_IHAAR, 1));
   return WCC_OK;
 }
@@ -597,7 +601,7 @@ wcc_status wcc_scatter_ihaar(wcc_ctx *ctx, const wcc_desc *desc, const float *yc
   WCC_TRY(launch_jmap_from_idx(idx, desc->B, N, k, jmap, nullptr, 0.f, s));
   WCC_TRY(launch_scatter_ihaar(*desc, k, yc, jmap, y,
                                reinterpret_cast<float *>(static_cast<char *>(ctx->ws) + L.scratch),
-                               nullptr, s));
+                               nullptr, k, s));
   return WCC_OK;
 }
 

@@ -272,7 +272,7 @@ hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const i
                             const float *wdw /*nullable*/,
                             float q_alpha, const float *alpha_src /*nullable*/, int n_alpha,
                             float *alpha_pub /*nullable: receives that largest value*/,
-                            hipStream_t s);
+                            int64_t prefix /*jmap null: the positions kept, the first ones*/, hipStream_t s);
 hipError_t launch_norm_reduce(const float *norm_part, const StorePlan &sp, int64_t BN, float *norm, hipStream_t s);
 hipError_t launch_channel_norm(const float *coef, int B, int C, int64_t N, bool squares, float *norm,
                                hipStream_t s);
@@ -334,9 +334,9 @@ hipError_t launch_pointwise_packed(const wcc_desc &d, int64_t k, const PackJob &
                                    const void *xc, const float *alpha, int n_alpha, float *alpha_out,
                                    float *yc, hipStream_t s);
 // scratch: kInvScratchBytes of device memory that the kernel may overwrite with anything
-// residual (nullable): [B, C_out, H, W] added to the result (may be y itself)
+// residual (nullable): [B, C_out, H, W] added to the result (may be y itself); jmap, prefix as in launch_haar_keep
 hipError_t launch_scatter_ihaar(const wcc_desc &d, int64_t k, const float *yc, const int32_t *jmap,
-                                void *y, float *scratch, const void *residual, hipStream_t s);
+                                void *y, float *scratch, const void *residual, int64_t prefix, hipStream_t s);
 // out[i] = the two signed 4-bit codes of packed[i / 2] widened to int8 (n = number of codes, even)
 hipError_t launch_unpack_i4(const uint8_t *packed, int8_t *out, int64_t n, hipStream_t s);
 // depthwise 3x3, stride 1, zero padding 1: x, y [B, C, H, W], w [C, 3, 3]
