@@ -57,15 +57,60 @@ struct RegRow {
   }
 };
 
+// The passes are bound by their vector instructions, so the factors 1/2 of the butterflies are left out where a power of two
+// can be carried along instead (scaling by it is exact, so the sums and roundings are those of the transforms of the
+// other routes, bit for bit, where nothing leaves the range of normal numbers): a level of the synthesis returns twice its
+// rows, and the level below halves them inside a multiply-add; the analysis leaves coefficients of level l scaled by
+// 2^(l + 1) (2 of them from the synthesis), which the sinks take off: the norm pass once a walk, the keep pass in the
+// multiplication it had.  Vector instructions a channel of the norm pass 709 -> 591; with the vector unit 91 % busy, at 1.9 GHz,
+// it takes 336 us for 8 x 1024 channels of 256 x 256, a quarter kept (361), the keep pass 440 (460).
+
+// Synthesis levels D..L of a strip: twice its rows of level L - 1 (inv_levels without the factors).
+template <int D, int V, int L, class Source>
+__device__ __forceinline__ void inv_levels_twice(float (&out)[rows_at(D, L - 1)][cols_at(V, L - 1)], const LanePos<D> &p,
+                                                 const Source &src) {
+  constexpr int R2 = rows_at(D, L), VI = cols_at(V, L - 1), V2 = cols_at(V, L);
+  constexpr int SI = span_at(V, L - 1);
+  float ll[R2][V2];
+  if constexpr (L < D) {
+    inv_levels_twice<D, V, L + 1>(ll, p, src);
+  } else {
+#pragma unroll
+    for (int i = 0; i < R2; ++i) src.template get_row<L, 0>(i, ll[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < R2; ++i) {
+    float y2[V2], y3[V2], y4[V2];
+    src.template get_row<L, 1>(i, y2);
+    src.template get_row<L, 2>(i, y3);
+    src.template get_row<L, 3>(i, y4);
+#pragma unroll
+    for (int e = 0; e < V2; ++e) {
+      const float s1 = L < D ? fmaf(0.5f, ll[i][e], y3[e]) : ll[i][e] + y3[e];
+      const float s2 = L < D ? fmaf(0.5f, ll[i][e], -y3[e]) : ll[i][e] - y3[e];
+      const float d1 = y2[e] + y4[e], d2 = y2[e] - y4[e];
+      if constexpr (VI >= 2) {
+        out[2 * i][2 * e] = s1 + d1; out[2 * i][2 * e + 1] = s1 - d1;
+        out[2 * i + 1][2 * e] = s2 + d2; out[2 * i + 1][2 * e + 1] = s2 - d2;
+      } else {
+        // every lane of the group holds the same (y1..y4); the left half keeps the left pixel
+        const bool left = (p.lc & SI) == 0;
+        out[2 * i][0] = s1 + (left ? d1 : -d1);
+        out[2 * i + 1][0] = s2 + (left ? d2 : -d2);
+      }
+    }
+  }
+}
+
 // One image row of a strip: its last one (BOTTOM) or its first one.  The same expressions as
-// inv_levels evaluates for that row.
+// inv_levels_twice evaluates for that row.
 template <int D, int V, int L, bool BOTTOM, class Source>
-__device__ __forceinline__ void inv_row(float (&out)[cols_at(V, L - 1)], const LanePos<D> &p,
-                                        const Source &src) {
+__device__ __forceinline__ void inv_row_twice(float (&out)[cols_at(V, L - 1)], const LanePos<D> &p,
+                                              const Source &src) {
   constexpr int VI = cols_at(V, L - 1), V2 = cols_at(V, L);
   constexpr int SI = span_at(V, L - 1);
   float ll[V2];
-  if constexpr (L < D) inv_row<D, V, L + 1, BOTTOM>(ll, p, src);
+  if constexpr (L < D) inv_row_twice<D, V, L + 1, BOTTOM>(ll, p, src);
   else src.template get<L, 0>(ll);
   float y2[V2], y3[V2], y4[V2];
   src.template get<L, 1>(y2);
@@ -73,18 +118,92 @@ __device__ __forceinline__ void inv_row(float (&out)[cols_at(V, L - 1)], const L
   src.template get<L, 3>(y4);
 #pragma unroll
   for (int e = 0; e < V2; ++e) {
-    const float s1 = ll[e] + y3[e], s2 = ll[e] - y3[e];
-    const float d1 = y2[e] + y4[e], d2 = y2[e] - y4[e];
-    const float l = BOTTOM ? 0.5f * (s2 + d2) : 0.5f * (s1 + d1);
-    const float r = BOTTOM ? 0.5f * (s2 - d2) : 0.5f * (s1 - d1);
+    const float y3s = BOTTOM ? -y3[e] : y3[e];
+    const float s = L < D ? fmaf(0.5f, ll[e], y3s) : ll[e] + y3s;
+    const float d = BOTTOM ? y2[e] - y4[e] : y2[e] + y4[e];
     if constexpr (VI >= 2) {
-      out[2 * e] = l;
-      out[2 * e + 1] = r;
+      out[2 * e] = s + d;
+      out[2 * e + 1] = s - d;
     } else {
-      out[0] = ((p.lc & SI) == 0) ? l : r;
+      out[0] = s + (((p.lc & SI) == 0) ? d : -d);
     }
   }
 }
+
+// Analysis levels L..D: `in` holds 2^L times the rows of level L - 1; the sink gets the coefficients as they are, or
+// (Sink::kScaled) 2^(level + 1) times them.
+template <int D, int V, int L, class Sink>
+__device__ __forceinline__ void fwd_levels_scaled(const float (&in)[rows_at(D, L - 1)][cols_at(V, L - 1)],
+                                                  const LanePos<D> &p, Sink &sink) {
+  constexpr int R2 = rows_at(D, L), VI = cols_at(V, L - 1), V2 = cols_at(V, L);
+  constexpr int SI = span_at(V, L - 1), S2 = span_at(V, L);
+  constexpr float kScale = Sink::kScaled ? 1.f : 1.f / (float)(2 << L);
+  float ll[R2][V2];
+  const bool owner = p.active && ((S2 == 1) || ((p.lc & (S2 - 1)) == 0));
+#pragma unroll
+  for (int i = 0; i < R2; ++i) {
+    float y1[V2], y2[V2], y3[V2], y4[V2];
+#pragma unroll
+    for (int e = 0; e < V2; ++e) {
+      float a, b, c, d;
+      if constexpr (VI >= 2) {
+        a = in[2 * i][2 * e]; b = in[2 * i][2 * e + 1];
+        c = in[2 * i + 1][2 * e]; d = in[2 * i + 1][2 * e + 1];
+      } else {
+        const float o0 = in[2 * i][0], o1 = in[2 * i + 1][0];
+        const float q0 = lane_xor<SI>(o0), q1 = lane_xor<SI>(o1);
+        const bool left = (p.lc & SI) == 0;
+        a = left ? o0 : q0; b = left ? q0 : o0;
+        c = left ? o1 : q1; d = left ? q1 : o1;
+      }
+      const float s1 = a + b, s2 = c + d, d1 = a - b, d2 = c - d;
+      ll[i][e] = s1 + s2;
+      y1[e] = kScale * ll[i][e];
+      y2[e] = kScale * (d1 + d2);
+      y3[e] = kScale * (s1 - s2);
+      y4[e] = kScale * (d1 - d2);
+    }
+    sink.template put_row<L, 1>(p, i, y2, owner);
+    sink.template put_row<L, 2>(p, i, y3, owner);
+    sink.template put_row<L, 3>(p, i, y4, owner);
+    if constexpr (L == D) sink.template put_row<L, 0>(p, i, y1, owner);
+  }
+  if constexpr (L < D) fwd_levels_scaled<D, V, L + 1>(ll, p, sink);
+}
+
+// Sink of the norm pass: per slot the sum of |coefficient| (SQ: of squares) and the largest |coefficient| over the
+// channels, both of scaled coefficients until finish().
+template <int D, bool SQ>
+struct ChainNormSink {
+  static constexpr bool kScaled = true;
+  float acc[slot_count(D, V4)], top[slot_count(D, V4)];
+  template <int L, int J>
+  __device__ __forceinline__ void put_row(const LanePos<D> &, int i, const float (&v)[cols_at(V4, L)], bool) {
+    constexpr int CV = cols_at(V4, L), base = slot_base(D, V4, L, J);
+#pragma unroll
+    for (int e = 0; e < CV; ++e) {
+      float &a = acc[base + i * CV + e], &t = top[base + i * CV + e];
+      a = SQ ? fmaf(v[e], v[e], a) : a + fabsf(v[e]);
+      // (fmaxf first quiets a value that the compiler does not know to be quiet: a second instruction a slot)
+      asm("v_max_f32_e64 %0, %1, |%2|" : "=v"(t) : "v"(t), "v"(v[e]));
+    }
+  }
+  __device__ __forceinline__ void finish() {
+    auto level = [&](auto Lc) {
+      constexpr int L = decltype(Lc)::value;
+      constexpr float kDown = 1.f / (float)(2 << L);
+      constexpr int first = slot_base(D, V4, L, L == D ? 0 : 1), last = L == D ? slot_count(D, V4) : slot_base(D, V4, L, 3) + rows_at(D, L) * cols_at(V4, L);
+#pragma unroll
+      for (int s = first; s < last; ++s) {
+        acc[s] *= SQ ? kDown * kDown : kDown;
+        top[s] *= kDown;
+      }
+    };
+    level(std::integral_constant<int, 1>{});
+    if constexpr (D >= 2) level(std::integral_constant<int, 2>{});
+    if constexpr (D >= 3) level(std::integral_constant<int, 3>{});
+  }
+};
 
 // ---- the channel walk ----------------------------------------------------------------------------
 constexpr int kChainCap = 2048;  // packed entries per wave (32 a lane)
@@ -185,11 +304,11 @@ __device__ __forceinline__ ChainGeo<D> chain_setup(const int32_t *__restrict__ j
 // tile (laid out [lane][slot]; its other cells stay zero), the strip's 2^d rows and the rows above and below are
 // rebuilt from it, convolved with the channel's 3x3 kernel (wdw: first channel's, 9 floats a
 // channel) and transformed into `sink`; after(sink) runs once per channel.
-// Waves whose list is packed fetch it with dense loads, one or two channels ahead; the others
+// Waves whose list is packed fetch it with dense loads, one channel ahead; the others
 // (strips that keep more than kChainCap positions) load slot by slot from the ranks they hold in
 // registers, a channel's loads in flight together.
 // NI_FIXED > 0: the packed list is walked with that many rows a wave (the caller has checked that
-// it fits); 0: the shortest of 4, 8, 16, 32 rows that holds it.
+// it fits); 0: the shortest of 4, 8, 16, 24, 32 rows that holds it.
 // SEGS > 1: the plane's row is shared by the SEGS waves of the workgroup (this one holds segment
 // `seg`); xchg is the workgroup's exchange buffer (ChainXchg<D, SEGS>::kWords floats).  Every wave
 // of the workgroup then runs compute() once per channel, whatever path it takes: one barrier each.
@@ -223,16 +342,16 @@ __device__ __forceinline__ void chain_walk(const float *__restrict__ plane, int6
       const RegStrip<D, V, NT> own{cells};
       const RegRow<D, V, NT> up{cells, NS}, dn{cells, NS + HS};
       float mid[R][V];
-      inv_levels<D, V, 1>(mid, p, own);
+      inv_levels_twice<D, V, 1>(mid, p, own);
 #pragma unroll
       for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int e = 0; e < V; ++e) six[r + 1][e + 1] = mid[r][e];
       float edge[V];
-      inv_row<D, V, 1, true>(edge, p, up);
+      inv_row_twice<D, V, 1, true>(edge, p, up);
 #pragma unroll
       for (int e = 0; e < V; ++e) six[0][e + 1] = edge[e];
-      inv_row<D, V, 1, false>(edge, p, dn);
+      inv_row_twice<D, V, 1, false>(edge, p, dn);
 #pragma unroll
       for (int e = 0; e < V; ++e) six[RR - 1][e + 1] = edge[e];
     }
@@ -270,7 +389,16 @@ __device__ __forceinline__ void chain_walk(const float *__restrict__ plane, int6
     }
 #pragma unroll
     for (int i = 0; i < RR; ++i) {
-      float l = __shfl_up(six[i][V], 1, kWave), r = __shfl_down(six[i][1], 1, kWave);
+      // (the neighbouring lanes' columns: through LDS where the vector unit is the bound, by its data-parallel moves in the
+      // keep pass, which keeps LDS busy as it is: 455 -> 440 us there, 333 -> 339 in the norm pass)
+      float l, r;
+      if constexpr (Sink::kScaled) {
+        l = __shfl_up(six[i][V], 1, kWave);
+        r = __shfl_down(six[i][1], 1, kWave);
+      } else {
+        l = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(six[i][V]), 0x138, 0xf, 0xf, true));  // wave_shr:1
+        r = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(six[i][1]), 0x130, 0xf, 0xf, true));  // wave_shl:1
+      }
       if (first_lane) l = beyond[i];
       if (last_lane) r = left_only ? 0.f : beyond[i];
       six[i][0] = l;
@@ -288,17 +416,13 @@ __device__ __forceinline__ void chain_walk(const float *__restrict__ plane, int6
 #pragma unroll
           for (int e = 0; e < V; ++e) t1[o][e] = fmaf(k[i * 3 + j], six[o + i][e + j], t1[o][e]);
     }
-    fwd_levels<D, V, 1>(t1, p, sink);
+    fwd_levels_scaled<D, V, 1>(t1, p, sink);
     after(sink);
   };
 
   if (cg.packed) {
     auto run = [&](auto ni_c) {
       constexpr int NI = decltype(ni_c)::value;
-      // Channels of values in flight ahead of the one being worked on: two for short lists, one
-      // for longer ones (registers; the 32-row walk spills some of them, which still costs far
-      // less than waiting for every channel's values where they are needed).
-      constexpr int DEPTH = NI <= 8 ? 2 : 1;
       constexpr uint32_t kRank = (1u << kInvRankBits) - 1u;
       // this lane's share of the list: entries lane + 64 i.  Past the end of the list an entry
       // repeats the list's first one: it fetches the same value and drops it into the same cell,
@@ -322,34 +446,15 @@ __device__ __forceinline__ void chain_walk(const float *__restrict__ plane, int6
 #pragma unroll
         for (int i = 0; i < NI; ++i) tile[mine[i] >> kInvRankBits] = __float_as_uint(src[i]);
       };
-      if constexpr (DEPTH == 0) {
-        for (int c = 0; c < n_ch; ++c) {
-          float v[NI];
-          fetch(v, c);
-          drop(v);
-          compute(wdw + (size_t)c * 9);
-        }
-      } else {
-        float vn[DEPTH][NI];
-#pragma unroll
-        for (int u = 0; u < DEPTH; ++u) fetch(vn[u], u);
-        int c = 0;
-        for (; c + DEPTH <= n_ch; c += DEPTH) {
-#pragma unroll
-          for (int u = 0; u < DEPTH; ++u) {
-            drop(vn[u]);
-            fetch(vn[u], c + u + DEPTH);  // travels while the channels in between are worked on
-            __builtin_amdgcn_sched_barrier(0);
-            compute(wdw + (size_t)(c + u) * 9);
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < DEPTH - 1; ++u) {
-          if (c + u < n_ch) {
-            drop(vn[u]);
-            compute(wdw + (size_t)(c + u) * 9);
-          }
-        }
+      // One channel of values in flight ahead of the one being worked on.  (Two for short lists double the loops, and with
+      // them the code that waves on lists of different lengths run side by side: norm pass 351 us, 336 now.)
+      float vn[NI];
+      fetch(vn, 0);
+      for (int c = 0; c < n_ch; ++c) {
+        drop(vn);
+        fetch(vn, c + 1);  // travels while this channel is worked on
+        __builtin_amdgcn_sched_barrier(0);
+        compute(wdw + (size_t)c * 9);
       }
     };
     if (cg.count == 0) {  // nothing kept around this strip: every channel is zero
@@ -365,6 +470,7 @@ __device__ __forceinline__ void chain_walk(const float *__restrict__ plane, int6
       if (ni <= 4) run(std::integral_constant<int, 4>{});
       else if (ni <= 8) run(std::integral_constant<int, 8>{});
       else if (ni <= 16) run(std::integral_constant<int, 16>{});
+      else if (ni <= 24) run(std::integral_constant<int, 24>{});
       else run(std::integral_constant<int, 32>{});
     }
     return;
@@ -392,6 +498,7 @@ __device__ __forceinline__ void chain_walk(const float *__restrict__ plane, int6
 template <int D, bool Q8, int NI>
 struct ChainStagedSink {
   using Out = std::conditional_t<Q8, int8_t, float>;
+  static constexpr bool kScaled = false;
   static constexpr uint32_t kDropped = 0xFFFFFFFFu;
   static constexpr int NS = slot_count(D, V4);
   __amdgpu_buffer_rsrc_t xc_c;  // xc[b, c, :]
@@ -501,25 +608,19 @@ __global__ __launch_bounds__(chain_waves(SEGS) * kWave, 4 / chain_waves(SEGS)) v
   const bool up_in = row0 > 0, dn_in = row0 + (1 << D) < g.H;
   const ChainGeo<D> cg = chain_setup<D>(jm1, k1, p, active, up_in, dn_in, tiles[wv]);
 
-  FwdSink<D, V4, false, SQ> sink;
+  ChainNormSink<D, SQ> sink;
 #pragma unroll
-  for (int s = 0; s < NS; ++s) sink.acc[s] = 0.f;
-  if constexpr (FwdSink<D, V4, false, SQ>::MX) {
-#pragma unroll
-    for (int s = 0; s < NS; ++s) sink.top[s] = 0.f;
-  }
-  sink.plane = nullptr;
+  for (int s = 0; s < NS; ++s) sink.acc[s] = sink.top[s] = 0.f;
   // (the last groups have no channels where C does not fill them -- 42 channels in 8 groups of 6 --; their
   // planes are zeros: the selection adds the planes of all groups)
   if (n_ch > 0)
     chain_walk<D, SEGS>(yc1 + ((size_t)b * C + c0) * k1, k1, n_ch, wdw + (size_t)c0 * 9, cg, tiles[wv], p,
                         p.lc == 0, p.lc == m.lpr - 1 || col0 + V4 >= g.W, xchg, wv, sink,
-                        [](FwdSink<D, V4, false, SQ> &) {});
+                        [](ChainNormSink<D, SQ> &) {});
+  sink.finish();
   if (!active) return;
   write_slots<D, V4>(norm_part + ((size_t)grp * B + b) * g.N, sink.acc, p);
-  if constexpr (FwdSink<D, V4, false, SQ>::MX) {
-    if (max_part != nullptr) write_slots<D, V4>(max_part + ((size_t)grp * B + b) * g.N, sink.top, p);
-  }
+  if (max_part != nullptr) write_slots<D, V4>(max_part + ((size_t)grp * B + b) * g.N, sink.top, p);
 }
 
 // ---- second pass: the kept coefficients of HWT(K_dw t1) ---------------------------------------------
@@ -635,7 +736,7 @@ __global__ __launch_bounds__(chain_waves(SEGS) * kWave, 4 / chain_waves(SEGS)) v
     // Kept at a quarter, 256 columns, three levels, lists of 8 and 17 rows are the rule, just above a power of two: with 12
     // and 24 rows between 8/16 and 16/32 the pass takes 455-473 us (8x1024 channels, before 476-481), and 4/12 instead of
     // 4/8 takes 3 % off blocks kept at an eighth (at two levels, where 4/8 holds the lists, it costs 1.6 %).  20 rows
-    // in place of 16 or 24 were slower, 467-482 us, and so is the norm pass with 24 or 20 (368-381 against 361-368).
+    // in place of 16 or 24 were slower, 467-482 us.
     auto staged = [&](auto ni3_c, auto ni1_c) {
       constexpr int NI3 = decltype(ni3_c)::value, NI1 = decltype(ni1_c)::value;
       ChainStagedSink<D, Q8, NI3> st(Q8 ? q_alpha : 0.f);

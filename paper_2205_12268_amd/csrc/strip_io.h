@@ -86,6 +86,7 @@ __device__ __forceinline__ void write_slots(float *np, const float *vals, const 
 template <int D, int V, bool Q8, int QF = 0>
 struct KeepSink {
   using Out = std::conditional_t<Q8, int8_t, float>;
+  static constexpr bool kScaled = false;  // (fwd_levels_scaled)
   // Every slot is stored through a buffer descriptor of the channel's compressed vector, with
   // the byte offset of the slot's rank, or an offset beyond the vector for a position that is
   // not kept: the hardware drops such a lane's store.  No store sits behind a branch, so the
