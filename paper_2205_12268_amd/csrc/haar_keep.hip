@@ -424,6 +424,227 @@ __global__ __launch_bounds__(256) void haar_keep_words_kernel(const XT *__restri
   }
 }
 
+// ---- codes of four channels a word, in the order of the ranks ----------------------------------------
+// The second pass of layers whose codes are decided in it: four channels' codes of a position leave as one word,
+// [B, ceil(C / 4), k], which the contraction reads as it multiplies (four channels of a column are a word of its operand).
+// A byte store a code costs the memory pipeline four times the instructions, and lines of 64 bytes at best.  Byte by byte and
+// in words: 8 x 256 channels of 256 x 256, a quarter kept, 118 -> 106 us; 8 x 128 of 192 x 640, a sixteenth, 95.6 -> 89; 16 x 256 of
+// 128 x 128, a half, 53 -> 50; 256 of 256 x 512 at two levels 25.3 -> 24.4 (its reads alone 20).  Three workgroups a compute
+// unit (168 registers, 179 now) lose on the long walks: 113, 90.5.
+// Groups take quads of channels y, y + G, ... .  The stores of a quad are issued behind the loads of the next one's
+// second channel: between a load and the wait for it every path has the same number of memory instructions.
+// grid = (ceil(units / 4), G, B), block = 256.
+
+// A strip that keeps few of its positions: through an LDS tile [slot][lane] and the packed list (see KeepStagedSink).
+template <int D, int V, int NI>
+struct QuadListSink {
+  uint32_t *tile;     // [slot][lane]
+  int lane;
+  uint32_t cell[NI];  // tile index of the entry's position
+  uint32_t at[NI];    // byte offset of the entry's rank, or kRowDropped
+  uint32_t word[NI];
+  Quant quant;
+  __device__ __forceinline__ explicit QuadListSink(const Quant &q) : quant(q) {}
+  template <int L, int J>
+  __device__ __forceinline__ void put_row(const LanePos<D> &, int i, const float (&v)[cols_at(V, L)], bool) {
+    constexpr int CV = cols_at(V, L), base = slot_base(D, V, L, J);
+#pragma unroll
+    for (int e = 0; e < CV; ++e) tile[(base + i * CV + e) * kWave + lane] = __float_as_uint(v[e]);
+  }
+  __device__ __forceinline__ void code() {
+    wave_lds_fence();
+    float v[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) v[i] = __uint_as_float(tile[cell[i]]);
+    auto shift_in = [&](auto fast_c) {  // the new code comes in at the top, the oldest leaves at the bottom
+      constexpr bool FAST = decltype(fast_c)::value;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        word[i] = __builtin_amdgcn_alignbyte((uint32_t)(int)quant.template level_as<FAST>(v[i]), word[i], 1);
+    };
+    if (quant.fast) shift_in(std::true_type{}); else shift_in(std::false_type{});
+    wave_lds_fence();
+  }
+  __device__ __forceinline__ void store(__amdgpu_buffer_rsrc_t to) const {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) __builtin_amdgcn_raw_buffer_store_b32(word[i], to, at[i], 0, 0);
+  }
+};
+
+// Any strip: a word a slot.
+template <int D, int V, bool FAST>
+struct QuadSlotSink {
+  uint32_t at[slot_count(D, V)];  // byte offset of the slot's rank, or kRowDropped
+  uint32_t word[slot_count(D, V)];
+  Quant quant;
+  __device__ __forceinline__ explicit QuadSlotSink(const Quant &q) : quant(q) {}
+  template <int L, int J>
+  __device__ __forceinline__ void put_row(const LanePos<D> &, int i, const float (&v)[cols_at(V, L)], bool) {
+    constexpr int CV = cols_at(V, L), base = slot_base(D, V, L, J);
+#pragma unroll
+    for (int e = 0; e < CV; ++e) {
+      uint32_t &w = word[base + i * CV + e];
+      w = __builtin_amdgcn_alignbyte((uint32_t)(int)quant.template level_as<FAST>(v[e]), w, 1);
+    }
+  }
+  __device__ __forceinline__ void code() {}
+  __device__ __forceinline__ void store(__amdgpu_buffer_rsrc_t to) const {
+#pragma unroll
+    for (int s = 0; s < slot_count(D, V); ++s) __builtin_amdgcn_raw_buffer_store_b32(word[s], to, at[s], 0, 0);
+  }
+};
+
+template <int D, int V, class XT, bool NT>
+__global__ __launch_bounds__(256) void haar_keep_quads_kernel(const XT *__restrict__ x, const int32_t *__restrict__ jmap,
+                                                              uint32_t *__restrict__ xw, Geo g, StripMap m, int C,
+                                                              int64_t ks, float q_alpha,
+                                                              const float *__restrict__ alpha_src, int n_alpha,
+                                                              float *alpha_pub, int64_t prefix) {
+  constexpr int NS = slot_count(D, V), R = 1 << D;
+  constexpr bool kStaged = (V == 4 && (D == 2 || D == 3)) || D == 4;
+  constexpr int kRankBits = 20;  // list entry = rank | tile index << 20
+  __shared__ uint32_t tiles[kStaged ? 4 : 1][kStaged ? NS * kWave : 1];
+  const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int unit = blockIdx.x * 4 + wv, grp = blockIdx.y, G = gridDim.y;
+  const int b = gridDim.z - 1 - blockIdx.z;  // (last to first: what the norm pass left in the cache is the tail)
+  LanePos<D> p;
+  int row0, col0;
+  const bool active = locate<D, V>(m, g, unit, p, row0, col0);
+  const int quads = (C + 3) / 4, nq = (quads - grp + G - 1) / G;  // (G <= quads)
+
+  // ranks of this lane's positions, or -1
+  int at[NS];
+  auto ranks = [&](auto &&rank_of) {
+    auto fetch = [&](auto Lc, auto Jc) {
+      constexpr int L = decltype(Lc)::value, J = decltype(Jc)::value;
+      constexpr int CV = cols_at(V, L), S2 = span_at(V, L);
+      const bool owner = (S2 == 1) || ((p.lc & (S2 - 1)) == 0);
+#pragma unroll
+      for (int i = 0; i < rows_at(D, L); ++i)
+#pragma unroll
+        for (int e = 0; e < CV; ++e) {
+          constexpr int base = slot_base(D, V, L, J);
+          int j = -1;
+          if (active && owner) j = rank_of(J * p.nl[L] + p.off[L] + i * p.rowlen[L] + e);
+          at[base + i * CV + e] = j;
+        }
+    };
+    auto each_level = [&](auto Lc) {
+      constexpr int L = decltype(Lc)::value;
+      fetch(Lc, std::integral_constant<int, 1>{});
+      fetch(Lc, std::integral_constant<int, 2>{});
+      fetch(Lc, std::integral_constant<int, 3>{});
+      if constexpr (L == D) fetch(Lc, std::integral_constant<int, 0>{});
+    };
+    each_level(std::integral_constant<int, 1>{});
+    if constexpr (D >= 2) each_level(std::integral_constant<int, 2>{});
+    if constexpr (D >= 3) each_level(std::integral_constant<int, 3>{});
+    if constexpr (D >= 4) each_level(std::integral_constant<int, 4>{});
+  };
+  if (jmap != nullptr) {  // (uniform over the grid)
+    const int32_t *jm = jmap + (size_t)b * g.N;
+    ranks([&](int pos) { return jm[pos]; });
+  } else {
+    const int first = (int)prefix;
+    ranks([&](int pos) { return pos < first ? pos : -1; });
+  }
+  if (alpha_src != nullptr) {  // (uniform over the grid; behind the rank loads)
+    q_alpha = alpha_max(alpha_src, n_alpha);
+    if (alpha_pub != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0)
+      alpha_pub[0] = q_alpha;
+  }
+  if (__ballot(active) == 0) return;  // whole waves leave (no barrier below)
+  const Quant quant(q_alpha);
+  // (lanes outside the plane read the plane's first rows; nothing of theirs is ever stored)
+  const XT *src = x + (size_t)b * C * g.N + (active ? (size_t)row0 * g.W + col0 : (size_t)0);
+  uint32_t *out = xw + (size_t)b * quads * ks;
+  auto walk = [&](auto &sink) {
+    // row of the signal, -1: nothing yet
+    auto store = [&](int row) {
+      sink.store(__builtin_amdgcn_make_buffer_rsrc(out + (size_t)max(row, 0) * ks, 0,
+                                                   row >= 0 ? (int)(uint32_t)(ks * 4) : 0, 0x00020000));
+    };
+    // (channels past the last one repeat it; they meet weights of zero)
+    auto channel = [&](int i) { return min((grp + (i >> 2) * G) * 4 + (i & 3), C - 1); };
+    Row<V, XT> buf[2][R];
+    auto load = [&](Row<V, XT> (&to)[R], int i) {
+      const XT *nx = src + (size_t)channel(min(i, 4 * nq - 1)) * g.N;
+#pragma unroll
+      for (int r = 0; r < R; ++r) to[r].template load<NT>(nx + (size_t)r * g.W);
+    };
+    load(buf[0], 0);
+    int pending = -1;
+    for (int qd = 0; qd < nq; ++qd) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        load(buf[(u + 1) & 1], 4 * qd + u + 1);
+        if (u == 0) store(pending);
+        __builtin_amdgcn_sched_barrier(0);
+        float in[R][V];
+#pragma unroll
+        for (int r = 0; r < R; ++r) buf[u & 1][r].get(in[r]);
+        fwd_levels<D, V, 1>(in, p, sink);
+        sink.code();
+      }
+      pending = grp + qd * G;
+    }
+    store(pending);
+  };
+
+  if constexpr (kStaged) {
+    int count = 0;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) count += __popcll(__ballot(at[s] >= 0));
+    const int ni = (count + kWave - 1) / kWave;
+    if (ni <= NS / 2 && ni <= 16 && ks <= ((int64_t)1 << kRankBits)) {
+      if (count == 0) return;
+      uint32_t *tile = tiles[wv];
+      int running = 0;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int j = at[s];
+        const uint64_t kept = __ballot(j >= 0);
+        const int to = running + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(kept >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)kept, 0u));
+        if (j >= 0) tile[to] = (uint32_t)j | ((uint32_t)(s * kWave + lane) << kRankBits);
+        running += __popcll(kept);
+      }
+      wave_lds_fence();
+      auto run = [&](auto ni_c) {
+        constexpr int NI = decltype(ni_c)::value;
+        QuadListSink<D, V, NI> sink(quant);
+        sink.tile = tile;
+        sink.lane = lane;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          const int e = lane + kWave * i;
+          const uint32_t packed = e < count ? tile[e] : 0u;
+          sink.cell[i] = e < count ? packed >> kRankBits : (uint32_t)lane;
+          sink.at[i] = e < count ? (packed & ((1u << kRankBits) - 1u)) * 4u : kRowDropped;
+          sink.word[i] = 0;
+        }
+        wave_lds_fence();
+        walk(sink);
+      };
+      if (ni <= 4) run(std::integral_constant<int, 4>{});
+      else if (ni <= 8) run(std::integral_constant<int, 8>{});
+      else if (D == 3 && ni <= 12) run(std::integral_constant<int, 12>{});
+      else run(std::integral_constant<int, 16>{});
+      return;
+    }
+  }
+  auto slots = [&](auto fast_c) {
+    QuadSlotSink<D, V, decltype(fast_c)::value> sink(quant);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      sink.at[s] = at[s] >= 0 ? (uint32_t)at[s] * 4u : kRowDropped;
+      sink.word[s] = 0;
+    }
+    walk(sink);
+  };
+  if (quant.fast) slots(std::true_type{}); else slots(std::false_type{});
+}
+
 // the lanes of all strips follow each other, 64 a wave: four units
 inline StripMap words_map(const wcc_desc &d) {
   StripMap m = make_map(d, lane_cols(d));
@@ -459,6 +680,8 @@ hipError_t words_launch(const wcc_desc &d, int64_t ks, const XT *x, const int32_
 inline StripMap keep_map(const wcc_desc &d, bool folded) {
   return folded ? make_map(d, lane_cols(d)) : make_flat_map(d, lane_cols(d));
 }
+
+constexpr int64_t kQuadWaves = 1024;
 
 int keep_groups(const wcc_desc &d, bool folded, bool late) {
   // About two thousand waves, down to two channels each at d <= 2, where a wave has few rows in flight
@@ -542,6 +765,51 @@ hipError_t keep_dispatch(const wcc_desc &d, int64_t k, const void *x, const int3
     case 3: return keep_launch<3, 4>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s);
     case 4: return keep_launch<4, 2>(d, k, x, jmap, xc, alpha_slots, wg_max, pl, wdw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s);
   }
+  return hipErrorInvalidValue;
+}
+
+// Groups of quads of channels, or 0: codes leave byte by byte.  As many groups as the byte-wise launch has, as long as its waves'
+// walks, which end with the longest, grow by a tenth at most for going by whole quads (11 x 400 channels of 8 x 608, 64 groups
+// of one or two quads, where the byte-wise ones walk 7 channels: layer 62 us, 58.5; in 100 groups of one quad 63.6; 8 x 618 of
+// 48 x 332, 18 groups in place of 16, which fill the chip evenly: 65 and 57).  Where there are fewer quads than groups
+// they make do with as many waves as the quads give, from a thousand on.
+static int quad_groups(const wcc_desc &d) {
+  const int G0 = keep_groups(d, false, false), quads = (d.C_in + 3) / 4;
+  if (quads <= G0) return (int64_t)keep_map(d, false).units * quads * d.B >= kQuadWaves ? quads : 0;
+  return 40 * ((quads + G0 - 1) / G0) <= 11 * ((d.C_in + G0 - 1) / G0) ? G0 : 0;
+}
+
+bool keep_in_quads(const wcc_desc &d) { return quad_groups(d) > 0; }
+
+template <int D, int V, class XT>
+static hipError_t quads_launch(const wcc_desc &d, int64_t ks, const void *x, const int32_t *jmap, uint32_t *xw, float q_alpha,
+                               const float *alpha_src, int n_alpha, float *alpha_pub, int64_t prefix, hipStream_t s) {
+  const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
+  const StripMap m = keep_map(d, false);
+  const dim3 grid((m.units + 3) / 4, quad_groups(d), d.B);
+  if (streams(d))
+    hipLaunchKernelGGL((haar_keep_quads_kernel<D, V, XT, true>), grid, dim3(256), 0, s, static_cast<const XT *>(x), jmap, xw, g,
+                       m, d.C_in, ks, q_alpha, alpha_src, n_alpha, alpha_pub, prefix);
+  else
+    hipLaunchKernelGGL((haar_keep_quads_kernel<D, V, XT, false>), grid, dim3(256), 0, s, static_cast<const XT *>(x), jmap, xw, g,
+                       m, d.C_in, ks, q_alpha, alpha_src, n_alpha, alpha_pub, prefix);
+  return hipGetLastError();
+}
+
+hipError_t launch_haar_keep_quads(const wcc_desc &d, int64_t ks, const void *x, const int32_t *jmap, uint32_t *xw, float q_alpha,
+                                  const float *alpha_src, int n_alpha, float *alpha_pub, int64_t prefix, hipStream_t s) {
+  if (!keep_in_quads(d)) return hipErrorInvalidValue;
+#define WCC_QUADS(D, V)                                                                                                 \
+  return d.act_dtype == WCC_BF16                                                                                        \
+             ? quads_launch<D, V, bf16_t>(d, ks, x, jmap, xw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s)        \
+             : quads_launch<D, V, float>(d, ks, x, jmap, xw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s)
+  switch (d.levels) {
+    case 1: if (lane_cols(d) == 4) WCC_QUADS(1, 4); else WCC_QUADS(1, 2);
+    case 2: WCC_QUADS(2, 4);
+    case 3: WCC_QUADS(3, 4);
+    case 4: WCC_QUADS(4, 2);
+  }
+#undef WCC_QUADS
   return hipErrorInvalidValue;
 }
 

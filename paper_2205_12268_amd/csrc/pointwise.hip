@@ -48,12 +48,19 @@ __device__ __forceinline__ float load_alpha(const float *__restrict__ alpha, int
   return a;
 }
 
+// In which form the compressed signal comes: int8 codes [K, k], fp32 [K, k] (quantised on load), or codes of four
+// channels a word, [ceil(K / 4), k], as the second transform pass of the fused layer writes them: a patch is then a quarter
+// of the loads, four times as wide, and transposed as the matrix instructions want it.
+enum { kCodes = 0, kFloats = 1, kWords = 2 };
+typedef uint32_t word4 __attribute__((ext_vector_type(4)));
+
 // A thread's raw CPT (channels) x 4 (positions) patch of one 64-channel chunk.
-// F32: unquantised kept coefficients (16 bytes a channel); else int8 codes (4 bytes a channel).
-template <bool F32, int CPT>
+template <int FORM, int CPT>
 struct Patch {
+  static constexpr bool F32 = FORM == kFloats, WORDS = FORM == kWords;
   float4 f[F32 ? CPT : 1];
-  uint32_t c[F32 ? 1 : CPT];
+  uint32_t c[FORM == kCodes ? CPT : 1];
+  word4 q[WORDS ? CPT / 4 : 1];
   // Loaded through a buffer descriptor of the sample's compressed signal: off is the byte
   // offset of this thread's four positions in the patch's first channel.  No branch, no lane
   // mask: a load never faults (outside the buffer it returns zeros, a wrapped offset lands
@@ -62,22 +69,30 @@ struct Patch {
   // and for positions >= k it feeds columns that are never stored.
   __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t xdesc, uint32_t off, int64_t k) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    if constexpr (WORDS) {
+#pragma unroll
+      for (int r = 0; r < CPT / 4; ++r)
+        q[r] = __builtin_amdgcn_raw_buffer_load_b128(xdesc, off + (uint32_t)r * (uint32_t)k * 4u, 0, 0);
+      return;
+    }
 #pragma unroll
     for (int r = 0; r < CPT; ++r) {
       if constexpr (F32) {
         const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(xdesc, off + (uint32_t)r * (uint32_t)k * 4u, 0, 0);
         f[r] = make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
-      } else {
+      } else if constexpr (!WORDS) {
         c[r] = __builtin_amdgcn_raw_buffer_load_b32(xdesc, off + (uint32_t)r * (uint32_t)k, 0, 0);
       }
     }
   }
   // level of channel r, position i, as a float holding an integer in [-127, 127]
   template <bool FAST>
-  __device__ __forceinline__ float level(int r, int i, const Quant &q) const {
+  __device__ __forceinline__ float level(int r, int i, const Quant &quant) const {
     if constexpr (F32) {
       const float v = i == 0 ? f[r].x : i == 1 ? f[r].y : i == 2 ? f[r].z : f[r].w;
-      return q.template level_as<FAST>(v);
+      return quant.template level_as<FAST>(v);
+    } else if constexpr (WORDS) {
+      return (float)((int)(q[r >> 2][i] << (24 - 8 * (r & 3))) >> 24);
     } else {
       return (float)((int)(c[r] << (24 - 8 * i)) >> 24);
     }
@@ -88,11 +103,12 @@ struct Patch {
 // K % 2 == 0 (bf16 weights) or K % 4 == 0 (int8 weights).
 // RAG: a weight row is not a whole number of 16-byte loads (K % 8 or K % 16 != 0): what the last load
 // of a row brings in of the next one is cleared on its way to LDS.
-template <int BM, int BN, bool F32, bool I8W, bool RAG>
+template <int BM, int BN, int FORM, bool I8W, bool RAG>
 __global__ __launch_bounds__(2 * BM) void pointwise_mfma_kernel(
     const void *__restrict__ w, const float *__restrict__ w_scale, const void *__restrict__ xq,
     const float *__restrict__ alpha, int n_alpha, float *alpha_out, float *__restrict__ yc, int M,
     int K, int64_t k, bool stream_out) {
+  constexpr bool F32 = FORM == kFloats, WORDS = FORM == kWords;
   constexpr int T = 2 * BM;
   constexpr int NB = BN / 32;                // 32-column blocks of the tile: 4 or 2
   constexpr int NG = BN / 4;                 // groups of four positions
@@ -106,7 +122,8 @@ __global__ __launch_bounds__(2 * BM) void pointwise_mfma_kernel(
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int b = blockIdx.z;
   const int64_t n0 = (int64_t)blockIdx.x * BN;
-  const void *xb = static_cast<const char *>(xq) + (size_t)b * K * k * (F32 ? 4 : 1);
+  const int64_t xbytes = (WORDS ? (K + 3) / 4 * 4 : K) * k * (F32 ? 4 : 1);  // of a sample
+  const void *xb = static_cast<const char *>(xq) + (size_t)b * xbytes;
   const unsigned char *wb = static_cast<const unsigned char *>(w);
   const int a_row = t >> 1, a_half = t & 1;  // weight loader: row, which half of the chunk
   const int g = t % NG, kq = t / NG;         // activation loader: n group (4 n), channel group
@@ -122,7 +139,7 @@ __global__ __launch_bounds__(2 * BM) void pointwise_mfma_kernel(
   const __amdgpu_buffer_rsrc_t wdesc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<unsigned char *>(wb), 0, (int)(uint32_t)((int64_t)M * K * ESZ), 0x00020000);
   const __amdgpu_buffer_rsrc_t xdesc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<void *>(xb), 0, (int)(uint32_t)((int64_t)K * k * (F32 ? 4 : 1)), 0x00020000);
+      const_cast<void *>(xb), 0, (int)(uint32_t)xbytes, 0x00020000);
   // A workgroup takes the row tiles blockIdx.y, blockIdx.y + gridDim.y, ...: with one workgroup
   // per column tile (gridDim.y = 1) the stores of a row tile drain while the next one is being
   // computed, instead of holding the compute unit until they are out.
@@ -148,14 +165,17 @@ __global__ __launch_bounds__(2 * BM) void pointwise_mfma_kernel(
     }
   };
 
-  Patch<F32, CPT> raw;  // the one chunk of activations in flight
+  Patch<FORM, CPT> raw;  // the one chunk of activations in flight
   // activations: quantise, transpose the CPT x 4 patch, store with the n rows permuted
-  auto stage_patch = [&](const Patch<F32, CPT> &pt, const Quant &quant, auto fast_c) {
+  auto stage_patch = [&](const Patch<FORM, CPT> &pt, const Quant &quant, auto fast_c) {
     constexpr bool FAST = decltype(fast_c)::value;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       uint32_t pk[I8W ? (CPT / 4) : (CPT / 2)];
-      if constexpr (I8W) {
+      if constexpr (I8W && WORDS) {
+#pragma unroll
+        for (int r = 0; r < CPT; r += 4) pk[r / 4] = pt.q[r / 4][i];
+      } else if constexpr (I8W) {
 #pragma unroll
         for (int r = 0; r < CPT; r += 4) {
           const uint32_t c0 = (uint32_t)(int)pt.template level<FAST>(r, i, quant) & 0xFFu;
@@ -187,7 +207,7 @@ __global__ __launch_bounds__(2 * BM) void pointwise_mfma_kernel(
 
   // this thread's four positions in channel kq * CPT of chunk 0
   constexpr uint32_t XB = F32 ? 4u : 1u;  // bytes of an activation
-  const uint32_t xoff = ((uint32_t)(kq * CPT) * (uint32_t)k + (uint32_t)(n0 + 4 * g)) * XB;
+  const uint32_t xoff = (uint32_t)(kq * CPT) * (uint32_t)k * XB + (uint32_t)(n0 + 4 * g) * (WORDS ? 4u : XB);
   load_w(0);
   raw.load(xdesc, xoff, k);
   for (int kc = 0; kc < nchunks; ++kc) {
@@ -291,7 +311,7 @@ __global__ __launch_bounds__(2 * BM) void pointwise_mfma_kernel(
 
 template <int BM, int BN, bool I8W>
 hipError_t mfma_launch(const wcc_desc &d, int64_t k, const void *w, const float *w_scale,
-                       const void *xc, bool f32, const float *alpha, int n_alpha, float *alpha_out,
+                       const void *xc, int form, const float *alpha, int n_alpha, float *alpha_out,
                        float *yc, hipStream_t s) {
   dim3 grid((unsigned)((k + BN - 1) / BN), (d.C_out + BM - 1) / BM, d.B), block(2 * BM);
   // several row tiles: one workgroup walks them all where the column tiles alone fill the chip
@@ -300,11 +320,12 @@ hipError_t mfma_launch(const wcc_desc &d, int64_t k, const void *w, const float 
   // better left there (measured); beyond that the output is streamed past it.
   const bool stream_out = (int64_t)d.B * d.C_out * k * 4 > ((int64_t)512 << 20);
   const bool rag = d.C_in % (I8W ? 16 : 8) != 0;
-#define WCC_STREAM(F32, RAG)                                                                          \
-  hipLaunchKernelGGL((pointwise_mfma_kernel<BM, BN, F32, I8W, RAG>), grid, block, 0, s, w, w_scale,   \
+#define WCC_STREAM(FORM, RAG)                                                                         \
+  hipLaunchKernelGGL((pointwise_mfma_kernel<BM, BN, FORM, I8W, RAG>), grid, block, 0, s, w, w_scale,   \
                      xc, alpha, n_alpha, alpha_out, yc, d.C_out, d.C_in, k, stream_out)
-  if (f32) { if (rag) WCC_STREAM(true, true); else WCC_STREAM(true, false); }
-  else     { if (rag) WCC_STREAM(false, true); else WCC_STREAM(false, false); }
+  if (form == kFloats)     { if (rag) WCC_STREAM(kFloats, true); else WCC_STREAM(kFloats, false); }
+  else if (form == kWords) { if (rag) WCC_STREAM(kWords, true); else WCC_STREAM(kWords, false); }
+  else                     { if (rag) WCC_STREAM(kCodes, true); else WCC_STREAM(kCodes, false); }
 #undef WCC_STREAM
   return hipGetLastError();
 }
@@ -564,7 +585,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(PackJob job) {
   if (e < job.total) job.out[e] = pack_piece(job, e);
 }
 
-template <bool I8W, int WM, int CB>
+template <bool I8W, int WM, int CB, bool WORDS>
 __global__ __launch_bounds__(256, CB == 4 ? 2 : 3) void pointwise_wide_kernel(
     const uint4 *__restrict__ w, const float *__restrict__ w_scale, const int8_t *__restrict__ xq,
     const float *__restrict__ alpha, int n_alpha, float *alpha_out, float *__restrict__ yc, int M,
@@ -621,26 +642,46 @@ __global__ __launch_bounds__(256, CB == 4 ? 2 : 3) void pointwise_wide_kernel(
     a[ks][1] = __builtin_amdgcn_raw_buffer_load_b128(wdesc, at + (uint32_t)stages * 4096u, 0, 0);
   };
   // activations: CPT channels x 4 positions a patch
-  uint32_t x[PT][CPT];
+  uint32_t x[PT][WORDS ? 1 : CPT];
+  word4 xw[PT][WORDS ? CPT / 4 : 1];  // (C_in is a multiple of four)
   uint32_t xcol[PT];
 #pragma unroll
   for (int p = 0; p < PT; ++p) {
     const int e = t + 256 * p, g = e % NG, kq = e / NG;
-    xcol[p] = (uint32_t)(n0 + 4 * g) + (uint32_t)(kq * CPT) * (uint32_t)k;
+    xcol[p] = (uint32_t)(n0 + 4 * g) * (WORDS ? 4u : 1u) + (uint32_t)(kq * CPT) * (uint32_t)k;
   }
   auto load_x = [&](int st) {
 #pragma unroll
     for (int p = 0; p < PT; ++p)
 #pragma unroll
-      for (int c = 0; c < CPT; ++c)
-        x[p][c] = __builtin_amdgcn_raw_buffer_load_b32(xdesc, xcol[p] + (uint32_t)(st * KC + c) * (uint32_t)k, 0, 0);
+      for (int c = 0; c < CPT; c += WORDS ? 4 : 1) {
+        const uint32_t at = xcol[p] + (uint32_t)(st * KC + c) * (uint32_t)k;
+        if constexpr (WORDS) xw[p][c / 4] = __builtin_amdgcn_raw_buffer_load_b128(xdesc, at, 0, 0);
+        else x[p][c] = __builtin_amdgcn_raw_buffer_load_b32(xdesc, at, 0, 0);
+      }
   };
   auto stash = [&](int buf) {
 #pragma unroll
     for (int p = 0; p < PT; ++p) {
       const int e = t + 256 * p, g = e % NG, kq = e / NG;
       uint32_t o[4][CPT * ESZ / 4];  // [position][words]
-      if constexpr (I8W) {
+      if constexpr (WORDS) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int c = 0; c < CPT; c += 4) {
+            const uint32_t four = xw[p][c / 4][i];
+            if constexpr (I8W) {
+              o[i][c / 4] = four;
+            } else {
+              float f[4];
+#pragma unroll
+              for (int u = 0; u < 4; ++u) f[u] = (float)((int)(four << (24 - 8 * u)) >> 24);
+              o[i][c / 2] = __builtin_amdgcn_perm(__float_as_uint(f[1]), __float_as_uint(f[0]), 0x07060302u);
+              o[i][c / 2 + 1] = __builtin_amdgcn_perm(__float_as_uint(f[3]), __float_as_uint(f[2]), 0x07060302u);
+            }
+          }
+      } else if constexpr (I8W) {
 #pragma unroll
         for (int c = 0; c < CPT; c += 4) {
           const uint32_t lo01 = __builtin_amdgcn_perm(x[p][c + 1], x[p][c], 0x05010400u);
@@ -744,16 +785,21 @@ __global__ __launch_bounds__(256, CB == 4 ? 2 : 3) void pointwise_wide_kernel(
 
 template <bool I8W, int WM, int CB>
 hipError_t wide_launch(const wcc_desc &d, int64_t k, const uint4 *packed, const float *w_scale, const void *xc,
-                       const float *alpha, int n_alpha, float *alpha_out, float *yc, hipStream_t s) {
+                       bool words, const float *alpha, int n_alpha, float *alpha_out, float *yc, hipStream_t s) {
   constexpr int TM = 64 * WM, TN = 32 * CB * (4 / WM);
   const int64_t gx = (k + TN - 1) / TN, gy = (d.C_out + TM - 1) / TM;
   const int64_t tiles = gx * gy * d.B;
   if (tiles > (int64_t)1 << 30) return hipErrorInvalidValue;
   dim3 grid((unsigned)((tiles + kDies - 1) / kDies * kDies)), block(256);
   const bool stream_out = (int64_t)d.B * d.C_out * k * 4 > ((int64_t)512 << 20);
-  hipLaunchKernelGGL((pointwise_wide_kernel<I8W, WM, CB>), grid, block, 0, s, packed, w_scale,
-                     static_cast<const int8_t *>(xc), alpha, n_alpha, alpha_out, yc, d.C_out, d.C_in, k,
-                     stream_out, (int)gx, (int)gy, (int)tiles);
+  if (words)
+    hipLaunchKernelGGL((pointwise_wide_kernel<I8W, WM, CB, true>), grid, block, 0, s, packed, w_scale,
+                       static_cast<const int8_t *>(xc), alpha, n_alpha, alpha_out, yc, d.C_out, d.C_in, k,
+                       stream_out, (int)gx, (int)gy, (int)tiles);
+  else
+    hipLaunchKernelGGL((pointwise_wide_kernel<I8W, WM, CB, false>), grid, block, 0, s, packed, w_scale,
+                       static_cast<const int8_t *>(xc), alpha, n_alpha, alpha_out, yc, d.C_out, d.C_in, k,
+                       stream_out, (int)gx, (int)gy, (int)tiles);
   return hipGetLastError();
 }
 
@@ -792,11 +838,11 @@ static bool wants_tile_kernel(const wcc_desc &d, int64_t k, bool f32) {
 // once), as long as they give every compute unit a workgroup; otherwise smaller ones.
 template <bool I8W>
 hipError_t mfma_dispatch(const wcc_desc &d, int64_t k, const void *w, const float *w_scale,
-                         const void *xc, bool f32, const float *alpha, int n_alpha, float *alpha_out,
+                         const void *xc, int form, const float *alpha, int n_alpha, float *alpha_out,
                          float *yc, hipStream_t s) {
 #define WCC_MFMA(BM_, BN_) \
-  return mfma_launch<BM_, BN_, I8W>(d, k, w, w_scale, xc, f32, alpha, n_alpha, alpha_out, yc, s)
-  if (wants_tile_kernel(d, k, f32))
+  return mfma_launch<BM_, BN_, I8W>(d, k, w, w_scale, xc, form, alpha, n_alpha, alpha_out, yc, s)
+  if (form != kWords && wants_tile_kernel(d, k, form == kFloats))
     return tile_launch<I8W>(d, k, w, w_scale, xc, alpha, n_alpha, alpha_out, yc, s);
   const int64_t want = 256;  // compute units
   auto wgs = [&](int bm, int bn) {
@@ -1065,7 +1111,7 @@ hipError_t launch_pack(const PackJob &job, hipStream_t s) {
 }
 
 hipError_t launch_pointwise_packed(const wcc_desc &d, int64_t k, const PackJob &job, const float *w_scale,
-                                   const void *xc, const float *alpha, int n_alpha, float *alpha_out,
+                                   const void *xc, bool words, const float *alpha, int n_alpha, float *alpha_out,
                                    float *yc, hipStream_t s) {
   // The largest tile that still gives a compute unit two workgroups: 256 x 128, or 128 x 128 for layers of up
   // to 128 rows; else 256 x 64, also for those: half its waves then multiply zeros, but it makes twice the
@@ -1074,35 +1120,43 @@ hipError_t launch_pointwise_packed(const wcc_desc &d, int64_t k, const PackJob &
   auto wgs = [&](int tm, int tn) { return (k + tn - 1) / tn * ((d.C_out + tm - 1) / tm) * (int64_t)d.B; };
 #define WCC_WIDE(WM, CB)                                                                                          \
   return job.wt == WCC_BF16                                                                                       \
-             ? wide_launch<false, WM, CB>(d, k, job.out, w_scale, xc, alpha, n_alpha, alpha_out, yc, s)           \
-             : wide_launch<true, WM, CB>(d, k, job.out, w_scale, xc, alpha, n_alpha, alpha_out, yc, s)
+             ? wide_launch<false, WM, CB>(d, k, job.out, w_scale, xc, words, alpha, n_alpha, alpha_out, yc, s)           \
+             : wide_launch<true, WM, CB>(d, k, job.out, w_scale, xc, words, alpha, n_alpha, alpha_out, yc, s)
   if (d.C_out > 128 && wgs(256, 128) >= 512) WCC_WIDE(4, 4);
   if (d.C_out <= 128 && wgs(128, 128) >= 512) WCC_WIDE(2, 2);
   WCC_WIDE(4, 2);
 #undef WCC_WIDE
 }
 
-hipError_t launch_pointwise(const wcc_desc &d, int64_t k, const void *w, const float *w_scale,
-                            const void *xc, bool xc_is_f32, const float *alpha, int n_alpha,
-                            float *alpha_out, float *yc, hipStream_t s) {
-  const bool quant = d.act_quant_bits == 8;
+// The layers of the stream kernel: rows of yc of whole words of four, rows of the weights of whole dwords, and 32-bit byte offsets
+// into the activations (xbytes of them a sample) and the weights (more take the fp32 kernel).
+static bool wants_stream_kernel(const wcc_desc &d, int64_t k, int64_t xbytes) {
   const int K = d.C_in;
-  // the matrix-core kernels address the activations and the weights with 32-bit byte offsets
-  // (4 GB of weights or of one sample's compressed signal take the plain kernel below)
   const int64_t limit = (int64_t)0xFFFFFFF0;
-  const bool narrow = (int64_t)(d.C_out + 256) * K * 2 <= limit && (int64_t)K * k * (xc_is_f32 ? 4 : 1) <= limit;
   // (Few channels into few rows leave the stream kernel's large tile, 128 rows x 64 channels, mostly empty: the
   // fp32 kernel's 32 rows x 16 channels fit them.  8 -> 8 channels, int8 weights, 15 x 265760 positions: 205 us
   // there, 94 here; 32 -> 16, 8 x 100000: 52 and 32; 40 -> 32, bf16, 4 x 60000: 17.1 and 16.8; 64 -> 32: 17.9 and
   // 21.7.  The sums of int8 codes are exact either way: 32 * 127 * 127 < 2^24.  Signals too short for that tile stay
   // with the 64 x 64 one: 24 -> 4, quantised on load, 8 x 2688, 5.0 us there and 5.7; 32 -> 16, 4 x 3840, 5.7 and 5.3.)
   const bool few = K <= 32 && d.C_out <= 32 && (k + 127) / 128 * (int64_t)d.B >= 256;
-  if (narrow && quant && k % 4 == 0 && !few) {
-    // (rows of the weights start at whole dwords)
-    if (d.w_dtype == WCC_BF16 && K % 2 == 0)
-      return mfma_dispatch<false>(d, k, w, w_scale, xc, xc_is_f32, alpha, n_alpha, alpha_out, yc, s);
-    if (d.w_dtype == WCC_I8 && K % 4 == 0)
-      return mfma_dispatch<true>(d, k, w, w_scale, xc, xc_is_f32, alpha, n_alpha, alpha_out, yc, s);
+  if (d.act_quant_bits != 8 || k % 4 != 0 || few) return false;
+  if ((int64_t)(d.C_out + 256) * K * 2 > limit || xbytes > limit) return false;
+  return d.w_dtype == WCC_BF16 ? K % 2 == 0 : (d.w_dtype == WCC_I8 || d.w_dtype == WCC_I4) && K % 4 == 0;
+}
+
+bool pointwise_takes_words(const wcc_desc &d, int64_t k) {
+  return wants_stream_kernel(d, k, (int64_t)(d.C_in + 3) / 4 * 4 * k) && !wants_tile_kernel(d, k, false);
+}
+
+hipError_t launch_pointwise(const wcc_desc &d, int64_t k, const void *w, const float *w_scale,
+                            const void *xc, bool xc_is_f32, bool words, const float *alpha, int n_alpha,
+                            float *alpha_out, float *yc, hipStream_t s) {
+  const bool quant = d.act_quant_bits == 8;
+  if (words && !pointwise_takes_words(d, k)) return hipErrorInvalidValue;
+  if (wants_stream_kernel(d, k, (int64_t)d.C_in * k * (xc_is_f32 ? 4 : 1))) {
+    const int form = words ? kWords : xc_is_f32 ? kFloats : kCodes;
+    if (d.w_dtype == WCC_BF16) return mfma_dispatch<false>(d, k, w, w_scale, xc, form, alpha, n_alpha, alpha_out, yc, s);
+    if (d.w_dtype == WCC_I8) return mfma_dispatch<true>(d, k, w, w_scale, xc, form, alpha, n_alpha, alpha_out, yc, s);
   }
   const int xm = !quant ? 0 : (xc_is_f32 ? 2 : 1);
   switch (d.w_dtype) {

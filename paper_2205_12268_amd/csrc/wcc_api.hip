@@ -171,16 +171,16 @@ WsLayout ws_layout(const wcc_desc &d, int front, bool pad) {
 
 // The contraction, with 4-bit weight codes widened to int8 in the workspace first.
 hipError_t pointwise_any(char *ws, const WsLayout &L, const wcc_desc &d, int64_t k, const void *w,
-                         const float *w_scale, const void *xc, bool xc_is_f32, const float *alpha,
+                         const float *w_scale, const void *xc, bool xc_is_f32, bool words, const float *alpha,
                          int n_alpha, float *alpha_out, float *yc, hipStream_t s) {
   if (d.w_dtype != WCC_I4)
-    return launch_pointwise(d, k, w, w_scale, xc, xc_is_f32, alpha, n_alpha, alpha_out, yc, s);
+    return launch_pointwise(d, k, w, w_scale, xc, xc_is_f32, words, alpha, n_alpha, alpha_out, yc, s);
   int8_t *w8 = reinterpret_cast<int8_t *>(ws + L.w8);
   const hipError_t e = launch_unpack_i4(static_cast<const uint8_t *>(w), w8, (int64_t)d.C_out * d.C_in, s);
   if (e != hipSuccess) return e;
   wcc_desc d8 = d;
   d8.w_dtype = WCC_I8;
-  return launch_pointwise(d8, k, w8, w_scale, xc, xc_is_f32, alpha, n_alpha, alpha_out, yc, s);
+  return launch_pointwise(d8, k, w8, w_scale, xc, xc_is_f32, words, alpha, n_alpha, alpha_out, yc, s);
 }
 
 // Where the index set I of a layer comes from.
@@ -247,7 +247,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   int n_alpha = early ? 1 : kAlphaSlots;
   float *top = early ? reinterpret_cast<float *>(ws + L.max_part) : nullptr;
   // Packed weights go where the codes leave room: xc32 is sized for fp32.
-  const size_t codes_bytes = align256((size_t)d.B * d.C_in * ks), xc_bytes = (size_t)d.B * d.C_in * ks * 4;
+  const size_t codes_bytes = align256((size_t)d.B * ((d.C_in + 3) / 4 * 4) * ks), xc_bytes = (size_t)d.B * d.C_in * ks * 4;
   PackJob pack{nullptr, nullptr, 0, 0, 0, 0, 0};
   if (!tail && codes_now && xc_bytes > codes_bytes)
     pack = pack_job(d, ks, w, ws + L.xc32 + codes_bytes, xc_bytes - codes_bytes);
@@ -270,6 +270,8 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   // 33.5 us, three 31.6).  The launch stays where it has something else to write: the caller's copy of the list, the
   // caller's alpha or the cleared slots.
   if (list == kListPrefix && !tail && idx_out == nullptr && (!quant || wg_max)) jmap = nullptr;
+  // Four channels' codes a word, where this pass decides them from x itself and the contraction reads such words.
+  const bool words = codes_now && !tail && !src && !wdw && keep_in_quads(d) && (pack.total > 0 || pointwise_takes_words(d, ks));
   if (list == kListSelect) {
     // A: the transform, first pass: only the channel norms of X_wt leave the chip (the same
     // kernel clears the selection state)
@@ -306,6 +308,9 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
     WCC_TRY(launch_chain_keep(d, ks, *src, wdw, jmap, xc32, late ? slots : nullptr,
                               (given && codes_now) ? alpha_in : 0.f, early ? tops : nullptr, n_top,
                               early ? slots : nullptr, s));
+  else if (words)
+    WCC_TRY(launch_haar_keep_quads(d, ks, x, jmap, reinterpret_cast<uint32_t *>(xc32), given ? alpha_in : 0.f,
+                                   early ? tops : nullptr, n_top, early ? slots : nullptr, k, s));
   else
     WCC_TRY(launch_haar_keep(d, ks, x, jmap, xc32, (late && !wg_max) ? slots : nullptr, wg_max, wdw,
                              (given && codes_now) ? alpha_in : 0.f, early ? tops : nullptr, n_top,
@@ -326,9 +331,9 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   WCC_TRY(mark(WCC_T_POINTWISE, 0));
   if (pack.total > 0) {
     if (!packed) WCC_TRY(launch_pack(pack, s));
-    WCC_TRY(launch_pointwise_packed(d, ks, pack, w_scale, xc32, slots, n_alpha, alpha_out_dev, yc, s));
+    WCC_TRY(launch_pointwise_packed(d, ks, pack, w_scale, xc32, words, slots, n_alpha, alpha_out_dev, yc, s));
   } else {
-    WCC_TRY(pointwise_any(ws, L, d, ks, w, w_scale, xc32, !codes_now, wg_max ? wg_max : slots, n_alpha,
+    WCC_TRY(pointwise_any(ws, L, d, ks, w, w_scale, xc32, !codes_now, words, wg_max ? wg_max : slots, n_alpha,
                           quant ? alpha_out_dev : nullptr, yc, s));
   }
   WCC_TRY(mark(WCC_T_POINTWISE, 1));
@@ -581,7 +586,7 @@ wcc_status wcc_pointwise(wcc_ctx *ctx, const wcc_desc *desc, const void *w, cons
   const WsLayout L = ws_layout(*desc);
   if (desc->w_dtype == WCC_I4 && (st = need_ws(ctx, L)) != WCC_OK) return st;
   WCC_TRY(pointwise_any(static_cast<char *>(ctx->ws), L, *desc, kept_count(*desc), w, w_scale, xc,
-                        desc->act_quant_bits == 0, alpha_dev, 1, nullptr, yc,
+                        desc->act_quant_bits == 0, false, alpha_dev, 1, nullptr, yc,
                         static_cast<hipStream_t>(stream)));
   return WCC_OK;
 }

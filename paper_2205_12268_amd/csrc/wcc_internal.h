@@ -273,6 +273,10 @@ hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const i
                             float q_alpha, const float *alpha_src /*nullable*/, int n_alpha,
                             float *alpha_pub /*nullable: receives that largest value*/,
                             int64_t prefix /*jmap null: the positions kept, the first ones*/, hipStream_t s);
+// The same pass writing codes of four channels a word, xw [B, ceil(C / 4), k]; alpha as above, known beforehand.
+bool keep_in_quads(const wcc_desc &d);
+hipError_t launch_haar_keep_quads(const wcc_desc &d, int64_t ks, const void *x, const int32_t *jmap, uint32_t *xw, float q_alpha,
+                                  const float *alpha_src, int n_alpha, float *alpha_pub, int64_t prefix, hipStream_t s);
 hipError_t launch_norm_reduce(const float *norm_part, const StorePlan &sp, int64_t BN, float *norm, hipStream_t s);
 hipError_t launch_channel_norm(const float *coef, int B, int C, int64_t N, bool squares, float *norm,
                                hipStream_t s);
@@ -324,14 +328,17 @@ hipError_t launch_quantize(const float *xc32, int64_t n, const float *alpha_src,
 // alpha points at n_alpha partial maxima whose largest is the clipping parameter (combined in
 // the kernel, and written to alpha_out[0] if that is not null); n_alpha = 1: alpha itself.
 hipError_t launch_pointwise(const wcc_desc &d, int64_t k, const void *w, const float *w_scale,
-                            const void *xc, bool xc_is_f32, const float *alpha, int n_alpha,
+                            const void *xc, bool xc_is_f32, bool words, const float *alpha, int n_alpha,
                             float *alpha_out, float *yc, hipStream_t s);
+// words: xc is codes of four channels a word, [B, ceil(C_in / 4), k], for layers that pointwise_takes_words() or packed
+// weights
+bool pointwise_takes_words(const wcc_desc &d, int64_t k);
 // The contraction on packed weights (int8 codes in): pack_job says whether the layer takes it (total
 // > 0) given `room` for them; launch_select or launch_pack carries the job out.
 PackJob pack_job(const wcc_desc &d, int64_t k, const void *w, void *room, size_t room_bytes);
 hipError_t launch_pack(const PackJob &job, hipStream_t s);
 hipError_t launch_pointwise_packed(const wcc_desc &d, int64_t k, const PackJob &job, const float *w_scale,
-                                   const void *xc, const float *alpha, int n_alpha, float *alpha_out,
+                                   const void *xc, bool words, const float *alpha, int n_alpha, float *alpha_out,
                                    float *yc, hipStream_t s);
 // scratch: kInvScratchBytes of device memory that the kernel may overwrite with anything
 // residual (nullable): [B, C_out, H, W] added to the result (may be y itself); jmap, prefix as in launch_haar_keep
