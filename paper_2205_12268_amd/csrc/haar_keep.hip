@@ -10,8 +10,9 @@ namespace {
 // n_alpha entries (what the selection found as max |kept coefficient|); alpha_slots and wg_max must
 // be null then.  Otherwise the workgroup's max |kept coefficient| goes to wg_max[its number] (a plain
 // store, combined by the consumer) or raises one of the alpha slots (both nullable).
-// jmap null: the first `prefix` positions are kept, each its own rank.
-template <int D, int V, int PF, int DWM, bool Q8, class XT, bool NT = false>
+// PREFIX: the first `prefix` positions are kept, each its own rank (jmap unused).  An instance of its own: a branch in the others
+// costs the smallest layers 0.1 us of instruction fetches.
+template <int D, int V, int PF, int DWM, bool Q8, class XT, bool NT = false, bool PREFIX = false>
 __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x,
                                                         const int32_t *__restrict__ jmap,
                                                         void *__restrict__ xc, float *alpha_slots,
@@ -65,12 +66,12 @@ __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x
     if constexpr (D >= 3) each_level(std::integral_constant<int, 3>{});
     if constexpr (D >= 4) each_level(std::integral_constant<int, 4>{});
   };
-  if (jmap != nullptr) {  // (uniform over the grid)
-    const int32_t *jm = jmap + (size_t)b * g.N;
-    ranks([&](int at) { return jm[at]; });
-  } else {
+  if constexpr (PREFIX) {
     const int first = (int)prefix;
     ranks([&](int at) { return at < first ? at : -1; });
+  } else {
+    const int32_t *jm = jmap + (size_t)b * g.N;
+    ranks([&](int at) { return jm[at]; });
   }
   if constexpr (Q8) {
     // The clipping parameter the selection found: the largest of its workgroups' maxima.  Taken
@@ -499,7 +500,7 @@ __global__ __launch_bounds__(256) void haar_keep_quads_kernel(const XT *__restri
                                                               uint32_t *__restrict__ xw, Geo g, StripMap m, int C,
                                                               int64_t ks, float q_alpha,
                                                               const float *__restrict__ alpha_src, int n_alpha,
-                                                              float *alpha_pub, int64_t prefix) {
+                                                              float *alpha_pub) {
   constexpr int NS = slot_count(D, V), R = 1 << D;
   constexpr bool kStaged = (V == 4 && (D == 2 || D == 3)) || D == 4;
   constexpr int kRankBits = 20;  // list entry = rank | tile index << 20
@@ -514,40 +515,32 @@ __global__ __launch_bounds__(256) void haar_keep_quads_kernel(const XT *__restri
 
   // ranks of this lane's positions, or -1
   int at[NS];
-  auto ranks = [&](auto &&rank_of) {
-    auto fetch = [&](auto Lc, auto Jc) {
-      constexpr int L = decltype(Lc)::value, J = decltype(Jc)::value;
-      constexpr int CV = cols_at(V, L), S2 = span_at(V, L);
-      const bool owner = (S2 == 1) || ((p.lc & (S2 - 1)) == 0);
+  const int32_t *jm = jmap + (size_t)b * g.N;
+  auto fetch = [&](auto Lc, auto Jc) {
+    constexpr int L = decltype(Lc)::value, J = decltype(Jc)::value;
+    constexpr int CV = cols_at(V, L), S2 = span_at(V, L);
+    const bool owner = (S2 == 1) || ((p.lc & (S2 - 1)) == 0);
 #pragma unroll
-      for (int i = 0; i < rows_at(D, L); ++i)
+    for (int i = 0; i < rows_at(D, L); ++i)
 #pragma unroll
-        for (int e = 0; e < CV; ++e) {
-          constexpr int base = slot_base(D, V, L, J);
-          int j = -1;
-          if (active && owner) j = rank_of(J * p.nl[L] + p.off[L] + i * p.rowlen[L] + e);
-          at[base + i * CV + e] = j;
-        }
-    };
-    auto each_level = [&](auto Lc) {
-      constexpr int L = decltype(Lc)::value;
-      fetch(Lc, std::integral_constant<int, 1>{});
-      fetch(Lc, std::integral_constant<int, 2>{});
-      fetch(Lc, std::integral_constant<int, 3>{});
-      if constexpr (L == D) fetch(Lc, std::integral_constant<int, 0>{});
-    };
-    each_level(std::integral_constant<int, 1>{});
-    if constexpr (D >= 2) each_level(std::integral_constant<int, 2>{});
-    if constexpr (D >= 3) each_level(std::integral_constant<int, 3>{});
-    if constexpr (D >= 4) each_level(std::integral_constant<int, 4>{});
+      for (int e = 0; e < CV; ++e) {
+        constexpr int base = slot_base(D, V, L, J);
+        int j = -1;
+        if (active && owner) j = jm[J * p.nl[L] + p.off[L] + i * p.rowlen[L] + e];
+        at[base + i * CV + e] = j;
+      }
   };
-  if (jmap != nullptr) {  // (uniform over the grid)
-    const int32_t *jm = jmap + (size_t)b * g.N;
-    ranks([&](int pos) { return jm[pos]; });
-  } else {
-    const int first = (int)prefix;
-    ranks([&](int pos) { return pos < first ? pos : -1; });
-  }
+  auto each_level = [&](auto Lc) {
+    constexpr int L = decltype(Lc)::value;
+    fetch(Lc, std::integral_constant<int, 1>{});
+    fetch(Lc, std::integral_constant<int, 2>{});
+    fetch(Lc, std::integral_constant<int, 3>{});
+    if constexpr (L == D) fetch(Lc, std::integral_constant<int, 0>{});
+  };
+  each_level(std::integral_constant<int, 1>{});
+  if constexpr (D >= 2) each_level(std::integral_constant<int, 2>{});
+  if constexpr (D >= 3) each_level(std::integral_constant<int, 3>{});
+  if constexpr (D >= 4) each_level(std::integral_constant<int, 4>{});
   if (alpha_src != nullptr) {  // (uniform over the grid; behind the rank loads)
     q_alpha = alpha_max(alpha_src, n_alpha);
     if (alpha_pub != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0)
@@ -713,6 +706,16 @@ hipError_t keep_launch_t(const wcc_desc &d, int64_t k, const XT *x, const int32_
   const int cstep = wdw == nullptr ? pl.G : 1;
   dim3 grid((m.units + 3) / 4, pl.G, d.B);
   const bool q8 = q_alpha > 0.f || alpha_src != nullptr;
+  if (jmap == nullptr) {  // the first positions; alpha, if any, is found in this pass
+    if (q8 || wdw != nullptr) return hipErrorInvalidValue;
+    if (pl.stream)
+      hipLaunchKernelGGL((haar_keep_kernel<D, V, 1, 0, false, XT, true, true>), grid, dim3(256), 0, s, x, jmap, xc, alpha_slots,
+                         wg_max, g, m, d.C_in, Cg, cstep, k, wdw, 0.f, nullptr, 0, nullptr, prefix);
+    else
+      hipLaunchKernelGGL((haar_keep_kernel<D, V, 1, 0, false, XT, false, true>), grid, dim3(256), 0, s, x, jmap, xc, alpha_slots,
+                         wg_max, g, m, d.C_in, Cg, cstep, k, wdw, 0.f, nullptr, 0, nullptr, prefix);
+    return hipGetLastError();
+  }
 #define WCC_KEEP(PF, DWM)                                                                          \
   do {                                                                                             \
     if (q8)                                                                                        \
@@ -783,26 +786,26 @@ bool keep_in_quads(const wcc_desc &d) { return quad_groups(d) > 0; }
 
 template <int D, int V, class XT>
 static hipError_t quads_launch(const wcc_desc &d, int64_t ks, const void *x, const int32_t *jmap, uint32_t *xw, float q_alpha,
-                               const float *alpha_src, int n_alpha, float *alpha_pub, int64_t prefix, hipStream_t s) {
+                               const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
   const Geo g{d.H, d.W, d.levels, (int64_t)d.H * d.W};
   const StripMap m = keep_map(d, false);
   const dim3 grid((m.units + 3) / 4, quad_groups(d), d.B);
   if (streams(d))
     hipLaunchKernelGGL((haar_keep_quads_kernel<D, V, XT, true>), grid, dim3(256), 0, s, static_cast<const XT *>(x), jmap, xw, g,
-                       m, d.C_in, ks, q_alpha, alpha_src, n_alpha, alpha_pub, prefix);
+                       m, d.C_in, ks, q_alpha, alpha_src, n_alpha, alpha_pub);
   else
     hipLaunchKernelGGL((haar_keep_quads_kernel<D, V, XT, false>), grid, dim3(256), 0, s, static_cast<const XT *>(x), jmap, xw, g,
-                       m, d.C_in, ks, q_alpha, alpha_src, n_alpha, alpha_pub, prefix);
+                       m, d.C_in, ks, q_alpha, alpha_src, n_alpha, alpha_pub);
   return hipGetLastError();
 }
 
 hipError_t launch_haar_keep_quads(const wcc_desc &d, int64_t ks, const void *x, const int32_t *jmap, uint32_t *xw, float q_alpha,
-                                  const float *alpha_src, int n_alpha, float *alpha_pub, int64_t prefix, hipStream_t s) {
+                                  const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s) {
   if (!keep_in_quads(d)) return hipErrorInvalidValue;
 #define WCC_QUADS(D, V)                                                                                                 \
   return d.act_dtype == WCC_BF16                                                                                        \
-             ? quads_launch<D, V, bf16_t>(d, ks, x, jmap, xw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s)        \
-             : quads_launch<D, V, float>(d, ks, x, jmap, xw, q_alpha, alpha_src, n_alpha, alpha_pub, prefix, s)
+             ? quads_launch<D, V, bf16_t>(d, ks, x, jmap, xw, q_alpha, alpha_src, n_alpha, alpha_pub, s)        \
+             : quads_launch<D, V, float>(d, ks, x, jmap, xw, q_alpha, alpha_src, n_alpha, alpha_pub, s)
   switch (d.levels) {
     case 1: if (lane_cols(d) == 4) WCC_QUADS(1, 4); else WCC_QUADS(1, 2);
     case 2: WCC_QUADS(2, 4);

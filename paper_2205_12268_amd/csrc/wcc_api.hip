@@ -310,7 +310,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
                               early ? slots : nullptr, s));
   else if (words)
     WCC_TRY(launch_haar_keep_quads(d, ks, x, jmap, reinterpret_cast<uint32_t *>(xc32), given ? alpha_in : 0.f,
-                                   early ? tops : nullptr, n_top, early ? slots : nullptr, k, s));
+                                   early ? tops : nullptr, n_top, early ? slots : nullptr, s));
   else
     WCC_TRY(launch_haar_keep(d, ks, x, jmap, xc32, (late && !wg_max) ? slots : nullptr, wg_max, wdw,
                              (given && codes_now) ? alpha_in : 0.f, early ? tops : nullptr, n_top,
