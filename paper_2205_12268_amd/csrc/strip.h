@@ -435,7 +435,9 @@ __device__ __forceinline__ DwLane dw_lane(const Geo &g, const StripMap &m, const
   return q;
 }
 
-template <int D, int V, bool EDGE, bool PEEL, bool NT, class XT, class Sink, class After>
+// QUADS: after() runs once per four channels, behind the loads that follow the quad before, and at the end; channels that fill the
+// last quad repeat the last one.
+template <int D, int V, bool EDGE, bool PEEL, bool NT, bool QUADS = false, class XT, class Sink, class After>
 __device__ __forceinline__ void channel_loop_dw(const XT *__restrict__ src,
                                                 const float *__restrict__ wdw, int64_t N, int n_ch,
                                                 const DwLane &q, const LanePos<D> &p, Sink &sink,
@@ -490,9 +492,22 @@ __device__ __forceinline__ void channel_loop_dw(const XT *__restrict__ src,
           for (int e = 0; e < V; ++e) tile[o][e] = fmaf(k[i * 3 + j], six[o + i][e + j], tile[o][e]);
     }
     fwd_levels<D, V, 1>(tile, p, sink);
-    after(sink);
+    if constexpr (!QUADS) after(sink);
   };
   load_tile(0, 0);
+  if constexpr (QUADS) {
+    for (int c = 0; c < n_ch; c += 4) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        load_tile((u + 1) & 1, c + u + 1);
+        if (u == 0) after(sink);
+        __builtin_amdgcn_sched_barrier(0);
+        transform(u & 1, min(c + u, n_ch - 1));
+      }
+    }
+    after(sink);
+    return;
+  }
   auto round = [&](int c) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {

@@ -271,7 +271,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
   // caller's alpha or the cleared slots.
   if (list == kListPrefix && !tail && idx_out == nullptr && (!quant || wg_max)) jmap = nullptr;
   // Four channels' codes a word, where this pass decides them from x itself and the contraction reads such words.
-  const bool words = codes_now && !tail && !src && !wdw && keep_in_quads(d) && (pack.total > 0 || pointwise_takes_words(d, ks));
+  const bool words = codes_now && !tail && !src && keep_in_quads(d, wdw != nullptr) && (pack.total > 0 || pointwise_takes_words(d, ks));
   if (list == kListSelect) {
     // A: the transform, first pass: only the channel norms of X_wt leave the chip (the same
     // kernel clears the selection state)
@@ -309,7 +309,7 @@ wcc_status forward_on(wcc_ctx *ctx, char *ws, const WsLayout &L, const wcc_desc 
                               (given && codes_now) ? alpha_in : 0.f, early ? tops : nullptr, n_top,
                               early ? slots : nullptr, s));
   else if (words)
-    WCC_TRY(launch_haar_keep_quads(d, ks, x, jmap, reinterpret_cast<uint32_t *>(xc32), given ? alpha_in : 0.f,
+    WCC_TRY(launch_haar_keep_quads(d, ks, x, jmap, reinterpret_cast<uint32_t *>(xc32), wdw, given ? alpha_in : 0.f,
                                    early ? tops : nullptr, n_top, early ? slots : nullptr, s));
   else
     WCC_TRY(launch_haar_keep(d, ks, x, jmap, xc32, (late && !wg_max) ? slots : nullptr, wg_max, wdw,

@@ -274,9 +274,9 @@ hipError_t launch_haar_keep(const wcc_desc &d, int64_t k, const void *x, const i
                             float *alpha_pub /*nullable: receives that largest value*/,
                             int64_t prefix /*jmap null: the positions kept, the first ones*/, hipStream_t s);
 // The same pass writing codes of four channels a word, xw [B, ceil(C / 4), k]; alpha as above, known beforehand.
-bool keep_in_quads(const wcc_desc &d);
-hipError_t launch_haar_keep_quads(const wcc_desc &d, int64_t ks, const void *x, const int32_t *jmap, uint32_t *xw, float q_alpha,
-                                  const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s);
+bool keep_in_quads(const wcc_desc &d, bool folded_dw);
+hipError_t launch_haar_keep_quads(const wcc_desc &d, int64_t ks, const void *x, const int32_t *jmap, uint32_t *xw,
+                                  const float *wdw /*nullable*/, float q_alpha, const float *alpha_src, int n_alpha, float *alpha_pub, hipStream_t s);
 hipError_t launch_norm_reduce(const float *norm_part, const StorePlan &sp, int64_t BN, float *norm, hipStream_t s);
 hipError_t launch_channel_norm(const float *coef, int B, int C, int64_t N, bool squares, float *norm,
                                hipStream_t s);
