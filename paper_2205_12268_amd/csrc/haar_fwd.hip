@@ -30,6 +30,7 @@ __global__ __launch_bounds__(WPU == 1 ? 256 : 64 * WPU) void haar_fwd_kernel(con
                                                        SelectPrep prep,
                                                        const float *__restrict__ wdw, int split) {
   constexpr int NS = slot_count(D, V);
+  fetch_args(x, m.units, prep.alpha_in);
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int unit = WPU > 1 ? (int)blockIdx.x : (int)blockIdx.x * 4 + wv;
   constexpr bool kSplit = STORE && WPU == 1;

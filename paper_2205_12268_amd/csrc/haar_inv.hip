@@ -131,6 +131,7 @@ __global__ __launch_bounds__(256) void scatter_ihaar_kernel(const float *__restr
   __shared__ __attribute__((aligned(16))) uint32_t tiles[kStaged ? 4 : 1][kStaged ? STRIDE * kWave : 1];
   __shared__ uint32_t shared_list[SHARE ? CAP : 1];
   __shared__ int shared_count[4];
+  fetch_args(jmap, m.units, gridDim.z);
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int unit = SHARE ? (int)blockIdx.x : (int)blockIdx.x * 4 + wv;
   // Samples are taken last to first: the contraction wrote yc first to last, so what is still

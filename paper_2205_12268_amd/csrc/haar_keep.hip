@@ -22,6 +22,7 @@ __global__ __launch_bounds__(256) void haar_keep_kernel(const XT *__restrict__ x
                                                         const float *__restrict__ alpha_src,
                                                         int n_alpha, float *alpha_pub, int64_t prefix) {
   __shared__ float wmax[4];
+  fetch_args(jmap, m.units, gridDim.z);
   const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int grp = blockIdx.y;
   // Samples are taken last to first: what the norm pass has left of x in the memory-side cache is its
@@ -237,6 +238,7 @@ __global__ __launch_bounds__(256) void haar_keep_words_kernel(const XT *__restri
   constexpr int D = WordSink::D, V = WordSink::V, NS = slot_count(D, V), R = 1 << D;
   __shared__ float wmax[4];
   __shared__ uint32_t tiles[4][NS * kWave];
+  fetch_args(jmap, m.units, gridDim.z);
   const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int unit = blockIdx.x * 4 + wv, grp = blockIdx.y, G = gridDim.y;
   const int b = gridDim.z - 1 - blockIdx.z;  // (last to first: what the norm pass left in the cache is the tail)
@@ -647,6 +649,7 @@ __global__ __launch_bounds__(256) void haar_keep_dw_quads_kernel(const float *__
                                                                  const float *__restrict__ alpha_src, int n_alpha,
                                                                  float *alpha_pub) {
   constexpr int NS = slot_count(D, V);
+  fetch_args(jmap, m.units, gridDim.z);
   const int unit = blockIdx.x * 4 + (threadIdx.x >> 6), grp = blockIdx.y;
   const int b = gridDim.z - 1 - blockIdx.z;
   LanePos<D> p;

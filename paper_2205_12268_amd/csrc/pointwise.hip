@@ -110,6 +110,7 @@ __global__ __launch_bounds__(2 * BM) void pointwise_mfma_kernel(
     int K, int64_t k, bool stream_out) {
   constexpr bool F32 = FORM == kFloats, WORDS = FORM == kWords;
   constexpr int T = 2 * BM;
+  fetch_args(w, k);
   constexpr int NB = BN / 32;                // 32-column blocks of the tile: 4 or 2
   constexpr int NG = BN / 4;                 // groups of four positions
   constexpr int CPT = BK / (T / NG);         // channels of a chunk per thread: 4, 8 or 16
@@ -591,6 +592,7 @@ __global__ __launch_bounds__(256, CB == 4 ? 2 : 3) void pointwise_wide_kernel(
     const float *__restrict__ alpha, int n_alpha, float *alpha_out, float *__restrict__ yc, int M,
     int K, int64_t k, bool stream_out, int gx, int gy, int tiles) {
   constexpr int ESZ = I8W ? 1 : 2;
+  fetch_args(w, k);
   constexpr int KB = 128, LDR = KB + 16;   // bytes of K a stage, LDS row bytes
   constexpr int KC = KB / ESZ;             // channels a stage: 64 or 128
   constexpr int WN = 4 / WM;               // waves along the positions
@@ -906,6 +908,7 @@ __global__ __launch_bounds__(256) void pointwise_f32_kernel(const void *__restri
                                                             float *__restrict__ yc, int M, int K,
                                                             int64_t k) {
   constexpr int TM = 32 * WVM * MB, TN = 32 * (4 / WVM) * NB;
+  fetch_args(w, k);
     constexpr int LDA = FK + 1, LDB = TN + 32;  // LDS row words: the 64 lanes of a read of Bs hit 64 banks
                                               // (of As 47; FK + 2, which makes that 64, measured the same)
   constexpr int NA = TM * FK / 256;           // weights a thread and stage

@@ -319,6 +319,7 @@ __global__ __launch_bounds__(kSmallThreads) void select_small_kernel(
   __shared__ uint32_t ends[2 * kSmallWaves];
   __shared__ uint32_t tmp[kSmallSlots * kSmallWaves];
   __shared__ uint32_t bcast[4];  // prefix, remaining rank, keys in the bin, entries in the list
+  fetch_args(src, job.total);
   const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int64_t BN = (int64_t)B * N;
   auto clear = [&]() {

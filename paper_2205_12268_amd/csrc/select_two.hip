@@ -78,6 +78,7 @@ __global__ __launch_bounds__(kThreads) void select_group_kernel(const float *src
   __shared__ __attribute__((aligned(16))) uint32_t lh[kFine];
   __shared__ __attribute__((aligned(16))) uint32_t sorted[kChunk];
   __shared__ uint32_t tmp[kWaves];
+  fetch_args(src, job.total);
   const int b = blockIdx.y, t = threadIdx.x;
   const int64_t c0 = (int64_t)blockIdx.x * kChunk;
   const int n = (int)min((int64_t)kChunk, N - c0);  // (a multiple of 4)
