@@ -29,8 +29,8 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "int8": 5000.0, "f32": 157.3}
 CACHE_BYTES = 256 << 20  # memory-side cache
 
 
-# stage of wcc_forward -> the kernel that takes its time (norm_select is four small kernels; where contraction and
-# inverse are one kernel, see fold_tail, a small one that counts kept positions stands in front of the gather's)
+# stage of wcc_forward -> the kernel that takes its time (norm_select is one, two or four small kernels; where contraction
+# and inverse are one kernel, see fold_tail, a small one that counts kept positions stands in front of the gather's)
 STAGE_KERNEL = {"haar_fwd": "haar_fwd_kernel", "gather": "haar_keep_kernel",
                 "pointwise": "pointwise", "scatter_ihaar": "scatter_ihaar_kernel"}
 
@@ -621,6 +621,8 @@ def main() -> int:
     dom = max(kernel_of, key=lambda n: stage_us[n])  # the single kernel that takes longest
     achieved = alg[dom] / (stage_us[dom] * 1e-6) / 1e9
     prof = os.path.join(ROOT, "profiles")
+    if dom == "gather" and contraction == "pointwise":
+        kernel_of[dom] = profiled_kernel_name(prof, cfg.name, "haar_keep", kernel_of[dom])
     traffic = read_traffic(prof, cfg.name, kernel_of[dom])
     x_bytes = act_bytes * pix_ch
     wname = {0: "f32", 1: "bf16", 2: "int8", 3: "int8"}[cfg.w_dtype] if cfg.act_bits == 8 else "f32"
