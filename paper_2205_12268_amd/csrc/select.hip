@@ -670,7 +670,7 @@ hipError_t launch_select(const wcc_desc &d, const float *norm_or_part, int G, fl
   }
   if (L.two_nblk > 0)
     return launch_select_two(d, norm_or_part, G, norm_out, k, ws + L.two_tables,
-                             reinterpret_cast<uint32_t *>(ws + L.norm_part), L.two_slots, L.two_nblk, idx, jmap, top_part, block_top, job, s);
+                             reinterpret_cast<uint32_t *>(ws + L.two_grouped), L.two_slots, L.two_nblk, idx, jmap, top_part, block_top, job, s);
   switch (L.sel_slots) {
     case 4: return launch_passes<4>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, job, s);
     case 2: return launch_passes<2>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, job, s);

@@ -18,12 +18,19 @@
 // the keys with digit D do not fit in LDS (large classes of equal keys, noise over many channels, whose norms
 // lie close together, scales outside that range) they are read from memory until those that still matter do.
 //
-// Bound by latency: 4.5 us for the first kernel, 8-9 for the second (its chain is two table reads and the segments,
-// 1 us each, another die wrote them, and a dozen barriers; 256 or 512 threads in place of 1024 take 9-11 us).  Measured
-// against the four launches, kernel times: 131072 positions 18.5 -> 13.7 us, 2 x 21200 (two planes of partial norms)
-// 17.0 -> 12.5, 4 x 61440 17.8 -> 12.3, 8 x 122880 21.5 -> 15.5, 4 x 524288 29.8 -> 23.  What it loses: planes of
-// which a tenth and more lies within one step (131072 equal keys 21 -> 60 us; norms of noise with a deviation of 3 %
-// 21 -> 20, of 1024 x 1024 35 -> 62): a plane of real coefficients has its ties at zero, a digit of their own.
+// Such digits are too coarse where norms lie close together (noise over many channels) or are equal (a blank frame): every
+// workgroup would read the whole class, which took 131072 equal keys 60 us.  So the first kernel looks at a few hundred
+// keys from all over the sample, the same ones in every workgroup: where too many fall into the step that rank k lies in, the
+// digits are cut by those keys instead, sorted, with a digit for what equals one of them.
+//
+// Bound by latency: 5 us for the first kernel, 8-9 for the second (its chain is two table reads and the segments,
+// 1 us each, another die wrote them, and a dozen barriers; 256 or 512 threads in place of 1024 take 9-11 us); looking at
+// the keys is 0.1-0.8 of it, with 16 planes of partial norms 3 (8 x 65536 positions 12.1 -> 15.3: scattered lines of all planes).
+// Kernel times against the four launches, without the gaps between them, of spread norms: 131072 positions 16.1 -> 12.5 us,
+// 4 x 61440 15.8 -> 12.2, 8 x 122880 19.2 -> 13.8, 4 x 524288 26.4 -> 18.3, 1024 x 1024 28.2 -> 18.7.  Crowded: equal norms,
+// 131072 of them 16.6 -> 16.4 (60 by the fixed digits), 1024 x 1024 33.0 -> 20.1 (398); norms of noise with a deviation of 3 %, cut
+// at the median, 131072 18.0 -> 18.2 (20.3), 512 x 1024 33.6 -> 25.0 (41.5), 1024 x 1024 35.1 -> 29.1 (73).  What it loses: several
+// such planes at once, 8 x 122880 22.9 -> 28.0, 4 x 524288 28.3 -> 33.5 (the gaps, 1-2 us each, not counted).
 #include "select_dev.h"
 
 namespace wcc {
@@ -35,9 +42,12 @@ constexpr int kCoarse = 64;                  // coarse digits; the tables hold k
 constexpr int kFine = 64 * kCoarse;          // digits
 constexpr uint32_t kBase = (127u - 32u) << 6;  // digit 0 begins at 2^-32: key >> 17 counts 64 steps an octave
 constexpr int kStepBits = 17;                // key bits below a step
-constexpr uint32_t kListCap = 16384;         // keys of one digit that the second kernel holds in LDS
+constexpr uint32_t kListCap = 32768;         // keys of one digit that the second kernel holds in LDS (128 of its 149 KiB)
 constexpr int kSteps = 6;                    // of six bits: a whole key
 constexpr int kFieldBits = 12;               // bits a pass over memory decides, where the keys do not fit
+constexpr int kProbes = 256;                 // most quads of keys that are looked at to see whether a digit is crowded
+constexpr int kSplits = kProbes - 1;         // keys that part a crowded sample, then the largest of all
+constexpr int kHeader = 4 + kProbes;         // words a sample: whether it is crowded, three unused, those keys
 
 // monotone in the key (as an unsigned number: also for bit patterns that are no norm)
 __device__ __forceinline__ uint32_t digit_of(uint32_t key) {
@@ -64,63 +74,209 @@ __device__ __forceinline__ uint32_t hist_rank(uint32_t *lh, uint32_t digit, bool
   return r;
 }
 
+// load_keys<true> of this thread's keys (if `in`) and of a quad elsewhere, whose sums are returned and not written; the loads of
+// both travel together.
+__device__ __forceinline__ uint4 load_keys_and_probe(const float *__restrict__ src, float *__restrict__ norm, int G, int64_t BN,
+                                                     int64_t at, bool in, int64_t probe_at, uint4 &keys) {
+  auto quad = [&](int64_t i) { return *reinterpret_cast<const float4 *>(src + i); };
+  auto add = [](float4 &v, const float4 &o) { v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w; };
+  const int64_t mine = in ? at : probe_at;
+  float4 v = quad(mine), p = quad(probe_at);
+  int g = 1;
+  for (; g + 4 <= G; g += 4) {
+    float4 tv[4], tp[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      tv[i] = quad(mine + (g + i) * BN);
+      tp[i] = quad(probe_at + (g + i) * BN);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      add(v, tv[i]);
+      add(p, tp[i]);
+    }
+  }
+  for (; g < G; ++g) {
+    const float4 tv = quad(mine + g * BN), tp = quad(probe_at + g * BN);
+    add(v, tv);
+    add(p, tp);
+  }
+  auto bits = [](const float4 &f) {
+    return make_uint4(__float_as_uint(f.x), __float_as_uint(f.y), __float_as_uint(f.z), __float_as_uint(f.w));
+  };
+  if (in) {
+    *reinterpret_cast<float4 *>(norm + at) = v;
+    keys = bits(v);
+  }
+  return bits(p);
+}
+
+// What the first kernel's workgroups look at to see whether a digit is crowded.
+struct Probes {
+  int n;           // quads of keys, one of each stretch of
+  uint32_t quads;  // so many quads
+  uint32_t crowd;  // this many of their keys in one step are too many ...
+  int from, to;    // ... if any of them may be the one of rank k: between these of the probes' ranks
+};
+
 // First kernel.  grid = (nblk, B), block = 1024; a workgroup takes a chunk of 4096 * SLOTS positions (slot s
 // of thread t: the four from (s * 1024 + t) * 4 on).  src: norms, or with REDUCE the partial norms [G, B, N],
-// whose sums it writes to norm.  grouped [B, N]: each chunk's keys, largest digit first (may be plane 0 of
-// src where REDUCE: a workgroup reads its positions before it writes them).  sfx [B, nblk, kFine]: how many of
+// whose sums it writes to norm.  grouped [B, N]: each chunk's keys, largest digit first.  sfx [B, nblk, kFine]: how many of
 // the chunk's keys have that digit or a larger one; csfx [B, nblk, kCoarse] the same for digit 64 c.
+// hdr [B, kHeader].  Every workgroup of a sample looks at the same keys of it and so comes to the same digits: where too many
+// fall into one step that rank k may lie in, 255 of them, sorted, part the sample instead: digit
+// 2 j + 1 is what equals the j-th, the even ones lie between two.  (The probes lie anywhere in the plane, so grouped must
+// be no plane of src.)
 // Also carries out `job`.
 template <bool REDUCE, int SLOTS>
-__global__ __launch_bounds__(kThreads) void select_group_kernel(const float *src, float *norm, int G, int64_t N,
-                                                                int B, uint32_t *grouped, uint16_t *sfx,
-                                                                uint16_t *csfx, PackJob job) {
+__global__ __launch_bounds__(kThreads) void select_group_kernel(const float *__restrict__ src, float *__restrict__ norm, int G,
+                                                                int64_t N, int B, uint32_t *__restrict__ grouped,
+                                                                uint16_t *__restrict__ sfx, uint16_t *__restrict__ csfx,
+                                                                uint32_t *__restrict__ hdr, Probes look, PackJob job) {
   constexpr int kChunk = 4 * kThreads * SLOTS;
   __shared__ __attribute__((aligned(16))) uint32_t lh[kFine];
+  __shared__ __attribute__((aligned(16))) uint32_t probed[kFine];
   __shared__ __attribute__((aligned(16))) uint32_t sorted[kChunk];
+  __shared__ uint32_t picked[kProbes], runs[kProbes], splits[kProbes], tree[kProbes];
   __shared__ uint32_t tmp[kWaves];
+  __shared__ int crowded;
   fetch_args(src, job.total);
   const int b = blockIdx.y, t = threadIdx.x;
   const int64_t c0 = (int64_t)blockIdx.x * kChunk;
   const int n = (int)min((int64_t)kChunk, N - c0);  // (a multiple of 4)
+  // (one quad of each stretch of the plane, anywhere in it; by the first waves alone: a few threads of every wave cost all of
+  // them a wait of its own, 14.8 -> 24 us on 8 x 65536 positions of 16 planes)
+  const bool looks = t < look.n;
+  const int64_t probe_at = (int64_t)b * N + ((int64_t)t * look.quads + __umulhi(t * 2654435761u, look.quads)) * 4;
+  uint4 probe = make_uint4(0, 0, 0, 0);
+  if (!REDUCE && looks) probe = *reinterpret_cast<const uint4 *>(src + probe_at);
   uint4 k4[SLOTS];
 #pragma unroll
   for (int s = 0; s < SLOTS; ++s) {
     const int at = (s * kThreads + t) * 4;
     k4[s] = make_uint4(0, 0, 0, 0);
-    if (at < n) k4[s] = load_keys<REDUCE>(src, norm, G, (int64_t)B * N, (int64_t)b * N + c0 + at);
+    if (s == 0 && REDUCE && looks) probe = load_keys_and_probe(src, norm, G, (int64_t)B * N, (int64_t)b * N + c0 + at, at < n, probe_at, k4[s]);
+    else if (at < n) k4[s] = load_keys<REDUCE>(src, norm, G, (int64_t)B * N, (int64_t)b * N + c0 + at);
   }
   const PackOnTheSide side(job, (int)((blockIdx.y * gridDim.x + blockIdx.x) * kThreads + t));
   static_assert(kFine == 4 * kThreads, "four digits a thread");
   reinterpret_cast<uint4 *>(lh)[t] = make_uint4(0, 0, 0, 0);
+  reinterpret_cast<uint4 *>(probed)[t] = make_uint4(0, 0, 0, 0);
+  if (t < kProbes) picked[t] = 0xFFFFFFFFu;
+  if (t == 0) crowded = 0;
   __syncthreads();
-  uint32_t rank[4 * SLOTS];
+  uint32_t digit[4 * SLOTS], rank[4 * SLOTS];
 #pragma unroll
   for (int s = 0; s < SLOTS; ++s) {
     const bool in = (s * kThreads + t) * 4 < n;
     const uint32_t key[4] = {k4[s].x, k4[s].y, k4[s].z, k4[s].w};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) rank[4 * s + e] = hist_rank(lh, digit_of(key[e]), in);
+    for (int e = 0; e < 4; ++e) {
+      digit[4 * s + e] = digit_of(key[e]);
+      rank[4 * s + e] = hist_rank(lh, digit[4 * s + e], in);
+    }
+  }
+  if (looks) {
+    const uint32_t key[4] = {probe.x, probe.y, probe.z, probe.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      atomicAdd(&probed[digit_of(key[e])], 1u);
+      if (e == 0 || 4 * look.n <= kProbes) picked[e * look.n + t] = key[e];
+    }
   }
   __syncthreads();
-  // four digits a thread, from the top: where each begins in the grouped chunk, and the tables
-  {
-    const int low = kFine - 4 - 4 * t;  // the thread's lowest digit
+  const size_t blk = (size_t)b * gridDim.x + blockIdx.x;
+  const int low = kFine - 4 - 4 * t;  // four digits a thread, from the top: its lowest one
+  // where each digit begins in the grouped chunk, and the tables; LOOK: at the probes as well
+  auto place = [&](auto look_c) {
+    constexpr bool LOOK = decltype(look_c)::value;
     const uint4 c = reinterpret_cast<const uint4 *>(lh)[low / 4];
-    const uint32_t above = block_exclusive_scan<kWaves>(c.x + c.y + c.z + c.w, tmp);
-    const uint32_t a3 = above, a2 = a3 + c.w, a1 = a2 + c.z, a0 = a1 + c.y, all = a0 + c.x;
+    uint4 pc = make_uint4(0, 0, 0, 0);
+    if constexpr (LOOK) pc = reinterpret_cast<const uint4 *>(probed)[low / 4];
+    // (keys of the chunk | keys of the probes << 16)
+    const uint32_t both = block_exclusive_scan<kWaves>((c.x + c.y + c.z + c.w) | (pc.x + pc.y + pc.z + pc.w) << 16, tmp);
+    const uint32_t a3 = both & 0xFFFFu, a2 = a3 + c.w, a1 = a2 + c.z, a0 = a1 + c.y, all = a0 + c.x;
     reinterpret_cast<uint4 *>(lh)[low / 4] = make_uint4(a0, a1, a2, a3);
-    const size_t blk = (size_t)b * gridDim.x + blockIdx.x;
     // (counts of digit d and above: what the next lower digit begins with)
     *reinterpret_cast<uint2 *>(sfx + blk * kFine + low) = make_uint2(all | (a0 << 16), a1 | (a2 << 16));
     if (low % 64 == 0) csfx[blk * kCoarse + low / 64] = (uint16_t)all;
-  }
+    if constexpr (LOOK) {
+      int upto = (int)(both >> 16);
+      auto see = [&](uint32_t m, int d) {  // (zero has a digit of its own)
+        if (m >= look.crowd && d != 0 && upto <= look.to && upto + (int)m >= look.from) crowded = 1;
+        upto += (int)m;
+      };
+      see(pc.w, low + 3);
+      see(pc.z, low + 2);
+      see(pc.y, low + 1);
+      see(pc.x, low);
+    }
+  };
+  place(std::true_type{});
   __syncthreads();
+  if (__builtin_expect(__builtin_amdgcn_readfirstlane(crowded) != 0, 0)) {  // again, by the other digits
+    // Sorted: every wave its 64 by counting, then each key its place among the others' runs.
+    const int lane = t & 63, wv = t >> 6;
+    uint32_t mine = 0, at = 0;
+    if (t < kProbes) {
+      mine = picked[t];
+#pragma unroll 4
+      for (int j = 0; j < 64; ++j) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)mine, j);
+        at += o < mine || (o == mine && j < lane);
+      }
+      runs[wv * 64 + at] = mine;
+    }
+    reinterpret_cast<uint4 *>(lh)[t] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    if (t < kProbes) {
+#pragma unroll 1
+      for (int r = 1; r < kProbes / 64; ++r) {
+        const int other = (wv + r) & (kProbes / 64 - 1);
+        const uint32_t *run = runs + other * 64;
+        const uint32_t past = other < wv ? 1u : 0u;  // equal keys of earlier runs come first
+        int c = 0;
+#pragma unroll
+        for (int step = 32; step > 0; step >>= 1)
+          if (run[c + step - 1] < mine || (past && run[c + step - 1] == mine)) c += step;
+        c += run[c] < mine || (past && run[c] == mine);
+        at += c;
+      }
+      splits[at] = at < kSplits ? mine : 0xFFFFFFFFu;
+      // (and as a search tree, level by level: the reads of a level hit different banks)
+      if (at < kSplits) tree[((at + 1) | kProbes) >> __ffs((int)(at + 1))] = mine;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+      const uint32_t key[4] = {k4[s].x, k4[s].y, k4[s].z, k4[s].w};
+      uint32_t node[4] = {1, 1, 1, 1};
+#pragma unroll 1
+      for (int level = kProbes / 2; level > 0; level >>= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) node[e] = 2 * node[e] + (tree[node[e]] < key[e]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t below = node[e] - kProbes;  // keys of `splits` that are smaller
+        digit[4 * s + e] = 2 * below + (splits[below] == key[e]);
+        rank[4 * s + e] = hist_rank(lh, digit[4 * s + e], (s * kThreads + t) * 4 < n);
+      }
+    }
+    __syncthreads();
+    place(std::false_type{});
+    __syncthreads();
+  }
+  if (blockIdx.x == 0) {
+    uint32_t *h = hdr + (size_t)b * kHeader;
+    if (t == 0) h[0] = (uint32_t)crowded;
+    if (t < kProbes) h[4 + t] = splits[t];
+  }
 #pragma unroll
   for (int s = 0; s < SLOTS; ++s) {
     if ((s * kThreads + t) * 4 < n) {
       const uint32_t key[4] = {k4[s].x, k4[s].y, k4[s].z, k4[s].w};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sorted[lh[digit_of(key[e])] + rank[4 * s + e]] = key[e];
+      for (int e = 0; e < 4; ++e) sorted[lh[digit[4 * s + e]] + rank[4 * s + e]] = key[e];
     }
   }
   __syncthreads();
@@ -149,7 +305,7 @@ template <int SLOTS>
 __global__ __launch_bounds__(kThreads) void select_place_kernel(const float *__restrict__ norm, int64_t N, int64_t k,
                                                                 const uint32_t *__restrict__ grouped,
                                                                 const uint16_t *__restrict__ sfx,
-                                                                const uint16_t *__restrict__ csfx,
+                                                                const uint16_t *__restrict__ csfx, const uint32_t *__restrict__ hdr,
                                                                 int32_t *__restrict__ idx, int32_t *__restrict__ jmap,
                                                                 const float *__restrict__ top_part, int G, int B,
                                                                 float *block_top) {
@@ -160,6 +316,7 @@ __global__ __launch_bounds__(kThreads) void select_place_kernel(const float *__r
   __shared__ uint32_t bins[kSteps][64];
   __shared__ uint32_t counts[2][kCoarse];
   __shared__ uint32_t seg[kSelectTwoBlocks];
+  __shared__ uint32_t head[kHeader];
   __shared__ uint32_t tmp[64];
   __shared__ uint32_t sums[2][kWaves];
   __shared__ uint32_t bcast[3];
@@ -174,6 +331,8 @@ __global__ __launch_bounds__(kThreads) void select_place_kernel(const float *__r
   sfx += (size_t)b * nblk * kFine;
   csfx += (size_t)b * nblk * kCoarse;
   grouped += (size_t)b * N;
+  hdr += (size_t)b * kHeader;
+  const uint32_t head_t = t < kHeader ? hdr[t] : 0u;  // (a scalar load would hold up every access to LDS)
 
   // rank k's coarse digit: every wave reads the tables of its share of the chunks, lane c the counts of coarse digit
   // c and above
@@ -193,6 +352,7 @@ __global__ __launch_bounds__(kThreads) void select_place_kernel(const float *__r
       if (top_part) top4[s] = load_top(top_part, G, (int64_t)B * N, (int64_t)b * N + c0 + at);
     }
   }
+  if (t < kHeader) head[t] = head_t;
   for (int i = t; i < 2 * kCoarse; i += kThreads) (&counts[0][0])[i] = 0;
   for (int i = t; i < kSteps * 64; i += kThreads) (&bins[0][0])[i] = 0;
   workgroup_lds_barrier();
@@ -230,13 +390,28 @@ __global__ __launch_bounds__(kThreads) void select_place_kernel(const float *__r
       if (wv == 0 && i < mine) above += sg[q] & 0xFFFFu;  // keys above digit D in the chunks before this one
     }
   }
-  uint32_t T = 0;  // the threshold key
-  v = 0;           // keys equal to it in the chunks before this one
-  if (D != 0) {    // (digit 0 is the key 0 alone)
-    // T's bits from `hi` up are fixed
-    const bool inner = D != 1 && D != kFine - 1;
-    int hi = inner ? kStepBits : 32;
-    T = inner ? (D + kBase) << kStepBits : 0u;
+  // the threshold key: its bits from `hi` up are the same in all keys with digit D; `alone`: digit D is one key
+  uint32_t T = 0;
+  int hi = 32;
+  bool alone = D == 0;
+  const uint32_t *splits = head + 4;
+  if (head[0] == 0) {
+    if (D != 0 && D != 1 && D != kFine - 1) {
+      hi = kStepBits;
+      T = (D + kBase) << kStepBits;
+    }
+  } else {
+    const uint32_t j = D >> 1;
+    alone = D & 1;
+    T = splits[j];
+    if (!alone) {  // keys in [low, top]
+      const uint32_t low = j > 0 ? splits[j - 1] + 1 : 0u, top = j < kSplits ? T - 1 : 0xFFFFFFFFu;
+      hi = low == top ? 0 : 32 - __builtin_clz(low ^ top);
+      T = hi < 32 ? low >> hi << hi : 0u;
+    }
+  }
+  v = 0;  // keys equal to T in the chunks before this one
+  if (!alone) {
     // The list holds the keys that agree with T so far: `before` of chunks before this one at its start, `rest` others
     // from rest_at on.
     uint32_t before = off_mine, rest = M - off_mine, rest_at = off_mine;
@@ -257,9 +432,28 @@ __global__ __launch_bounds__(kThreads) void select_place_kernel(const float *__r
           first[u] = (uint32_t)lane < m[u] ? p[u][lane] : 0u;
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < 4; ++u)
           if ((uint32_t)lane < m[u]) list[to[u] + lane] = first[u];
-          for (uint32_t e = lane + 64; e < m[u]; e += 64) list[to[u] + e] = p[u][e];
+      }
+      // (what is longer, eight loads in flight; one loop for all of it: its instructions are fetched even where it does not run)
+      if (__ballot(max(max(sg[0], sg[1]), max(sg[2], sg[3])) >> 16 > 64) != 0) {
+        static_assert(kQuads == 4, "");
+#pragma unroll 1
+        for (int i = wv; i < nblk; i += kWaves) {
+          const int q = i >> 6;
+          const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)(q < 2 ? (q ? sg[1] : sg[0]) : q == 2 ? sg[2] : sg[3]), i & 63);
+          const uint32_t to = (uint32_t)__builtin_amdgcn_readlane((int)(q < 2 ? (q ? off[1] : off[0]) : q == 2 ? off[2] : off[3]), i & 63);
+          const uint32_t *p = grouped + (size_t)i * kChunk + (w & 0xFFFFu);
+          const uint32_t m = w >> 16;
+#pragma unroll 1
+          for (uint32_t e0 = 64; e0 < m; e0 += 8 * 64) {
+            uint32_t more[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) more[x] = p[min(e0 + x * 64 + lane, m - 1)];
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+              if (e0 + x * 64 + lane < m) list[to + e0 + x * 64 + lane] = more[x];
+          }
         }
       }
       workgroup_lds_barrier();
@@ -420,37 +614,51 @@ __global__ __launch_bounds__(kThreads) void select_place_kernel(const float *__r
     publish_top<kWaves>(kept_top, block_top, (size_t)b * nblk + mine, tmp);
 }
 
+// (Each costs a line of memory a plane of partial norms.)  Crowded: a digit with some 16384 keys, half of what the second
+// kernel's list takes, but at least what six (three) of the quads hold, which may be neighbours of one value.
+Probes probes_of(int G, int64_t N, int64_t k) {
+  Probes p{N > 1 << 17 ? kProbes : G > 4 ? kProbes / 8 : kProbes / 4, 0, 0, 0, 0};
+  p.quads = (uint32_t)(N / 4 / p.n);
+  p.crowd = std::max<uint32_t>(std::max(12, p.n * 24 / kProbes), (uint32_t)((int64_t)p.n * 4 * 16384 / N));
+  const int rank = (int)((int64_t)p.n * 4 * k / N), slack = p.n / 4;  // (two deviations of the median of 256 quads of equal keys)
+  p.from = rank - slack;
+  p.to = rank + slack;
+  return p;
+}
+
 template <int SLOTS>
 hipError_t launch(const wcc_desc &d, const float *norm_or_part, int G, float *norm_out, int64_t k, uint32_t *grouped,
-                  uint16_t *sfx, uint16_t *csfx, int nblk, int32_t *idx, int32_t *jmap, const float *top_part,
+                  uint16_t *sfx, uint16_t *csfx, uint32_t *hdr, int nblk, int32_t *idx, int32_t *jmap, const float *top_part,
                   float *block_top, const PackJob &job, hipStream_t s) {
   const int64_t N = (int64_t)d.H * d.W;
+  const Probes look = probes_of(G, N, k);
   const dim3 grid(nblk, d.B), block(kThreads);
   const float *norm = G > 1 ? norm_out : norm_or_part;
   if (G > 1)
     hipLaunchKernelGGL((select_group_kernel<true, SLOTS>), grid, block, 0, s, norm_or_part, norm_out, G, N, d.B, grouped,
-                       sfx, csfx, job);
+                       sfx, csfx, hdr, look, job);
   else
     hipLaunchKernelGGL((select_group_kernel<false, SLOTS>), grid, block, 0, s, norm_or_part, nullptr, 1, N, d.B, grouped,
-                       sfx, csfx, job);
-  hipLaunchKernelGGL((select_place_kernel<SLOTS>), grid, block, 0, s, norm, N, k, grouped, sfx, csfx, idx, jmap, top_part,
+                       sfx, csfx, hdr, look, job);
+  hipLaunchKernelGGL((select_place_kernel<SLOTS>), grid, block, 0, s, norm, N, k, grouped, sfx, csfx, hdr, idx, jmap, top_part,
                      G, d.B, block_top);
   return hipGetLastError();
 }
 
 }  // namespace
 
-size_t select_two_bytes(int B, int nblk) { return (size_t)B * nblk * (kFine + kCoarse) * 2; }
+size_t select_two_bytes(int B, int nblk) { return (size_t)B * nblk * (kFine + kCoarse) * 2 + (size_t)B * kHeader * 4; }
 int select_two_chunk(int slots) { return 4 * kThreads * slots; }
 
 hipError_t launch_select_two(const wcc_desc &d, const float *norm_or_part, int G, float *norm_out, int64_t k,
                              void *tables, uint32_t *grouped, int slots, int nblk, int32_t *idx, int32_t *jmap,
                              const float *top_part, float *block_top, const PackJob &job, hipStream_t s) {
   uint16_t *sfx = static_cast<uint16_t *>(tables), *csfx = sfx + (size_t)d.B * nblk * kFine;
+  uint32_t *hdr = reinterpret_cast<uint32_t *>(csfx + (size_t)d.B * nblk * kCoarse);
   switch (slots) {
-    case 4: return launch<4>(d, norm_or_part, G, norm_out, k, grouped, sfx, csfx, nblk, idx, jmap, top_part, block_top, job, s);
-    case 2: return launch<2>(d, norm_or_part, G, norm_out, k, grouped, sfx, csfx, nblk, idx, jmap, top_part, block_top, job, s);
-    default: return launch<1>(d, norm_or_part, G, norm_out, k, grouped, sfx, csfx, nblk, idx, jmap, top_part, block_top, job, s);
+    case 4: return launch<4>(d, norm_or_part, G, norm_out, k, grouped, sfx, csfx, hdr, nblk, idx, jmap, top_part, block_top, job, s);
+    case 2: return launch<2>(d, norm_or_part, G, norm_out, k, grouped, sfx, csfx, hdr, nblk, idx, jmap, top_part, block_top, job, s);
+    default: return launch<1>(d, norm_or_part, G, norm_out, k, grouped, sfx, csfx, hdr, nblk, idx, jmap, top_part, block_top, job, s);
   }
 }
 

@@ -106,11 +106,11 @@ constexpr size_t kSelectMinBlocks = 512;
 
 // Two-launch selection: workgroups at most, one a compute unit, in chunks as small as that allows.  With two a unit
 // 4 x 512 x 1024 positions take 30 us in chunks of 4096 and 23 in chunks of 8192 (30 in the four launches); beyond the
-// largest chunk the four launches are quicker (16 x 512 x 1024 positions: 62 us, 63 in two launches; 16 x 1024 x 1024 110
-// and 122, 256 x 256 x 256 113 and 106).
+// largest chunk, with several workgroups a unit, it measured no better on the whole (16 x 512 x 1024 positions: 62 us in four launches, 63
+// in two; 16 x 1024 x 1024 110 and 122; 256 x 256 x 256 113 and 106).
 constexpr size_t kSelectTwoWorkgroups = 256;
-// ... and positions a sample at most: from there on the keys of one digit begin to leave LDS (1024 x 1024: 22.7 us, 30 in
-// four launches; 1024 x 2048: 42 and 38.5).
+// ... and positions a sample at most: from there on the keys of one digit begin to leave LDS (1024 x 1024, spread norms: 18.7 us, 28.2 in
+// four launches; 1024 x 2048 with the fixed digits: 42 and 38.5).
 constexpr size_t kSelectTwoMaxN = 1 << 20;
 
 WsLayout ws_layout(const wcc_desc &d, int front, bool pad) {
@@ -155,6 +155,12 @@ WsLayout ws_layout(const wcc_desc &d, int front, bool pad) {
     const size_t bytes = select_two_bytes(d.B, (int)chunks);
     const bool at_hist = bytes <= L.jmap - L.hist;
     if (!at_hist && bytes > yc_end - L.yc) continue;
+    // (the grouped keys: where no plane of partial norms lies, the second kernel writes nothing and no packed weights go)
+    const size_t yc_free = L.yc + (at_hist ? 0 : align256(bytes));
+    if (L.G == 1) L.two_grouped = L.norm_part;
+    else if (yc_free + B * N * 4 <= yc_end) L.two_grouped = yc_free;
+    else if (N * 4 <= (size_t)d.C_in * L.ks) L.two_grouped = L.xc32;
+    else continue;
     L.two_nblk = (int)chunks;
     L.two_slots = sl;
     L.two_tables = at_hist ? L.hist : L.yc;

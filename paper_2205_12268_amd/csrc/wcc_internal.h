@@ -56,6 +56,7 @@ struct WsLayout {
   int two_nblk;       // chunks per sample of the two-launch selection; 0: not taken
   int two_slots;      // 16-byte loads per thread there: 1, 2 or 4
   size_t two_tables;  // its tables: in the memory of the histograms, or of yc
+  size_t two_grouped; // [B, N] u32: in the memory of norm_part, yc or the codes in xc32
 };
 
 struct SelectState {
@@ -294,7 +295,7 @@ hipError_t launch_norm_reduce(const float *norm_part, const StorePlan &sp, int64
 hipError_t launch_channel_norm(const float *coef, int B, int C, int64_t N, bool squares, float *norm,
                                hipStream_t s);
 // Selection in two launches (select_two.hip): bytes of its tables, positions a chunk (slots: 16-byte loads a
-// thread).  grouped: [B, N] words of scratch memory, may be plane 0 of norm_or_part where G > 1.
+// thread).  grouped: [B, N] words of scratch memory.
 size_t select_two_bytes(int B, int nblk);
 int select_two_chunk(int slots);
 hipError_t launch_select_two(const wcc_desc &d, const float *norm_or_part, int G, float *norm_out, int64_t k,
