@@ -59,11 +59,13 @@ struct RegRow {
 
 // The passes are bound by their vector instructions, so the factors 1/2 of the butterflies are left out where a power of two
 // can be carried along instead (scaling by it is exact, so the sums and roundings are those of the transforms of the
-// other routes, bit for bit, where nothing leaves the range of normal numbers): a level of the synthesis returns twice its
-// rows, and the level below halves them inside a multiply-add; the analysis leaves coefficients of level l scaled by
-// 2^(l + 1) (2 of them from the synthesis), which the sinks take off: the norm pass once a walk, the keep pass in the
-// multiplication it had.  Vector instructions a channel of the norm pass 709 -> 591; with the vector unit 91 % busy, at 1.9 GHz,
-// it takes 336 us for 8 x 1024 channels of 256 x 256, a quarter kept (361), the keep pass 440 (460).
+// other routes, bit for bit, where nothing is smaller than a normal number): a level of the synthesis returns twice its
+// rows, and the level below halves them inside a multiply-add; the convolution's taps take 2^-(D + 1), so that the analysis
+// leaves the coefficients of level l scaled by 2^(l - D), at most what they are: nothing overflows that the other
+// routes hold, and what lies below 2^-122 may lose bits.  The sinks take the powers off: the norm pass once a walk (of squares before
+// they are squared), the keep pass in the multiplication it had.  Vector instructions a channel of the norm pass 709 -> 601.
+// With the scale on the coefficients, up to 16 times what they are, and none on the taps it was 591, but the norms
+// overflowed from 2^124 on; 8 x 1024 channels of 256 x 256, a quarter kept, in one run: norm pass 346 -> 328 us, keep pass 457 -> 470.
 
 // Synthesis levels D..L of a strip: twice its rows of level L - 1 (inv_levels without the factors).
 template <int D, int V, int L, class Source>
@@ -130,14 +132,14 @@ __device__ __forceinline__ void inv_row_twice(float (&out)[cols_at(V, L - 1)], c
   }
 }
 
-// Analysis levels L..D: `in` holds 2^L times the rows of level L - 1; the sink gets the coefficients as they are, or
-// (Sink::kScaled) 2^(level + 1) times them.
+// Analysis levels L..D: `in` holds 2^(L - 1 - D) times the rows of level L - 1; the sink gets the coefficients as they are, or
+// (Sink::kScaled) 2^(level - D) times them.
 template <int D, int V, int L, class Sink>
 __device__ __forceinline__ void fwd_levels_scaled(const float (&in)[rows_at(D, L - 1)][cols_at(V, L - 1)],
                                                   const LanePos<D> &p, Sink &sink) {
   constexpr int R2 = rows_at(D, L), VI = cols_at(V, L - 1), V2 = cols_at(V, L);
   constexpr int SI = span_at(V, L - 1), S2 = span_at(V, L);
-  constexpr float kScale = Sink::kScaled ? 1.f : 1.f / (float)(2 << L);
+  constexpr float kScale = Sink::kScaled ? 1.f : (float)(1 << (D - L));
   float ll[R2][V2];
   const bool owner = p.active && ((S2 == 1) || ((p.lc & (S2 - 1)) == 0));
 #pragma unroll
@@ -172,7 +174,7 @@ __device__ __forceinline__ void fwd_levels_scaled(const float (&in)[rows_at(D, L
 }
 
 // Sink of the norm pass: per slot the sum of |coefficient| (SQ: of squares) and the largest |coefficient| over the
-// channels, both of scaled coefficients until finish().
+// channels, of scaled coefficients until finish() (but for the squares).
 template <int D, bool SQ>
 struct ChainNormSink {
   static constexpr bool kScaled = true;
@@ -183,7 +185,8 @@ struct ChainNormSink {
 #pragma unroll
     for (int e = 0; e < CV; ++e) {
       float &a = acc[base + i * CV + e], &t = top[base + i * CV + e];
-      a = SQ ? fmaf(v[e], v[e], a) : a + fabsf(v[e]);
+      const float c = (float)(1 << (D - L)) * v[e];  // (squares leave the normal numbers early enough unscaled)
+      a = SQ ? fmaf(c, c, a) : a + fabsf(v[e]);
       // (fmaxf first quiets a value that the compiler does not know to be quiet: a second instruction a slot)
       asm("v_max_f32_e64 %0, %1, |%2|" : "=v"(t) : "v"(t), "v"(v[e]));
     }
@@ -191,12 +194,12 @@ struct ChainNormSink {
   __device__ __forceinline__ void finish() {
     auto level = [&](auto Lc) {
       constexpr int L = decltype(Lc)::value;
-      constexpr float kDown = 1.f / (float)(2 << L);
+      constexpr float kUp = (float)(1 << (D - L));
       constexpr int first = slot_base(D, V4, L, L == D ? 0 : 1), last = L == D ? slot_count(D, V4) : slot_base(D, V4, L, 3) + rows_at(D, L) * cols_at(V4, L);
 #pragma unroll
       for (int s = first; s < last; ++s) {
-        acc[s] *= SQ ? kDown * kDown : kDown;
-        top[s] *= kDown;
+        if constexpr (!SQ) acc[s] *= kUp;
+        top[s] *= kUp;
       }
     };
     level(std::integral_constant<int, 1>{});
@@ -329,7 +332,7 @@ __device__ __forceinline__ void chain_walk(const float *__restrict__ plane, int6
   auto compute = [&](const float *kw) {
     float k[9];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) k[t] = kw[t];
+    for (int t = 0; t < 9; ++t) k[t] = kw[t] * (1.f / (float)(2 << D));  // (the rows below are twice what they are)
     wave_lds_fence();
     float six[RR][V + 2];
     {
@@ -390,7 +393,7 @@ __device__ __forceinline__ void chain_walk(const float *__restrict__ plane, int6
 #pragma unroll
     for (int i = 0; i < RR; ++i) {
       // (the neighbouring lanes' columns: through LDS where the vector unit is the bound, by its data-parallel moves in the
-      // keep pass, which keeps LDS busy as it is: 455 -> 440 us there, 333 -> 339 in the norm pass)
+      // keep pass, which keeps LDS busy as it is: 455 -> 440 us there, 333 -> 339 in the norm pass, both with the taps unscaled)
       float l, r;
       if constexpr (Sink::kScaled) {
         l = __shfl_up(six[i][V], 1, kWave);
