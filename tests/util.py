@@ -95,3 +95,16 @@ def check_block_without_middle_outputs(ref, ctx, cfg, d, xd, x_np, w1d, w1s, wdd
     if same:
         assert torch.equal(y_p, y_mat)
     return same
+
+
+def codes_in_workspace(ctx, xc):
+    """In which form a fused call left the 8-bit codes xc [B, C, k] (as the stage call wcc_gather_quant gives them) in the
+    workspace, at the start of one of its 256-byte lines: "words" (four channels' codes of a position, the last channel repeated
+    past the end), "bytes", or None.  Needs k >= 256."""
+    lines = ctx._ws[:ctx._ws.numel() // 256 * 256].view(-1, 256)
+    quad = [min(c, xc.shape[1] - 1) for c in range(4)]
+    forms = {"words": xc[0, quad, :64].t(), "bytes": xc[0, 0, :256]}
+    for name, line in forms.items():
+        if bool((lines == line.contiguous().view(torch.uint8).reshape(1, 256)).all(1).any()):
+            return name
+    return None
