@@ -1,6 +1,6 @@
 """The chained block carries powers of two through its transforms instead of the butterflies' halves (needs an MI355X).
-They cancel exactly, so a block without a quantiser on inputs scaled by a power of two gives that power times its
-result, bit for bit, and keeps the same positions, whatever the size of the numbers."""
+A block without a quantiser on inputs scaled by a power of two gives that power times its result, bit for bit, and keeps
+the same positions.  (That the powers of the levels cancel, test_gpu_chain_range.py compares with the other route.)"""
 import pytest
 import torch
 
