@@ -25,7 +25,8 @@
 //
 // Bound by latency: 5 us for the first kernel, 8-9 for the second (its chain is two table reads and the segments,
 // 1 us each, another die wrote them, and a dozen barriers; 256 or 512 threads in place of 1024 take 9-11 us); looking at
-// the keys is 0.1-0.8 of it, with 16 planes of partial norms 3 (8 x 65536 positions 12.1 -> 15.3: scattered lines of all planes).
+// the keys is 0.1-0.7 of it.  Where the norms come as planes of partial norms the look goes to plane 0 first and to the sums only where it finds a
+// crowd there (to the sums at once: 12.1 -> 15.3 on 8 x 65536 positions of 16 planes, 58 -> 80 on 44800 of 256; now 12.6).
 // Kernel times against the four launches, without the gaps between them, of spread norms: 131072 positions 16.1 -> 12.5 us,
 // 4 x 61440 15.8 -> 12.2, 8 x 122880 19.2 -> 13.8, 4 x 524288 26.4 -> 18.3, 1024 x 1024 28.2 -> 18.7.  Crowded: equal norms,
 // 131072 of them 16.6 -> 16.4 (60 by the fixed digits), 1024 x 1024 33.0 -> 20.1 (398); norms of noise with a deviation of 3 %, cut
@@ -74,41 +75,22 @@ __device__ __forceinline__ uint32_t hist_rank(uint32_t *lh, uint32_t digit, bool
   return r;
 }
 
-// load_keys<true> of this thread's keys (if `in`) and of a quad elsewhere, whose sums are returned and not written; the loads of
-// both travel together.
-__device__ __forceinline__ uint4 load_keys_and_probe(const float *__restrict__ src, float *__restrict__ norm, int G, int64_t BN,
-                                                     int64_t at, bool in, int64_t probe_at, uint4 &keys) {
-  auto quad = [&](int64_t i) { return *reinterpret_cast<const float4 *>(src + i); };
-  auto add = [](float4 &v, const float4 &o) { v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w; };
-  const int64_t mine = in ? at : probe_at;
-  float4 v = quad(mine), p = quad(probe_at);
+// The sums of load_keys<true> at `at`, not written.
+__device__ __forceinline__ uint4 sum_of_parts(const float *__restrict__ src, int G, int64_t BN, int64_t at) {
+  float4 v = *reinterpret_cast<const float4 *>(src + at);
   int g = 1;
-  for (; g + 4 <= G; g += 4) {
-    float4 tv[4], tp[4];
+  for (; g + 8 <= G; g += 8) {
+    float4 p[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      tv[i] = quad(mine + (g + i) * BN);
-      tp[i] = quad(probe_at + (g + i) * BN);
-    }
+    for (int i = 0; i < 8; ++i) p[i] = *reinterpret_cast<const float4 *>(src + (g + i) * BN + at);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      add(v, tv[i]);
-      add(p, tp[i]);
-    }
+    for (int i = 0; i < 8; ++i) { v.x += p[i].x; v.y += p[i].y; v.z += p[i].z; v.w += p[i].w; }
   }
   for (; g < G; ++g) {
-    const float4 tv = quad(mine + g * BN), tp = quad(probe_at + g * BN);
-    add(v, tv);
-    add(p, tp);
+    const float4 p = *reinterpret_cast<const float4 *>(src + g * BN + at);
+    v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
   }
-  auto bits = [](const float4 &f) {
-    return make_uint4(__float_as_uint(f.x), __float_as_uint(f.y), __float_as_uint(f.z), __float_as_uint(f.w));
-  };
-  if (in) {
-    *reinterpret_cast<float4 *>(norm + at) = v;
-    keys = bits(v);
-  }
-  return bits(p);
+  return make_uint4(__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w));
 }
 
 // What the first kernel's workgroups look at to see whether a digit is crowded.
@@ -125,7 +107,8 @@ struct Probes {
 // the chunk's keys have that digit or a larger one; csfx [B, nblk, kCoarse] the same for digit 64 c.
 // hdr [B, kHeader].  Every workgroup of a sample looks at the same keys of it and so comes to the same digits: where too many
 // fall into one step that rank k may lie in, 255 of them, sorted, part the sample instead: digit
-// 2 j + 1 is what equals the j-th, the even ones lie between two.  (The probes lie anywhere in the plane, so grouped must
+// 2 j + 1 is what equals the j-th, the even ones lie between two.  REDUCE: first at plane 0, where a digit of any rank counts, then at the
+// sums; planes that are crowded only together are not seen, and the second kernel then reads their digit from memory.  (The probes lie anywhere in the plane, so grouped must
 // be no plane of src.)
 // Also carries out `job`.
 template <bool REDUCE, int SLOTS>
@@ -144,19 +127,18 @@ __global__ __launch_bounds__(kThreads) void select_group_kernel(const float *__r
   const int b = blockIdx.y, t = threadIdx.x;
   const int64_t c0 = (int64_t)blockIdx.x * kChunk;
   const int n = (int)min((int64_t)kChunk, N - c0);  // (a multiple of 4)
-  // (one quad of each stretch of the plane, anywhere in it; by the first waves alone: a few threads of every wave cost all of
-  // them a wait of its own, 14.8 -> 24 us on 8 x 65536 positions of 16 planes)
+  // (one quad of each stretch of the plane, anywhere in it; by the first waves alone: a few threads of every wave would cost
+  // all of them a wait of its own)
   const bool looks = t < look.n;
   const int64_t probe_at = (int64_t)b * N + ((int64_t)t * look.quads + __umulhi(t * 2654435761u, look.quads)) * 4;
   uint4 probe = make_uint4(0, 0, 0, 0);
-  if (!REDUCE && looks) probe = *reinterpret_cast<const uint4 *>(src + probe_at);
+  if (looks) probe = *reinterpret_cast<const uint4 *>(src + probe_at);  // (REDUCE: of plane 0 alone)
   uint4 k4[SLOTS];
 #pragma unroll
   for (int s = 0; s < SLOTS; ++s) {
     const int at = (s * kThreads + t) * 4;
     k4[s] = make_uint4(0, 0, 0, 0);
-    if (s == 0 && REDUCE && looks) probe = load_keys_and_probe(src, norm, G, (int64_t)B * N, (int64_t)b * N + c0 + at, at < n, probe_at, k4[s]);
-    else if (at < n) k4[s] = load_keys<REDUCE>(src, norm, G, (int64_t)B * N, (int64_t)b * N + c0 + at);
+    if (at < n) k4[s] = load_keys<REDUCE>(src, norm, G, (int64_t)B * N, (int64_t)b * N + c0 + at);
   }
   const PackOnTheSide side(job, (int)((blockIdx.y * gridDim.x + blockIdx.x) * kThreads + t));
   static_assert(kFine == 4 * kThreads, "four digits a thread");
@@ -176,17 +158,28 @@ __global__ __launch_bounds__(kThreads) void select_group_kernel(const float *__r
       rank[4 * s + e] = hist_rank(lh, digit[4 * s + e], in);
     }
   }
-  if (looks) {
+  auto count_probe = [&]() {
+    if (!looks) return;
     const uint32_t key[4] = {probe.x, probe.y, probe.z, probe.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       atomicAdd(&probed[digit_of(key[e])], 1u);
       if (e == 0 || 4 * look.n <= kProbes) picked[e * look.n + t] = key[e];
     }
-  }
+  };
+  count_probe();
   __syncthreads();
   const size_t blk = (size_t)b * gridDim.x + blockIdx.x;
   const int low = kFine - 4 - 4 * t;  // four digits a thread, from the top: its lowest one
+  // whether one of the thread's digits is crowded: pc of the probes' keys in them, upto above them (anywhere: whatever their rank)
+  auto see = [&](const uint4 &pc, int upto, bool anywhere) {
+    const uint32_t c[4] = {pc.w, pc.z, pc.y, pc.x};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {  // (zero has a digit of its own)
+      if (c[i] >= look.crowd && low + 3 - i != 0 && (anywhere || (upto <= look.to && upto + (int)c[i] >= look.from))) crowded = 1;
+      upto += (int)c[i];
+    }
+  };
   // where each digit begins in the grouped chunk, and the tables; LOOK: at the probes as well
   auto place = [&](auto look_c) {
     constexpr bool LOOK = decltype(look_c)::value;
@@ -200,21 +193,24 @@ __global__ __launch_bounds__(kThreads) void select_group_kernel(const float *__r
     // (counts of digit d and above: what the next lower digit begins with)
     *reinterpret_cast<uint2 *>(sfx + blk * kFine + low) = make_uint2(all | (a0 << 16), a1 | (a2 << 16));
     if (low % 64 == 0) csfx[blk * kCoarse + low / 64] = (uint16_t)all;
-    if constexpr (LOOK) {
-      int upto = (int)(both >> 16);
-      auto see = [&](uint32_t m, int d) {  // (zero has a digit of its own)
-        if (m >= look.crowd && d != 0 && upto <= look.to && upto + (int)m >= look.from) crowded = 1;
-        upto += (int)m;
-      };
-      see(pc.w, low + 3);
-      see(pc.z, low + 2);
-      see(pc.y, low + 1);
-      see(pc.x, low);
-    }
+    if constexpr (LOOK) see(pc, (int)(both >> 16), REDUCE);
   };
   place(std::true_type{});
   __syncthreads();
-  if (__builtin_expect(__builtin_amdgcn_readfirstlane(crowded) != 0, 0)) {  // again, by the other digits
+  bool again = __builtin_amdgcn_readfirstlane(crowded) != 0;
+  if (REDUCE && __builtin_expect(again, 0)) {  // what is crowded in plane 0 is looked at in the sums
+    if (looks) probe = sum_of_parts(src, G, (int64_t)B * N, probe_at);
+    reinterpret_cast<uint4 *>(probed)[t] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    if (t == 0) crowded = 0;
+    count_probe();
+    __syncthreads();
+    const uint4 pc = reinterpret_cast<const uint4 *>(probed)[low / 4];
+    see(pc, (int)block_exclusive_scan<kWaves>(pc.x + pc.y + pc.z + pc.w, tmp), false);
+    __syncthreads();
+    again = __builtin_amdgcn_readfirstlane(crowded) != 0;
+  }
+  if (__builtin_expect(again, 0)) {  // again, by the other digits
     // Sorted: every wave its 64 by counting, then each key its place among the others' runs.
     const int lane = t & 63, wv = t >> 6;
     uint32_t mine = 0, at = 0;
@@ -614,10 +610,10 @@ __global__ __launch_bounds__(kThreads) void select_place_kernel(const float *__r
     publish_top<kWaves>(kept_top, block_top, (size_t)b * nblk + mine, tmp);
 }
 
-// (Each costs a line of memory a plane of partial norms.)  Crowded: a digit with some 16384 keys, half of what the second
+// Crowded: a digit with some 16384 keys, half of what the second
 // kernel's list takes, but at least what six (three) of the quads hold, which may be neighbours of one value.
-Probes probes_of(int G, int64_t N, int64_t k) {
-  Probes p{N > 1 << 17 ? kProbes : G > 4 ? kProbes / 8 : kProbes / 4, 0, 0, 0, 0};
+Probes probes_of(int64_t N, int64_t k) {
+  Probes p{N > 1 << 17 ? kProbes : kProbes / 4, 0, 0, 0, 0};
   p.quads = (uint32_t)(N / 4 / p.n);
   p.crowd = std::max<uint32_t>(std::max(12, p.n * 24 / kProbes), (uint32_t)((int64_t)p.n * 4 * 16384 / N));
   const int rank = (int)((int64_t)p.n * 4 * k / N), slack = p.n / 4;  // (two deviations of the median of 256 quads of equal keys)
@@ -631,7 +627,7 @@ hipError_t launch(const wcc_desc &d, const float *norm_or_part, int G, float *no
                   uint16_t *sfx, uint16_t *csfx, uint32_t *hdr, int nblk, int32_t *idx, int32_t *jmap, const float *top_part,
                   float *block_top, const PackJob &job, hipStream_t s) {
   const int64_t N = (int64_t)d.H * d.W;
-  const Probes look = probes_of(G, N, k);
+  const Probes look = probes_of(N, k);
   const dim3 grid(nblk, d.B), block(kThreads);
   const float *norm = G > 1 ? norm_out : norm_or_part;
   if (G > 1)
