@@ -289,9 +289,9 @@ constexpr int kSmallBits = 13;  // bits of a field
 constexpr int kSmallBins = 1 << kSmallBits;
 constexpr uint32_t kSmallList = 512;
 
-// The G partial planes of a small map summed (and their maxima taken) by the whole chip before
-// the one-workgroup-a-sample kernel below: with many groups that kernel would otherwise read
-// G x N values per sample through a single compute unit.  grid = (ceil(N / 1024), B), block = 256.
+// The G partial planes summed (and their maxima taken) by the whole chip before the one-workgroup-a-sample kernel below, or
+// the two-launch selection: with many groups these would otherwise read G x N values per sample through one or a few
+// compute units.  grid = (ceil(N / 1024), B), block = 256.
 // The maxima land in group 0's plane of top_part (each position is read and written by one thread).
 __global__ __launch_bounds__(256) void combine_parts_kernel(const float *__restrict__ part,
                                                             float *__restrict__ norm, int G, int64_t N,
@@ -307,6 +307,10 @@ __global__ __launch_bounds__(256) void combine_parts_kernel(const float *__restr
 // that the extra launch (5 us) costs more than the one workgroup's reads (16384 positions in 8
 // groups, 262144 values: 25 us alone, 5 + 12 us combined first)
 constexpr int64_t kCombineValues = 1 << 17;
+// ... and in front of the two-launch selection from this many planes on: its few workgroups of 1024 threads read them one after
+// another, and the maxima again (44800 positions in 256 planes: 118 us, 68 combined first; 20736 in 128 55 and 41; 18432 in 32 22.3 and
+// 20.0; below that it loses, 65536 x 2 in 16 planes 5 us)
+constexpr int kCombineTwo = 32;
 
 // grid = B, block = 1024.  SLOTS: loads a thread (1, 2 or 4).  REDUCE as in load_keys.
 template <bool REDUCE, int SLOTS>
@@ -668,9 +672,16 @@ hipError_t launch_select(const wcc_desc &d, const float *norm_or_part, int G, fl
 #undef WCC_SMALL
     return hipGetLastError();
   }
-  if (L.two_nblk > 0)
+  if (L.two_nblk > 0) {
+    if (G >= kCombineTwo) {
+      hipLaunchKernelGGL(combine_parts_kernel, dim3((unsigned)((N + 1023) / 1024), d.B), dim3(256), 0, s,
+                         norm_or_part, norm_out, G, N, d.B, top_part);
+      norm_or_part = norm_out;
+      G = 1;
+    }
     return launch_select_two(d, norm_or_part, G, norm_out, k, ws + L.two_tables,
                              reinterpret_cast<uint32_t *>(ws + L.two_grouped), L.two_slots, L.two_nblk, idx, jmap, top_part, block_top, job, s);
+  }
   switch (L.sel_slots) {
     case 4: return launch_passes<4>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, job, s);
     case 2: return launch_passes<2>(d, norm_or_part, G, norm_out, k, hist, st, sfx, gthi, nblk, idx, jmap, top_part, block_top, job, s);

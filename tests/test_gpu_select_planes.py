@@ -1,6 +1,7 @@
 """The two-launch selection where the norms come as two to 256 planes of partial norms (needs an MI355X).  Its first kernel looks
-for crowded digits in plane 0, and in the sums where it finds some.  Planes that are crowded, sums that are, both and
-neither, against a host sort and the stage calls."""
+for crowded digits in plane 0, and in the sums where it finds some; from 32 planes on they are added up first.  Planes that
+are crowded, sums that are, both and neither, against a host sort and the stage calls; and the time, which must not
+grow with the planes."""
 import numpy as np
 import pytest
 import torch
@@ -24,7 +25,7 @@ KINDS = {
     (2, 64, 128, 160, 1),     # 2 planes
     (1, 256, 128, 160, 1),    # 8
     (2, 128, 128, 144, 4),    # 16
-    (1, 640, 128, 144, 4),    # 32
+    (1, 640, 128, 144, 4),    # 32: added up first
 ])
 def test_planes_and_sums(B, C, H, W, levels, kind):
     # One pixel of each 2 x 2 square is not zero, its amplitude the same all over a block of 2^levels: all coefficients of the
@@ -63,4 +64,28 @@ def test_planes_and_sums(B, C, H, W, levels, kind):
             np.testing.assert_array_equal(idx[b].cpu().numpy(), want)
             np.testing.assert_array_equal(idx2[b].cpu().numpy(), want)
         assert torch.equal(alpha, alpha2) and torch.equal(y, y2)
+    ctx.close()
+
+
+# A block whose second norm pass leaves 256 planes of norms and 256 of maxima: a few workgroups that read them all took 1.6 to
+# 2.1 times as long as that pass.
+def test_many_planes_take_less_than_the_pass_that_wrote_them():
+    B, C, e, H, W = 1, 256, 5, 80, 560
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    x = torch.randn((B, C, H, W), generator=gen, device="cuda").bfloat16()
+    w1, w3 = (torch.randn(s, generator=gen, device="cuda").bfloat16() / 16 for s in ((C * e, C), (C, C * e)))
+    wdw = torch.randn((C * e, 3, 3), generator=gen, device="cuda")
+    d = wcc.make_block_desc(B, C, e, H, W, 3, 3, 4, wcc.BF16, 8, wcc.BF16)
+    ctx = wcc.Context(0)
+    ctx.ensure_workspace(d)
+    ctx.set_profiling(True)
+    ctx.set_block_profile_layer(1)
+    y, times = torch.empty_like(x), []
+    for _ in range(12):
+        ctx.wcc_block_forward(d, x, w1, None, wdw, w3, None, y)
+        torch.cuda.synchronize()
+        times.append(ctx.stage_times())
+    best = lambda stage: min(t[stage] for t in times[2:])
+    assert best("norm_select") < 1.1 * best("haar_fwd")
     ctx.close()
