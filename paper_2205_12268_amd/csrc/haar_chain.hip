@@ -67,6 +67,16 @@ struct RegRow {
 // With the scale on the coefficients, up to 16 times what they are, and none on the taps it was 591, but the norms
 // overflowed from 2^124 on; 8 x 1024 channels of 256 x 256, a quarter kept, in one run: norm pass 346 -> 328 us, keep pass 457 -> 470.
 
+// 2^-P v for a value that is the same in every lane, on its bits by scalar instructions: there are no scalar multiplications, and the
+// vector's put nine taps into registers of every lane.  What falls below the normal numbers becomes zero.  For the keep pass at three
+// levels, which is short of registers: 8 x 1024 channels of 256 x 256, a quarter kept, 449 -> 435 us, 2 x 512 of 64 x 64 34.7 -> 32.0; at two
+// levels it loses (4 x 384 of 192 x 192 87.5 -> 89.8), and so does the norm pass, which then waits for the taps at once (324 -> 360-474).
+template <int P>
+__device__ __forceinline__ float scaled_down(float v) {
+  const uint32_t bits = __float_as_uint(v);
+  return __uint_as_float((bits & 0x7F800000u) > ((uint32_t)P << 23) ? bits - ((uint32_t)P << 23) : bits & 0x80000000u);
+}
+
 // Synthesis levels D..L of a strip: twice its rows of level L - 1 (inv_levels without the factors).
 template <int D, int V, int L, class Source>
 __device__ __forceinline__ void inv_levels_twice(float (&out)[rows_at(D, L - 1)][cols_at(V, L - 1)], const LanePos<D> &p,
@@ -332,7 +342,8 @@ __device__ __forceinline__ void chain_walk(const float *__restrict__ plane, int6
   auto compute = [&](const float *kw) {
     float k[9];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) k[t] = kw[t] * (1.f / (float)(2 << D));  // (the rows below are twice what they are)
+    for (int t = 0; t < 9; ++t)  // (the rows below are twice what they are)
+      k[t] = !Sink::kScaled && D == 3 ? scaled_down<D + 1>(kw[t]) : kw[t] * (1.f / (float)(2 << D));
     wave_lds_fence();
     float six[RR][V + 2];
     {
