@@ -747,6 +747,7 @@ inline StripMap keep_map(const wcc_desc &d, bool folded) {
 }
 
 constexpr int64_t kQuadWaves = 1024;
+constexpr int64_t kQuadRound = 512;  // workgroups, two a compute unit
 
 int keep_groups(const wcc_desc &d, bool folded, bool late) {
   // About two thousand waves, down to two channels each at d <= 2, where a wave has few rows in flight
@@ -850,8 +851,19 @@ hipError_t keep_dispatch(const wcc_desc &d, int64_t k, const void *x, const int3
 // they make do with as many waves as the quads give, from a thousand on.
 static int quad_groups(const wcc_desc &d) {
   const int G0 = keep_groups(d, false, false), quads = (d.C_in + 3) / 4;
-  if (quads <= G0) return (int64_t)keep_map(d, false).units * quads * d.B >= kQuadWaves ? quads : 0;
-  return 40 * ((quads + G0 - 1) / G0) <= 11 * ((d.C_in + G0 - 1) / G0) ? G0 : 0;
+  const int64_t units = keep_map(d, false).units;
+  int G = 0;
+  if (quads <= G0) G = units * quads * d.B >= kQuadWaves ? quads : 0;
+  else if (40 * ((quads + G0 - 1) / G0) <= 11 * ((d.C_in + G0 - 1) / G0)) G = G0;
+  if (G == 0) return 0;
+  // From three levels on two workgroups of this pass share a compute unit, of the byte-wise one three: a last round of them that is
+  // half empty or more costs short walks more than the words give, up to a half kept.  Layers by words and by bytes: 8 x 128 channels of
+  // 96 x 160, 768 workgroups of one quad, half kept, 74.0 us and 70.0; 12 x 496 of 80 x 32 at four levels, two quads, 80.6 and 71.3; 4 x 128 of
+  // 128 x 320, 640 of one, 76.1 and 73.5, all kept 87.8 and 90.2; in full rounds, and with four quads and more, 0.91 to 1.01.
+  const int64_t wgs = (units + 3) / 4 * G * d.B, rounds = (wgs + kQuadRound - 1) / kQuadRound;
+  const bool few = 2 * kept_count(d) <= (int64_t)d.H * d.W;
+  if (d.levels >= 3 && few && quads <= 3 * G && wgs > kQuadRound && 3 * kQuadRound * rounds >= 4 * wgs) return 0;
+  return G;
 }
 
 // ... with K_dw in front: quads a group, or 0

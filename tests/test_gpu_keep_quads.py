@@ -20,11 +20,11 @@ CASES = [
     (2, 134, 40, 100, 212, 2, (1, 3), wcc.BF16),     # 8 rows, idle lanes, rows of yc that are padded
     (4, 128, 16, 64, 128, 2, (9, 10), wcc.I8),       # a word a slot
     (4, 64, 96, 256, 256, 3, (1, 8), wcc.BF16),
-    (8, 128, 136, 96, 160, 3, (1, 2), wcc.I8),       # 16 rows and a word a slot, side by side
+    (8, 128, 136, 96, 128, 3, (1, 2), wcc.I8),       # 16 rows and a word a slot, side by side
     (3, 256, 130, 128, 128, 3, (1, 3), wcc.I8),      # packed weights
     (8, 64, 40, 256, 256, 2, (1, 16), wcc.I4),       # several quads a group
     (4, 64, 40, 128, 320, 3, (1, 4), wcc.BF16),      # 12 rows, lanes of all strips follow each other
-    (4, 128, 72, 128, 320, 3, (1, 4), wcc.I8),
+    (4, 128, 72, 128, 320, 3, (3, 4), wcc.I8),
     (2, 256, 72, 64, 512, 2, (1, 4), wcc.BF16),      # packed bf16 weights
     (2, 58, 24, 128, 256, 3, (1, 3), wcc.BF16),      # 15 quads in 8 groups, the last a quad of two
     (2, 114, 40, 192, 320, 1, (1, 2), wcc.BF16),     # 29 quads in 16 groups, the last a quad of two
@@ -38,6 +38,10 @@ BYTES = [
     (2, 264, 72, 64, 512, 2, (1, 4), wcc.BF16),      # 66 for 32
     (4, 64, 40, 128, 128, 4, (1, 8), wcc.BF16),      # too few waves by quads
     (4, 64, 48, 128, 96, 4, (3, 4), wcc.I8),
+    (8, 128, 136, 96, 160, 3, (1, 2), wcc.I8),       # 768 workgroups of one quad: a round and a half-empty one
+    (4, 128, 72, 128, 320, 3, (1, 4), wcc.I8),       # 640
+    (11, 456, 24, 64, 48, 3, (1, 8), wcc.BF16),     # 704 of two
+    (9, 484, 24, 80, 32, 4, (1, 4), wcc.BF16),
 ]
 
 
