@@ -26,7 +26,7 @@
  *             prints.  A HIP launch failure returns WCC_ERR_HIP.
  * Numbers.    Activations are fp32.  NaN/Inf inputs give unspecified results
  *             (never undefined behaviour on the host).  Magnitudes below 2^-122 may
- *             lose bits.
+ *             lose bits or count as zero.
  *
  * Layouts (all row-major, last index contiguous); N = H*W, n_l = (H>>l)*(W>>l)
  * ---------------------------------------------------------------------------

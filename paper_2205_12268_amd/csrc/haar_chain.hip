@@ -65,7 +65,8 @@ struct RegRow {
 // routes hold, and what lies below 2^-122 may lose bits.  The sinks take the powers off: the norm pass once a walk (of squares before
 // they are squared), the keep pass in the multiplication it had.  Vector instructions a channel of the norm pass 709 -> 601.
 // With the scale on the coefficients, up to 16 times what they are, and none on the taps it was 591, but the norms
-// overflowed from 2^124 on; 8 x 1024 channels of 256 x 256, a quarter kept, in one run: norm pass 346 -> 328 us, keep pass 457 -> 470.
+// overflowed from 2^124 on; 8 x 1024 channels of 256 x 256, a quarter kept, in one run: norm pass 335 -> 323 us on smooth maps and 320 -> 332 on
+// noise, whose lists are of other lengths, keep pass 441 -> 439 and 436 -> 435.
 
 // 2^-P v for a value that is the same in every lane, on its bits by scalar instructions: there are no scalar multiplications, and the
 // vector's put nine taps into registers of every lane.  What falls below the normal numbers becomes zero.  For the keep pass at three

@@ -909,7 +909,7 @@ __global__ __launch_bounds__(256) void pointwise_f32_kernel(const void *__restri
                                                             int64_t k) {
   constexpr int TM = 32 * WVM * MB, TN = 32 * (4 / WVM) * NB;
   fetch_args(w, k);
-    constexpr int LDA = FK + 1, LDB = TN + 32;  // LDS row words: the 64 lanes of a read of Bs hit 64 banks
+  constexpr int LDA = FK + 1, LDB = TN + 32;  // LDS row words: the 64 lanes of a read of Bs hit 64 banks
                                               // (of As 47; FK + 2, which makes that 64, measured the same)
   constexpr int NA = TM * FK / 256;           // weights a thread and stage
   constexpr int XV = VEC ? 4 : 1;             // positions a load
