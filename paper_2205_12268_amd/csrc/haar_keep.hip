@@ -866,10 +866,14 @@ static int quad_groups(const wcc_desc &d) {
   return G;
 }
 
-// ... with K_dw in front: quads a group, or 0
+// ... with K_dw in front: quads a group, or 0.  (At three levels, short walks in a second round as above, whatever is kept.  Blocks by words and by
+// bytes: 6 x 960 channels of 48 x 56, 720 workgroups of two quads, half kept, 200 us and 188; 7 x 1008 of 16 x 256, 882 of two, all kept, 309 and
+// 304; 5 x 512 of 48 x 184, 640 of two, 294 and 291; 7 x 336 of 88 x 184, 588 of three, 355 and 360.)
 static int dw_quads_a_group(const wcc_desc &d) {
   const int G0 = keep_groups(d, true, false), quads = (d.C_in + 3) / 4, each = (quads + G0 - 1) / G0;
-  return d.act_dtype == WCC_F32 && quads >= G0 && 40 * each <= 11 * ((d.C_in + G0 - 1) / G0) ? each : 0;
+  if (d.act_dtype != WCC_F32 || quads < G0 || 40 * each > 11 * ((d.C_in + G0 - 1) / G0)) return 0;
+  const int64_t wgs = (int64_t)(keep_map(d, true).units + 3) / 4 * ((quads + each - 1) / each) * d.B;
+  return d.levels == 3 && each <= 3 && 4 * wgs >= 5 * kQuadRound ? 0 : each;
 }
 
 bool keep_in_quads(const wcc_desc &d, bool folded) { return folded ? dw_quads_a_group(d) > 0 : quad_groups(d) > 0; }

@@ -37,6 +37,7 @@ BYTES = [
     (4, 22, 5, 96, 96, 3),        # (fp32: a small layer)
     (2, 40, 4, 64, 768, 3),
     (4, 24, 6, 128, 160, 4),
+    (6, 192, 5, 48, 56, 3),       # 720 workgroups of two quads
 ]
 
 
